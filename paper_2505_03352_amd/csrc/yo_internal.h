@@ -8,7 +8,6 @@
 
 #define YO_MAX_PORTS 8
 #define YO_MAX_SLOTS 32
-#define YO_TX 62          // owned x-cells per wave (lanes 1..62; lanes 0 and 63 are halo)
 #define YO_TY 4           // rows per wave
 #define YO_TY2 6          // rows per wave of the two-step region's taller tiles
 #define YO_MAX_WPB 8      // waves per block of the step kernel: 4 or 8
@@ -16,12 +15,22 @@
 // Field arrays carry one ghost layer on every face and keep the components
 // of one (j, k) row together: component c of cell (x, j, k), x in [-1, nx],
 // j in [-1, ny], k in [-1, nz], of an array with nc components sits at
-//   (((k + 1) * (ny + 2) + (j + 1)) * nc + c) * nxp + (x + 1).
+//   (((k + 1) * (ny + 2) + (j + 1)) * nc + c) * nxp + yo_col(x).
+// A row of nx cells is cut into strips of sw = 64 - 2 lead cells, each in a
+// segment of 64 floats (two 128-byte lines) with `lead` pad floats on either
+// side (the last segment: as many whole lines as its cells need): the cells a
+// wave owns, its lanes over the pads storing values nobody reads, so that
+// every row of a whole strip is stored in whole lines.  lead = 1 for plans
+// that take one step per launch, 2 for two (the halo lanes on either side).
+// Where the pads would push a limit (2 GiB of state or CPML memory, the
+// static workspace) that plain rows keep, rows are plain (slead = 1, one
+// strip).
 // The state of one right-hand side and step parity is one such array with
 // nc = 6 (Ex Ey Ez Ht_x Ht_y Ht_z), kappa one with nc = 3, so a row group
-// of all components is one contiguous block of memory.  Ghosts are zero and
-// never written, which realises the perfect-conductor box (values outside
-// the grid read as zero) without branches.
+// of all components is one contiguous block of memory.  Ghost rows and planes
+// are zero and never written, and columns outside the grid are read past the
+// buffer (zero), which realises the perfect-conductor box (values outside the
+// grid read as zero) without branches.
 
 struct YoPlaneD {
     int axis, index, lo0, lo1, n0, n1;
@@ -39,7 +48,8 @@ struct YoRhsD {
     // (E one slot, Ht two by step parity), with nbuf = 3 twelve (E three
     // slots, Ht three, the step's in slot step % 3); each [2 comps] of the
     // axis' slab layout
-    // (x [nz][ny][Wx], y [nz][Wy][nxp], z [Wz][ny][nxp])
+    // (x [side][nz][ny][lo], or [nz][ny][lo + hi] where the two slabs differ,
+    // y [nz][Wy][nxp], z [Wz][ny][nxp] with the rows' column layout)
     float *psi;
     float2 *dft_box;         // [3][bz][by][bx]
     float2 *dft_mon;         // concatenated port planes [2][n1][n0]
@@ -66,6 +76,9 @@ struct YoPlanD {
     const float *prof[3];    // per axis [6][n_a]: bE cE kiE bH cH kiH
     int psi_off[3], psi_n[3];
     int psi_total;           // floats of CPML memory per right-hand side
+    int psi_xrp, psi_xside;  // x-slab memories: floats from row to row and from the low slab's to the high one's
+    int lead, strips;        // halo lanes before a wave's first owned column; rows in strips or plain
+    int sw, slead;           // column layout, see yo_col
     int box[6];              // x0 y0 z0 bx by bz
     int n_ports;
     int n_steps;
@@ -85,7 +98,7 @@ struct YoPlanD {
 };
 
 // A tile is one wave's work (or, in the cooperative layout, one block's):
-// owned x in [x0, x0+xn) (xn <= 62), rows [j0, j0+jn) (jn <= YO_TY, or
+// owned x in [x0, x0+xn) (xn <= 64 - 2 lead), rows [j0, j0+jn) (jn <= YO_TY, or
 // YO_TY * waves per block), planes [k0, k1).  Packed as int4
 // (x0 | xn << 16, j0 | jn << 16, k0 | k1 << 16, tile class).
 struct YoSlot {
@@ -182,9 +195,9 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s);
 // dense [ncomp][nz][ny][nx] <-> components c0 .. c0+ncomp-1 of a ghost-layout
 // array with nc components
 hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
-                              int ny, int nx, int nxp, hipStream_t s);
+                              int ny, int nx, int nxp, int sw, int slead, hipStream_t s);
 hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
-                                int ny, int nx, int nxp, hipStream_t s);
+                                int ny, int nx, int nxp, int sw, int slead, hipStream_t s);
 // in-place phasor fit of n complex sums; sets *bad to 1 if a result is not
 // finite (*bad is left alone otherwise)
 hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g10, float g11,
@@ -192,7 +205,7 @@ hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g
 hipError_t yo_launch_alpha(const float2 *mon_dft, const float2 *weights, int n, float2 *out,
                            hipStream_t s);
 hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float beta,
-                                   float *kappa, int nx, int ny, int nz, int nxp, int i0, int j0,
+                                   float *kappa, int ny, int nxp, int sw, int slead, int i0, int j0,
                                    int k_lo, int k_hi, hipStream_t s);
 #define YO_MAX_GF 32
 #define YO_MAX_GA 64
@@ -206,7 +219,7 @@ struct YoGradArgs {
     float *gbox;                   // optional [3][bz][by][bx] dF/dkappa
     float *gmap;                   // optional [4][G1][G0] z-summed maps
     int n_src, n_ports, n_freq;
-    int nxp, ny, nz;
+    int nxp, ny, sw, slead;
     int box[6];
     int k_lo, k_hi, G0, G1;
 };
@@ -220,8 +233,16 @@ hipError_t yo_launch_adam(float *C, const float *G, float *M, float *V, int n, f
 hipError_t yo_launch_zsum(const float *gbox, const int *box, int k_lo, int k_hi, float *gmap, int G0,
                           int G1, hipStream_t s);
 
-// ghost-layout offset of component c of (x, j, k) in an array of nc components
-__host__ __device__ inline size_t yo_off(int c, int x, int j, int k, int ny, int nxp, int nc)
+// column of cell x in a row (see the layout above)
+__host__ __device__ inline int yo_col(int x, int sw, int slead)
 {
-    return (((size_t)(k + 1) * (ny + 2) + (size_t)(j + 1)) * nc + c) * nxp + (size_t)(x + 1);
+    const int s = x / sw;
+    return s * 64 + slead + (x - s * sw);
+}
+
+// ghost-layout offset of component c of column col of row (j, k) in an array
+// of nc components
+__host__ __device__ inline size_t yo_off(int c, int col, int j, int k, int ny, int nxp, int nc)
+{
+    return (((size_t)(k + 1) * (ny + 2) + (size_t)(j + 1)) * nc + c) * nxp + (size_t)col;
 }

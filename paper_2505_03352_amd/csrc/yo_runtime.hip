@@ -21,6 +21,7 @@
 namespace {
 
 constexpr double kC0 = 299792458.0;
+constexpr int kMinChunk = 2, kFillWaves = 1280;   // see short_chunk
 thread_local std::string g_err;
 
 yo_status fail(yo_status st, const char *fmt, ...)
@@ -119,10 +120,14 @@ struct yo_plan {
     std::vector<yo_plane> src_planes, port_planes;
     double dt = 0, sx = 0, sy = 0, sz = 0;
     int nxp = 0;
+    // column layout (yo_col): strips of sw = 64 - 2 lead cells, or plain rows
+    int lead = 1, sw = 62, slead = 1;
+    bool strips = true;
     int plo[3] = {0, 0, 0}, phi[3] = {0, 0, 0};
     size_t cells_p = 0;          // padded cells per component
     size_t psi_per_rhs = 0;      // floats
     size_t psi_axis_off[3] = {0, 0, 0}, psi_axis_n[3] = {0, 0, 0};   // per RHS, per axis slab size (floats per comp)
+    int psi_xrp = 0, psi_xside = 0;   // x-slab memories: row pitch, offset of the high slab
     size_t bsz = 0;              // box cells
     int box[6] = {0, 0, 0, 0, 0, 0};
     size_t mon_total = 0;        // complex entries per RHS
@@ -150,7 +155,8 @@ struct yo_plan {
     std::vector<float> ginv;     // [n_freq][4]
     std::vector<double> omega_dt;
     std::vector<char> src_set, port_set;
-    int kc = 16, tflags = 0;     // z-planes per tile; tiling flags (YO_TILE_* below)
+    int kc = 16, tflags = 0;     // z-planes per tile asked for; tiling flags (YO_TILE_* below)
+    int kce = 16;                // z-planes per tile of the tables (short_chunk)
     int n_int = 0, n_tiles = 0;  // tile table: interior tiles [0, n_int), CPML shell [n_int, n_tiles)
     // temporal blocking (yo_set_time_blocking): steps per sweep the interior
     // may take, state buffers per right-hand side, the two-step region and
@@ -304,7 +310,7 @@ size_t morph_bytes(const yo_plan *p, size_t n, size_t t)
 // CPML slabs (per right-hand side): per axis, 2 components per slot, three
 // slots (E one, Ht two) with two state buffers, six (three each) with three;
 // false when they would pass 2 GiB (32-bit buffer offsets).
-static bool set_psi_layout(yo_plan *p)
+bool set_psi_layout(yo_plan *p)
 {
     const yo_grid &g = p->grid;
     const size_t W[3] = {(size_t)p->plo[0] + p->phi[0], (size_t)p->plo[1] + p->phi[1],
@@ -319,12 +325,54 @@ static bool set_psi_layout(yo_plan *p)
         off += arrays * slab[a];
     }
     p->psi_per_rhs = off;
+    // x-slabs of one width: each side by itself, so that the rows of a tile
+    // (which meets one side) are one run of memory
+    const bool even = p->plo[0] == p->phi[0];
+    p->psi_xrp = even ? p->plo[0] : p->plo[0] + p->phi[0];
+    p->psi_xside = even ? (int)((size_t)g.nz * g.ny * p->plo[0]) : p->plo[0];
     return off * sizeof(float) < ((size_t)1 << 31);
+}
+
+// Column layout and what follows from it; false when a state array or the
+// CPML memories of one right-hand side would pass 2 GiB.
+bool set_columns(yo_plan *p, bool strips)
+{
+    const yo_grid &g = p->grid;
+    p->lead = p->tsteps == 2 ? 2 : 1;
+    p->strips = strips;
+    p->sw = strips ? 64 - 2 * p->lead : 1 << 20;
+    p->slead = strips ? p->lead : 1;
+    if (strips) {
+        const int full = g.nx / p->sw, rem = g.nx % p->sw;
+        p->nxp = 64 * full + (rem ? (p->slead + rem + 31) & ~31 : 0);
+    } else {
+        p->nxp = (g.nx + 2 + 31) & ~31;
+    }
+    p->cells_p = (size_t)(g.nz + 2) * (g.ny + 2) * p->nxp;
+    return set_psi_layout(p) && 6 * p->cells_p * sizeof(float) < ((size_t)1 << 31);
+}
+
+void build_regions(yo_plan *p);
+
+// Layout of the columns and of the workspace: strips, or plain rows where
+// only those keep within the 2 GiB limits or the static workspace.
+bool build_layout(yo_plan *p)
+{
+    if (!set_columns(p, false)) return false;
+    build_regions(p);
+    const size_t plain = p->L.total;
+    if (set_columns(p, true)) {
+        build_regions(p);
+        if (p->L.total <= YO_STATIC_WS_BYTES || plain > YO_STATIC_WS_BYTES) return true;
+    }
+    set_columns(p, false);
+    build_regions(p);
+    return true;
 }
 
 // Workspace regions (fields, CPML memories and descriptors per stepped
 // right-hand side; DFT results per output right-hand side).
-void build_layout(yo_plan *p)
+void build_regions(yo_plan *p)
 {
     const yo_design &d = p->des;
     const yo_grid &g = p->grid;
@@ -479,6 +527,23 @@ void split_axis(int n, int lo, int hi, int w, std::vector<std::pair<int, int>> &
     }
 }
 
+// The same along x: cuts at lo, hi and at every strip of w = 64 - 2 lead
+// cells (a tile lies in one strip, so its rows are whole lines but at lo and
+// hi).
+void split_x(int n, int lo, int hi, int w, std::vector<std::pair<int, int>> &out, std::vector<char> &interior)
+{
+    out.clear();
+    interior.clear();
+    for (int a = 0; a < n;) {
+        int b = std::min((a / w + 1) * w, n);
+        if (a < lo) b = std::min(b, lo);
+        else if (a < hi) b = std::min(b, hi);
+        out.emplace_back(a, b - a);
+        interior.push_back(a >= lo && a < hi);
+        a = b;
+    }
+}
+
 // Two-step region R2 inside the interior region [lo, hi) and its tiles.
 // Along each axis R2 keeps two cells clear of the absorbing slabs (the
 // two-step kernel recomputes step n+1's Ht two cells below and its E one
@@ -521,14 +586,14 @@ void build_pair_tiles(yo_plan *p, const int lo[3], const int hi[3])
     // two-step tiles
     std::vector<std::pair<int, int>> ax, ay, az;
     std::vector<char> ix, iy, iz;
-    split_axis(n[0], r[0], r[1], 60, ax, ix);
+    split_x(n[0], r[0], r[1], 60, ax, ix);
     // rows per tile: per wave (YO_TY or YO_TY2), times the waves of a
     // block in the cooperative layout
     const int wpb = (p->tflags & YO_TILE_WPB8) ? 8 : 4;
     split_axis(n[1], r[2], r[3],
                ((p->tflags & YO_TILE_PAIR6) ? YO_TY2 : YO_TY) * ((p->tflags & YO_TILE_COOP_PAIRS) ? wpb : 1),
                ay, iy);
-    split_axis(n[2], r[4], r[5], p->kc, az, iz);
+    split_axis(n[2], r[4], r[5], p->kce, az, iz);
     for (size_t k = 0; k < az.size(); ++k)
         for (size_t j = 0; j < ay.size(); ++j)
             for (size_t i = 0; i < ax.size(); ++i) {
@@ -559,9 +624,20 @@ void build_pair_tiles(yo_plan *p, const int lo[3], const int hi[3])
             }
         }
     };
-    pieces(0, YO_TX, ax, ix);
+    {
+        // x: the columns of [lo, hi), cut at R2's faces and at the strips
+        split_x(hi[0], r[0], r[1], 60, ax, ix);
+        while (!ax.empty() && ax.front().first + ax.front().second <= lo[0]) {
+            ax.erase(ax.begin());
+            ix.erase(ix.begin());
+        }
+        if (!ax.empty() && ax.front().first < lo[0]) {
+            ax.front().second -= lo[0] - ax.front().first;
+            ax.front().first = lo[0];
+        }
+    }
     pieces(1, YO_TY, ay, iy);
-    pieces(2, p->kc, az, iz);
+    pieces(2, p->kce, az, iz);
     for (size_t k = 0; k < az.size(); ++k)
         for (size_t j = 0; j < ay.size(); ++j)
             for (size_t i = 0; i < ax.size(); ++i) {
@@ -583,18 +659,18 @@ void build_pair_tiles(yo_plan *p, const int lo[3], const int hi[3])
     // YO_TILE_ZPAIRS: when R2 is the whole interior (no plane cuts it, so the
     // frame is empty and the shell's class-4 tiles are exactly the z-slabs
     // under R2), those z-slabs go two steps per launch too, in strips of 60
-    // cells, YO_TY rows and at most kc planes
+    // cells, YO_TY rows and at most kce planes
     bool whole = (p->tflags & YO_TILE_ZPAIRS) && (p->plo[2] > 0 || p->phi[2] > 0);
     for (int a = 0; a < 3; ++a) whole = whole && r[2 * a] == lo[a] && r[2 * a + 1] == hi[a];
     if (!whole) return;
-    split_axis(n[0], r[0], r[1], 60, ax, ix);
+    split_x(n[0], r[0], r[1], 60, ax, ix);
     split_axis(n[1], r[2], r[3], YO_TY, ay, iy);
     az.clear();
     const int zs[2][2] = {{0, lo[2]}, {hi[2], n[2]}};
     for (const auto &z : zs) {
         const int len = z[1] - z[0];
         if (len <= 0) continue;
-        const int np = (len + p->kc - 1) / p->kc;
+        const int np = (len + p->kce - 1) / p->kce;
         int st = z[0];
         for (int q = 0; q < np; ++q) {
             const int sz = len / np + (q < len % np ? 1 : 0);
@@ -617,6 +693,23 @@ void build_pair_tiles(yo_plan *p, const int lo[3], const int hi[3])
     p->nz2 = (int)(p->tiles_host.size() - z2_0);
 }
 
+// Planes per tile: those asked for, or fewer where a plan's right-hand sides
+// would not give kFillWaves waves (5 on each of 256 CUs; more than that and
+// plans that share launches lose): a step's time is
+// then the march of one wave, plane after plane.  Measured per step (single
+// steps): 91x103x88 with 2 right-hand sides 94 us at 10 planes, 72 at 6, 68 at
+// 3, 75 at 1; 56x56x36 84 us at 16, 45 at 4, 33 at 2; a grid that fills the chip loses with
+// short chunks (320x240x96 with 6: 777 us at 10, 858 at 4).
+int short_chunk(const yo_plan *p)
+{
+    const yo_grid &g = p->grid;
+    const long xy = (long)((g.nx + 63 - 2 * p->lead) / (64 - 2 * p->lead)) * ((g.ny + YO_TY - 1) / YO_TY) *
+                    std::max(p->n_phys, 1);
+    int kc = p->kc;
+    while (kc > kMinChunk && xy * ((g.nz + kc - 1) / kc) < kFillWaves) --kc;
+    return kc;
+}
+
 // Tile table: the interior tiles, then the CPML shell, each in space order
 // (z, y, x fastest).  Along each axis the region clear of the absorbing
 // slabs is [lo + 1, n - hi) for a CPML of lo/hi cells (no owned site and no
@@ -630,50 +723,50 @@ void build_pair_tiles(yo_plan *p, const int lo[3], const int hi[3])
 // With two steps per launch (YO_TILE_PAIRS) the region clear of the slabs is
 // [lo + 2, n - hi - 1), the two-step region's own margin, so that no
 // single-step interior layer one cell thick lies between that region and
-// the shell (the shell runs the layer, its CPML code idle there); and
-// YO_TILE_XFULL then cuts whole 60-cell strips of the two-step launch out
-// of the row between the x-normal source and port planes.
+// the shell (the shell runs the layer, its CPML code idle there).
+// Along x the cut is at whole strips of the column layout: a strip that
+// meets a slab is the shell's as a whole, because lines stored in part cost
+// more than CPML code that idles (and a row of narrow tiles as many waves as
+// whole ones).  With pairs that is asked for with YO_TILE_XSTRIPS or
+// YO_TILE_XFULL (the same cut), between the x-normal source and port planes.
 void build_tiles(yo_plan *p)
 {
     const int n[3] = {p->grid.nx, p->grid.ny, p->grid.nz};
+    p->kce = short_chunk(p);
     const int wpb = (p->tflags & YO_TILE_WPB8) ? 8 : 4;
     const bool pr = p->tsteps == 2 && (p->tflags & YO_TILE_PAIRS);
     int lo[3], hi[3];
     for (int a = 0; a < 3; ++a) {
         lo[a] = p->plo[a] > 0 ? p->plo[a] + (pr ? 2 : 1) : 0;
         hi[a] = n[a] - p->phi[a] - (pr && p->phi[a] > 0 ? 1 : 0);
-        int a0 = lo[a], a1 = hi[a];
-        if (a == 0 && pr) cut_planes(p, 0, a0, a1);
-        if (a == 0 && pr && (p->tflags & YO_TILE_XFULL) && a1 - a0 >= 60) {
-            // whole 60-cell two-step strips, centred in the row where the
-            // planes allow; the shell strips take the rest
-            const int whole = (a1 - a0) / 60 * 60;
-            const int wlo = std::min(std::max((n[0] - whole) / 2, a0), a1 - whole);
-            lo[0] = wlo;
-            hi[0] = wlo + whole;
-        } else if (a == 0 && (p->tflags & YO_TILE_XFULL) && hi[0] - lo[0] >= YO_TX) {
-            // the interior takes as many whole strips as fit; the rest of the
-            // row goes to the two shell strips (which then also carry
-            // interior columns)
-            const int whole = (hi[0] - lo[0]) / YO_TX * YO_TX;
-            const int rest = n[0] - whole;
-            int wlo = p->plo[0] > 0 ? (p->phi[0] > 0 ? rest / 2 : rest) : 0;
-            wlo = std::max(wlo, lo[0]);
-            wlo = std::min(wlo, n[0] - whole - (n[0] - hi[0]));
-            lo[0] = wlo;
-            hi[0] = wlo + whole;
-        } else if (a == 0 && (p->tflags & YO_TILE_XSTRIPS)) {
-            // full-width CPML strips: the shell strips also carry interior columns
-            if (p->plo[0] > 0) lo[0] = std::max(lo[0], std::min(YO_TX, n[0]));
-            if (p->phi[0] > 0) hi[0] = std::min(hi[0], n[0] - YO_TX);
+        if (a == 0 && (!pr || (p->tflags & (YO_TILE_XSTRIPS | YO_TILE_XFULL)))) {
+            // whole strips: those that meet a slab belong to the shell; with
+            // pairs also those between a slab and the source and port planes
+            // normal to x.  Where no strip is left the cut is at the slabs (or, in
+            // single steps with YO_TILE_XSTRIPS, every strip the shell's); with
+            // pairs also where whole strips leave under 3/4 of the two-step
+            // columns (320x240x96, 85 %: 712 us per step against 789 at the
+            // slabs; six designs of 108 to 197 columns, 38 to 76 %: 23.0 ms
+            // against 24.2 for 60 steps)
+            const int w = 64 - 2 * p->lead;
+            int a0 = lo[a], a1 = hi[a];
+            if (pr) cut_planes(p, 0, a0, a1);
+            const int s0 = (a0 + w - 1) / w * w, s1 = a1 == n[0] ? a1 : a1 / w * w;
+            if (pr ? 4 * (s1 - s0) >= 3 * (a1 - a0) : s1 > s0 || (p->tflags & YO_TILE_XSTRIPS)) {
+                lo[0] = s0;
+                hi[0] = s1;
+            } else if (pr && a1 - a0 >= 4) {
+                lo[0] = a0;
+                hi[0] = a1;
+            }
         }
         hi[a] = std::max(hi[a], 0);
         lo[a] = std::min(lo[a], hi[a]);
     }
     std::vector<std::pair<int, int>> ax, ay, az;
     std::vector<char> ix, iy, iz;
-    split_axis(n[0], lo[0], hi[0], YO_TX, ax, ix);
-    split_axis(n[2], lo[2], hi[2], p->kc, az, iz);
+    split_x(n[0], lo[0], hi[0], 64 - 2 * p->lead, ax, ix);
+    split_axis(n[2], lo[2], hi[2], p->kce, az, iz);
     auto emit = [&](bool shell, int rows, std::vector<int4> &out) {
         split_axis(n[1], lo[1], hi[1], rows, ay, iy);
         for (size_t k = 0; k < az.size(); ++k)
@@ -709,7 +802,7 @@ void build_tiles(yo_plan *p)
 
 size_t tiles_capacity(const yo_grid &g, int ty_min, int kc_min)
 {
-    const size_t ntx = g.nx / YO_TX + 4;
+    const size_t ntx = g.nx / 60 + 6;
     const size_t nty = g.ny / ty_min + 4;
     const size_t ntz = g.nz / kc_min + 4;
     return ntx * nty * ntz;
@@ -860,18 +953,6 @@ yo_status yo_plan_create(const yo_grid *grid, const yo_design *des, int n_steps,
     p->src_set.assign(n_src, 0);
     p->port_set.assign(n_ports, 0);
 
-    // ghost layout: one zero layer on every face, rows padded to 128 bytes
-    // ghosts at x = -1 and x = nx, rounded up to 32 floats
-    p->nxp = (g.nx + 2 + 31) & ~31;
-    p->cells_p = (size_t)(g.nz + 2) * (g.ny + 2) * p->nxp;
-    if (6 * p->cells_p * sizeof(float) >= ((size_t)1 << 31)) {
-        delete p;
-        return fail(YO_EUNSUPPORTED, "one state array (6 components) must stay below 2 GiB");
-    }
-    if (!set_psi_layout(p)) {
-        delete p;
-        return fail(YO_EUNSUPPORTED, "the CPML memories of one right-hand side must stay below 2 GiB");
-    }
     p->box[0] = d.i0 - 1;
     p->box[1] = d.j0 - 1;
     p->box[2] = d.k_lo - 1;
@@ -890,11 +971,16 @@ yo_status yo_plan_create(const yo_grid *grid, const yo_design *des, int n_steps,
     p->G0 = d.md + 4;
     p->G1 = d.nd + 4;
     p->tmax = 2 * (int)std::ceil(d.filter_r) + 2;
-    p->tiles_cap = tiles_capacity(g, 4, 4);
+    p->tiles_cap = tiles_capacity(g, YO_TY, kMinChunk);
 
     p->n_phys = p->n_rhs;
     p->n_pfwd = p->n_fwd;
-    build_layout(p);
+    if (!build_layout(p)) {
+        const bool state = 6 * p->cells_p * sizeof(float) >= ((size_t)1 << 31);
+        delete p;
+        return fail(YO_EUNSUPPORTED, state ? "one state array (6 components) must stay below 2 GiB"
+                                           : "the CPML memories of one right-hand side must stay below 2 GiB");
+    }
 
     build_profiles(p);
     build_steptab(p);
@@ -986,6 +1072,12 @@ static yo_status rebuild_descriptors(yo_plan *p)
         P.psi_n[a] = (int)p->psi_axis_n[a];
     }
     P.psi_total = (int)p->psi_per_rhs;
+    P.psi_xrp = p->psi_xrp;
+    P.psi_xside = p->psi_xside;
+    P.lead = p->lead;
+    P.strips = p->strips;
+    P.sw = p->sw;
+    P.slead = p->slead;
     P.n_ports = p->n_ports;
     P.mon_nc = p->mon_nc;
     P.n_steps = p->n_steps;
@@ -1219,6 +1311,7 @@ yo_status yo_set_pulse(yo_plan *p, double omega0, double sigma_steps, double t0_
         p->n_pfwd = p->n_src;
     }
     build_steptab(p);
+    build_tiles(p);   // the chunks follow the number of stepped right-hand sides
     build_layout(p);
     return YO_OK;
 }
@@ -1296,20 +1389,22 @@ yo_status yo_set_time_blocking(yo_plan *p, int steps)
     if (!p) return fail(YO_EINVAL, "null argument");
     if (p->ws) return fail(YO_ESTATE, "set the time blocking before binding a workspace");
     if (steps != 1 && steps != 2) return fail(YO_EINVAL, "steps per sweep must be 1 or 2");
-    const int nbuf_was = p->nbuf;
+    const int nbuf_was = p->nbuf, tsteps_was = p->tsteps;
+    const size_t cap_was = p->tiles_cap;
     p->nbuf = steps == 2 ? 3 : 2;
-    if (!set_psi_layout(p)) {
+    p->tsteps = steps;
+    // the two-step and frame tiles can add up to twice the single-step count
+    p->tiles_cap = tiles_capacity(p->grid, YO_TY, kMinChunk) * (steps == 2 ? 3 : 1);
+    if (!build_layout(p)) {
         p->nbuf = nbuf_was;
-        set_psi_layout(p);
+        p->tsteps = tsteps_was;
+        p->tiles_cap = cap_was;
+        build_layout(p);
         return fail(YO_EUNSUPPORTED, "the CPML memories of one right-hand side must stay below 2 GiB");
     }
-    p->tsteps = steps;
     if (steps == 1)
         p->tflags &= ~(YO_TILE_PAIRS | YO_TILE_OVERLAP | YO_TILE_ZPAIRS | YO_TILE_PAIR6 | YO_TILE_COOP_PAIRS);
-    // the two-step and frame tiles can add up to twice the single-step count
-    p->tiles_cap = tiles_capacity(p->grid, 4, 4) * (steps == 2 ? 3 : 1);
     build_tiles(p);
-    build_layout(p);
     return YO_OK;
 }
 
@@ -1398,7 +1493,7 @@ yo_status yo_set_background(yo_plan *p, const float *kappa, const float *mask, y
     if (yo_status st_ = ws_check(p)) return st_;
     hipStream_t s = (hipStream_t)stream;
     const yo_grid &g = p->grid;
-    HIPCHK(yo_launch_to_ghost(kappa, wsp<float>(p, p->L.kappa), 3, 0, 3, g.nz, g.ny, g.nx, p->nxp, s));
+    HIPCHK(yo_launch_to_ghost(kappa, wsp<float>(p, p->L.kappa), 3, 0, 3, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead, s));
     HIPCHK(hipMemcpyAsync(p->chain.mask, mask, sizeof(float) * p->U * p->V, hipMemcpyDeviceToDevice, s));
     p->bg_set = true;
     p->design_set = false;
@@ -1525,8 +1620,8 @@ yo_status yo_set_design(yo_plan *p, const float *C, double beta, yo_stream strea
     if (!p->bg_set) return fail(YO_ESTATE, "yo_set_background first");
     if (!(beta > 0)) return fail(YO_EINVAL, "beta must be positive");
     const yo_design &d = p->des;
-    HIPCHK(yo_launch_chain_forward(p->chain, C, (float)beta, wsp<float>(p, p->L.kappa), p->grid.nx,
-                                   p->grid.ny, p->grid.nz, p->nxp, d.i0, d.j0, d.k_lo, d.k_hi,
+    HIPCHK(yo_launch_chain_forward(p->chain, C, (float)beta, wsp<float>(p, p->L.kappa),
+                                   p->grid.ny, p->nxp, p->sw, p->slead, d.i0, d.j0, d.k_lo, d.k_hi,
                                    (hipStream_t)stream));
     p->beta = beta;
     p->design_set = true;
@@ -2009,7 +2104,8 @@ static yo_status grad_common(yo_plan *p, const float *coef, float *gbox, float *
     a.n_freq = p->n_freq;
     a.nxp = p->nxp;
     a.ny = p->grid.ny;
-    a.nz = p->grid.nz;
+    a.sw = p->sw;
+    a.slead = p->slead;
     for (int i = 0; i < 6; ++i) a.box[i] = p->box[i];
     a.k_lo = p->des.k_lo;
     a.k_hi = p->des.k_hi;
@@ -2222,8 +2318,8 @@ yo_status yo_set_fields(yo_plan *p, int rhs, const float *E, const float *H, yo_
     const YoRhsD &R = p->hrhs[rhs];
     const int par = p->steps_done % p->nbuf;
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_to_ghost(E, R.F[par], 3, 0, 6, g.nz, g.ny, g.nx, p->nxp, s));
-    HIPCHK(yo_launch_to_ghost(H, R.F[par], 3, 3, 6, g.nz, g.ny, g.nx, p->nxp, s));
+    HIPCHK(yo_launch_to_ghost(E, R.F[par], 3, 0, 6, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead, s));
+    HIPCHK(yo_launch_to_ghost(H, R.F[par], 3, 3, 6, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead, s));
     return YO_OK;
 }
 
@@ -2236,8 +2332,8 @@ yo_status yo_get_fields(const yo_plan *p, int rhs, float *E, float *H, yo_stream
     const YoRhsD &R = p->hrhs[rhs];
     const int par = p->steps_done % p->nbuf;
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_from_ghost(R.F[par], E, 3, 0, 6, g.nz, g.ny, g.nx, p->nxp, s));
-    HIPCHK(yo_launch_from_ghost(R.F[par], H, 3, 3, 6, g.nz, g.ny, g.nx, p->nxp, s));
+    HIPCHK(yo_launch_from_ghost(R.F[par], E, 3, 0, 6, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead, s));
+    HIPCHK(yo_launch_from_ghost(R.F[par], H, 3, 3, 6, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead, s));
     return YO_OK;
 }
 
@@ -2247,7 +2343,8 @@ yo_status yo_get_kappa(const yo_plan *p, float *kappa, yo_stream stream)
     if (yo_status st_ = ws_check(p)) return st_;
     const yo_grid &g = p->grid;
     HIPCHK(yo_launch_from_ghost(reinterpret_cast<const float *>(p->ws + p->L.kappa.off), kappa, 3,
-                                0, 3, g.nz, g.ny, g.nx, p->nxp, (hipStream_t)stream));
+                                0, 3, g.nz, g.ny, g.nx, p->nxp, p->sw, p->slead,
+                                (hipStream_t)stream));
     return YO_OK;
 }
 

@@ -123,6 +123,7 @@ struct CpmlCtx {
     int nx, ny, nz, nxp;
     int plo[3], phi[3], W[3];
     int off[3], n[3];        // CPML memory layout (floats), see YoRhsD
+    int xrp;                 // x-slab memories: floats from one (j, k) row to the next
     int qEo, qEn, qHo, qHn;  // memories (first component) read and written this step, E and Ht
     Rsrc ps;                 // this right-hand side's CPML memories
     Cpml cyE, cyH;           // lane l: row j0 - 1 + l
@@ -167,160 +168,146 @@ __device__ __forceinline__ void cpml_slots(int nbuf, int step, int &qEo, int &qE
     }
 }
 
-// Byte offsets of CPML memory q (a slot's first component + c, see
-// cpml_slots) of axis A at site (x, j, k): the lane part (voff) and the wave-uniform part
-// (soff); false when the site is outside the axis' slabs.
+// Byte offset of CPML memory q (a slot's first component + c, see
+// cpml_slots) of axis A at row j of plane k, the wave-uniform part; false
+// when the row is outside the axis' slabs (x-slab: the lane part decides).
+// The lane part is the column's byte offset, as in the field arrays (y and z
+// slabs), or px, that of the column inside the x-slabs (negative outside).
 template <int A>
-__device__ __forceinline__ bool psi_at(const CpmlCtx &C, int q, int x, int j, int k, int pxs,
-                                       int &voff, int &soff)
+__device__ __forceinline__ bool psi_at(const CpmlCtx &C, int q, int j, int k, int &soff)
 {
     if (A == 0) {
-        voff = pxs * (int)sizeof(float);
-        soff = (C.off[0] + q * C.n[0] + (k * C.ny + j) * C.W[0]) * (int)sizeof(float);
-        return pxs >= 0;
+        soff = (C.off[0] + q * C.n[0] + (k * C.ny + j) * C.xrp) * (int)sizeof(float);
+        return true;
     }
     if (A == 1) {
         const int py = slab_index(j, C.ny, C.plo[1], C.phi[1]);
-        voff = x * (int)sizeof(float);
         soff = (C.off[1] + q * C.n[1] + (k * C.W[1] + py) * C.nxp) * (int)sizeof(float);
         return py >= 0;
     }
     const int pz = slab_index(k, C.nz, C.plo[2], C.phi[2]);
-    voff = x * (int)sizeof(float);
     soff = (C.off[2] + q * C.n[2] + (pz * C.ny + j) * C.nxp) * (int)sizeof(float);
     return pz >= 0;
 }
 
-// CPML corrections of the six differences of one Ht site row (x = this
-// lane, row j, plane k): each difference inside an absorbing slab of its
-// axis becomes d/kp + psi with psi <- b psi + c d.  Ht's memories are read
-// from one slot and written to another (halo rows recompute Ht, reading psi
-// of the old step); only the owner writes the new value.  PRE: the old
-// values were loaded with the plane's fields (q[axis][component]); else they
-// are loaded here.
-template <int PM, bool PRE>
-__device__ __forceinline__ void h_cpml(const CpmlCtx &C, int x, int j, int k, int pxs,
-                                       const Cpml &cxH, bool own, const float (&q)[3][2],
-                                       float &dxEz, float &dxEy, float &dyEz, float &dyEx,
-                                       float &dzEy, float &dzEx)
+// What a lane does of a row: the byte offset of its column in a row for loads
+// (past every buffer for columns outside the grid: they read zero) and for
+// stores, that of its column inside the x-slabs (negative outside), whether
+// it owns the column and whether it stores (own, or a pad column of the
+// strip: see yo_col).
+struct LaneX {
+    int xl, xs, px;
+    bool own, st;
+};
+constexpr int kFar = (int)0x80000000;   // past every buffer (all are below 2 GiB)
+
+// lead: lanes before the first owned column (columns x0 - lead + lane)
+__device__ __forceinline__ LaneX lane_x(const YoPlanD &P, int x0, int xn, int lane, int lead)
 {
-    const bool xin = (x >= 0) && (x < C.nx);
-    const bool jin = (j >= 0) && (j < C.ny);
-    if (!(jin && xin && k >= 0)) return;
-    const int qo = C.qHo, qn = C.qHn;
-    int v, s0, s1, t0, t1;
-    if ((PM & 1) && psi_at<0>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<0>(C, qo + 1, x, j, k, pxs, v, s1);
-        float n0, n1;
-        dxEz = pml_diff(dxEz, cxH, PRE ? q[0][0] : bload(C.ps, v, s0), n0);   // Hy
-        dxEy = pml_diff(dxEy, cxH, PRE ? q[0][1] : bload(C.ps, v, s1), n1);   // Hz
-        if (own) {
-            psi_at<0>(C, qn, x, j, k, pxs, v, t0);
-            psi_at<0>(C, qn + 1, x, j, k, pxs, v, t1);
-            bstore(n0, C.ps, v, t0);
-            bstore(n1, C.ps, v, t1);
-        }
-    }
-    if ((PM & 2) && psi_at<1>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<1>(C, qo + 1, x, j, k, pxs, v, s1);
-        const Cpml cy = lane_cpml(C.cyH, j - C.j0m);
-        float n0, n1;
-        dyEz = pml_diff(dyEz, cy, PRE ? q[1][0] : bload(C.ps, v, s0), n0);   // Hx
-        dyEx = pml_diff(dyEx, cy, PRE ? q[1][1] : bload(C.ps, v, s1), n1);   // Hz
-        if (own) {
-            psi_at<1>(C, qn, x, j, k, pxs, v, t0);
-            psi_at<1>(C, qn + 1, x, j, k, pxs, v, t1);
-            bstore(n0, C.ps, v, t0);
-            bstore(n1, C.ps, v, t1);
-        }
-    }
-    if ((PM & 4) && psi_at<2>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<2>(C, qo + 1, x, j, k, pxs, v, s1);
-        const Cpml cz = lane_cpml(C.czH, k - C.k0m);
-        float n0, n1;
-        dzEy = pml_diff(dzEy, cz, PRE ? q[2][0] : bload(C.ps, v, s0), n0);   // Hx
-        dzEx = pml_diff(dzEx, cz, PRE ? q[2][1] : bload(C.ps, v, s1), n1);   // Hy
-        if (own) {
-            psi_at<2>(C, qn, x, j, k, pxs, v, t0);
-            psi_at<2>(C, qn + 1, x, j, k, pxs, v, t1);
-            bstore(n0, C.ps, v, t0);
-            bstore(n1, C.ps, v, t1);
-        }
+    LaneX L;
+    const int x = x0 - lead + lane;
+    const bool in = x >= 0 && x < P.nx && lane <= lead + xn;
+    L.own = lane >= lead && lane < lead + xn;
+    L.xl = in ? yo_col(x, P.sw, P.slead) * (int)sizeof(float) : kFar;
+    // position in the strip that holds the tile: the lanes over its pad
+    // columns store too (values nobody reads), so that a whole strip's row is
+    // stored in whole 128-byte lines.  A line stored in part costs about four
+    // line transfers here: tiles of 60 columns at plain offsets streamed 2.8
+    // TB/s, the same columns in strips with stored pads 4.7 TB/s (a copy: 4.8)
+    const int s = x0 / P.sw, pos = x0 - s * P.sw + lane;   // slead == lead in the strip layout
+    const bool pad = P.strips && (pos < lead || pos >= lead + P.sw || x >= P.nx) && pos < 64 &&
+                     64 * s + pos < P.nxp && lane < xn + 2 * lead + (x >= P.nx ? 64 : 0);
+    L.st = L.own || pad;
+    L.xs = pad ? (64 * s + pos) * (int)sizeof(float) : L.xl;
+    L.px = -1;
+    return L;
+}
+
+// CPML corrections of the six differences of one Ht site row (row j, plane
+// k): each difference inside an absorbing slab of its axis becomes d/kp + psi
+// with psi <- b psi + c d.  Ht's memories are read from one slot and written
+// to another (halo rows recompute Ht, reading psi of the old step); only the
+// owner writes the new value.  PRE: the old values were loaded with the
+// plane's fields (q[axis][component]); else they are loaded here.
+template <int A, bool PRE>
+__device__ __forceinline__ void psi_pair(const CpmlCtx &C, int qo, int qn, int j, int k, const LaneX &L,
+                                         const Cpml &c, bool store, const float (&q)[2], float &d0, float &d1)
+{
+    int s0, s1, t0, t1;
+    if (!psi_at<A>(C, qo, j, k, s0)) return;
+    if (A == 0 && L.px < 0) return;
+    psi_at<A>(C, qo + 1, j, k, s1);
+    const int vl = A == 0 ? L.px : L.xl;
+    float n0, n1;
+    d0 = pml_diff(d0, c, PRE ? q[0] : bload(C.ps, vl, s0), n0);
+    d1 = pml_diff(d1, c, PRE ? q[1] : bload(C.ps, vl, s1), n1);
+    if (store) {
+        const int vs = A == 0 ? L.px : L.xs;
+        psi_at<A>(C, qn, j, k, t0);
+        psi_at<A>(C, qn + 1, j, k, t1);
+        bstore(n0, C.ps, vs, t0);
+        bstore(n1, C.ps, vs, t1);
     }
 }
 
-// CPML corrections of the six differences of one owned E site (each E
+template <int PM, bool PRE>
+__device__ __forceinline__ void h_cpml(const CpmlCtx &C, int j, int k, const LaneX &L, const Cpml &cxH, bool own_row,
+                                       const float (&q)[3][2], float &dxEz, float &dxEy, float &dyEz,
+                                       float &dyEx, float &dzEy, float &dzEx)
+{
+    if (j < 0 || j >= C.ny || k < 0) return;
+    if (PM & 1)   // Hy, Hz
+        psi_pair<0, PRE>(C, C.qHo, C.qHn, j, k, L, cxH, own_row && L.own, q[0], dxEz, dxEy);
+    if (PM & 2)   // Hx, Hz
+        psi_pair<1, PRE>(C, C.qHo, C.qHn, j, k, L, lane_cpml(C.cyH, j - C.j0m), own_row && L.st, q[1], dyEz, dyEx);
+    if (PM & 4)   // Hx, Hy
+        psi_pair<2, PRE>(C, C.qHo, C.qHn, j, k, L, lane_cpml(C.czH, k - C.k0m), own_row && L.st, q[2], dzEy, dzEx);
+}
+
+// CPML corrections of the six differences of one owned E site row (each E
 // memory is read and written by its owner only: one slot, read and written
 // in place, or with three state buffers the slot of the step read and the
 // next one written).  PRE as for h_cpml.
 template <int PM, bool PRE>
-__device__ __forceinline__ void e_cpml(const CpmlCtx &C, int x, int j, int k, int pxs, const Cpml &cxE,
+__device__ __forceinline__ void e_cpml(const CpmlCtx &C, int j, int k, const LaneX &L, const Cpml &cxE,
                                        const float (&q)[3][2], float &dxHz, float &dxHy, float &dyHz,
                                        float &dyHx, float &dzHy, float &dzHx)
 {
-    const int qo = C.qEo, qn = C.qEn;
-    int v, s0, s1, t0, t1;
-    if ((PM & 1) && psi_at<0>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<0>(C, qo + 1, x, j, k, pxs, v, s1);
-        float n0, n1;
-        dxHz = pml_diff(dxHz, cxE, PRE ? q[0][0] : bload(C.ps, v, s0), n0);   // Ey
-        dxHy = pml_diff(dxHy, cxE, PRE ? q[0][1] : bload(C.ps, v, s1), n1);   // Ez
-        psi_at<0>(C, qn, x, j, k, pxs, v, t0);
-        psi_at<0>(C, qn + 1, x, j, k, pxs, v, t1);
-        bstore(n0, C.ps, v, t0);
-        bstore(n1, C.ps, v, t1);
-    }
-    if ((PM & 2) && psi_at<1>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<1>(C, qo + 1, x, j, k, pxs, v, s1);
-        const Cpml cy = lane_cpml(C.cyE, j - C.j0m);
-        float n0, n1;
-        dyHz = pml_diff(dyHz, cy, PRE ? q[1][0] : bload(C.ps, v, s0), n0);   // Ex
-        dyHx = pml_diff(dyHx, cy, PRE ? q[1][1] : bload(C.ps, v, s1), n1);   // Ez
-        psi_at<1>(C, qn, x, j, k, pxs, v, t0);
-        psi_at<1>(C, qn + 1, x, j, k, pxs, v, t1);
-        bstore(n0, C.ps, v, t0);
-        bstore(n1, C.ps, v, t1);
-    }
-    if ((PM & 4) && psi_at<2>(C, qo, x, j, k, pxs, v, s0)) {
-        psi_at<2>(C, qo + 1, x, j, k, pxs, v, s1);
-        const Cpml cz = lane_cpml(C.czE, k - C.k0m);
-        float n0, n1;
-        dzHy = pml_diff(dzHy, cz, PRE ? q[2][0] : bload(C.ps, v, s0), n0);   // Ex
-        dzHx = pml_diff(dzHx, cz, PRE ? q[2][1] : bload(C.ps, v, s1), n1);   // Ey
-        psi_at<2>(C, qn, x, j, k, pxs, v, t0);
-        psi_at<2>(C, qn + 1, x, j, k, pxs, v, t1);
-        bstore(n0, C.ps, v, t0);
-        bstore(n1, C.ps, v, t1);
-    }
+    if (PM & 1)   // Ey, Ez
+        psi_pair<0, PRE>(C, C.qEo, C.qEn, j, k, L, cxE, L.own, q[0], dxHz, dxHy);
+    if (PM & 2)   // Ex, Ez
+        psi_pair<1, PRE>(C, C.qEo, C.qEn, j, k, L, lane_cpml(C.cyE, j - C.j0m), L.st, q[1], dyHz, dyHx);
+    if (PM & 4)   // Ex, Ey
+        psi_pair<2, PRE>(C, C.qEo, C.qEn, j, k, L, lane_cpml(C.czE, k - C.k0m), L.st, q[2], dzHy, dzHx);
 }
 
-// Old CPML memories q (a slot's first component, see cpml_slots) of every axis in PM at one
-// site, or 0 where `use` is false or the site is outside the slab (such a
-// lane's offset is past the buffer, so the load moves no data and the
+// Old CPML memories q (a slot's first component, see cpml_slots) of every
+// axis in PM at one row, or 0 where `use` is false or the lane is outside the
+// slab (its offset is past the buffer, so the load moves no data and the
 // loads need no branch).
 template <int PM>
-__device__ __forceinline__ void psi_preload(const CpmlCtx &C, int q, int x, int j, int k, int pxs,
-                                            bool use, float (&out)[3][2])
+__device__ __forceinline__ void psi_preload(const CpmlCtx &C, int q, int j, int k, const LaneX &L, bool use,
+                                            float (&out)[3][2])
 {
-    const int far = (int)0x80000000;
-    int v, s0, s1;
+    int s0, s1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         if (!(PM & (1 << a))) continue;
         bool in = false;
         if (a == 0) {
-            in = psi_at<0>(C, q, x, j, k, pxs, v, s0);
-            psi_at<0>(C, q + 1, x, j, k, pxs, v, s1);
+            in = psi_at<0>(C, q, j, k, s0);
+            psi_at<0>(C, q + 1, j, k, s1);
         } else if (a == 1) {
-            in = psi_at<1>(C, q, x, j, k, pxs, v, s0);
-            psi_at<1>(C, q + 1, x, j, k, pxs, v, s1);
+            in = psi_at<1>(C, q, j, k, s0);
+            psi_at<1>(C, q + 1, j, k, s1);
         } else {
-            in = psi_at<2>(C, q, x, j, k, pxs, v, s0);
-            psi_at<2>(C, q + 1, x, j, k, pxs, v, s1);
+            in = psi_at<2>(C, q, j, k, s0);
+            psi_at<2>(C, q + 1, j, k, s1);
         }
         in = in && use;
-        out[a][0] = bload(C.ps, in ? v : far, in ? s0 : 0);
-        out[a][1] = bload(C.ps, in ? v : far, in ? s1 : 0);
+        const int v = a == 0 ? (L.px >= 0 ? L.px : kFar) : L.xl;
+        out[a][0] = bload(C.ps, in ? v : kFar, in ? s0 : 0);
+        out[a][1] = bload(C.ps, in ? v : kFar, in ? s1 : 0);
     }
 }
 
@@ -376,13 +363,13 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
     auto xslot = [&](int pp, int dw, int c) -> float & {
         return xme[(pp * YO_MAX_WPB + dw) * 4 * 64 + c * 64];
     };
-    const int x = x0 - 1 + lane;
     // lanes past the halo lane after the last owned one take no part: their
     // column offset lies past every buffer, so their loads move no data (a
     // narrow strip costs only its own columns)
-    const bool lane_used = lane <= xn + 1;
-    const int xo = lane_used ? (clampi(x, -1, nx) + 1) * (int)sizeof(float) : 0x40000000;
-    const bool own_x = (lane >= 1) && (lane <= xn);
+    LaneX L = lane_x(P, x0, xn, lane, P.lead);
+    const int x = x0 - P.lead + lane;
+    const int xo = L.xl, xs_ = L.xs;
+    const bool st_x = L.st;
     // wave-uniform byte offsets of row group (j, k) in the state and kappa arrays
     auto ro = [&](int j, int k) -> int {
         return ((k + 1) * rows + (clampi(j, -1, ny) + 1)) * 6 * rowb;
@@ -392,8 +379,6 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
     };
 
     // ---- CPML data (CPML classes only), read before any store ----
-    const bool xin = (x >= 0) && (x < nx);
-    int pxs = -1;
     Cpml cxE = {1.0f, 0.0f, 1.0f}, cxH = {1.0f, 0.0f, 1.0f};
     CpmlCtx C;
     if (PM) {
@@ -406,6 +391,7 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             C.off[a] = P.psi_off[a];
             C.n[a] = P.psi_n[a];
         }
+        C.xrp = P.psi_xrp;
         C.ps = rsrc_of(R.psi, (size_t)P.psi_total);
         cpml_slots(P.nbuf, step, C.qEo, C.qEn, C.qHo, C.qHn);
         C.j0m = j0 - 1;
@@ -426,12 +412,11 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
                 C.czH = cpml_at(P.prof[2], nz, 3, kk);
             }
         }
-        if ((PM & 1) && xin && lane_used) {
-            pxs = slab_index(x, nx, P.plo[0], P.phi[0]);
-            if (pxs >= 0) {
-                cxE = cpml_at(P.prof[0], nx, 0, x);
-                cxH = cpml_at(P.prof[0], nx, 3, x);
-            }
+        if ((PM & 1) && xo != kFar && slab_index(x, nx, P.plo[0], P.phi[0]) >= 0) {
+            // low slab first, then the high one (YoPlanD::psi_xside floats on)
+            L.px = (x < P.plo[0] ? x : P.psi_xside + x - (nx - P.phi[0])) * (int)sizeof(float);
+            cxE = cpml_at(P.prof[0], nx, 0, x);
+            cxH = cpml_at(P.prof[0], nx, 3, x);
         }
     }
 
@@ -519,13 +504,13 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
 #pragma unroll
             for (int r = 0; r <= TY; ++r) {
                 const int j = j0 - 1 + r;
-                const bool use = (r > 0 || bottom) && xin && lane_used && kin && j >= 0 && j < ny;
-                psi_preload<PM>(C, C.qHo, x, j, k, pxs, use, qH[r]);
+                const bool use = (r > 0 || bottom) && kin && j >= 0 && j < ny;
+                psi_preload<PM>(C, C.qHo, j, k, L, use, qH[r]);
             }
 #pragma unroll
             for (int r = 1; r <= TY; ++r) {
-                const bool use = own_x && k >= k0 && r <= jn;
-                psi_preload<PM>(C, C.qEo, x, j0 - 1 + r, k, pxs, use, qE[r - 1]);
+                const bool use = k >= k0 && r <= jn;
+                psi_preload<PM>(C, C.qEo, j0 - 1 + r, k, L, use, qE[r - 1]);
             }
         }
         const int pp = k & 1;
@@ -548,21 +533,19 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             float dxEz = ez_i1 - Ec[2][r];
             float dxEy = ey_i1 - Ec[1][r];
             float dyEx = Ec[0][r + 1] - Ec[0][r];
-            const bool own = own_x && own_k && (r >= 1) && (r <= jn);
-            if (PM)
-                h_cpml<PM, PRE>(C, lane_used ? x : -1, j, k, pxs, cxH, own, qH[r], dxEz, dxEy,
-                                dyEz, dyEx, dzEy, dzEx);
+            const bool own_row = own_k && (r >= 1) && (r <= jn);
+            if (PM) h_cpml<PM, PRE>(C, j, k, L, cxH, own_row, qH[r], dxEz, dxEy, dyEz, dyEx, dzEy, dzEx);
             const float hx = Ho_[0][r] - fmaf(sy, dyEz, -(sz * dzEy));
             const float hy = Ho_[1][r] - fmaf(sz, dzEx, -(sx * dxEz));
             const float hz = Ho_[2][r] - fmaf(sx, dxEy, -(sy * dyEx));
             Hc[0][r] = hx;
             Hc[1][r] = hy;
             Hc[2][r] = hz;
-            if (own) {
+            if (own_row && st_x) {
                 const int o = ro(j, k) + hb;
-                bstore_nt(hx, Fn, xo, o);
-                bstore_nt(hy, Fn, xo, rowb + o);
-                bstore_nt(hz, Fn, xo, 2 * rowb + o);
+                bstore_nt(hx, Fn, xs_, o);
+                bstore_nt(hy, Fn, xs_, rowb + o);
+                bstore_nt(hz, Fn, xs_, 2 * rowb + o);
             }
         }
         if (COOP) {
@@ -591,8 +574,7 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             float dxHz = Hc[2][r] - hz_im;
             float dxHy = Hc[1][r] - hy_im;
             float dyHx = Hc[0][r] - Hc[0][r - 1];
-            if (PM && own_x)
-                e_cpml<PM, PRE>(C, x, j, k, pxs, cxE, qE[r - 1], dxHz, dxHy, dyHz, dyHx, dzHy, dzHx);
+            if (PM) e_cpml<PM, PRE>(C, j, k, L, cxE, qE[r - 1], dxHz, dxHy, dyHz, dyHx, dzHy, dzHx);
             float ex = fmaf(Kv[0][r - 1], fmaf(sy, dyHz, -(sz * dzHy)), Ec[0][r]);
             float ey = fmaf(Kv[1][r - 1], fmaf(sz, dzHx, -(sx * dxHz)), Ec[1][r]);
             float ez = fmaf(Kv[2][r - 1], fmaf(sx, dxHy, -(sy * dyHx)), Ec[2][r]);
@@ -600,11 +582,11 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             ex = (j == 0 || k == 0) ? 0.0f : ex;
             ey = (x == 0 || k == 0) ? 0.0f : ey;
             ez = (x == 0 || j == 0) ? 0.0f : ez;
-            if (own_x) {
+            if (st_x) {
                 const int o = ro(j, k) + eb;
-                bstore_nt(ex, Fn, xo, o);
-                bstore_nt(ey, Fn, xo, rowb + o);
-                bstore_nt(ez, Fn, xo, 2 * rowb + o);
+                bstore_nt(ex, Fn, xs_, o);
+                bstore_nt(ey, Fn, xs_, rowb + o);
+                bstore_nt(ez, Fn, xs_, 2 * rowb + o);
             }
         }
 #pragma unroll
@@ -739,7 +721,7 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                                            const int4 t, const int w, const int wpb, const int lane,
                                            float *xs)
 {
-    const int nx = P.nx, ny = P.ny, nxp = P.nxp;
+    const int ny = P.ny, nxp = P.nxp;
     const int rows = ny + 2;
     const size_t groups = (size_t)(P.nz + 2) * rows;
     const int rowb = nxp * (int)sizeof(float);
@@ -771,8 +753,10 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
         return xme[(pp * wpb + dw) * 20 * 64 + q * 64];
     };
     const int x = x0 - 2 + lane;
-    const int xo = (clampi(x, -1, nx) + 1) * (int)sizeof(float);
-    const bool own_x = (lane >= 2) && (lane < 2 + xn);
+    const LaneX L = lane_x(P, x0, xn, lane, 2);
+    const int xo = x <= x0 + xn + 1 && x >= 0 && x < P.nx ? yo_col(x, P.sw, P.slead) * (int)sizeof(float) : kFar;
+    const int xs_ = L.xs;
+    const bool own_x = L.own, st_x = L.st;
     // R2's outermost layer, whose step-n+1 state the tiles around R2 read
     const int ra0 = P.r2[0], ra1 = P.r2[1], rb0 = P.r2[2], rb1 = P.r2[3], rc0 = P.r2[4], rc1 = P.r2[5];
     const bool rim_x = own_x && (x == ra0 || x == ra1 - 1);
@@ -781,7 +765,6 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
     const int nz = P.nz, zlo = P.plo[2], zhi = P.phi[2];
     const Rsrc PS = rsrc_of(R.psi, (size_t)P.psi_total);
     const int s0 = step % 3, s1 = (step + 1) % 3, s2 = (step + 2) % 3;
-    const int xv = clampi(x, 0, nx - 1) * (int)sizeof(float);
     auto zo = [&](int q, int pz, int j) -> int {
         return (P.psi_off[2] + q * P.psi_n[2] + (pz * ny + j) * nxp) * (int)sizeof(float);
     };
@@ -919,8 +902,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
             float dzEy_ = dzEy, dzEx_ = dzEx;
             if (ZP && pz >= 0) {
                 const int o = zo(6 + 2 * s0, pz, j0 - 2 + r);
-                dzEy_ = pml_diff(dzEy, czH, bload(PS, xv, o), qH1[0][r]);                       // Hx
-                dzEx_ = pml_diff(dzEx, czH, bload(PS, xv, o + P.psi_n[2] * 4), qH1[1][r]);   // Hy
+                dzEy_ = pml_diff(dzEy, czH, bload(PS, xo, o), qH1[0][r]);                       // Hx
+                dzEx_ = pml_diff(dzEx, czH, bload(PS, xo, o + P.psi_n[2] * 4), qH1[1][r]);   // Hy
             }
             Hh[0][r] = Ho[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
             Hh[1][r] = Ho[1][r] - fmaf(sz, dzEx_, -(sx * dxEz));
@@ -945,8 +928,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                 float dzHy_ = dzHy, dzHx_ = dzHx;
                 if (ZP && pz >= 0) {
                     const int o = zo(2 * s0, pz, j);
-                    dzHy_ = pml_diff(dzHy, czE, bload(PS, xv, o), qE1[0][r]);                       // Ex
-                    dzHx_ = pml_diff(dzHx, czE, bload(PS, xv, o + P.psi_n[2] * 4), qE1[1][r]);   // Ey
+                    dzHy_ = pml_diff(dzHy, czE, bload(PS, xo, o), qE1[0][r]);                       // Ex
+                    dzHx_ = pml_diff(dzHx, czE, bload(PS, xo, o + P.psi_n[2] * 4), qE1[1][r]);   // Ey
                 }
                 float ex = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), Ec[0][r]);
                 float ey = fmaf(Kc[1][r], fmaf(sz, dzHx_, -(sx * dxHz)), Ec[1][r]);
@@ -960,17 +943,17 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                 E1c[2][r] = ez;
                 // the step-n+1 state of R2's outermost layer
                 const bool own_r = r >= 2 && r - 2 < jn;
-                if (own_k && own_r && own_x && (rim_k || rim_x || j == rb0 || j == rb1 - 1)) {
+                if (own_k && own_r && ((st_x && (rim_k || j == rb0 || j == rb1 - 1)) || rim_x)) {
                     const int o = ro(j, k);
-                    bstore_nt(ex, FB, xo, eb + o);
-                    bstore_nt(ey, FB, xo, eb + rowb + o);
-                    bstore_nt(ez, FB, xo, eb + 2 * rowb + o);
-                    bstore_nt(Hh[0][r], FB, xo, hb + o);
-                    bstore_nt(Hh[1][r], FB, xo, hb + rowb + o);
-                    bstore_nt(Hh[2][r], FB, xo, hb + 2 * rowb + o);
+                    bstore_nt(ex, FB, xs_, eb + o);
+                    bstore_nt(ey, FB, xs_, eb + rowb + o);
+                    bstore_nt(ez, FB, xs_, eb + 2 * rowb + o);
+                    bstore_nt(Hh[0][r], FB, xs_, hb + o);
+                    bstore_nt(Hh[1][r], FB, xs_, hb + rowb + o);
+                    bstore_nt(Hh[2][r], FB, xs_, hb + 2 * rowb + o);
                     if (ZP && pz >= 0) {
-                        bstore(qH1[0][r], PS, xv, zo(6 + 2 * s1, pz, j));
-                        bstore(qH1[1][r], PS, xv, zo(6 + 2 * s1 + 1, pz, j));
+                        bstore(qH1[0][r], PS, xs_, zo(6 + 2 * s1, pz, j));
+                        bstore(qH1[1][r], PS, xs_, zo(6 + 2 * s1 + 1, pz, j));
                     }
                 }
             }
@@ -993,10 +976,10 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     float n0, n1;
                     dzEy_ = pml_diff(dzEy, czHp, qH1p[0][r], n0);   // Hx
                     dzEx_ = pml_diff(dzEx, czHp, qH1p[1][r], n1);   // Hy
-                    if (own_x && r >= 2 && r - 2 < jn && km >= k0 && km < k1) {
+                    if (st_x && r >= 2 && r - 2 < jn && km >= k0 && km < k1) {
                         const int j = j0 - 2 + r;
-                        bstore(n0, PS, xv, zo(6 + 2 * s2, pzp, j));
-                        bstore(n1, PS, xv, zo(6 + 2 * s2 + 1, pzp, j));
+                        bstore(n0, PS, xs_, zo(6 + 2 * s2, pzp, j));
+                        bstore(n1, PS, xs_, zo(6 + 2 * s2 + 1, pzp, j));
                     }
                 }
                 H2[0][r] = Hhp[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
@@ -1022,9 +1005,9 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                         float n0, n1;
                         dzHy_ = pml_diff(dzHy, czEp, qE1p[0][r], n0);   // Ex
                         dzHx_ = pml_diff(dzHx, czEp, qE1p[1][r], n1);   // Ey
-                        if (own_x) {
-                            bstore(n0, PS, xv, zo(2 * s2, pzp, j));
-                            bstore(n1, PS, xv, zo(2 * s2 + 1, pzp, j));
+                        if (st_x) {
+                            bstore(n0, PS, xs_, zo(2 * s2, pzp, j));
+                            bstore(n1, PS, xs_, zo(2 * s2 + 1, pzp, j));
                         }
                     }
                     float ex = fmaf(Kp[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), E1p[0][r]);
@@ -1033,14 +1016,14 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     ex = (j == 0 || km == 0) ? 0.0f : ex;
                     ey = (x == 0 || km == 0) ? 0.0f : ey;
                     ez = (x == 0 || j == 0) ? 0.0f : ez;
-                    if (own_x) {
+                    if (st_x) {
                         const int o = ro(j, km);
-                        bstore_nt(ex, FC, xo, eb + o);
-                        bstore_nt(ey, FC, xo, eb + rowb + o);
-                        bstore_nt(ez, FC, xo, eb + 2 * rowb + o);
-                        bstore_nt(H2[0][r], FC, xo, hb + o);
-                        bstore_nt(H2[1][r], FC, xo, hb + rowb + o);
-                        bstore_nt(H2[2][r], FC, xo, hb + 2 * rowb + o);
+                        bstore_nt(ex, FC, xs_, eb + o);
+                        bstore_nt(ey, FC, xs_, eb + rowb + o);
+                        bstore_nt(ez, FC, xs_, eb + 2 * rowb + o);
+                        bstore_nt(H2[0][r], FC, xs_, hb + o);
+                        bstore_nt(H2[1][r], FC, xs_, hb + rowb + o);
+                        bstore_nt(H2[2][r], FC, xs_, hb + 2 * rowb + o);
                     }
                 }
             }
@@ -1164,7 +1147,7 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
         const int c = q / bsz, rem = q - c * bsz;
         const int bk = rem / (bx * by), rem2 = rem - bk * bx * by;
         const int bj = rem2 / bx, bi = rem2 - bj * bx;
-        e = F[yo_off(c, P.box[0] + bi, P.box[1] + bj, P.box[2] + bk, P.ny, P.nxp, 6)];
+        e = F[yo_off(c, yo_col(P.box[0] + bi, P.sw, P.slead), P.box[1] + bj, P.box[2] + bk, P.ny, P.nxp, 6)];
         acc = R.dft_box + q;
         fstride = R.box_fstride;
     } else {
@@ -1181,7 +1164,7 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
         const int cx = sel3(pl.axis, idx, pl.lo0 + ai, pl.lo0 + ai);
         const int cy = sel3(pl.axis, pl.lo0 + ai, idx, pl.lo1 + b);
         const int cz = sel3(pl.axis, pl.lo1 + b, pl.lo1 + b, idx);
-        e = F[yo_off(c, cx, cy, cz, P.ny, P.nxp, 6)];
+        e = F[yo_off(c, yo_col(cx, P.sw, P.slead), cy, cz, P.ny, P.nxp, 6)];
         acc = R.dft_mon + qm;
         fstride = R.mon_fstride;
     }
@@ -1216,11 +1199,12 @@ __global__ __launch_bounds__(256) void k_source(const YoAuxArgs a)
     const int cx = sel3(pl.axis, idx, pl.lo0 + ai, pl.lo0 + ai);
     const int cy = sel3(pl.axis, pl.lo0 + ai, idx, pl.lo1 + b);
     const int cz = sel3(pl.axis, pl.lo1 + b, pl.lo1 + b, idx);
-    const size_t o = yo_off(c, cx, cy, cz, P.ny, P.nxp, 6);
+    const int col = yo_col(cx, P.sw, P.slead);
+    const size_t o = yo_off(c, col, cy, cz, P.ny, P.nxp, 6);
     const float2 jv = R.src_j[q];
     const float j = fmaf(jv.x, st.x, jv.y * st.y);
     float *F = R.F[(step + 1) % P.nbuf];
-    F[o] = fmaf(-P.kappa[yo_off(c, cx, cy, cz, P.ny, P.nxp, 3)], j, F[o]);
+    F[o] = fmaf(-P.kappa[yo_off(c, col, cy, cz, P.ny, P.nxp, 3)], j, F[o]);
 }
 
 __global__ void k_ctr(const YoCtrArgs a, int set_value)
