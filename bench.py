@@ -29,9 +29,11 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Gcell-updates/s + % HBM peak; adjoint gradients/hour; p50/p99 solve latency"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ["paper_2505_03352_amd/csrc/yo_step.hip", "paper_2505_03352_amd/csrc/yo_internal.h"]
+KERNEL_SOURCES = ["paper_2505_03352_amd/csrc/" + f for f in ("yo_step.hip", "yo_pair.hip", "yo_device.h",
+                                                             "yo_internal.h")]
 PROFILES = os.path.join(ROOT, "profiles")
-PART_NAMES = ("interior", "shell", "two_step", "frame", "zslab_two_step", "shell_paired")
+PART_NAMES = ("interior", "shell", "two_step", "frame", "zslab_two_step", "shell_paired",
+              "whole_pair", "whole_pair_shell")
 
 
 def log(*a):
@@ -54,10 +56,10 @@ def kernel_sha() -> str:
 # around it (the same and no prefetch), the z-slabs' two-step launch and the
 # shell of paired steps (2048 decides which tiles each holds; 4096 and 8192
 # the two-step tiles' rows and blocks; 16384 the shell tiles' rows); 512
-# (two steps per launch) in all
+# (two steps per launch) in all, and alone in the whole-grid pairs' launches
 SPLIT_BITS = (1 | 2 | 16 | 32 | 128 | 256 | 512, 1 | 2 | 4 | 8 | 64 | 128 | 256 | 512 | 2048 | 16384,
               1 | 2 | 128 | 256 | 512 | 4096 | 8192, 1 | 2 | 32 | 128 | 256 | 512,
-              1 | 2 | 128 | 256 | 512 | 2048, 1 | 2 | 4 | 8 | 64 | 128 | 256 | 512 | 2048 | 16384)
+              1 | 2 | 128 | 256 | 512 | 2048, 1 | 2 | 4 | 8 | 64 | 128 | 256 | 512 | 2048 | 16384, 512, 512)
 
 
 def part_split(tiling, part: int) -> str:
@@ -267,7 +269,9 @@ KERNEL_OF_PART = ("k_yee_step interior tiles", "k_yee_step CPML shell tiles",
                   "k_yee_step2 two-step region (two steps per launch)",
                   "k_yee_step interior tiles around the two-step region",
                   "k_yee_step2 z-slabs under the two-step region (two steps per launch)",
-                  "k_yee_step CPML shell tiles of the steps in pairs")
+                  "k_yee_step CPML shell tiles of the steps in pairs",
+                  "k_yee_pair whole-grid tiles clear of slabs and planes (two steps per launch)",
+                  "k_yee_pair whole-grid tiles, or those with slabs or planes (two steps per launch)")
 
 
 def part_rooflines(plan, timed, tiling, workload, sha):
@@ -343,7 +347,7 @@ def realistic_gradients(args, torch, n_timed=1):
         grad(True)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / n_timed
-    timed = [plan.timing(q) for q in range(6)]
+    timed = [plan.timing(q) for q in range(len(PART_NAMES))]
     plan.set_timing(0, 0)
     plan.reset(YO_BOTH)
     plan.advance(YO_BOTH, 4)
@@ -437,7 +441,7 @@ def bench_headline(args):
         bench_step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    timed = [plan.timing(q) for q in range(6)]
+    timed = [plan.timing(q) for q in range(len(PART_NAMES))]
     plan.set_timing(0, 0)
     ms = (t1 - t0) / args.steps * 1e3
     cells_per_step = plan.n_rhs * dev.cells * block

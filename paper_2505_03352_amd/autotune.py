@@ -203,11 +203,16 @@ def tune(plan, which: int = YO_BOTH, shared: Optional[Iterable] = None, n_launch
             ff = min(tf, key=tf.get)
             fs = min(ts, key=ts.get)
             per_step = 0.5 * (t2 + t4) + tf[ff] + ts[fs]
+            # plans whose pairs cover the whole grid in their own launches
+            # (parts 6 and 7) run those whatever the split of the others
+            tw = sum(_time(plan, zc2, fl0, part, which, n_launch, stream) for part in (6, 7))
+            if tw > 0.0:
+                per_step = 0.5 * tw
             fl = fl0 | ff | fs
             timings[f"pairs_z{zc2}f{base}"] = dict(two_step=round(t2, 4), zslab_two_step=round(t4, 4),
                                                    frame={str(k): round(v, 4) for k, v in tf.items()},
                                                    shell={str(k): round(v, 4) for k, v in ts.items()},
-                                                   best=fl, ms=round(per_step, 4))
+                                                   whole_grid=round(tw, 4), best=fl, ms=round(per_step, 4))
             if per_step < total:
                 total, zc, flags = per_step, zc2, fl
     overlap = None

@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libyeeopt.so")
-SOURCES = ["yo_step.hip", "yo_chain.hip", "yo_runtime.hip"]
+SOURCES = ["yo_step.hip", "yo_pair.hip", "yo_chain.hip", "yo_runtime.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -11,6 +11,10 @@
 #define YO_TY 4           // rows per wave
 #define YO_TY2 6          // rows per wave of the two-step region's taller tiles
 #define YO_MAX_WPB 8      // waves per block of the step kernel: 4 or 8
+#define YO_PAIR_TY 2      // whole-grid pairs: rows per wave,
+#define YO_PAIR_W 8       // waves per block,
+#define YO_PAIR_GROUP 32  // tiles that consecutive blocks take for one right-hand side,
+#define YO_PAIR_YROWS 12  // and the most y-slab rows a block may hold
 
 // Field arrays carry one ghost layer on every face and keep the components
 // of one (j, k) row together: component c of cell (x, j, k), x in [-1, nx],
@@ -188,6 +192,9 @@ hipError_t yo_launch_step(int pm, bool coop, bool prefetch, const YoStepArgs &ar
 // tile per block, its waves stacked in y and sharing rows through LDS
 hipError_t yo_launch_step2(bool zslab, int rows, bool coop, const YoStepArgs &args, int blocks,
                            hipStream_t s);
+// two steps over whole-grid tiles (one block each, YO_PAIR_W waves); shell:
+// tiles with x- or y-slabs, source planes or the grid's first column or row
+hipError_t yo_launch_pair(bool shell, const YoStepArgs &args, int blocks, hipStream_t s);
 hipError_t yo_launch_dft(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_source(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_ctr(const YoCtrArgs &args, int set_value, hipStream_t s);

@@ -169,6 +169,11 @@ struct yo_plan {
     // and the shell's tiles they replace in steps that go in pairs (its last
     // n_c4 tiles, those of class 4)
     int nz2 = 0, n_c4 = 0;
+    // whole-grid pairs (build_all_tiles): their tiles, the table's last n_all
+    // (0: the plan's pairs go through the two-step region and its
+    // surroundings), the first n_allc of them clear of the x- and y-slabs
+    // and the planes
+    int n_all = 0, n_allc = 0;
     bool bg_set = false, design_set = false;
     double beta = 0;
     int steps_done = 0;
@@ -196,8 +201,8 @@ struct yo_plan {
     // every part); tm_ev[q] holds the event pairs of part q (see part_range)
     // recorded since yo_set_timing (tm_done[q] of them), created as needed
     int tm_part = 0, tm_n = 0;
-    int tm_done[6] = {0, 0, 0, 0, 0, 0};
-    std::vector<hipEvent_t> tm_ev[6];
+    int tm_done[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    std::vector<hipEvent_t> tm_ev[8];
 };
 
 namespace {
@@ -710,6 +715,87 @@ int short_chunk(const yo_plan *p)
     return kc;
 }
 
+// Whole-grid pairs (yo_pair.hip): tiles of one strip of columns, at most
+// W TY - 4 rows and a chunk of planes, one block each.  They take every cell
+// two steps per launch, the absorbing layers and the sources included, where
+// the kernel can: planes normal to x only, and y-slab rows and x-slab columns
+// that fit its LDS.  Planes per tile: the chip holds about kPairSlots blocks,
+// a tile costs its planes plus the three it recomputes, so the chunk with the
+// fewest rounds times planes is taken.
+constexpr int kPairSlots = 512;
+void build_all_tiles(yo_plan *p)
+{
+    p->n_all = 0;
+    const int n[3] = {p->grid.nx, p->grid.ny, p->grid.nz};
+    constexpr int LR = YO_PAIR_W * YO_PAIR_TY;
+    for (const yo_plane &pl : p->src_planes)
+        if (pl.axis != 0) return;
+    for (const yo_plane &pl : p->port_planes)
+        if (pl.axis != 0) return;
+    if (p->plo[0] + p->phi[0] > 32 || p->plo[1] > YO_PAIR_YROWS || p->phi[1] > YO_PAIR_YROWS) return;
+    const int nyb = (n[1] + LR - 5) / (LR - 4);
+    std::vector<int> yj, yn;
+    for (int b = 0, j = 0; b < nyb; ++b) {
+        const int jn = n[1] / nyb + (b < n[1] % nyb ? 1 : 0);
+        int lo = 0, hi = 0;
+        for (int q = j - 2; q < j - 2 + LR; ++q) {
+            lo += q >= 0 && q < p->plo[1];
+            hi += q < n[1] && q >= n[1] - p->phi[1];
+        }
+        if (lo && hi) return;
+        yj.push_back(j);
+        yn.push_back(jn);
+        j += jn;
+    }
+    const long flat = (long)((n[0] + 59) / 60) * nyb * std::max(p->n_phys, 1);
+    int nzc = 1;
+    long best = -1;
+    for (int q = 1; q == 1 || n[2] / q >= 4; ++q) {
+        const long cost = (flat * q + kPairSlots - 1) / kPairSlots * ((n[2] + q - 1) / q + 3);
+        if (best < 0 || cost < best) {
+            best = cost;
+            nzc = q;
+        }
+    }
+    const size_t t0 = p->tiles_host.size();
+    for (int c = 0, k = 0; c < nzc; ++c) {
+        const int kn = n[2] / nzc + (c < n[2] % nzc ? 1 : 0);
+        for (int b = 0; b < nyb; ++b)
+            for (int x = 0; x < n[0]; x += 60) {
+                const int xn = std::min(60, n[0] - x);
+                int4 t;
+                t.x = x | (xn << 16);
+                t.y = yj[b] | (yn[b] << 16);
+                t.z = k | ((k + kn) << 16);
+                t.w = (x - 2 < p->plo[0] || x + xn + 2 > n[0] - p->phi[0] ? 1 : 0) |
+                      (yj[b] - 2 < p->plo[1] || yj[b] - 2 + LR > n[1] - p->phi[1] ? 2 : 0) |
+                      (k < p->plo[2] || k + kn > n[2] - p->phi[2] ? 4 : 0);
+                p->tiles_host.push_back(t);
+            }
+        k += kn;
+    }
+    p->n_all = (int)(p->tiles_host.size() - t0);
+    // tiles clear of the x- and y-slabs, the planes and the grid's first column
+    // and row
+    auto clear = [&](const int4 &t) {
+        const int xa = (t.x & 0xffff) - 2, xb = (t.x & 0xffff) + (t.x >> 16) + 2;
+        bool plane = false;
+        auto meets = [&](const yo_plane &pl, int nc) { plane = plane || (pl.index + (nc == 5) >= xa && pl.index < xb); };
+        for (const yo_plane &pl : p->src_planes) meets(pl, 2);
+        for (const yo_plane &pl : p->port_planes) meets(pl, p->mon_nc);
+        return !(t.w & 3) && !plane && (t.x & 0xffff) && (t.y & 0xffff);
+    };
+    // go first, in a launch of their own without the code for all that, where either launch fills the chip several times over; else one launch
+    // takes all (320x240x96 with 6 right-hand sides: 463 us per step in one,
+    // 516 in two, whose tails leave the chip idle; 600x400x120 with 25: 6.2 ms in
+    // one, 5.8 in two)
+    const auto first = p->tiles_host.begin() + t0;
+    const long inner = std::count_if(first, p->tiles_host.end(), clear), rhs = std::max(p->n_phys, 1);
+    const bool two = inner * rhs >= 4 * kPairSlots && (p->n_all - inner) * rhs >= 4 * kPairSlots;
+    p->n_allc = two ? (int)inner : 0;
+    if (two) std::stable_partition(first, p->tiles_host.end(), clear);
+}
+
 // Tile table: the interior tiles, then the CPML shell, each in space order
 // (z, y, x fastest).  Along each axis the region clear of the absorbing
 // slabs is [lo + 1, n - hi) for a CPML of lo/hi cells (no owned site and no
@@ -797,7 +883,11 @@ void build_tiles(yo_plan *p)
         p->n_c4 = (int)(p->tiles_host.end() - mid);
     }
     for (int i = 0; i < 6; ++i) p->r2[i] = 0;
-    if (p->tsteps == 2 && (p->tflags & YO_TILE_PAIRS)) build_pair_tiles(p, lo, hi);
+    p->n_all = 0;
+    if (p->tsteps == 2 && (p->tflags & YO_TILE_PAIRS)) {
+        build_pair_tiles(p, lo, hi);
+        build_all_tiles(p);
+    }
 }
 
 size_t tiles_capacity(const yo_grid &g, int ty_min, int kc_min)
@@ -1027,7 +1117,7 @@ void yo_plan_destroy(yo_plan *p)
     if (p->side_stream) (void)hipStreamDestroy(p->side_stream);
     if (p->ov_fork) (void)hipEventDestroy(p->ov_fork);
     if (p->ov_join) (void)hipEventDestroy(p->ov_join);
-    for (int q = 0; q < 6; ++q)
+    for (int q = 0; q < 8; ++q)
         for (hipEvent_t e : p->tm_ev[q]) (void)hipEventDestroy(e);
     delete p;
 }
@@ -1393,8 +1483,9 @@ yo_status yo_set_time_blocking(yo_plan *p, int steps)
     const size_t cap_was = p->tiles_cap;
     p->nbuf = steps == 2 ? 3 : 2;
     p->tsteps = steps;
-    // the two-step and frame tiles can add up to twice the single-step count
-    p->tiles_cap = tiles_capacity(p->grid, YO_TY, kMinChunk) * (steps == 2 ? 3 : 1);
+    // the two-step and frame tiles can add up to twice the single-step count,
+    // the whole-grid pairs' are fewer
+    p->tiles_cap = tiles_capacity(p->grid, YO_TY, kMinChunk) * (steps == 2 ? 4 : 1);
     if (!build_layout(p)) {
         p->nbuf = nbuf_was;
         p->tsteps = tsteps_was;
@@ -1699,7 +1790,7 @@ static void aux_args(yo_plan *const *plans, const int *which, int cnt, bool dft,
 // tiles of launch part `part`: 0 interior, 1 CPML shell, 2 two-step region,
 // 3 the interior around it (single steps), 4 the z-slabs under the two-step
 // region (two steps, YO_TILE_ZPAIRS), 5 the CPML shell of steps that go in
-// pairs (without the tiles of part 4)
+// pairs (without the tiles of part 4), 6 whole-grid pairs (two steps)
 static void part_range(const yo_plan *p, int part, int &t0, int &t1)
 {
     switch (part) {
@@ -1708,6 +1799,8 @@ static void part_range(const yo_plan *p, int part, int &t0, int &t1)
     case 2: t0 = p->n_tiles; t1 = p->n_tiles + p->n2; break;
     case 3: t0 = p->n_tiles + p->n2; t1 = t0 + p->nfr; break;
     case 4: t0 = p->n_tiles + p->n2 + p->nfr; t1 = t0 + p->nz2; break;
+    case 6: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + p->n_allc; break;
+    case 7: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2 + p->n_allc; t1 = t0 + p->n_all - p->n_allc; break;
     default: t0 = p->n_int; t1 = p->n_tiles - (p->nz2 ? p->n_c4 : 0); break;
     }
 }
@@ -1718,9 +1811,10 @@ static int step_args(yo_plan *const *plans, const int *which, int cnt, int part,
 {
     memset(&a, 0, sizeof(YoStepArgs));
     a.n_slots = cnt;
-    const int wpb = (plans[0]->tflags & YO_TILE_WPB8) ? 8 : 4;
+    const int wpb = part >= 6 ? YO_PAIR_W : (plans[0]->tflags & YO_TILE_WPB8) ? 8 : 4;
     const int f = plans[0]->tflags;
-    const bool coop = part == 0   ? (f & YO_TILE_COOP_INT) != 0
+    const bool coop = part >= 6   ? true
+                      : part == 0   ? (f & YO_TILE_COOP_INT) != 0
                       : part == 2 ? (f & YO_TILE_COOP_PAIRS) != 0
                                   : (part == 1 || part == 5) && (f & YO_TILE_COOP_SHELL) != 0;
     int tot = 0;
@@ -1755,6 +1849,7 @@ static hipError_t launch_part(const yo_plan *p0, int part, const YoStepArgs &a, 
     if (part == 2)
         return yo_launch_step2(false, (f & YO_TILE_PAIR6) ? YO_TY2 : YO_TY, (f & YO_TILE_COOP_PAIRS) != 0, a,
                                blocks, s);
+    if (part >= 6) return yo_launch_pair(part == 7, a, blocks, s);
     if (part == 4) return yo_launch_step2(true, YO_TY, false, a, blocks, s);
     if (part == 3)
         return yo_launch_step((f & YO_TILE_XINT) ? 1 : 0, false, !(f & YO_TILE_NOPF_INT), a, blocks, s);
@@ -1785,12 +1880,15 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
                               int dft_every = 1, bool pairs = false)
 {
     yo_plan *const p0 = plans[0];
-    const bool overlap = pairs && (p0->tflags & YO_TILE_OVERLAP) && p0->side_stream;
+    // whole-grid pairs where every plan's can go that way
+    bool whole = pairs;
+    for (int i = 0; i < n; ++i) whole = whole && plans[i]->n_all > 0;
+    const bool overlap = pairs && !whole && (p0->tflags & YO_TILE_OVERLAP) && p0->side_stream;
     for (int base = 0; base < n; base += YO_MAX_SLOTS) {
         const int cnt = std::min(YO_MAX_SLOTS, n - base);
-        static thread_local YoStepArgs A[6];
-        int blocks[6] = {0, 0, 0, 0, 0, 0};
-        for (int part = 0; part < (pairs ? 6 : 2); ++part)
+        static thread_local YoStepArgs A[8];
+        int blocks[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int part = 0; part < (pairs ? 8 : 2); ++part)
             blocks[part] = step_args(plans + base, which + base, cnt, part, A[part]);
         YoAuxArgs ad, as;
         aux_args(plans + base, which + base, cnt, true, ad);
@@ -1822,7 +1920,11 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
                 ad.k_offset = k;
                 HIPCHK(yo_launch_dft(ad, s));
             }
-            if (pairs && k + 1 < n_launch) {
+            if (whole && k + 1 < n_launch) {
+                if ((st = launch(6, k, s))) return st;
+                if ((st = launch(7, k, s))) return st;
+                k += 2;
+            } else if (pairs && k + 1 < n_launch) {
                 // the two-step launches (R2, and with YO_TILE_ZPAIRS the
                 // z-slabs under it: part 5 is then the shell without them)
                 hipStream_t s2 = overlap ? p0->side_stream : s;
@@ -1863,12 +1965,16 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
 // step (no DFT in the call, or pulse DFTs on even steps only).
 static bool pairs_ok(yo_plan *const *plans, int n, int n_launch, bool with_dft, int every)
 {
+    bool region = true, whole = true;
     for (int i = 0; i < n; ++i) {
         const yo_plan *p = plans[i];
-        // (a plan whose two-step region came out empty has no frame tiles either)
-        if (!(p->tflags & YO_TILE_PAIRS) || p->tsteps != 2 || p->n2 == 0) return false;
+        if (!(p->tflags & YO_TILE_PAIRS) || p->tsteps != 2) return false;
         if (p->steps_done + n_launch > p->n_steps) return false;
+        // (a plan whose two-step region came out empty has no frame tiles either)
+        region = region && p->n2 > 0;
+        whole = whole && p->n_all > 0;
     }
+    if (!region && !whole) return false;
     if (with_dft) {
         if (every % 2) return false;
         for (int i = 0; i < n; ++i)
@@ -2183,14 +2289,14 @@ yo_status yo_set_timing(yo_plan *p, int part, int n_last)
     // starting clears what was recorded; stopping (n_last = 0) keeps it for
     // yo_get_timing
     if (n_last > 0)
-        for (int q = 0; q < 6; ++q) p->tm_done[q] = 0;
+        for (int q = 0; q < 8; ++q) p->tm_done[q] = 0;
     return YO_OK;
 }
 
 yo_status yo_get_timing(yo_plan *p, int part, float *avg_ms, int *count)
 {
     if (!p || !avg_ms || !count) return fail(YO_EINVAL, "null argument");
-    if (part < 0 || part > 5) return fail(YO_EINVAL, "part must be 0 to 5");
+    if (part < 0 || part > 7) return fail(YO_EINVAL, "part must be 0 to 7");
     *avg_ms = 0.0f;
     const int n = p->tm_done[part];
     *count = n;
@@ -2210,7 +2316,7 @@ yo_status yo_get_timing(yo_plan *p, int part, float *avg_ms, int *count)
 yo_status yo_tile_table(const yo_plan *p, int part, int *out, int cap, int *n)
 {
     if (!p || !n || (cap > 0 && !out)) return fail(YO_EINVAL, "null argument");
-    if (part < 0 || part > 5) return fail(YO_EINVAL, "part must be 0 to 5");
+    if (part < 0 || part > 7) return fail(YO_EINVAL, "part must be 0 to 7");
     int t0, t1;
     part_range(p, part, t0, t1);
     *n = t1 - t0;
@@ -2233,9 +2339,9 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
 {
     if (!p || !avg_ms || !bytes || !cells) return fail(YO_EINVAL, "null argument");
     if (yo_status st_ = ws_check(p)) return st_;
-    if (cls < 0 || cls > 5 || n_launch < 1) return fail(YO_EINVAL, "bad part or count");
+    if (cls < 0 || cls > 7 || n_launch < 1) return fail(YO_EINVAL, "bad part or count");
     if (!p->active) return fail(YO_ESTATE, "yo_reset first");
-    if ((cls == 2 || cls == 4) && p->steps_done + 2 > p->n_steps)
+    if ((cls == 2 || cls == 4 || cls >= 6) && p->steps_done + 2 > p->n_steps)
         return fail(YO_ESTATE, "the two-step launch needs two steps left in the run");
     hipStream_t s = (hipStream_t)stream;
     int r0, r1;
@@ -2266,7 +2372,7 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
     const double R = r1 - r0;
     // the two-step launch advances its cells two steps: twice the bytes
     // two one-step sweeps must move
-    const double steps = (cls == 2 || cls == 4) ? 2.0 : 1.0;
+    const double steps = (cls == 2 || cls == 4 || cls >= 6) ? 2.0 : 1.0;
     *bytes = steps * (own * (48.0 * R + 12.0) + 32.0 * R * in_pml);
     *cells = steps * own * R;
     if (!blocks || r1 <= r0) {
