@@ -28,24 +28,24 @@ __global__ void k_fill(float *p, size_t n, float v)
 // under 2^31 values in three components), 64-bit divisions here cost more than
 // the copy
 __global__ void k_to_ghost(const float *src, float *dst, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
-                           unsigned nx, int nxp, int sw, int slead)
+                           unsigned nx, int ns)
 {
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const unsigned row = i / nx, x = i - row * nx;
         const unsigned pl = row / ny, y = row - pl * ny;
         const unsigned q = pl / nz, z = pl - q * nz;
-        dst[yo_off(c0 + (int)q, yo_col((int)x, sw, slead), (int)y, (int)z, (int)ny, nxp, nc)] = src[i];
+        dst[yo_off(c0 + (int)q, (int)x, (int)y, (int)z, (int)ny, ns, nc)] = src[i];
     }
 }
 
 __global__ void k_from_ghost(const float *src, float *dst, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
-                             unsigned nx, int nxp, int sw, int slead)
+                             unsigned nx, int ns)
 {
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const unsigned row = i / nx, x = i - row * nx;
         const unsigned pl = row / ny, y = row - pl * ny;
         const unsigned q = pl / nz, z = pl - q * nz;
-        dst[i] = src[yo_off(c0 + (int)q, yo_col((int)x, sw, slead), (int)y, (int)z, (int)ny, nxp, nc)];
+        dst[i] = src[yo_off(c0 + (int)q, (int)x, (int)y, (int)z, (int)ny, ns, nc)];
     }
 }
 
@@ -220,7 +220,7 @@ __device__ __forceinline__ void sobel(const float *R, int G0, int G1, int n, int
 }
 
 // Sobel normals, Eq. (7), extrusion through the slab into the 3-D kappa.
-__global__ void k_smooth(YoChainBufs c, float *kappa, int ny, int nxp, int sw, int slead, int i0,
+__global__ void k_smooth(YoChainBufs c, float *kappa, int ny, int ns, int i0,
                          int j0, int k_lo, int k_hi)
 {
     const int wm = c.md + 2, wn = c.nd + 2;
@@ -244,14 +244,14 @@ __global__ void k_smooth(YoChainBufs c, float *kappa, int ny, int nxp, int sw, i
     c.aux[3 * gsz + pix] = gyx;
     c.aux[4 * gsz + pix] = gxy;
     c.aux[5 * gsz + pix] = gyy;
-    const int x = yo_col(i0 - 2 + m, sw, slead), y = j0 - 2 + n;
+    const int x = i0 - 2 + m, y = j0 - 2 + n;
     for (int k = k_lo; k <= k_hi; ++k) {
-        kappa[yo_off(0, x, y, k, ny, nxp, 3)] = kx;
-        kappa[yo_off(1, x, y, k, ny, nxp, 3)] = ky;
+        kappa[yo_off(0, x, y, k, ny, ns, 3)] = kx;
+        kappa[yo_off(1, x, y, k, ny, ns, 3)] = ky;
     }
-    for (int k = k_lo; k < k_hi; ++k) kappa[yo_off(2, x, y, k, ny, nxp, 3)] = kzi;
-    kappa[yo_off(2, x, y, k_lo - 1, ny, nxp, 3)] = kzf;
-    kappa[yo_off(2, x, y, k_hi, ny, nxp, 3)] = kzf;
+    for (int k = k_lo; k < k_hi; ++k) kappa[yo_off(2, x, y, k, ny, ns, 3)] = kzi;
+    kappa[yo_off(2, x, y, k_lo - 1, ny, ns, 3)] = kzf;
+    kappa[yo_off(2, x, y, k_hi, ny, ns, 3)] = kzf;
 }
 
 // ------------------------------------------------------------- Eq. (1)
@@ -288,7 +288,7 @@ __global__ void k_grad(const YoGradArgs a)
                 }
             }
             const int x = a.box[0] + bi, y = a.box[1] + bj, z = a.box[2] + bk;
-            const float kap = a.kappa[yo_off(c, yo_col(x, a.sw, a.slead), y, z, a.ny, a.nxp, 3)];
+            const float kap = a.kappa[yo_off(c, x, y, z, a.ny, a.ns, 3)];
             const float gk = -ge / (kap * kap);
             if (a.gbox) a.gbox[o] = gk;
             if (c < 2) {
@@ -585,26 +585,26 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s)
 }
 
 hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
-                              int ny, int nx, int nxp, int sw, int slead, hipStream_t s)
+                              int ny, int nx, int ns, hipStream_t s)
 {
     const size_t n = (size_t)ncomp * nz * ny * nx;
     if (!n) return hipSuccess;
     int blocks = nblk(n);
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_to_ghost, dim3(blocks), dim3(BS), 0, s, dense, ghost, (unsigned)n, c0, nc,
-                       (unsigned)nz, (unsigned)ny, (unsigned)nx, nxp, sw, slead);
+                       (unsigned)nz, (unsigned)ny, (unsigned)nx, ns);
     return hipGetLastError();
 }
 
 hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
-                                int ny, int nx, int nxp, int sw, int slead, hipStream_t s)
+                                int ny, int nx, int ns, hipStream_t s)
 {
     const size_t n = (size_t)ncomp * nz * ny * nx;
     if (!n) return hipSuccess;
     int blocks = nblk(n);
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_from_ghost, dim3(blocks), dim3(BS), 0, s, ghost, dense, (unsigned)n, c0, nc,
-                       (unsigned)nz, (unsigned)ny, (unsigned)nx, nxp, sw, slead);
+                       (unsigned)nz, (unsigned)ny, (unsigned)nx, ns);
     return hipGetLastError();
 }
 
@@ -625,7 +625,7 @@ hipError_t yo_launch_alpha(const float2 *mon, const float2 *w, int n, float2 *ou
 }
 
 hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float beta, float *kappa,
-                                   int ny, int nxp, int sw, int slead, int i0, int j0, int k_lo,
+                                   int ny, int ns, int i0, int j0, int k_lo,
                                    int k_hi, hipStream_t s)
 {
     const size_t UV = (size_t)c.U * c.V;
@@ -638,7 +638,7 @@ hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float b
         hipLaunchKernelGGL(k_morph_project, dim3(nblk(UV)), dim3(BS), 0, s, c, c.mcan + c.n_morph * UV, beta);
     hipLaunchKernelGGL(k_box, dim3(nblk((size_t)3 * c.G0 * c.G1)), dim3(BS), 0, s, c);
     hipLaunchKernelGGL(k_smooth, dim3(nblk((size_t)(c.md + 2) * (c.nd + 2))), dim3(BS), 0, s, c,
-                       kappa, ny, nxp, sw, slead, i0, j0, k_lo, k_hi);
+                       kappa, ny, ns, i0, j0, k_lo, k_hi);
     return hipGetLastError();
 }
 

@@ -23,27 +23,26 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? l
 // wave-uniform scalars, the only per-lane operand is the column offset, so a
 // load costs no vector address arithmetic.  Reads past the buffer return 0.
 typedef __amdgpu_buffer_rsrc_t Rsrc;
-__device__ __forceinline__ Rsrc rsrc_of(const float *p, size_t n_floats)
+__device__ __forceinline__ Rsrc rsrc_of(const float *p, unsigned bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0,
-                                             (int)(n_floats * sizeof(float)), 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float bload(Rsrc r, int voff, int soff)
+__device__ __forceinline__ float bload(Rsrc r, int voff, unsigned soff)
 {
-    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, (int)soff, 0));
 }
-__device__ __forceinline__ void bstore(float v, Rsrc r, int voff, int soff)
+__device__ __forceinline__ void bstore(float v, Rsrc r, int voff, unsigned soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, voff, (int)soff, 0);
 }
 
 // Store of a new field value: no wave of this launch reads it again, so it
 // is marked non-temporal (cache-policy bit 1) to leave the caches to the
 // halo rows and planes that neighbouring tiles do re-read.  (The CPML
 // memories keep the default policy: marked the same way, measured slower.)
-__device__ __forceinline__ void bstore_nt(float v, Rsrc r, int voff, int soff)
+__device__ __forceinline__ void bstore_nt(float v, Rsrc r, int voff, unsigned soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, voff, soff, 2);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, voff, (int)soff, 2);
 }
 
 __device__ __forceinline__ int slab_index(int u, int n, int lo, int hi)
@@ -58,14 +57,10 @@ __device__ __forceinline__ int slab_index(int u, int n, int lo, int hi)
 struct Cpml {
     float b, c, ki;
 };
-__device__ __forceinline__ Cpml cpml_at(const float *prof, int n, int which, int u)
+__device__ __forceinline__ Cpml cpml_at(const float4 *prof, int which, int u)   // which: 0 E sites, 1 Ht sites
 {
-    // prof layout [6][n]: bE cE kiE bH cH kiH ; which = 0 (E sites) or 3 (H sites)
-    Cpml p;
-    p.b = prof[(which + 0) * n + u];
-    p.c = prof[(which + 1) * n + u];
-    p.ki = prof[(which + 2) * n + u];
-    return p;
+    const float4 v = prof[2 * u + which];
+    return Cpml{v.x, v.y, v.z};
 }
 __device__ __forceinline__ float pml_diff(float d, const Cpml &p, float psi_old, float &psi_new)
 {
@@ -91,61 +86,74 @@ __device__ __forceinline__ Cpml lane_cpml(const Cpml &c, int l)
     return o;
 }
 
-// CPML memory slots of each axis, as first components (two components per
-// slot): with two state buffers, E one slot (0) read and written in place
-// and Ht two (2, 4) by step parity, since halo rows recompute Ht from the
-// old step's memory while its owner writes the new one; with three state
-// buffers (two steps per launch) three slots each, E at 0, 2, 4 and Ht at
-// 6, 8, 10, the step's memories in slot step % 3: a two-step launch reads
-// slot n % 3 around its cells and writes slot (n + 2) % 3 of its own while
-// single steps write (n + 1) % 3.
-__device__ __forceinline__ void cpml_slots(int nbuf, int step, int &qEo, int &qEn, int &qHo, int &qHn)
+// The buffer (and CPML memory slot) that holds the state at the launch, and
+// the one it goes to when the launch advances it by `adv` steps.
+__device__ __forceinline__ int buf_now(const YoPlanD &P, int step, int b_offset)
 {
-    if (nbuf == 3) {
-        const int s0 = step % 3, s1 = (step + 1) % 3;
-        qEo = 2 * s0;
-        qEn = 2 * s1;
-        qHo = 6 + 2 * s0;
-        qHn = 6 + 2 * s1;
-    } else {
-        const int par = step & 1;
-        qEo = qEn = 0;
-        qHo = 2 + 2 * par;
-        qHn = 2 + 2 * (par ^ 1);
-    }
+    return P.nbuf == 3 ? step % 3 : (P.step_ctr[1] + b_offset) & 1;
+}
+template <class PP>   // PP: pointer to a YoPlanD in global or constant memory
+__device__ __forceinline__ int buf_next(PP P, int now, int adv)
+{
+    return P->nbuf == 3 ? (now + adv) % 3 : now ^ 1;
 }
 
-// What a lane does of a row: the byte offset of its column in a row for loads
-// (past every buffer for columns outside the grid: they read zero) and for
-// stores, that of its column inside the x-slabs (negative outside), whether
-// it owns the column and whether it stores (own, or a pad column of the
-// strip: see yo_col).
+// bytes of one array of nc components
+template <class PP>
+__device__ __forceinline__ unsigned array_bytes(PP P, int nc)
+{
+    return (unsigned)((P->nz * (P->ny + 1) + 1) * P->ns) * (unsigned)(64 * nc * sizeof(float));
+}
+
+// Lane offsets past every buffer (all are below 4 GiB less 4 KiB): loads give
+// zero, stores are dropped.  Component offsets are added to it.
+constexpr int kFar = (int)0xfffff000u;
+
+// What a lane does of a row of a tile (columns x0 - 2 + lane): the byte offset
+// of its column for loads from the state, kappa and the rows of CPML memories
+// (past the buffer for columns outside the grid or past the halo lanes) and
+// for stores to the state and the memories, and whether it owns the column.
+// Stores also go to the pads of the tile's strip, so that a whole strip's row
+// is stored in whole 128-byte lines.  A line stored in part costs about four
+// line transfers here: tiles of 60 columns at plain offsets streamed 2.8 TB/s,
+// the same columns in strips with stored pads 4.7 TB/s (a copy: 4.8).
 struct LaneX {
-    int xl, xs, px;
+    int x;
+    int xl, xk, xp;
+    int xs, xps;
+    int px;               // byte offset in an x-slab memory row (negative outside the slabs)
     bool own, st;
 };
-constexpr int kFar = (int)0x80000000;   // past every buffer (all are below 2 GiB)
-
-// lead: lanes before the first owned column (columns x0 - lead + lane)
-__device__ __forceinline__ LaneX lane_x(const YoPlanD &P, int x0, int xn, int lane, int lead)
+template <class PP>
+__device__ __forceinline__ LaneX lane_x(PP P, int x0, int xn, int lane)
 {
     LaneX L;
-    const int x = x0 - lead + lane;
-    const bool in = x >= 0 && x < P.nx && lane <= lead + xn;
-    L.own = lane >= lead && lane < lead + xn;
-    L.xl = in ? yo_col(x, P.sw, P.slead) * (int)sizeof(float) : kFar;
-    // position in the strip that holds the tile: the lanes over its pad
-    // columns store too (values nobody reads), so that a whole strip's row is
-    // stored in whole 128-byte lines.  A line stored in part costs about four
-    // line transfers here: tiles of 60 columns at plain offsets streamed 2.8
-    // TB/s, the same columns in strips with stored pads 4.7 TB/s (a copy: 4.8)
-    const int s = x0 / P.sw, pos = x0 - s * P.sw + lane;   // slead == lead in the strip layout
-    const bool pad = P.strips && (pos < lead || pos >= lead + P.sw || x >= P.nx) && pos < 64 &&
-                     64 * s + pos < P.nxp && lane < xn + 2 * lead + (x >= P.nx ? 64 : 0);
+    const int x = x0 - YO_LEAD + lane;
+    L.x = x;
+    const bool in = x >= 0 && x < P->nx && lane < xn + 2 * YO_LEAD;
+    L.own = lane >= YO_LEAD && lane < YO_LEAD + xn;
+    L.xl = in ? yo_col(x, 6) * 4 : kFar;
+    L.xk = in ? yo_col(x, 3) * 4 : kFar;
+    L.xp = in ? yo_col(x, 4) * 4 : kFar;
+    const int s = x0 / YO_SW, pos = x0 - s * YO_SW + lane;   // place in the tile's strip
+    // (past the grid's last column up to the end of its line)
+    const bool pad = ((pos < YO_LEAD || pos >= YO_LEAD + YO_SW) && pos < 64 && lane < xn + 2 * YO_LEAD) ||
+                     (x >= P->nx && pos < ((YO_LEAD + P->nx - s * YO_SW + 31) & ~31));
     L.st = L.own || pad;
-    L.xs = pad ? (64 * s + pos) * (int)sizeof(float) : L.xl;
+    L.xs = pad ? (s * 384 + pos) * 4 : (L.own ? L.xl : kFar);
+    L.xps = pad ? (s * 256 + pos) * 4 : (L.own ? L.xp : kFar);
     L.px = -1;
     return L;
+}
+
+// the lane's place in the x-slabs' memories, and their coefficients there
+template <class PP>
+__device__ __forceinline__ void lane_xslab(PP P, LaneX &L, Cpml &cxE, Cpml &cxH)
+{
+    if (L.xl == kFar || slab_index(L.x, P->nx, P->plo[0], P->phi[0]) < 0) return;
+    L.px = (L.x < P->plo[0] ? L.x : P->psi_xside + L.x - (P->nx - P->phi[0])) * 4;
+    cxE = cpml_at(P->prof[0], 0, L.x);
+    cxH = cpml_at(P->prof[0], 1, L.x);
 }
 
 __device__ __forceinline__ void block_sync_lds()

@@ -16,25 +16,22 @@
 #define YO_PAIR_GROUP 32  // tiles that consecutive blocks take for one right-hand side,
 #define YO_PAIR_YROWS 12  // and the most y-slab rows a block may hold
 
-// Field arrays carry one ghost layer on every face and keep the components
-// of one (j, k) row together: component c of cell (x, j, k), x in [-1, nx],
-// j in [-1, ny], k in [-1, nz], of an array with nc components sits at
-//   (((k + 1) * (ny + 2) + (j + 1)) * nc + c) * nxp + yo_col(x).
-// A row of nx cells is cut into strips of sw = 64 - 2 lead cells, each in a
-// segment of 64 floats (two 128-byte lines) with `lead` pad floats on either
-// side (the last segment: as many whole lines as its cells need): the cells a
-// wave owns, its lanes over the pads storing values nobody reads, so that
-// every row of a whole strip is stored in whole lines.  lead = 1 for plans
-// that take one step per launch, 2 for two (the halo lanes on either side).
-// Where the pads would push a limit (2 GiB of state or CPML memory, the
-// static workspace) that plain rows keep, rows are plain (slead = 1, one
-// strip).
-// The state of one right-hand side and step parity is one such array with
-// nc = 6 (Ex Ey Ez Ht_x Ht_y Ht_z), kappa one with nc = 3, so a row group
-// of all components is one contiguous block of memory.  Ghost rows and planes
-// are zero and never written, and columns outside the grid are read past the
+// Field arrays carry a ghost row on either side of y.  A row of
+// nx cells is cut into ns strips of 60, each in a segment of nc x 64 floats, the
+// components of a strip side by side: component c of cell (x, j, k), j in
+// [-1, ny], of an array with nc components sits at
+//   (((k * (ny + 1) + (j + 1)) * ns + s) * nc + c) * 64 + 2 + x - 60 s,
+// s = x / 60 (row ny of a plane is row -1 of the next, a ghost of both).  The 2 floats on either side of the 60 are pads: the lanes of a
+// wave that own no cell of its strip lie over them and store values nobody
+// reads, so that every row of a strip is stored in whole 128-byte lines, and a
+// component's offset from a strip's first is a constant of the instruction.
+// The state of one right-hand side and buffer is one such array with nc = 6
+// (Ex Ey Ez Ht_x Ht_y Ht_z), kappa one with nc = 3.  Ghost rows are zero and
+// never written, and columns and planes outside the grid are read past the
 // buffer (zero), which realises the perfect-conductor box (values outside the
 // grid read as zero) without branches.
+#define YO_SW 60          // cells per strip
+#define YO_LEAD 2         // pad floats (halo lanes) before them
 
 struct YoPlaneD {
     int axis, index, lo0, lo1, n0, n1;
@@ -43,20 +40,19 @@ struct YoPlaneD {
 // One right-hand side: its own field state, absorbing-layer memories, DFT
 // sums, source plane and per-step phase table.
 struct YoRhsD {
-    // state buffers, ghost layout, nc = 6 (E then Ht): the state after step
-    // s is in F[s % nbuf]; nbuf = 3 (a third buffer) when the plan may
-    // advance its interior two steps per sweep, else 2 (F[2] null)
+    // state buffers, ghost layout, nc = 6 (E then Ht): nbuf = 3 when the plan
+    // may advance its interior two steps per sweep, the state after step s in
+    // F[s % 3]; else 2, which a launch that advances the state swaps
     float *F[3];
-    // CPML memories: per axis a, at float offset psi_off[a] of the plan,
-    // arrays of psi_n[a] floats, two components per slot: with nbuf = 2 six
-    // (E one slot, Ht two by step parity), with nbuf = 3 twelve (E three
-    // slots, Ht three, the step's in slot step % 3); each [2 comps] of the
-    // axis' slab layout
-    // (x [side][nz][ny][lo], or [nz][ny][lo + hi] where the two slabs differ,
-    // y [nz][Wy][nxp], z [Wz][ny][nxp] with the rows' column layout)
+    // CPML memories: one slot per state buffer, of each axis four values (the
+    // two of E's components, the two of Ht's): axis a's slot q at float offset
+    // psi_off[a] + q psi_n[a]; rows of the y- and z-slabs ([nz][Wy], [Wz][ny])
+    // as the field rows' strips with nc = 4, those of the x-slabs
+    // [side][nz][ny][4][lo], or [nz][ny][4][lo + hi] where the slabs differ
     float *psi;
     float2 *dft_box;         // [3][bz][by][bx]
     float2 *dft_mon;         // concatenated port planes [2][n1][n0]
+    float *dft_mid;          // E after a pair's first step: the box, then the port planes
     const float4 *steptab;   // [n_steps]: source signal (x, y) at (n+1/2)dt, (cos, sin) at n dt
     const float2 *src_j;     // [2][n1][n0], nullptr if no source
     YoPlaneD src;
@@ -73,16 +69,14 @@ struct YoRhsD {
 
 // One plan (one geometry): shared material and geometry description.
 struct YoPlanD {
-    int nx, ny, nz, nxp;     // nxp: padded row pitch of the ghost layout
+    int nx, ny, nz, ns;      // ns: strips per row
     float sx, sy, sz, pad0;
     int plo[3], phi[3];      // PML cells low/high per axis
     const float *kappa;      // ghost layout (ghost values unused)
-    const float *prof[3];    // per axis [6][n_a]: bE cE kiE bH cH kiH
-    int psi_off[3], psi_n[3];
-    int psi_total;           // floats of CPML memory per right-hand side
-    int psi_xrp, psi_xside;  // x-slab memories: floats from row to row and from the low slab's to the high one's
-    int lead, strips;        // halo lanes before a wave's first owned column; rows in strips or plain
-    int sw, slead;           // column layout, see yo_col
+    const float4 *prof[3];   // per axis [n_a][2]: (b, c, 1/kappa, 0) at the E, then at the Ht sites
+    unsigned psi_off[3], psi_n[3];   // floats
+    unsigned psi_bytes;      // CPML memory per right-hand side
+    int psi_xrow, psi_xw, psi_xside;  // x-slab rows: floats per row, per value, and to the high slab
     int box[6];              // x0 y0 z0 bx by bz
     int n_ports;
     int n_steps;
@@ -92,7 +86,7 @@ struct YoPlanD {
     YoPlaneD ports[YO_MAX_PORTS];
     int mon_off[YO_MAX_PORTS];
     int mon_total;
-    int *step_ctr;           // device step counter of this plan
+    int *step_ctr;           // device counters of this plan: steps, launches that swapped its buffers
     int n_rhs;
     // component planes of a port's monitor (and of its adjoint source): 2 =
     // the tangential E on the plane; 5 = those, the normal E half a cell past
@@ -102,7 +96,7 @@ struct YoPlanD {
 };
 
 // A tile is one wave's work (or, in the cooperative layout, one block's):
-// owned x in [x0, x0+xn) (xn <= 64 - 2 lead), rows [j0, j0+jn) (jn <= YO_TY, or
+// owned x in [x0, x0+xn) (xn <= 60), rows [j0, j0+jn) (jn <= YO_TY, or
 // YO_TY * waves per block), planes [k0, k1).  Packed as int4
 // (x0 | xn << 16, j0 | jn << 16, k0 | k1 << 16, tile class).
 struct YoSlot {
@@ -114,7 +108,8 @@ struct YoSlot {
 
 struct YoStepArgs {
     int n_slots;
-    int k_offset;            // launch index inside the chunk; step = counter + k_offset
+    int k_offset;            // steps into the chunk; step = counter + k_offset
+    int b_offset;            // launches into the chunk that advanced the state
     int total_waves;
     int wpb;                 // waves per block (4 or 8)
     int prefix[YO_MAX_SLOTS + 1];
@@ -127,8 +122,9 @@ struct YoStepArgs {
 struct YoAuxArgs {
     int n_slots;
     int k_offset;
+    int b_offset;
+    int pair;                // k_dft: after a pair of steps, adding both
     int total_blocks;
-    int pad_;
     int prefix[YO_MAX_SLOTS + 1];   // blocks
     const YoPlanD *plan[YO_MAX_SLOTS];
     int rhs0[YO_MAX_SLOTS], nrhs[YO_MAX_SLOTS];
@@ -137,7 +133,7 @@ struct YoAuxArgs {
 
 struct YoCtrArgs {
     int n;
-    int add;
+    int add, add_b;          // steps, launches
     int *ctr[YO_MAX_SLOTS];
 };
 
@@ -194,7 +190,7 @@ hipError_t yo_launch_step2(bool zslab, int rows, bool coop, const YoStepArgs &ar
                            hipStream_t s);
 // two steps over whole-grid tiles (one block each, YO_PAIR_W waves); shell:
 // tiles with x- or y-slabs, source planes or the grid's first column or row
-hipError_t yo_launch_pair(bool shell, const YoStepArgs &args, int blocks, hipStream_t s);
+hipError_t yo_launch_pair(bool shell, bool dft, const YoStepArgs &args, int blocks, hipStream_t s);
 hipError_t yo_launch_dft(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_source(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_ctr(const YoCtrArgs &args, int set_value, hipStream_t s);
@@ -202,9 +198,9 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s);
 // dense [ncomp][nz][ny][nx] <-> components c0 .. c0+ncomp-1 of a ghost-layout
 // array with nc components
 hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
-                              int ny, int nx, int nxp, int sw, int slead, hipStream_t s);
+                              int ny, int nx, int ns, hipStream_t s);
 hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
-                                int ny, int nx, int nxp, int sw, int slead, hipStream_t s);
+                                int ny, int nx, int ns, hipStream_t s);
 // in-place phasor fit of n complex sums; sets *bad to 1 if a result is not
 // finite (*bad is left alone otherwise)
 hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g10, float g11,
@@ -212,7 +208,7 @@ hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g
 hipError_t yo_launch_alpha(const float2 *mon_dft, const float2 *weights, int n, float2 *out,
                            hipStream_t s);
 hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float beta,
-                                   float *kappa, int ny, int nxp, int sw, int slead, int i0, int j0,
+                                   float *kappa, int ny, int ns, int i0, int j0,
                                    int k_lo, int k_hi, hipStream_t s);
 #define YO_MAX_GF 32
 #define YO_MAX_GA 64
@@ -226,7 +222,7 @@ struct YoGradArgs {
     float *gbox;                   // optional [3][bz][by][bx] dF/dkappa
     float *gmap;                   // optional [4][G1][G0] z-summed maps
     int n_src, n_ports, n_freq;
-    int nxp, ny, sw, slead;
+    int ns, ny;
     int box[6];
     int k_lo, k_hi, G0, G1;
 };
@@ -240,16 +236,16 @@ hipError_t yo_launch_adam(float *C, const float *G, float *M, float *V, int n, f
 hipError_t yo_launch_zsum(const float *gbox, const int *box, int k_lo, int k_hi, float *gmap, int G0,
                           int G1, hipStream_t s);
 
-// column of cell x in a row (see the layout above)
-__host__ __device__ inline int yo_col(int x, int sw, int slead)
+// floats from the start of a row's component 0 to cell x in an array of nc
+// components (see the layout above)
+__host__ __device__ inline int yo_col(int x, int nc)
 {
-    const int s = x / sw;
-    return s * 64 + slead + (x - s * sw);
+    const int s = x / YO_SW;
+    return s * 64 * nc + YO_LEAD + (x - s * YO_SW);
 }
 
-// ghost-layout offset of component c of column col of row (j, k) in an array
-// of nc components
-__host__ __device__ inline size_t yo_off(int c, int col, int j, int k, int ny, int nxp, int nc)
+// ghost-layout offset of component c of (x, j, k) in an array of nc components
+__host__ __device__ inline size_t yo_off(int c, int x, int j, int k, int ny, int ns, int nc)
 {
-    return (((size_t)(k + 1) * (ny + 2) + (size_t)(j + 1)) * nc + c) * nxp + (size_t)col;
+    return ((size_t)k * (ny + 1) + (size_t)(j + 1)) * ns * 64 * nc + (size_t)(yo_col(x, nc) + 64 * c);
 }

@@ -32,98 +32,113 @@
 
 namespace {
 
-// scalar loads of data no kernel of this launch writes
-typedef const __attribute__((address_space(4))) float *ConstF;
-__device__ __forceinline__ Cpml cpml_uniform(const float *prof, int n, int which, int u)
+// Scalar loads of data no kernel of this launch writes.  `opaque` keeps such
+// loads, and uniform tests, where they are used: hoisted out of the march they
+// would not fit the scalar registers.
+template <class T> using Const = const __attribute__((address_space(4))) T *;
+template <class T>
+__device__ __forceinline__ Const<T> constant(const T *p)
 {
-    ConstF p = (ConstF)(uintptr_t)prof;
-    Cpml c;
-    c.b = p[(which + 0) * n + u];
-    c.c = p[(which + 1) * n + u];
-    c.ki = p[(which + 2) * n + u];
-    return c;
+    return (Const<T>)(uintptr_t)p;
+}
+template <class T> using Global = __attribute__((address_space(1))) T *;
+template <class T>
+__device__ __forceinline__ T opaque(T v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ Cpml cpml_uniform(const float4 *prof, int which, int u)
+{
+    Const<float> p = (Const<float>)(uintptr_t)(prof + 2 * u + which);
+    return Cpml{p[0], p[1], p[2]};
 }
 
-// CP: tiles that meet the x- or y-slabs, or a source plane; else only the
-// z-slabs' code is there
-template <int TY, int W, bool CP>
-__device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, const int step, const int4 t,
-                                          const int w, const int lane, float *lds)
+// tile flags (uniform): rows r owned, in the y-slabs, in the grid
+enum { F_OWN = 0, F_YSLAB = 4, F_IN = 8, F_X = 1 << 12, F_SRC = 1 << 13, F_X0 = 1 << 14, F_Y0 = 1 << 15,
+       F_BOX = 16, F_MON = 1 << 20 };
+
+// CP: tiles that meet the x- or y-slabs, a source plane or the grid's first
+// column or row; else only the z-slabs' code is there.  DFT: E^{n+1} of the
+// design box and the port planes is stored for the running DFT.
+template <int TY, int W, bool CP, bool DFT>
+__device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<YoRhsD> R, const int step, const int now,
+                                          const int4 t, const int w, const int lane, float *lds)
 {
-    const int nx = P.nx, ny = P.ny, nz = P.nz, nxp = P.nxp;
-    const int rows = ny + 2;
-    const size_t groups = (size_t)(nz + 2) * rows;
-    const int rowb = nxp * (int)sizeof(float);
-    const int s0 = step % 3, s2 = (step + 2) % 3;         // buffers and CPML memory slots
-    const Rsrc FA = rsrc_of(R.F[s0], 6 * groups * nxp);   // after step n
-    const Rsrc FC = rsrc_of(R.F[s2], 6 * groups * nxp);   // after step n+2
-    const Rsrc KR = rsrc_of(P.kappa, 3 * groups * nxp);
-    const Rsrc PS = rsrc_of(R.psi, (size_t)P.psi_total);
-    const float sx = P.sx, sy = P.sy, sz = P.sz;
+    const int ny = P->ny, nz = P->nz;
+    const unsigned gs = 1536u * P->ns, pstr = (unsigned)(ny + 1) * gs;   // state of a row, of a plane, bytes
+    const unsigned ps = 1024u * P->ns;                                   // CPML memories of a row
+    const int nxt = buf_next(P, now, 2);
+    const Rsrc FA = rsrc_of(R->F[now], array_bytes(P, 6));   // after step n
+    const Rsrc FC = rsrc_of(R->F[nxt], array_bytes(P, 6));   // after step n+2
+    const Rsrc KR = rsrc_of(P->kappa, array_bytes(P, 3));
+    const Rsrc PS = rsrc_of(R->psi, P->psi_bytes);
+    const float sx = P->sx, sy = P->sy, sz = P->sz;
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
     const int J0 = t.y & 0xffff, JN = t.y >> 16;
     const int k0 = t.z & 0xffff, k1 = t.z >> 16;
     const int jb = J0 - 2 + w * TY;        // this wave's first row
-    LaneX L = lane_x(P, x0, xn, lane, 2);
-    const int x = x0 - 2 + lane;
-    const bool xin = x >= 0 && x < nx && x <= x0 + xn + 1;
-    const int xl = xin ? yo_col(x, P.sw, P.slead) * (int)sizeof(float) : kFar;
-    const int xst = L.st ? L.xs : kFar;    // stores of lanes that store nothing are dropped
-    const bool x_first = x == 0;
+    LaneX L = lane_x(P, x0, xn, lane);
+    const int xl = L.xl, xk = L.xk, xp = L.xp;
+    const int xs = L.st ? L.xs : kFar, xps = L.st ? L.xps : kFar;   // stores of lanes that store nothing are dropped
 
-    // absorbing layers: x per lane (the tile's flag uniform), y per row, z per plane
-    const bool xc = CP && (t.w & 1), yc = CP && (t.w & 2);
-    int px = -1, xi = 0;
+    // absorbing layers: x per lane, y per row, z per plane
+    const int ylo = P->plo[1], zlo = P->plo[2], zhi = P->phi[2];
+    const int yh0 = ny - P->phi[1];                          // first row of the high y-slab
     Cpml cxE = {1.0f, 0.0f, 1.0f}, cxH = cxE;
-    if (xc) {
-        const int u = xin ? slab_index(x, nx, P.plo[0], P.phi[0]) : -1;
-        if (u >= 0) {
-            px = (x < P.plo[0] ? x : P.psi_xside + x - (nx - P.phi[0])) * (int)sizeof(float);
-            xi = u;
-            cxE = cpml_at(P.prof[0], nx, 0, x);
-            cxH = cpml_at(P.prof[0], nx, 3, x);
+    int xi = 0;
+    if (CP && (t.w & 1)) {
+        lane_xslab(P, L, cxE, cxH);
+        xi = L.px >= 0 ? slab_index(L.x, P->nx, P->plo[0], P->phi[0]) : 0;
+    }
+    const bool ylow = jb < ylo;
+    const int py0 = ylow ? jb : jb - yh0 + ylo;             // slab row of row 0
+    const int sr0 = ylow ? jb : jb - yh0;                   // and its place in the LDS
+    int fl0 = 0;
+    unsigned rb[TY];
+#pragma unroll
+    for (int r = 0; r < TY; ++r) {
+        const int j = jb + r;
+        rb[r] = (unsigned)(clampi(j, -1, ny) + 1) * gs;
+        if (j >= J0 && j < J0 + JN) fl0 |= 1 << (F_OWN + r);
+        if (j >= 0 && j < ny) fl0 |= 1 << (F_IN + r);
+        if (CP && j >= 0 && j < ny && (j < ylo || j >= yh0)) fl0 |= 1 << (F_YSLAB + r);
+        if (DFT && j >= J0 && j < J0 + JN && j >= P->box[1] && j < P->box[1] + P->box[4]) fl0 |= 1 << (F_BOX + r);
+        if (CP && j == 0) fl0 |= F_Y0;
+    }
+    if (CP && (t.w & 1)) fl0 |= F_X;
+    if (CP && x0 == 0) fl0 |= F_X0;
+    if (CP) {
+        // the source plane (normal to x) and this wave's rows
+        const int sp = R->src.index, lo0 = R->src.lo0, n0 = R->src.n0;
+        if (R->src_j && sp + (R->src_nc == 5 ? 1 : 0) >= x0 - 2 && sp <= x0 + xn + 1 && jb < lo0 + n0 && jb + TY > lo0)
+            fl0 |= F_SRC;
+    }
+    if (DFT) {
+        const bool xbox = x0 < P->box[0] + P->box[3] && x0 + xn > P->box[0];
+        if (!xbox) fl0 &= ~(0xf << F_BOX);
+        for (int q = 0; q < P->n_ports; ++q) {
+            const int ix = P->ports[q].index, lo0 = P->ports[q].lo0, n0 = P->ports[q].n0;
+            if (ix + (P->mon_nc == 5) >= x0 && ix < x0 + xn && jb < lo0 + n0 && jb + TY > lo0)
+                fl0 |= F_MON;
         }
     }
-    const float *profy = P.prof[1], *profz = P.prof[2];
-    const int ylo = P.plo[1], yhi = P.phi[1], zlo = P.plo[2], zhi = P.phi[2];
-    const int Wy = ylo + yhi, xrp = P.psi_xrp;
-    const int ox = P.psi_off[0], oy = P.psi_off[1], oz = P.psi_off[2];
-    const int nx1 = P.psi_n[0], ny1 = P.psi_n[1], nz1 = P.psi_n[2];
-    auto ax = [&](int q, int k, int j) { return (ox + q * nx1 + (k * ny + j) * xrp) * (int)sizeof(float); };
-    auto ay = [&](int q, int k, int py) { return (oy + q * ny1 + (k * Wy + py) * nxp) * (int)sizeof(float); };
-    auto az = [&](int q, int pz, int j) { return (oz + q * nz1 + (pz * ny + j) * nxp) * (int)sizeof(float); };
-
-    // the source plane (normal to x) and this tile
-    const YoPlaneD sp = R.src;
-    const bool src_on = CP && R.src_j != nullptr && sp.index + (R.src_nc == 5 ? 1 : 0) >= x0 - 2 &&
-                        sp.index <= x0 + xn + 1 && jb < sp.lo0 + sp.n0 && jb + TY > sp.lo0;
-    const float2 *sj = R.src_j;
-    const int snc = R.src_nc;
-    float4 st0 = {0, 0, 0, 0}, st1 = st0;
-    if (src_on) {
-        st0 = R.steptab[step];
-        st1 = R.steptab[step + 1];
-    }
+    const unsigned zb0 = 4u * (P->psi_off[2] + now * P->psi_n[2]), zb2 = 4u * (P->psi_off[2] + nxt * P->psi_n[2]);
+    const unsigned yb0 = 4u * (P->psi_off[1] + now * P->psi_n[1]), yb2 = 4u * (P->psi_off[1] + nxt * P->psi_n[1]);
+    const unsigned xb0 = 4u * (P->psi_off[0] + now * P->psi_n[0]), xb2 = 4u * (P->psi_off[0] + nxt * P->psi_n[0]);
+    const unsigned ypl = (unsigned)(ylo + P->phi[1]) * ps;   // a plane's y-slab rows
+    const unsigned xrow = 4u * P->psi_xrow, xw = 4u * P->psi_xw;
+    const float4 *profy = P->prof[1], *profz = P->prof[2];
 
     // LDS: rows for the neighbouring waves (12 slots of W x 64), then the
     // memories of step n+1 that the second step reads one plane later: y-slab
     // rows (slab row, value, plane parity), x-slab columns (row, value, parity)
-    float *const xs = lds + lane;
-    auto slot = [&](int q, int ww) -> float & { return xs[(q * W + ww) * 64]; };
+    float *const ex = lds + lane;
+    auto slot = [&](int q, int ww) -> float & { return ex[(q * W + ww) * 64]; };
     float *const ystash = lds + 12 * W * 64 + lane;
-    float *const xstash = lds + 12 * W * 64 + YO_PAIR_YROWS * 4 * 2 * 64 + w * TY * 4 * 2 * 32;
-    auto yst = [&](int sr, int v, int par) -> float & { return ystash[((sr * 4 + v) * 2 + par) * 64]; };
-    auto xst_ = [&](int r, int v, int par) -> float & { return xstash[((r * 4 + v) * 2 + par) * 32 + xi]; };
-
-    // byte offsets: of row r within a plane of the state (half that for kappa), and
-    // which rows this block owns
-    const int pstr = rows * 6 * rowb;
-    int rb[TY], own_rows = 0;
-#pragma unroll
-    for (int r = 0; r < TY; ++r) {
-        rb[r] = (clampi(jb + r, -1, ny) + 1) * 6 * rowb;
-        if (jb + r >= J0 && jb + r < J0 + JN) own_rows |= 1 << r;
-    }
+    float *const xstash = lds + 12 * W * 64 + YO_PAIR_YROWS * 4 * 2 * 64 + w * TY * 4 * 2 * 32 + xi;
+    auto yst = [&](int r, int v, int par) -> float & { return ystash[(((sr0 + r) * 4 + v) * 2 + par) * 64]; };
+    auto xst = [&](int r, int v, int par) -> float & { return xstash[((r * 4 + v) * 2 + par) * 32]; };
 
     // by plane parity: E^n, Ht^{n+1/2}, E^{n+1}, kappa, Ht^{n+3/2} and the z
     // memories of step n+1 (the second of a plane's two is the plane before)
@@ -132,14 +147,13 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
     const int kb = k0 == 0 ? 0 : k0 - 2;
 #pragma unroll
     for (int r = 0; r < TY; ++r) {
-        const int o = (kb + 1) * pstr + rb[r];
+        const unsigned o = (unsigned)kb * pstr + rb[r];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            E0[0][c][r] = bload(FA, xl, c * rowb + o);
+            E0[0][c][r] = bload(FA, xl + 256 * c, o);
             H[1][c][r] = E1_[1][c][r] = K[1][c][r] = 0.0f;
         }
         H2_[1][0][r] = H2_[1][1][r] = 0.0f;
-        zH_[1][0][r] = zH_[1][1][r] = zE_[1][0][r] = zE_[1][1][r] = 0.0f;
     }
     slot(2 * (kb & 1), w) = E0[0][0][0];
     slot(2 * (kb & 1) + 1, w) = E0[0][2][0];
@@ -147,20 +161,8 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
     slot(4 + 2 * ((kb - 1) & 1) + 1, w) = 0.0f;
     block_sync_lds();
 
-    // loads of plane k's operands: E^n of plane k+1, Ht and kappa of plane k
-    auto load_plane = [&](int k, float (&en)[3][TY], float (&hc)[3][TY], float (&kc)[3][TY]) {
-        const int oh = (k + 1) * pstr, oe = k + 1 > nz ? oh : oh + pstr;
-#pragma unroll
-        for (int r = 0; r < TY; ++r) {
-            const int e = oe + rb[r], h = oh + rb[r] + 3 * rowb, q = (oh + rb[r]) >> 1;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                en[c][r] = bload(FA, xl, c * rowb + e);
-                hc[c][r] = bload(FA, xl, c * rowb + h);
-                kc[c][r] = bload(KR, xl, c * rowb + q);
-            }
-        }
-    };
+    fl0 = __builtin_amdgcn_readfirstlane(fl0);
+    const int wu = w + 1 < W ? w + 1 : w, wd = w > 0 ? w - 1 : 0;
     int k = kb;
     // one plane; the arrays are those of plane k and of plane k-1, which the
     // next call swaps (so nothing is copied from plane to plane)
@@ -168,64 +170,68 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
                      float (&E1)[3][TY], float (&E1p)[3][TY], float (&Kc)[3][TY], float (&Kp)[3][TY],
                      float (&H2)[3][TY], float (&H2p)[3][TY], float (&zH)[2][TY], float (&zHp)[2][TY],
                      float (&zE)[2][TY], float (&zEp)[2][TY]) {
+        const int fl = opaque(fl0);
         const int par = k & 1;
         const int km = k - 1;
         const int pz = slab_index(k, nz, zlo, zhi), pzm = slab_index(km, nz, zlo, zhi);
-        const bool kin = k >= 0 && k < nz, kmin = km >= 0 && km < nz;
-        load_plane(k, En, Hc, Kc);
+        const bool kin = k < nz, kmin = km >= 0;   // k >= 0 always, km < nz
+        const bool ownk = km >= k0 && km < k1;
+        {
+            // planes past the grid read zero (past the buffer)
+            const unsigned oh = (unsigned)min(k, nz - 1) * pstr, oe = (unsigned)min(k + 1, nz - 1) * pstr;
+            const int ve = k + 1 < nz ? xl : kFar, vh = kin ? xl + 768 : kFar, vk = kin ? xk : kFar;
+#pragma unroll
+            for (int r = 0; r < TY; ++r) {
+                const unsigned e = oe + rb[r], h = oh + rb[r], q = h >> 1;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    En[c][r] = bload(FA, ve + 256 * c, e);
+                    Hc[c][r] = bload(FA, vh + 256 * c, h);
+                    Kc[c][r] = bload(KR, vk + 256 * c, q);
+                }
+            }
+        }
+        // old memories, loaded with the plane's fields so that one wait covers
+        // all: z; x and y (E, E, Ht, Ht)
         if (pz >= 0) {
 #pragma unroll
             for (int r = 0; r < TY; ++r) {
-                const int j = clampi(jb + r, 0, ny - 1);
+                const unsigned o = zb0 + (unsigned)(pz * ny + clampi(jb + r, 0, ny - 1)) * ps;
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    zH[c][r] = bload(PS, xl, az(6 + 2 * s0 + c, pz, j));
-                    zE[c][r] = bload(PS, xl, az(2 * s0 + c, pz, j));
+                    zE[c][r] = bload(PS, xp + 256 * c, o);
+                    zH[c][r] = bload(PS, xp + 512 + 256 * c, o);
                 }
             }
-        } else {
-#pragma unroll
-            for (int r = 0; r < TY; ++r) zH[0][r] = zH[1][r] = zE[0][r] = zE[1][r] = 0.0f;
         }
-        // old memories of the x- and y-slabs (H, H, E, E), loaded with the
-        // plane's fields so that one wait covers all
         float qx[CP ? 4 : 1][TY], qy[CP ? 4 : 1][TY];
         if constexpr (CP) {
-            if (xc && kin) {
-                const int pv = px >= 0 ? px : kFar;
+            if ((fl & F_X) && kin) {
+                const int pv = L.px >= 0 ? L.px : kFar;
 #pragma unroll
                 for (int r = 0; r < TY; ++r) {
-                    const int j = clampi(jb + r, 0, ny - 1);
+                    const unsigned o = xb0 + (unsigned)(k * ny + clampi(jb + r, 0, ny - 1)) * xrow;
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        qx[c][r] = bload(PS, pv, ax(6 + 2 * s0 + c, k, j));
-                        qx[2 + c][r] = bload(PS, pv, ax(2 * s0 + c, k, j));
-                    }
+                    for (int v = 0; v < 4; ++v) qx[v][r] = bload(PS, pv, o + v * xw);
                 }
             }
-            if (yc && kin) {
 #pragma unroll
-                for (int r = 0; r < TY; ++r) {
-                    const int py = slab_index(jb + r, ny, ylo, yhi);
+            for (int r = 0; r < TY; ++r)
+                if ((fl >> (F_YSLAB + r) & 1) && kin) {
+                    const unsigned o = yb0 + (unsigned)k * ypl + (unsigned)(py0 + r) * ps;
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        qy[c][r] = bload(PS, py >= 0 ? xl : kFar, ay(6 + 2 * s0 + c, k, py >= 0 ? py : 0));
-                        qy[2 + c][r] = bload(PS, py >= 0 ? xl : kFar, ay(2 * s0 + c, k, py >= 0 ? py : 0));
-                    }
+                    for (int v = 0; v < 4; ++v) qy[v][r] = bload(PS, xp + 256 * v, o);
                 }
-            }
         }
         slot(2 * (par ^ 1), w) = En[0][0];
         slot(2 * (par ^ 1) + 1, w) = En[2][0];
 
         // ---- S1 ----
-        Cpml cz = {1.0f, 0.0f, 1.0f};
-        if (pz >= 0) cz = cpml_uniform(profz, nz, 3, k);
-        const int wu = w + 1 < W ? w + 1 : w;
+        Cpml cz;
+        if (pz >= 0) cz = cpml_uniform(profz, 1, k);
         const float exu = slot(2 * par, wu), ezu = slot(2 * par + 1, wu);
 #pragma unroll
         for (int r = 0; r < TY; ++r) {
-            const int j = jb + r;
             const float eu0 = r + 1 < TY ? Ec[0][r + 1 < TY ? r + 1 : r] : exu;
             const float eu2 = r + 1 < TY ? Ec[2][r + 1 < TY ? r + 1 : r] : ezu;
             float dyEz = eu2 - Ec[2][r];
@@ -234,27 +240,26 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
             float dxEz = shfl_next(Ec[2][r]) - Ec[2][r];
             float dxEy = shfl_next(Ec[1][r]) - Ec[1][r];
             float dyEx = eu0 - Ec[0][r];
-            const bool jin = j >= 0 && j < ny;
-            if (xc && kin && jin && px >= 0) {
-                float n0, n1;
-                dxEz = pml_diff(dxEz, cxH, qx[0][r], n0);
-                dxEy = pml_diff(dxEy, cxH, qx[CP ? 1 : 0][r], n1);
-                xst_(r, 0, par) = n0;
-                xst_(r, 1, par) = n1;
-            }
-            if (yc && kin) {
-                const int py = slab_index(j, ny, ylo, yhi);
-                if (py >= 0) {
-                    const Cpml cy = cpml_uniform(profy, ny, 3, j);
-                    const int sr = j < ylo ? j : j - (ny - yhi);
+            if constexpr (CP) {
+                if ((fl & F_X) && kin && (fl >> (F_IN + r) & 1)) {
+                    if (L.px >= 0) {
+                        float n0, n1;
+                        dxEz = pml_diff(dxEz, cxH, qx[2][r], n0);
+                        dxEy = pml_diff(dxEy, cxH, qx[3][r], n1);
+                        xst(r, 0, par) = n0;
+                        xst(r, 1, par) = n1;
+                    }
+                }
+                if ((fl >> (F_YSLAB + r) & 1) && kin) {
+                    const Cpml cy = cpml_uniform(profy, 1, jb + r);
                     float n0, n1;
-                    dyEz = pml_diff(dyEz, cy, qy[0][r], n0);
-                    dyEx = pml_diff(dyEx, cy, qy[CP ? 1 : 0][r], n1);
-                    yst(sr, 0, par) = n0;
-                    yst(sr, 1, par) = n1;
+                    dyEz = pml_diff(dyEz, cy, qy[2][r], n0);
+                    dyEx = pml_diff(dyEx, cy, qy[3][r], n1);
+                    yst(r, 0, par) = n0;
+                    yst(r, 1, par) = n1;
                 }
             }
-            if (pz >= 0 && jin) {
+            if (pz >= 0 && (fl >> (F_IN + r) & 1)) {
                 dzEy = pml_diff(dzEy, cz, zH[0][r], zH[0][r]);
                 dzEx = pml_diff(dzEx, cz, zH[1][r], zH[1][r]);
             }
@@ -267,12 +272,10 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
         block_sync_lds();
 
         // ---- S2 ----
-        if (pz >= 0) cz = cpml_uniform(profz, nz, 0, k);
-        const int wd = w > 0 ? w - 1 : 0;
+        if (pz >= 0) cz = cpml_uniform(profz, 0, k);
         const float hxd = slot(8, wd), hzd = slot(9, wd);
 #pragma unroll
         for (int r = 0; r < TY; ++r) {
-            const int j = jb + r;
             const float hd0 = r > 0 ? Hc[0][r > 0 ? r - 1 : 0] : hxd;
             const float hd2 = r > 0 ? Hc[2][r > 0 ? r - 1 : 0] : hzd;
             float dyHz = Hc[2][r] - hd2;
@@ -281,71 +284,127 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
             float dxHz = Hc[2][r] - shfl_prev(Hc[2][r]);
             float dxHy = Hc[1][r] - shfl_prev(Hc[1][r]);
             float dyHx = Hc[0][r] - hd0;
-            const bool jin = j >= 0 && j < ny;
-            if (xc && kin && jin && px >= 0) {
-                float n0, n1;
-                dxHz = pml_diff(dxHz, cxE, qx[CP ? 2 : 0][r], n0);
-                dxHy = pml_diff(dxHy, cxE, qx[CP ? 3 : 0][r], n1);
-                xst_(r, 2, par) = n0;
-                xst_(r, 3, par) = n1;
-            }
-            if (yc && kin) {
-                const int py = slab_index(j, ny, ylo, yhi);
-                if (py >= 0) {
-                    const Cpml cy = cpml_uniform(profy, ny, 0, j);
-                    const int sr = j < ylo ? j : j - (ny - yhi);
+            if constexpr (CP) {
+                if ((fl & F_X) && kin && (fl >> (F_IN + r) & 1)) {
+                    if (L.px >= 0) {
+                        float n0, n1;
+                        dxHz = pml_diff(dxHz, cxE, qx[0][r], n0);
+                        dxHy = pml_diff(dxHy, cxE, qx[1][r], n1);
+                        xst(r, 2, par) = n0;
+                        xst(r, 3, par) = n1;
+                    }
+                }
+                if ((fl >> (F_YSLAB + r) & 1) && kin) {
+                    const Cpml cy = cpml_uniform(profy, 0, jb + r);
                     float n0, n1;
-                    dyHz = pml_diff(dyHz, cy, qy[CP ? 2 : 0][r], n0);
-                    dyHx = pml_diff(dyHx, cy, qy[CP ? 3 : 0][r], n1);
-                    yst(sr, 2, par) = n0;
-                    yst(sr, 3, par) = n1;
+                    dyHz = pml_diff(dyHz, cy, qy[0][r], n0);
+                    dyHx = pml_diff(dyHx, cy, qy[1][r], n1);
+                    yst(r, 2, par) = n0;
+                    yst(r, 3, par) = n1;
                 }
             }
-            if (pz >= 0 && jin) {
+            if (pz >= 0 && (fl >> (F_IN + r) & 1)) {
                 dzHy = pml_diff(dzHy, cz, zE[0][r], zE[0][r]);
                 dzHx = pml_diff(dzHx, cz, zE[1][r], zE[1][r]);
             }
-            float ex = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy)), Ec[0][r]);
-            float ey = fmaf(Kc[1][r], fmaf(sz, dzHx, -(sx * dxHz)), Ec[1][r]);
-            float ez = fmaf(Kc[2][r], fmaf(sx, dxHy, -(sy * dyHx)), Ec[2][r]);
-            E1[0][r] = CP && j == 0 ? 0.0f : ex;
-            E1[1][r] = CP && x_first ? 0.0f : ey;
-            E1[2][r] = CP && (x_first || j == 0) ? 0.0f : ez;
+            E1[0][r] = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy)), Ec[0][r]);
+            E1[1][r] = fmaf(Kc[1][r], fmaf(sz, dzHx, -(sx * dxHz)), Ec[1][r]);
+            E1[2][r] = fmaf(Kc[2][r], fmaf(sx, dxHy, -(sy * dyHx)), Ec[2][r]);
         }
-        if (k == 0) {   // perfect conductor (x = 0 and y = 0: CP tiles only)
+        // perfect conductor: tangential E on the planes x = 0, y = 0, z = 0
+        auto conductor = [&](int kk, float (&e)[3][TY]) {
+            if (kk == 0) {
 #pragma unroll
-            for (int r = 0; r < TY; ++r) E1[0][r] = E1[1][r] = 0.0f;
-        }
-        // the soft current source of step n on E^{n+1}
-        auto source = [&](int kk, const float4 &st, float (&e)[3][TY], const float (&kv)[3][TY]) {
-            if (!src_on || kk < sp.lo1 || kk >= sp.lo1 + sp.n1) return;
-            const int pl = sp.n0 * sp.n1, d = x - sp.index;
-            if (!(d == 0 || (snc == 5 && d == 1))) return;
+                for (int r = 0; r < TY; ++r) e[0][r] = e[1][r] = 0.0f;
+            }
+            if constexpr (CP) {
+                if (fl & F_X0) {
 #pragma unroll
-            for (int r = 0; r < TY; ++r) {
-                const int a = jb + r - sp.lo0;
-                if (a < 0 || a >= sp.n0) continue;
-                const float2 *q = sj + (kk - sp.lo1) * sp.n0 + a;
-                const float2 jy = q[(d ? 3 : 0) * pl], jz = q[(d ? 4 : 1) * pl];
-                e[1][r] = fmaf(-kv[1][r], fmaf(jy.x, st.x, jy.y * st.y), e[1][r]);
-                e[2][r] = fmaf(-kv[2][r], fmaf(jz.x, st.x, jz.y * st.y), e[2][r]);
-                if (snc == 5 && d == 0) {
-                    const float2 jx = q[2 * pl];
-                    e[0][r] = fmaf(-kv[0][r], fmaf(jx.x, st.x, jx.y * st.y), e[0][r]);
+                    for (int r = 0; r < TY; ++r) {
+                        e[1][r] = L.x == 0 ? 0.0f : e[1][r];
+                        e[2][r] = L.x == 0 ? 0.0f : e[2][r];
+                    }
+                }
+                if (fl & F_Y0) {
+#pragma unroll
+                    for (int r = 0; r < TY; ++r)
+                        if (jb + r == 0) e[0][r] = e[2][r] = 0.0f;
                 }
             }
         };
-        source(k, st0, E1, Kc);
+        // the soft current source of one step on E after it
+        auto source = [&](int kk, int n, float (&e)[3][TY], const float (&kv)[3][TY]) {
+            if (!CP || !(fl & F_SRC)) return;
+            Const<YoRhsD> Rc = opaque(R);
+            const int lo1 = Rc->src.lo1, n1 = Rc->src.n1;
+            if (kk < lo1 || kk >= lo1 + n1) return;
+            const int lo0 = Rc->src.lo0, n0 = Rc->src.n0, snc = Rc->src_nc;
+            Const<float> st = (Const<float>)(uintptr_t)(Rc->steptab + n);
+            const float stx = st[0], sty = st[1];
+            const int pl = n0 * n1, d = L.x - Rc->src.index;
+            if (!(d == 0 || (snc == 5 && d == 1))) return;
+            const Global<const float2> sj = (Global<const float2>)(uintptr_t)Rc->src_j;
+#pragma unroll
+            for (int r = 0; r < TY; ++r) {
+                const int a = jb + r - lo0;
+                if (a < 0 || a >= n0) continue;
+                const Global<const float2> q = sj + (kk - lo1) * n0 + a;
+                const Global<const float2> qy = q + (d ? 3 : 0) * pl, qz = q + (d ? 4 : 1) * pl;
+                e[1][r] = fmaf(-kv[1][r], fmaf(qy->x, stx, qy->y * sty), e[1][r]);
+                e[2][r] = fmaf(-kv[2][r], fmaf(qz->x, stx, qz->y * sty), e[2][r]);
+                if (snc == 5 && d == 0) {
+                    const Global<const float2> qx_ = q + 2 * pl;
+                    e[0][r] = fmaf(-kv[0][r], fmaf(qx_->x, stx, qx_->y * sty), e[0][r]);
+                }
+            }
+        };
+        conductor(k, E1);
+        source(k, step, E1, Kc);
+        if constexpr (DFT) {
+            // E^{n+1} on this tile's cells of the design box and the port planes,
+            // for the running DFT (k_dft, which adds both steps after this launch)
+            if (k >= k0 && k < k1 && (fl & (0xf << F_BOX | F_MON))) {
+                Const<YoPlanD> Pc = opaque(P);
+                const Global<float> mid = (Global<float>)(uintptr_t)opaque(R)->dft_mid;
+                const int bx = Pc->box[3], by = Pc->box[4], bz = Pc->box[5], bk = k - Pc->box[2];
+                const int bi = L.x - Pc->box[0];
+                if (bk >= 0 && bk < bz && (fl & 0xf << F_BOX) && L.own && bi >= 0 && bi < bx) {
+#pragma unroll
+                    for (int r = 0; r < TY; ++r) {
+                        if (!(fl >> (F_BOX + r) & 1)) continue;
+                        const int o = (bk * by + jb + r - Pc->box[1]) * bx + bi;
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) mid[c * bz * by * bx + o] = E1[c][r];
+                    }
+                }
+                if (fl & F_MON) {
+                    const Global<float> mon = mid + 3 * bz * by * bx;
+                    const int np = Pc->n_ports, nc = Pc->mon_nc;
+                    for (int q = 0; q < np; ++q) {
+                        const int lo0 = Pc->ports[q].lo0, n0 = Pc->ports[q].n0, n1 = Pc->ports[q].n1;
+                        const int bk1 = k - Pc->ports[q].lo1, d = L.x - Pc->ports[q].index;
+                        if (bk1 < 0 || bk1 >= n1 || !L.own || !(d == 0 || (nc == 5 && d == 1))) continue;
+                        const int pl = n0 * n1, o = Pc->mon_off[q] + bk1 * n0;
+#pragma unroll
+                        for (int r = 0; r < TY; ++r) {
+                            const int a = jb + r - lo0;
+                            if (!(fl >> (F_OWN + r) & 1) || a < 0 || a >= n0) continue;
+                            mon[o + (d ? 3 : 0) * pl + a] = E1[1][r];
+                            mon[o + (d ? 4 : 1) * pl + a] = E1[2][r];
+                            if (nc == 5 && d == 0) mon[o + 2 * pl + a] = E1[0][r];
+                        }
+                    }
+                }
+            }
+        }
         slot(4 + 2 * par, w) = E1[0][0];
         slot(4 + 2 * par + 1, w) = E1[2][0];
 
         // ---- S3 at plane k-1 ----
-        const bool ownk = km >= k0 && km < k1;
-        if (pzm >= 0) cz = cpml_uniform(profz, nz, 3, km);
+        if (pzm >= 0) cz = cpml_uniform(profz, 1, km);
         const float fxu = slot(4 + 2 * (par ^ 1), wu), fzu = slot(4 + 2 * (par ^ 1) + 1, wu);
 #pragma unroll
         for (int r = 0; r < TY; ++r) {
-            const int j = jb + r;
             const float eu0 = r + 1 < TY ? E1p[0][r + 1 < TY ? r + 1 : r] : fxu;
             const float eu2 = r + 1 < TY ? E1p[2][r + 1 < TY ? r + 1 : r] : fzu;
             float dyEz = eu2 - E1p[2][r];
@@ -354,38 +413,40 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
             float dxEz = shfl_next(E1p[2][r]) - E1p[2][r];
             float dxEy = shfl_next(E1p[1][r]) - E1p[1][r];
             float dyEx = eu0 - E1p[0][r];
-            const bool jin = j >= 0 && j < ny;
-            const bool own = ownk && (own_rows >> r & 1);
-            if (xc && kmin && jin && px >= 0) {
-                float n0, n1;
-                dxEz = pml_diff(dxEz, cxH, xst_(r, 0, par ^ 1), n0);
-                dxEy = pml_diff(dxEy, cxH, xst_(r, 1, par ^ 1), n1);
-                if (own && L.own) {
-                    bstore(n0, PS, px, ax(6 + 2 * s2, km, j));
-                    bstore(n1, PS, px, ax(6 + 2 * s2 + 1, km, j));
+            const bool own = ownk && (fl >> (F_OWN + r) & 1);
+            if constexpr (CP) {
+                if ((fl & F_X) && kmin && (fl >> (F_IN + r) & 1)) {
+                    if (L.px >= 0) {
+                        float n0, n1;
+                        dxEz = pml_diff(dxEz, cxH, xst(r, 0, par ^ 1), n0);
+                        dxEy = pml_diff(dxEy, cxH, xst(r, 1, par ^ 1), n1);
+                        if (own && L.own) {
+                            const unsigned o = xb2 + (unsigned)(km * ny + jb + r) * xrow;
+                            bstore(n0, PS, L.px, o + 2 * xw);
+                            bstore(n1, PS, L.px, o + 3 * xw);
+                        }
+                    }
                 }
-            }
-            if (yc && kmin) {
-                const int py = slab_index(j, ny, ylo, yhi);
-                if (py >= 0) {
-                    const Cpml cy = cpml_uniform(profy, ny, 3, j);
-                    const int sr = j < ylo ? j : j - (ny - yhi);
+                if ((fl >> (F_YSLAB + r) & 1) && kmin) {
+                    const Cpml cy = cpml_uniform(profy, 1, jb + r);
                     float n0, n1;
-                    dyEz = pml_diff(dyEz, cy, yst(sr, 0, par ^ 1), n0);
-                    dyEx = pml_diff(dyEx, cy, yst(sr, 1, par ^ 1), n1);
+                    dyEz = pml_diff(dyEz, cy, yst(r, 0, par ^ 1), n0);
+                    dyEx = pml_diff(dyEx, cy, yst(r, 1, par ^ 1), n1);
                     if (own) {
-                        bstore(n0, PS, xst, ay(6 + 2 * s2, km, py));
-                        bstore(n1, PS, xst, ay(6 + 2 * s2 + 1, km, py));
+                        const unsigned o = yb2 + (unsigned)km * ypl + (unsigned)(py0 + r) * ps;
+                        bstore(n0, PS, xps + 512, o);
+                        bstore(n1, PS, xps + 768, o);
                     }
                 }
             }
-            if (pzm >= 0 && jin) {
+            if (pzm >= 0 && (fl >> (F_IN + r) & 1)) {
                 float n0, n1;
                 dzEy = pml_diff(dzEy, cz, zHp[0][r], n0);
                 dzEx = pml_diff(dzEx, cz, zHp[1][r], n1);
                 if (own) {
-                    bstore(n0, PS, xst, az(6 + 2 * s2, pzm, j));
-                    bstore(n1, PS, xst, az(6 + 2 * s2 + 1, pzm, j));
+                    const unsigned o = zb2 + (unsigned)(pzm * ny + jb + r) * ps;
+                    bstore(n0, PS, xps + 512, o);
+                    bstore(n1, PS, xps + 768, o);
                 }
             }
             H2[0][r] = Hp[0][r] - fmaf(sy, dyEz, -(sz * dzEy));
@@ -397,12 +458,12 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
         block_sync_lds();
 
         // ---- S4 at plane k-1 ----
-        if (pzm >= 0) cz = cpml_uniform(profz, nz, 0, km);
+        if (!ownk || !(fl & ((1 << TY) - 1))) return;
+        if (pzm >= 0) cz = cpml_uniform(profz, 0, km);
         const float gxd = slot(10, wd), gzd = slot(11, wd);
         float E2[3][TY];
 #pragma unroll
         for (int r = 0; r < TY; ++r) {
-            const int j = jb + r;
             const float hd0 = r > 0 ? H2[0][r > 0 ? r - 1 : 0] : gxd;
             const float hd2 = r > 0 ? H2[2][r > 0 ? r - 1 : 0] : gzd;
             float dyHz = H2[2][r] - hd2;
@@ -411,58 +472,52 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
             float dxHz = H2[2][r] - shfl_prev(H2[2][r]);
             float dxHy = H2[1][r] - shfl_prev(H2[1][r]);
             float dyHx = H2[0][r] - hd0;
-            const bool own = ownk && (own_rows >> r & 1);
-            if (xc && own && px >= 0) {
-                float n0, n1;
-                dxHz = pml_diff(dxHz, cxE, xst_(r, 2, par ^ 1), n0);
-                dxHy = pml_diff(dxHy, cxE, xst_(r, 3, par ^ 1), n1);
-                if (L.own) {
-                    bstore(n0, PS, px, ax(2 * s2, km, j));
-                    bstore(n1, PS, px, ax(2 * s2 + 1, km, j));
+            const bool own = fl >> (F_OWN + r) & 1;
+            if constexpr (CP) {
+                if ((fl & F_X) && own) {
+                    if (L.px >= 0) {
+                        float n0, n1;
+                        dxHz = pml_diff(dxHz, cxE, xst(r, 2, par ^ 1), n0);
+                        dxHy = pml_diff(dxHy, cxE, xst(r, 3, par ^ 1), n1);
+                        if (L.own) {
+                            const unsigned o = xb2 + (unsigned)(km * ny + jb + r) * xrow;
+                            bstore(n0, PS, L.px, o);
+                            bstore(n1, PS, L.px, o + xw);
+                        }
+                    }
                 }
-            }
-            if (yc && own) {
-                const int py = slab_index(j, ny, ylo, yhi);
-                if (py >= 0) {
-                    const Cpml cy = cpml_uniform(profy, ny, 0, j);
-                    const int sr = j < ylo ? j : j - (ny - yhi);
+                if ((fl >> (F_YSLAB + r) & 1) && own) {
+                    const Cpml cy = cpml_uniform(profy, 0, jb + r);
                     float n0, n1;
-                    dyHz = pml_diff(dyHz, cy, yst(sr, 2, par ^ 1), n0);
-                    dyHx = pml_diff(dyHx, cy, yst(sr, 3, par ^ 1), n1);
-                    bstore(n0, PS, xst, ay(2 * s2, km, py));
-                    bstore(n1, PS, xst, ay(2 * s2 + 1, km, py));
+                    dyHz = pml_diff(dyHz, cy, yst(r, 2, par ^ 1), n0);
+                    dyHx = pml_diff(dyHx, cy, yst(r, 3, par ^ 1), n1);
+                    const unsigned o = yb2 + (unsigned)km * ypl + (unsigned)(py0 + r) * ps;
+                    bstore(n0, PS, xps, o);
+                    bstore(n1, PS, xps + 256, o);
                 }
             }
             if (pzm >= 0 && own) {
                 float n0, n1;
                 dzHy = pml_diff(dzHy, cz, zEp[0][r], n0);
                 dzHx = pml_diff(dzHx, cz, zEp[1][r], n1);
-                bstore(n0, PS, xst, az(2 * s2, pzm, j));
-                bstore(n1, PS, xst, az(2 * s2 + 1, pzm, j));
+                const unsigned o = zb2 + (unsigned)(pzm * ny + jb + r) * ps;
+                bstore(n0, PS, xps, o);
+                bstore(n1, PS, xps + 256, o);
             }
-            float ex = fmaf(Kp[0][r], fmaf(sy, dyHz, -(sz * dzHy)), E1p[0][r]);
-            float ey = fmaf(Kp[1][r], fmaf(sz, dzHx, -(sx * dxHz)), E1p[1][r]);
-            float ez = fmaf(Kp[2][r], fmaf(sx, dxHy, -(sy * dyHx)), E1p[2][r]);
-            E2[0][r] = CP && j == 0 ? 0.0f : ex;
-            E2[1][r] = CP && x_first ? 0.0f : ey;
-            E2[2][r] = CP && (x_first || j == 0) ? 0.0f : ez;
+            E2[0][r] = fmaf(Kp[0][r], fmaf(sy, dyHz, -(sz * dzHy)), E1p[0][r]);
+            E2[1][r] = fmaf(Kp[1][r], fmaf(sz, dzHx, -(sx * dxHz)), E1p[1][r]);
+            E2[2][r] = fmaf(Kp[2][r], fmaf(sx, dxHy, -(sy * dyHx)), E1p[2][r]);
         }
-        if (km == 0) {
+        conductor(km, E2);
+        source(km, step + 1, E2, Kp);
+        const unsigned om = (unsigned)km * pstr;
 #pragma unroll
-            for (int r = 0; r < TY; ++r) E2[0][r] = E2[1][r] = 0.0f;
-        }
-        source(km, st1, E2, Kp);
-        if (ownk) {
-            const int om = (km + 1) * pstr;
+        for (int r = 0; r < TY; ++r) {
+            if (!(fl >> (F_OWN + r) & 1)) continue;
 #pragma unroll
-            for (int r = 0; r < TY; ++r) {
-                if (!(own_rows >> r & 1)) continue;
-                const int o = om + rb[r];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    bstore_nt(E2[c][r], FC, xst, c * rowb + o);
-                    bstore_nt(H2[c][r], FC, xst, (3 + c) * rowb + o);
-                }
+            for (int c = 0; c < 3; ++c) {
+                bstore_nt(E2[c][r], FC, xs + 256 * c, om + rb[r]);
+                bstore_nt(H2[c][r], FC, xs + 768 + 256 * c, om + rb[r]);
             }
         }
     };
@@ -474,7 +529,7 @@ __device__ __forceinline__ void wave_pair(const YoPlanD &P, const YoRhsD &R, con
     }
 }
 
-template <int TY, int W, bool CP>
+template <int TY, int W, bool CP, bool DFT>
 __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
 {
     const int nb = gridDim.x, b = blockIdx.x;
@@ -488,10 +543,11 @@ __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
     int s = 0;
     while (s + 1 < a.n_slots && wave0 >= a.prefix[s + 1]) ++s;
     const YoSlot sl = a.slot[s];
-    const YoPlanD &P = *sl.plan;
-    const int step = *P.step_ctr + a.k_offset;
+    const Const<YoPlanD> P = constant(sl.plan);
+    const int step = *constant(P->step_ctr) + a.k_offset;
     // the host schedules a pair only where both steps remain
-    if (step + 1 >= P.n_steps) return;
+    if (step + 1 >= P->n_steps) return;
+    const int now = P->nbuf == 3 ? step % 3 : (constant(P->step_ctr)[1] + a.b_offset) & 1;
     const int blk = (wave0 - a.prefix[s]) / W;
     // consecutive blocks take neighbouring strips of the same rows (whose row
     // segments are neighbours in memory) of one right-hand side, then the same
@@ -505,19 +561,23 @@ __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
     const int r = sl.rhs0 + in_g / gsz;
     const int ti = g * G + in_g % gsz;
     extern __shared__ float lds[];
-    wave_pair<TY, W, CP>(P, P.rhs[r], step, sl.tiles[ti], w, lane, lds);
+    const Const<int> tp = (Const<int>)(uintptr_t)(sl.tiles + ti);
+    wave_pair<TY, W, CP, DFT>(P, constant(P->rhs + r), step, now, int4{tp[0], tp[1], tp[2], tp[3]}, w, lane, lds);
 }
 
 }  // namespace
 
-hipError_t yo_launch_pair(bool shell, const YoStepArgs &args, int blocks, hipStream_t s)
+hipError_t yo_launch_pair(bool shell, bool dft, const YoStepArgs &args, int blocks, hipStream_t s)
 {
     if (blocks <= 0) return hipSuccess;
     if (args.wpb != YO_PAIR_W) return hipErrorInvalidValue;
     const size_t lds = sizeof(float) * 12 * YO_PAIR_W * 64;
     const size_t lds_shell = lds + sizeof(float) * (YO_PAIR_YROWS * 4 * 2 * 64 + YO_PAIR_W * YO_PAIR_TY * 4 * 2 * 32);
     const dim3 g(blocks), b(64 * YO_PAIR_W);
-    if (shell) hipLaunchKernelGGL((k_yee_pair<YO_PAIR_TY, YO_PAIR_W, true>), g, b, lds_shell, s, args);
-    else hipLaunchKernelGGL((k_yee_pair<YO_PAIR_TY, YO_PAIR_W, false>), g, b, lds, s, args);
+    constexpr int T = YO_PAIR_TY, W = YO_PAIR_W;
+    if (shell && dft) hipLaunchKernelGGL((k_yee_pair<T, W, true, true>), g, b, lds_shell, s, args);
+    else if (shell) hipLaunchKernelGGL((k_yee_pair<T, W, true, false>), g, b, lds_shell, s, args);
+    else if (dft) hipLaunchKernelGGL((k_yee_pair<T, W, false, true>), g, b, lds, s, args);
+    else hipLaunchKernelGGL((k_yee_pair<T, W, false, false>), g, b, lds, s, args);
     return hipGetLastError();
 }

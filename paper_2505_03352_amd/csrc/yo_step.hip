@@ -47,36 +47,33 @@ namespace {
 // plus the y and z profile coefficients of the tile's rows and planes, one
 // row (plane) per lane, taken out with readlane when used.
 struct CpmlCtx {
-    int nx, ny, nz, nxp;
+    int ny, nz, ns;
     int plo[3], phi[3], W[3];
-    int off[3], n[3];        // CPML memory layout (floats), see YoRhsD
-    int xrp;                 // x-slab memories: floats from one (j, k) row to the next
-    int qEo, qEn, qHo, qHn;  // memories (first component) read and written this step, E and Ht
+    unsigned so[3], sn[3];   // each axis' slots read and written, bytes
+    int xrow, xw;            // x-slab rows: bytes per row and per value
     Rsrc ps;                 // this right-hand side's CPML memories
     Cpml cyE, cyH;           // lane l: row j0 - 1 + l
     Cpml czE, czH;           // lane l: plane k0 - 1 + l
     int j0m, k0m;            // j0 - 1, k0 - 1
 };
 
-// Byte offset of CPML memory q (a slot's first component + c, see
-// cpml_slots) of axis A at row j of plane k, the wave-uniform part; false
-// when the row is outside the axis' slabs (x-slab: the lane part decides).
-// The lane part is the column's byte offset, as in the field arrays (y and z
-// slabs), or px, that of the column inside the x-slabs (negative outside).
+// Byte offset of the memories of axis A at row j of plane k within a slot, the
+// wave-uniform part; false when the row is outside the axis' slabs (x-slab:
+// the lane part decides).
 template <int A>
-__device__ __forceinline__ bool psi_at(const CpmlCtx &C, int q, int j, int k, int &soff)
+__device__ __forceinline__ bool psi_at(const CpmlCtx &C, int j, int k, unsigned &o)
 {
     if (A == 0) {
-        soff = (C.off[0] + q * C.n[0] + (k * C.ny + j) * C.xrp) * (int)sizeof(float);
+        o = (unsigned)(k * C.ny + j) * C.xrow;
         return true;
     }
     if (A == 1) {
         const int py = slab_index(j, C.ny, C.plo[1], C.phi[1]);
-        soff = (C.off[1] + q * C.n[1] + (k * C.W[1] + py) * C.nxp) * (int)sizeof(float);
+        o = (unsigned)((k * C.W[1] + py) * C.ns) * 1024u;
         return py >= 0;
     }
     const int pz = slab_index(k, C.nz, C.plo[2], C.phi[2]);
-    soff = (C.off[2] + q * C.n[2] + (pz * C.ny + j) * C.nxp) * (int)sizeof(float);
+    o = (unsigned)((pz * C.ny + j) * C.ns) * 1024u;
     return pz >= 0;
 }
 
@@ -87,23 +84,21 @@ __device__ __forceinline__ bool psi_at(const CpmlCtx &C, int q, int j, int k, in
 // owner writes the new value.  PRE: the old values were loaded with the
 // plane's fields (q[axis][component]); else they are loaded here.
 template <int A, bool PRE>
-__device__ __forceinline__ void psi_pair(const CpmlCtx &C, int qo, int qn, int j, int k, const LaneX &L,
-                                         const Cpml &c, bool store, const float (&q)[2], float &d0, float &d1)
+__device__ __forceinline__ void psi_pair(const CpmlCtx &C, int v, int j, int k, const LaneX &L, const Cpml &c,
+                                         bool store, const float (&q)[2], float &d0, float &d1)
 {
-    int s0, s1, t0, t1;
-    if (!psi_at<A>(C, qo, j, k, s0)) return;
+    unsigned o;
+    if (!psi_at<A>(C, j, k, o)) return;
     if (A == 0 && L.px < 0) return;
-    psi_at<A>(C, qo + 1, j, k, s1);
-    const int vl = A == 0 ? L.px : L.xl;
+    const int vl = A == 0 ? L.px : L.xp + 256 * v, st = A == 0 ? C.xw : 256;
+    const unsigned ov = A == 0 ? o + v * C.xw : o;
     float n0, n1;
-    d0 = pml_diff(d0, c, PRE ? q[0] : bload(C.ps, vl, s0), n0);
-    d1 = pml_diff(d1, c, PRE ? q[1] : bload(C.ps, vl, s1), n1);
+    d0 = pml_diff(d0, c, PRE ? q[0] : bload(C.ps, vl, C.so[A] + ov), n0);
+    d1 = pml_diff(d1, c, PRE ? q[1] : bload(C.ps, vl, C.so[A] + ov + st), n1);
     if (store) {
-        const int vs = A == 0 ? L.px : L.xs;
-        psi_at<A>(C, qn, j, k, t0);
-        psi_at<A>(C, qn + 1, j, k, t1);
-        bstore(n0, C.ps, vs, t0);
-        bstore(n1, C.ps, vs, t1);
+        const int vs = A == 0 ? L.px : L.xps + 256 * v;
+        bstore(n0, C.ps, vs, C.sn[A] + ov);
+        bstore(n1, C.ps, vs, C.sn[A] + ov + st);
     }
 }
 
@@ -114,11 +109,11 @@ __device__ __forceinline__ void h_cpml(const CpmlCtx &C, int j, int k, const Lan
 {
     if (j < 0 || j >= C.ny || k < 0) return;
     if (PM & 1)   // Hy, Hz
-        psi_pair<0, PRE>(C, C.qHo, C.qHn, j, k, L, cxH, own_row && L.own, q[0], dxEz, dxEy);
+        psi_pair<0, PRE>(C, 2, j, k, L, cxH, own_row && L.own, q[0], dxEz, dxEy);
     if (PM & 2)   // Hx, Hz
-        psi_pair<1, PRE>(C, C.qHo, C.qHn, j, k, L, lane_cpml(C.cyH, j - C.j0m), own_row && L.st, q[1], dyEz, dyEx);
+        psi_pair<1, PRE>(C, 2, j, k, L, lane_cpml(C.cyH, j - C.j0m), own_row && L.st, q[1], dyEz, dyEx);
     if (PM & 4)   // Hx, Hy
-        psi_pair<2, PRE>(C, C.qHo, C.qHn, j, k, L, lane_cpml(C.czH, k - C.k0m), own_row && L.st, q[2], dzEy, dzEx);
+        psi_pair<2, PRE>(C, 2, j, k, L, lane_cpml(C.czH, k - C.k0m), own_row && L.st, q[2], dzEy, dzEx);
 }
 
 // CPML corrections of the six differences of one owned E site row (each E
@@ -131,40 +126,30 @@ __device__ __forceinline__ void e_cpml(const CpmlCtx &C, int j, int k, const Lan
                                        float &dyHx, float &dzHy, float &dzHx)
 {
     if (PM & 1)   // Ey, Ez
-        psi_pair<0, PRE>(C, C.qEo, C.qEn, j, k, L, cxE, L.own, q[0], dxHz, dxHy);
+        psi_pair<0, PRE>(C, 0, j, k, L, cxE, L.own, q[0], dxHz, dxHy);
     if (PM & 2)   // Ex, Ez
-        psi_pair<1, PRE>(C, C.qEo, C.qEn, j, k, L, lane_cpml(C.cyE, j - C.j0m), L.st, q[1], dyHz, dyHx);
+        psi_pair<1, PRE>(C, 0, j, k, L, lane_cpml(C.cyE, j - C.j0m), L.st, q[1], dyHz, dyHx);
     if (PM & 4)   // Ex, Ey
-        psi_pair<2, PRE>(C, C.qEo, C.qEn, j, k, L, lane_cpml(C.czE, k - C.k0m), L.st, q[2], dzHy, dzHx);
+        psi_pair<2, PRE>(C, 0, j, k, L, lane_cpml(C.czE, k - C.k0m), L.st, q[2], dzHy, dzHx);
 }
 
-// Old CPML memories q (a slot's first component, see cpml_slots) of every
-// axis in PM at one row, or 0 where `use` is false or the lane is outside the
-// slab (its offset is past the buffer, so the load moves no data and the
-// loads need no branch).
+// Old CPML memories v, v + 1 (0: E's, 2: Ht's) of every axis in PM at one
+// row, or 0 where `use` is false or the lane is outside the slab (its offset
+// is past the buffer, so the load moves no data and the loads need no branch).
 template <int PM>
-__device__ __forceinline__ void psi_preload(const CpmlCtx &C, int q, int j, int k, const LaneX &L, bool use,
+__device__ __forceinline__ void psi_preload(const CpmlCtx &C, int v, int j, int k, const LaneX &L, bool use,
                                             float (&out)[3][2])
 {
-    int s0, s1;
+    unsigned o;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         if (!(PM & (1 << a))) continue;
-        bool in = false;
-        if (a == 0) {
-            in = psi_at<0>(C, q, j, k, s0);
-            psi_at<0>(C, q + 1, j, k, s1);
-        } else if (a == 1) {
-            in = psi_at<1>(C, q, j, k, s0);
-            psi_at<1>(C, q + 1, j, k, s1);
-        } else {
-            in = psi_at<2>(C, q, j, k, s0);
-            psi_at<2>(C, q + 1, j, k, s1);
-        }
+        bool in = a == 0 ? psi_at<0>(C, j, k, o) : a == 1 ? psi_at<1>(C, j, k, o) : psi_at<2>(C, j, k, o);
         in = in && use;
-        const int v = a == 0 ? (L.px >= 0 ? L.px : kFar) : L.xl;
-        out[a][0] = bload(C.ps, in ? v : kFar, in ? s0 : 0);
-        out[a][1] = bload(C.ps, in ? v : kFar, in ? s1 : 0);
+        const int vl = !in ? kFar : a == 0 ? (L.px >= 0 ? L.px : kFar) : L.xp + 256 * v;
+        const unsigned so = in ? C.so[a] + o + (a == 0 ? v * C.xw : 0) : 0u, st = !in ? 0u : a == 0 ? C.xw : 256u;
+        out[a][0] = bload(C.ps, vl, so);
+        out[a][1] = bload(C.ps, vl, so + st);
     }
 }
 
@@ -181,18 +166,16 @@ __device__ __forceinline__ void psi_preload(const CpmlCtx &C, int q, int j, int 
 // recomputes the Ht row below the block and only its top wave loads the E
 // row above it; one barrier per plane.
 template <int TY, int PM, bool COOP, bool PF>
-__device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, const int step,
+__device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, const int now,
                                           const int4 t, const int w, const int lane, float *xs)
 {
-    const int nx = P.nx, ny = P.ny, nz = P.nz, nxp = P.nxp;
-    const int rows = ny + 2;
-    const size_t groups = (size_t)(nz + 2) * rows;           // row groups (j, k)
-    const int rowb = nxp * (int)sizeof(float);                // one component row, bytes
-    // state: 6 component rows per group (E then Ht); kappa: 3
-    const Rsrc Fo = rsrc_of(R.F[step % P.nbuf], 6 * groups * nxp);
-    const Rsrc Fn = rsrc_of(R.F[(step + 1) % P.nbuf], 6 * groups * nxp);
-    const Rsrc K = rsrc_of(P.kappa, 3 * groups * nxp);
-    const int eb = 0, hb = 3 * rowb;                          // E and Ht within a state group
+    const int ny = P.ny, nz = P.nz;
+    const int rows = ny + 1;
+    const unsigned gs = 1536u * P.ns;                         // state of one row, bytes (kappa: half)
+    const int nxt = buf_next(&P, now, 1);
+    const Rsrc Fo = rsrc_of(R.F[now], array_bytes(&P, 6));
+    const Rsrc Fn = rsrc_of(R.F[nxt], array_bytes(&P, 6));
+    const Rsrc K = rsrc_of(P.kappa, array_bytes(&P, 3));
     const float sx = P.sx, sy = P.sy, sz = P.sz;
 
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
@@ -215,34 +198,34 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
     // lanes past the halo lane after the last owned one take no part: their
     // column offset lies past every buffer, so their loads move no data (a
     // narrow strip costs only its own columns)
-    LaneX L = lane_x(P, x0, xn, lane, P.lead);
-    const int x = x0 - P.lead + lane;
-    const int xo = L.xl, xs_ = L.xs;
+    LaneX L = lane_x(&P, x0, xn, lane);
+    const int x = L.x;
+    const int xo = L.xl, xh = L.xl + 768, xs_ = L.xs;
     const bool st_x = L.st;
-    // wave-uniform byte offsets of row group (j, k) in the state and kappa arrays
-    auto ro = [&](int j, int k) -> int {
-        return ((k + 1) * rows + (clampi(j, -1, ny) + 1)) * 6 * rowb;
+    // wave-uniform byte offsets of row (j, k) in the state and kappa arrays, and
+    // the lane's for loads from plane k (past the buffer outside the grid)
+    auto ro = [&](int j, int k) -> unsigned {
+        return (unsigned)(clampi(k, 0, nz - 1) * rows + (clampi(j, -1, ny) + 1)) * gs;
     };
-    auto rk = [&](int j, int k) -> int {
-        return ((k + 1) * rows + (clampi(j, -1, ny) + 1)) * 3 * rowb;
-    };
+    auto at = [&](int v, int k) -> int { return k >= 0 && k < nz ? v : kFar; };
+    auto rk = [&](int j, int k) -> unsigned { return ro(j, k) >> 1; };
 
     // ---- CPML data (CPML classes only), read before any store ----
     Cpml cxE = {1.0f, 0.0f, 1.0f}, cxH = {1.0f, 0.0f, 1.0f};
     CpmlCtx C;
     if (PM) {
-        C.nx = nx; C.ny = ny; C.nz = nz; C.nxp = nxp;
+        C.ny = ny; C.nz = nz; C.ns = P.ns;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             C.plo[a] = P.plo[a];
             C.phi[a] = P.phi[a];
             C.W[a] = P.plo[a] + P.phi[a];
-            C.off[a] = P.psi_off[a];
-            C.n[a] = P.psi_n[a];
+            C.so[a] = 4u * (P.psi_off[a] + now * P.psi_n[a]);
+            C.sn[a] = 4u * (P.psi_off[a] + nxt * P.psi_n[a]);
         }
-        C.xrp = P.psi_xrp;
-        C.ps = rsrc_of(R.psi, (size_t)P.psi_total);
-        cpml_slots(P.nbuf, step, C.qEo, C.qEn, C.qHo, C.qHn);
+        C.xrow = P.psi_xrow * 4;
+        C.xw = P.psi_xw * 4;
+        C.ps = rsrc_of(R.psi, P.psi_bytes);
         C.j0m = j0 - 1;
         C.k0m = k0 - 1;
         const Cpml one = {1.0f, 0.0f, 1.0f};
@@ -250,23 +233,18 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
         if ((PM & 2) && lane <= TY) {
             const int jj = j0 - 1 + lane;
             if (jj >= 0 && jj < ny && slab_index(jj, ny, P.plo[1], P.phi[1]) >= 0) {
-                C.cyE = cpml_at(P.prof[1], ny, 0, jj);
-                C.cyH = cpml_at(P.prof[1], ny, 3, jj);
+                C.cyE = cpml_at(P.prof[1], 0, jj);
+                C.cyH = cpml_at(P.prof[1], 1, jj);
             }
         }
         if (PM & 4) {
             const int kk = k0 - 1 + lane;
             if (kk >= 0 && kk < k1 && slab_index(kk, nz, P.plo[2], P.phi[2]) >= 0) {
-                C.czE = cpml_at(P.prof[2], nz, 0, kk);
-                C.czH = cpml_at(P.prof[2], nz, 3, kk);
+                C.czE = cpml_at(P.prof[2], 0, kk);
+                C.czH = cpml_at(P.prof[2], 1, kk);
             }
         }
-        if ((PM & 1) && xo != kFar && slab_index(x, nx, P.plo[0], P.phi[0]) >= 0) {
-            // low slab first, then the high one (YoPlanD::psi_xside floats on)
-            L.px = (x < P.plo[0] ? x : P.psi_xside + x - (nx - P.phi[0])) * (int)sizeof(float);
-            cxE = cpml_at(P.prof[0], nx, 0, x);
-            cxH = cpml_at(P.prof[0], nx, 3, x);
-        }
+        if (PM & 1) lane_xslab(&P, L, cxE, cxH);
     }
 
     float Ec[3][TY + 2], Enx[3][TY + 2];
@@ -284,38 +262,39 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
     // unless top) are filled from neighbours or never read
     auto load_plane = [&](int k, float (&en)[3][TY + 2], float (&ho)[3][TY + 1],
                           float (&kv)[3][TY]) {
+        const int ve = at(xo, k + 1), vh = at(xh, k), vk = at(L.xk, k);
 #pragma unroll
         for (int r = 1; r <= TY; ++r) {
             const int o = ro(j0 - 1 + r, k + 1);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) en[c][r] = bload(Fo, xo, eb + c * rowb + o);
+            for (int c = 0; c < 3; ++c) en[c][r] = bload(Fo, ve + 256 * c, o);
         }
 #pragma unroll
         for (int r = 1; r <= TY; ++r) {
             const int o = ro(j0 - 1 + r, k);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) ho[c][r] = bload(Fo, xo, hb + c * rowb + o);
+            for (int c = 0; c < 3; ++c) ho[c][r] = bload(Fo, vh + 256 * c, o);
         }
 #pragma unroll
         for (int r = 1; r <= TY; ++r) {
             const int o = rk(j0 - 1 + r, k);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) kv[c][r - 1] = bload(K, xo, c * rowb + o);
+            for (int c = 0; c < 3; ++c) kv[c][r - 1] = bload(K, vk + 256 * c, o);
         }
         // last, so that the branches do not blur the wait counts of the rest
         if (bottom) {
             const int oe = ro(j0 - 1, k + 1), oh = ro(j0 - 1, k);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                en[c][0] = bload(Fo, xo, eb + c * rowb + oe);
-                ho[c][0] = bload(Fo, xo, hb + c * rowb + oh);
+                en[c][0] = bload(Fo, ve + 256 * c, oe);
+                ho[c][0] = bload(Fo, vh + 256 * c, oh);
             }
         }
         if (top) {
             // only Ex and Ez of the row above enter (as y-differences)
             const int o = ro(j0 + TY, k + 1);
-            en[0][TY + 1] = bload(Fo, xo, eb + o);
-            en[2][TY + 1] = bload(Fo, xo, eb + 2 * rowb + o);
+            en[0][TY + 1] = bload(Fo, ve, o);
+            en[2][TY + 1] = bload(Fo, ve + 512, o);
         }
     };
 
@@ -329,7 +308,7 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
         if (r == 0 && !bottom) continue;
         const int o = ro(j0 - 1 + r, k0 - 1);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) Ec[c][r] = bload(Fo, xo, eb + c * rowb + o);
+        for (int c = 0; c < 3; ++c) Ec[c][r] = bload(Fo, at(xo, k0 - 1) + 256 * c, o);
     }
 #pragma unroll
     for (int r = 0; r < TY; ++r) { Hp[0][r] = 0.0f; Hp[1][r] = 0.0f; }
@@ -354,12 +333,12 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             for (int r = 0; r <= TY; ++r) {
                 const int j = j0 - 1 + r;
                 const bool use = (r > 0 || bottom) && kin && j >= 0 && j < ny;
-                psi_preload<PM>(C, C.qHo, j, k, L, use, qH[r]);
+                psi_preload<PM>(C, 2, j, k, L, use, qH[r]);
             }
 #pragma unroll
             for (int r = 1; r <= TY; ++r) {
                 const bool use = k >= k0 && r <= jn;
-                psi_preload<PM>(C, C.qEo, j0 - 1 + r, k, L, use, qE[r - 1]);
+                psi_preload<PM>(C, 0, j0 - 1 + r, k, L, use, qE[r - 1]);
             }
         }
         const int pp = k & 1;
@@ -391,10 +370,10 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             Hc[1][r] = hy;
             Hc[2][r] = hz;
             if (own_row && st_x) {
-                const int o = ro(j, k) + hb;
-                bstore_nt(hx, Fn, xs_, o);
-                bstore_nt(hy, Fn, xs_, rowb + o);
-                bstore_nt(hz, Fn, xs_, 2 * rowb + o);
+                const unsigned o = ro(j, k);
+                bstore_nt(hx, Fn, xs_ + 768, o);
+                bstore_nt(hy, Fn, xs_ + 1024, o);
+                bstore_nt(hz, Fn, xs_ + 1280, o);
             }
         }
         if (COOP) {
@@ -432,10 +411,10 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             ey = (x == 0 || k == 0) ? 0.0f : ey;
             ez = (x == 0 || j == 0) ? 0.0f : ez;
             if (st_x) {
-                const int o = ro(j, k) + eb;
+                const unsigned o = ro(j, k);
                 bstore_nt(ex, Fn, xs_, o);
-                bstore_nt(ey, Fn, xs_, rowb + o);
-                bstore_nt(ez, Fn, xs_, 2 * rowb + o);
+                bstore_nt(ey, Fn, xs_ + 256, o);
+                bstore_nt(ez, Fn, xs_ + 512, o);
             }
         }
 #pragma unroll
@@ -470,22 +449,22 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
 // (int4 .w) selecting its code.
 #define YO_PM_ANY 8
 template <int PM, bool COOP, bool PF, int TY>
-__device__ __forceinline__ void tile_step(const YoPlanD &P, const YoRhsD &R, int step, const int4 t,
+__device__ __forceinline__ void tile_step(const YoPlanD &P, const YoRhsD &R, int now, const int4 t,
                                           int w, int lane, float *xs)
 {
     if constexpr (PM == YO_PM_ANY) {
         switch (t.w) {
-        case 1: wave_step<TY, 1, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 2: wave_step<TY, 2, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 3: wave_step<TY, 3, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 4: wave_step<TY, 4, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 5: wave_step<TY, 5, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 6: wave_step<TY, 6, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        case 7: wave_step<TY, 7, COOP, PF>(P, R, step, t, w, lane, xs); break;
-        default: wave_step<TY, 0, COOP, PF>(P, R, step, t, w, lane, xs); break;
+        case 1: wave_step<TY, 1, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 2: wave_step<TY, 2, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 3: wave_step<TY, 3, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 4: wave_step<TY, 4, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 5: wave_step<TY, 5, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 6: wave_step<TY, 6, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        case 7: wave_step<TY, 7, COOP, PF>(P, R, now, t, w, lane, xs); break;
+        default: wave_step<TY, 0, COOP, PF>(P, R, now, t, w, lane, xs); break;
         }
     } else {
-        wave_step<TY, PM, COOP, PF>(P, R, step, t, w, lane, xs);
+        wave_step<TY, PM, COOP, PF>(P, R, now, t, w, lane, xs);
     }
 }
 
@@ -510,6 +489,7 @@ __global__ __launch_bounds__(64 * YO_MAX_WPB) void k_yee_step(const YoStepArgs a
     const YoPlanD &P = *sl.plan;
     const int step = *P.step_ctr + a.k_offset;
     if (step >= P.n_steps) return;
+    const int now = buf_now(P, step, a.b_offset);
     const int local = wave - a.prefix[s];
     if (COOP) {
         // one tile per block; consecutive blocks take the same tile for the
@@ -520,7 +500,7 @@ __global__ __launch_bounds__(64 * YO_MAX_WPB) void k_yee_step(const YoStepArgs a
         const int r = sl.rhs0 + blk % sl.nrhs;
         const int ti = blk / sl.nrhs;
         if (ti >= sl.ntile) return;
-        tile_step<PM, true, PF, TY>(P, P.rhs[r], step, sl.tiles[ti], w, lane, xs);
+        tile_step<PM, true, PF, TY>(P, P.rhs[r], now, sl.tiles[ti], w, lane, xs);
     } else {
         // A block's waves take consecutive tiles (neighbouring x-strips of
         // the same rows) of one right-hand side, so together they stream
@@ -532,7 +512,7 @@ __global__ __launch_bounds__(64 * YO_MAX_WPB) void k_yee_step(const YoStepArgs a
         const int r = sl.rhs0 + in_grp / wpb;
         const int ti = grp * wpb + in_grp % wpb;
         if (ti >= sl.ntile) return;
-        tile_step<PM, false, PF, TY>(P, P.rhs[r], step, sl.tiles[ti], 0, lane, nullptr);
+        tile_step<PM, false, PF, TY>(P, P.rhs[r], now, sl.tiles[ti], 0, lane, nullptr);
     }
 }
 
@@ -570,16 +550,14 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                                            const int4 t, const int w, const int wpb, const int lane,
                                            float *xs)
 {
-    const int ny = P.ny, nxp = P.nxp;
-    const int rows = ny + 2;
-    const size_t groups = (size_t)(P.nz + 2) * rows;
-    const int rowb = nxp * (int)sizeof(float);
+    const int ny = P.ny, nz = P.nz;
+    const int rows = ny + 1;
+    const unsigned gs = 1536u * P.ns;
     const int nb = P.nbuf;
-    const Rsrc FA = rsrc_of(R.F[step % nb], 6 * groups * nxp);          // after step n
-    const Rsrc FB = rsrc_of(R.F[(step + 1) % nb], 6 * groups * nxp);    // after n+1 (rim)
-    const Rsrc FC = rsrc_of(R.F[(step + 2) % nb], 6 * groups * nxp);    // after n+2
-    const Rsrc K = rsrc_of(P.kappa, 3 * groups * nxp);
-    const int eb = 0, hb = 3 * rowb;
+    const Rsrc FA = rsrc_of(R.F[step % nb], array_bytes(&P, 6));          // after step n
+    const Rsrc FB = rsrc_of(R.F[(step + 1) % nb], array_bytes(&P, 6));    // after n+1 (rim)
+    const Rsrc FC = rsrc_of(R.F[(step + 2) % nb], array_bytes(&P, 6));    // after n+2
+    const Rsrc K = rsrc_of(P.kappa, array_bytes(&P, 3));
     const float sx = P.sx, sy = P.sy, sz = P.sz;
 
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
@@ -601,28 +579,25 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
     auto xslot = [&](int pp, int dw, int q) -> float & {
         return xme[(pp * wpb + dw) * 20 * 64 + q * 64];
     };
-    const int x = x0 - 2 + lane;
-    const LaneX L = lane_x(P, x0, xn, lane, 2);
-    const int xo = x <= x0 + xn + 1 && x >= 0 && x < P.nx ? yo_col(x, P.sw, P.slead) * (int)sizeof(float) : kFar;
-    const int xs_ = L.xs;
+    const LaneX L = lane_x(&P, x0, xn, lane);
+    const int x = L.x, xo = L.xl, xh = L.xl + 768, xs_ = L.xs;
     const bool own_x = L.own, st_x = L.st;
     // R2's outermost layer, whose step-n+1 state the tiles around R2 read
     const int ra0 = P.r2[0], ra1 = P.r2[1], rb0 = P.r2[2], rb1 = P.r2[3], rc0 = P.r2[4], rc1 = P.r2[5];
     const bool rim_x = own_x && (x == ra0 || x == ra1 - 1);
-    // z-axis CPML memories (ZP): slots as in cpml_slots, byte offsets of
-    // component c of slot q at row j of slab plane pz
-    const int nz = P.nz, zlo = P.plo[2], zhi = P.phi[2];
-    const Rsrc PS = rsrc_of(R.psi, (size_t)P.psi_total);
+    // z-axis CPML memories (ZP): byte offsets of slot q's memories at row j
+    // of slab plane pz
+    const int zlo = P.plo[2], zhi = P.phi[2];
+    const Rsrc PS = rsrc_of(R.psi, P.psi_bytes);
     const int s0 = step % 3, s1 = (step + 1) % 3, s2 = (step + 2) % 3;
-    auto zo = [&](int q, int pz, int j) -> int {
-        return (P.psi_off[2] + q * P.psi_n[2] + (pz * ny + j) * nxp) * (int)sizeof(float);
+    auto zo = [&](int q, int pz, int j) -> unsigned {   // slot q
+        return 4u * (P.psi_off[2] + q * P.psi_n[2]) + (unsigned)((pz * ny + j) * P.ns) * 1024u;
     };
-    auto ro = [&](int j, int k) -> int {
-        return ((k + 1) * rows + (clampi(j, -1, ny) + 1)) * 6 * rowb;
+    auto ro = [&](int j, int k) -> unsigned {
+        return (unsigned)(clampi(k, 0, nz - 1) * rows + (clampi(j, -1, ny) + 1)) * gs;
     };
-    auto rk = [&](int j, int k) -> int {
-        return ((k + 1) * rows + (clampi(j, -1, ny) + 1)) * 3 * rowb;
-    };
+    auto at = [&](int v, int k) -> int { return k >= 0 && k < nz ? v : kFar; };
+    auto rk = [&](int j, int k) -> unsigned { return ro(j, k) >> 1; };
     // row index r: j = j0 - 2 + r
     constexpr int NE = TY + 4;     // E^n rows 0..TY+3 (the last: Ex and Ez only)
     constexpr int NH = TY + 3;     // Ht^{n-1/2} and Ht^{n+1/2} rows 0..TY+2
@@ -641,21 +616,14 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
     // all: every row from memory; else (COOP) the rows a neighbour passes on
     // are left for the exchange
     auto load_e = [&](int k, float (&e)[3][NE], bool all) {
-        if (ZP && (k < -1 || k > nz)) {   // past the ghost planes
-#pragma unroll
-            for (int r = 0; r < NE; ++r)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) e[c][r] = 0.0f;
-            return;
-        }
 #pragma unroll
         for (int r = 0; r < NE; ++r) {
             if (COOP && !all && ((r < 2 && !bottom) || (r >= TY + 2 && !top))) continue;
-            const int o = ro(j0 - 2 + r, k);
+            const unsigned o = ro(j0 - 2 + r, k);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 if (r == NE - 1 && c == 1) { e[c][r] = 0.0f; continue; }
-                e[c][r] = bload(FA, xo, eb + c * rowb + o);
+                e[c][r] = bload(FA, at(xo, k) + 256 * c, o);
             }
         }
     };
@@ -672,19 +640,12 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
 
     for (int k = k0 - 2; k <= k1; ++k) {
         load_e(k + 1, Enx, false);
-        if (ZP && k < -1) {
 #pragma unroll
-            for (int r = 0; r < NH; ++r)
+        for (int r = 0; r < NH; ++r) {
+            if (COOP && ((r < 2 && !bottom) || (r >= TY + 2 && !top))) continue;
+            const unsigned o = ro(j0 - 2 + r, k);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) Ho[c][r] = 0.0f;
-        } else {
-#pragma unroll
-            for (int r = 0; r < NH; ++r) {
-                if (COOP && ((r < 2 && !bottom) || (r >= TY + 2 && !top))) continue;
-                const int o = ro(j0 - 2 + r, k);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) Ho[c][r] = bload(FA, xo, hb + c * rowb + o);
-            }
+            for (int c = 0; c < 3; ++c) Ho[c][r] = bload(FA, at(xh, k) + 256 * c, o);
         }
         if (COOP) {
             // the rows the neighbours share, then theirs
@@ -725,16 +686,16 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
         // are loaded where used)
         const int pz = ZP ? slab_index(k, nz, zlo, zhi) : -1;
         if (ZP && pz >= 0) {
-            czH = cpml_at(P.prof[2], nz, 3, k);
-            czE = cpml_at(P.prof[2], nz, 0, k);
+            czH = cpml_at(P.prof[2], 1, k);
+            czE = cpml_at(P.prof[2], 0, k);
         }
         const bool do_e1 = k >= k0 - 1;
         if (do_e1) {
 #pragma unroll
             for (int r = 1; r < NH; ++r) {
-                const int o = rk(j0 - 2 + r, k);
+                const unsigned o = rk(j0 - 2 + r, k);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) Kc[c][r] = bload(K, xo, c * rowb + o);
+                for (int c = 0; c < 3; ++c) Kc[c][r] = bload(K, at(L.xk, k) + 256 * c, o);
             }
         }
         // ---- step n+1's Ht at plane k, rows 0..TY+2 ----
@@ -750,9 +711,9 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
             const float dyEx = Ec[0][r + 1] - Ec[0][r];
             float dzEy_ = dzEy, dzEx_ = dzEx;
             if (ZP && pz >= 0) {
-                const int o = zo(6 + 2 * s0, pz, j0 - 2 + r);
-                dzEy_ = pml_diff(dzEy, czH, bload(PS, xo, o), qH1[0][r]);                       // Hx
-                dzEx_ = pml_diff(dzEx, czH, bload(PS, xo, o + P.psi_n[2] * 4), qH1[1][r]);   // Hy
+                const unsigned o = zo(s0, pz, j0 - 2 + r);
+                dzEy_ = pml_diff(dzEy, czH, bload(PS, L.xp + 512, o), qH1[0][r]);                       // Hx
+                dzEx_ = pml_diff(dzEx, czH, bload(PS, L.xp + 768, o), qH1[1][r]);   // Hy
             }
             Hh[0][r] = Ho[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
             Hh[1][r] = Ho[1][r] - fmaf(sz, dzEx_, -(sx * dxEz));
@@ -776,9 +737,9 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                 const float dyHx = Hh[0][r] - Hh[0][r - 1];
                 float dzHy_ = dzHy, dzHx_ = dzHx;
                 if (ZP && pz >= 0) {
-                    const int o = zo(2 * s0, pz, j);
-                    dzHy_ = pml_diff(dzHy, czE, bload(PS, xo, o), qE1[0][r]);                       // Ex
-                    dzHx_ = pml_diff(dzHx, czE, bload(PS, xo, o + P.psi_n[2] * 4), qE1[1][r]);   // Ey
+                    const unsigned o = zo(s0, pz, j);
+                    dzHy_ = pml_diff(dzHy, czE, bload(PS, L.xp, o), qE1[0][r]);                       // Ex
+                    dzHx_ = pml_diff(dzHx, czE, bload(PS, L.xp + 256, o), qE1[1][r]);   // Ey
                 }
                 float ex = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), Ec[0][r]);
                 float ey = fmaf(Kc[1][r], fmaf(sz, dzHx_, -(sx * dxHz)), Ec[1][r]);
@@ -793,16 +754,16 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                 // the step-n+1 state of R2's outermost layer
                 const bool own_r = r >= 2 && r - 2 < jn;
                 if (own_k && own_r && ((st_x && (rim_k || j == rb0 || j == rb1 - 1)) || rim_x)) {
-                    const int o = ro(j, k);
-                    bstore_nt(ex, FB, xs_, eb + o);
-                    bstore_nt(ey, FB, xs_, eb + rowb + o);
-                    bstore_nt(ez, FB, xs_, eb + 2 * rowb + o);
-                    bstore_nt(Hh[0][r], FB, xs_, hb + o);
-                    bstore_nt(Hh[1][r], FB, xs_, hb + rowb + o);
-                    bstore_nt(Hh[2][r], FB, xs_, hb + 2 * rowb + o);
+                    const unsigned o = ro(j, k);
+                    bstore_nt(ex, FB, xs_, o);
+                    bstore_nt(ey, FB, xs_ + 256, o);
+                    bstore_nt(ez, FB, xs_ + 512, o);
+                    bstore_nt(Hh[0][r], FB, xs_ + 768, o);
+                    bstore_nt(Hh[1][r], FB, xs_ + 1024, o);
+                    bstore_nt(Hh[2][r], FB, xs_ + 1280, o);
                     if (ZP && pz >= 0) {
-                        bstore(qH1[0][r], PS, xs_, zo(6 + 2 * s1, pz, j));
-                        bstore(qH1[1][r], PS, xs_, zo(6 + 2 * s1 + 1, pz, j));
+                        bstore(qH1[0][r], PS, L.xps + 512, zo(s1, pz, j));
+                        bstore(qH1[1][r], PS, L.xps + 768, zo(s1, pz, j));
                     }
                 }
             }
@@ -827,8 +788,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     dzEx_ = pml_diff(dzEx, czHp, qH1p[1][r], n1);   // Hy
                     if (st_x && r >= 2 && r - 2 < jn && km >= k0 && km < k1) {
                         const int j = j0 - 2 + r;
-                        bstore(n0, PS, xs_, zo(6 + 2 * s2, pzp, j));
-                        bstore(n1, PS, xs_, zo(6 + 2 * s2 + 1, pzp, j));
+                        bstore(n0, PS, L.xps + 512, zo(s2, pzp, j));
+                        bstore(n1, PS, L.xps + 768, zo(s2, pzp, j));
                     }
                 }
                 H2[0][r] = Hhp[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
@@ -855,8 +816,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                         dzHy_ = pml_diff(dzHy, czEp, qE1p[0][r], n0);   // Ex
                         dzHx_ = pml_diff(dzHx, czEp, qE1p[1][r], n1);   // Ey
                         if (st_x) {
-                            bstore(n0, PS, xs_, zo(2 * s2, pzp, j));
-                            bstore(n1, PS, xs_, zo(2 * s2 + 1, pzp, j));
+                            bstore(n0, PS, L.xps, zo(s2, pzp, j));
+                            bstore(n1, PS, L.xps + 256, zo(s2, pzp, j));
                         }
                     }
                     float ex = fmaf(Kp[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), E1p[0][r]);
@@ -866,13 +827,13 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     ey = (x == 0 || km == 0) ? 0.0f : ey;
                     ez = (x == 0 || j == 0) ? 0.0f : ez;
                     if (st_x) {
-                        const int o = ro(j, km);
-                        bstore_nt(ex, FC, xs_, eb + o);
-                        bstore_nt(ey, FC, xs_, eb + rowb + o);
-                        bstore_nt(ez, FC, xs_, eb + 2 * rowb + o);
-                        bstore_nt(H2[0][r], FC, xs_, hb + o);
-                        bstore_nt(H2[1][r], FC, xs_, hb + rowb + o);
-                        bstore_nt(H2[2][r], FC, xs_, hb + 2 * rowb + o);
+                        const unsigned o = ro(j, km);
+                        bstore_nt(ex, FC, xs_, o);
+                        bstore_nt(ey, FC, xs_ + 256, o);
+                        bstore_nt(ez, FC, xs_ + 512, o);
+                        bstore_nt(H2[0][r], FC, xs_ + 768, o);
+                        bstore_nt(H2[1][r], FC, xs_ + 1024, o);
+                        bstore_nt(H2[2][r], FC, xs_ + 1280, o);
                     }
                 }
             }
@@ -971,10 +932,12 @@ __device__ __forceinline__ void plane_component(int axis, int index, int tt, int
     idx = index + (tt >= 3 ? 1 : 0);
 }
 
-// Running DFT of E^n (called before step n): S += E^n exp(+i w n dt) on the
-// design box (3 components) and the port planes (2 tangential components),
-// for each frequency the right-hand side accumulates; under a pulse with a
-// DFT stride m > 1 only the steps divisible by m add.
+// Running DFT of E^n: S += E^n exp(+i w n dt) on the design box (3 components)
+// and the port planes (2 tangential components), for each frequency the
+// right-hand side accumulates; under a pulse with a DFT stride m > 1 only the
+// steps divisible by m add.  Called before step n, or, with a.pair, after the
+// launch that took steps n and n + 1: E^n is still in its buffer, E^{n+1} in
+// dft_mid, and each sum is read and written once for both.
 __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
 {
     int s, r, q;
@@ -983,12 +946,16 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
     const int step = *P.step_ctr + a.k_offset;
     if (step >= P.n_steps) return;
     const YoRhsD &R = P.rhs[r];
-    const int w = step - R.win_start;
-    if (w < 0 || w >= R.win_len) return;
-    if (P.dft_stride > 1 && step % P.dft_stride) return;
-    const float *F = R.F[step % P.nbuf];
+    auto takes = [&](int n) {
+        const int w = n - R.win_start;
+        return w >= 0 && w < R.win_len && !(P.dft_stride > 1 && n % P.dft_stride);
+    };
+    const bool d0 = takes(step), d1 = a.pair && takes(step + 1);
+    if (!d0 && !d1) return;
+    const float *F = R.F[buf_now(P, step, a.b_offset)];
     const int bx = P.box[3], by = P.box[4], bz = P.box[5];
     const int bsz = bx * by * bz;
+    const float e1 = d1 ? R.dft_mid[q] : 0.0f;
     float e;
     float2 *acc;
     int fstride;
@@ -996,7 +963,7 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
         const int c = q / bsz, rem = q - c * bsz;
         const int bk = rem / (bx * by), rem2 = rem - bk * bx * by;
         const int bj = rem2 / bx, bi = rem2 - bj * bx;
-        e = F[yo_off(c, yo_col(P.box[0] + bi, P.sw, P.slead), P.box[1] + bj, P.box[2] + bk, P.ny, P.nxp, 6)];
+        e = F[yo_off(c, P.box[0] + bi, P.box[1] + bj, P.box[2] + bk, P.ny, P.ns, 6)];
         acc = R.dft_box + q;
         fstride = R.box_fstride;
     } else {
@@ -1013,15 +980,21 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
         const int cx = sel3(pl.axis, idx, pl.lo0 + ai, pl.lo0 + ai);
         const int cy = sel3(pl.axis, pl.lo0 + ai, idx, pl.lo1 + b);
         const int cz = sel3(pl.axis, pl.lo1 + b, pl.lo1 + b, idx);
-        e = F[yo_off(c, yo_col(cx, P.sw, P.slead), cy, cz, P.ny, P.nxp, 6)];
+        e = F[yo_off(c, cx, cy, cz, P.ny, P.ns, 6)];
         acc = R.dft_mon + qm;
         fstride = R.mon_fstride;
     }
     for (int f = 0; f < R.n_dft; ++f) {
-        const float4 st = R.dfttab[(size_t)f * P.n_steps + step];
+        const float4 *st = R.dfttab + (size_t)f * P.n_steps + step;
         float2 v = acc[(size_t)f * fstride];
-        v.x = fmaf(e, st.z, v.x);
-        v.y = fmaf(e, st.w, v.y);
+        if (d0) {
+            v.x = fmaf(e, st[0].z, v.x);
+            v.y = fmaf(e, st[0].w, v.y);
+        }
+        if (d1) {
+            v.x = fmaf(e1, st[1].z, v.x);
+            v.y = fmaf(e1, st[1].w, v.y);
+        }
         acc[(size_t)f * fstride] = v;
     }
 }
@@ -1048,22 +1021,24 @@ __global__ __launch_bounds__(256) void k_source(const YoAuxArgs a)
     const int cx = sel3(pl.axis, idx, pl.lo0 + ai, pl.lo0 + ai);
     const int cy = sel3(pl.axis, pl.lo0 + ai, idx, pl.lo1 + b);
     const int cz = sel3(pl.axis, pl.lo1 + b, pl.lo1 + b, idx);
-    const int col = yo_col(cx, P.sw, P.slead);
-    const size_t o = yo_off(c, col, cy, cz, P.ny, P.nxp, 6);
+    const size_t o = yo_off(c, cx, cy, cz, P.ny, P.ns, 6);
     const float2 jv = R.src_j[q];
     const float j = fmaf(jv.x, st.x, jv.y * st.y);
-    float *F = R.F[(step + 1) % P.nbuf];
-    F[o] = fmaf(-P.kappa[yo_off(c, col, cy, cz, P.ny, P.nxp, 3)], j, F[o]);
+    float *F = R.F[buf_next(&P, buf_now(P, step, a.b_offset), 1)];
+    F[o] = fmaf(-P.kappa[yo_off(c, cx, cy, cz, P.ny, P.ns, 3)], j, F[o]);
 }
 
 __global__ void k_ctr(const YoCtrArgs a, int set_value)
 {
     const int i = threadIdx.x;
     if (i < a.n) {
-        if (set_value)
-            *a.ctr[i] = a.add;
-        else
-            *a.ctr[i] += a.add;
+        if (set_value) {
+            a.ctr[i][0] = a.add;
+            a.ctr[i][1] = a.add_b;
+        } else {
+            a.ctr[i][0] += a.add;
+            a.ctr[i][1] += a.add_b;
+        }
     }
 }
 

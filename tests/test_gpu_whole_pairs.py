@@ -21,7 +21,7 @@ def _plan(nx, ny, nz, npml, tb, device, src_x, port_x, two_term=False, steps=23,
     y0, z0, n0, n1 = npml[2], npml[4], ny - npml[2] - npml[3], nz - npml[4] - npml[5]
     src, port = Plane(0, src_x, y0, z0, n0, n1), Plane(0, port_x, y0 + 1, z0, n0 - 1, n1)
     dt = 0.4 * 36e-9 / 299792458.0
-    f = [FreqSpec(2 * np.pi / (19.0 + q) / dt, 5.0, steps - 2, 2) for q in range(nf)]
+    f = [FreqSpec(2 * np.pi / (19.0 + q) / dt, 5.0, steps - 5, 5 - q % 2) for q in range(nf)]
     return Plan(grid, design, steps, f, [src], [port], device=device, two_term=two_term, time_blocking=tb)
 
 
@@ -73,8 +73,8 @@ def test_whole_grid_pairs_bitwise_equal_single_steps(nx, ny, nz, npml, sx, px, t
     rng = np.random.default_rng(nx)
     kap = torch.as_tensor(1.0 / rng.uniform(2.0, 12.0, (3, nz, ny, nx)), dtype=torch.float32)
     out = {}
-    for tb, fl in ((1, 0), (2, 512)):
-        print(f"[gpu] whole pairs {nx}x{ny}x{nz} tb={tb}", flush=True)
+    for tb, fl in ((2, 0), (1, 0), (2, 512)):    # (2, 0): single steps
+        print(f"[gpu] whole pairs {nx}x{ny}x{nz} tb={tb} flags={fl}", flush=True)
         p = _plan(nx, ny, nz, npml, tb, "cuda", sx, px, two, nf=nf)
         p.bind()
         p.set_background(kap, torch.zeros(p.canvas_shape))
@@ -89,13 +89,21 @@ def test_whole_grid_pairs_bitwise_equal_single_steps(nx, ny, nz, npml, sx, px, t
         gen = torch.Generator(device="cuda").manual_seed(5)
         for q in range(p.n_rhs):
             p.set_fields(q, *(torch.randn(p.shape, generator=gen, device="cuda") for _ in range(2)))
-        assert (len(p.tile_table(7)) > 0) == (tb == 2)
-        assert (len(p.tile_table(6)) > 0) == (tb == 2 and nf == 16)
-        # graph of pairs, then pairs and a last odd step with plain launches
-        advance_many([p], [3], 12, chunk=6, use_graph=True)
+        pairs = tb == 1 or fl == 512
+        assert (len(p.tile_table(7)) > 0) == pairs
+        assert (len(p.tile_table(6)) > 0) == (pairs and nf == 16)
+        # graphs of pairs, plain pairs, and odd counts whose last step goes alone;
+        # the run's last steps are in the DFT window
+        advance_many([p], [3], 10, chunk=5, use_graph=True)
         advance_many([p], [3], 7, chunk=7, use_graph=False)
-        out[tb] = [x.cpu().numpy() for q in range(0, p.n_rhs, max(1, p.n_rhs // 4)) for x in p.get_fields(q)]
+        some = range(0, p.n_rhs, max(1, p.n_rhs // 4))
+        got = [x for q in some for x in p.get_fields(q)]
+        advance_many([p], [3], 6, chunk=6, use_graph=True)
+        p.finalize(3)
+        got += [p.get_dft(q, region) for q in some for region in (0, 1)]
+        out[tb, fl] = [x.cpu().numpy() for x in got]
         p.close()
-    assert np.abs(out[1][0]).max() > 0
-    for a, b in zip(out[1], out[2]):
-        assert np.array_equal(a, b)
+    assert all(np.abs(a).max() > 0 for a in out[2, 0])
+    for k in ((1, 0), (2, 512)):
+        for a, b in zip(out[2, 0], out[k]):
+            assert np.array_equal(a, b), k
