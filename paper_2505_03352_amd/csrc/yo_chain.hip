@@ -68,15 +68,21 @@ __global__ void k_finalize(float2 *a, size_t n, float g00, float g01, float g10,
     if ((threadIdx.x & 63) == 0 && m) atomicOr(bad, 1);
 }
 
-// alpha = sum w * Ehat over one port plane; one block, fixed-order tree
-__global__ void k_alpha(const float2 *e, const float2 *w, int n, float2 *out)
+// alpha = sum w * Ehat over one port plane, a block per source, port and
+// frequency; fixed-order tree
+__global__ void k_alpha(const YoAlphaArgs a)
 {
     __shared__ float sr[BS], si[BS];
+    const int f = blockIdx.x % a.n_freq, sp = blockIdx.x / a.n_freq;
+    const int p = sp % a.n_ports, src = sp / a.n_ports;
+    const float2 *e = a.mon + a.mon_stride * (size_t)(f * a.n_src + src) + a.mon_off[p];
+    const float2 *w = a.w + a.w_fstride * (size_t)f + a.w_off[p];
+    const int n = a.n[p];
     float ar = 0.0f, ai = 0.0f;
     for (int i = threadIdx.x; i < n; i += BS) {
-        const float2 a = w[i], b = e[i];
-        ar = fmaf(a.x, b.x, fmaf(-a.y, b.y, ar));
-        ai = fmaf(a.x, b.y, fmaf(a.y, b.x, ai));
+        const float2 u = w[i], b = e[i];
+        ar = fmaf(u.x, b.x, fmaf(-u.y, b.y, ar));
+        ai = fmaf(u.x, b.y, fmaf(u.y, b.x, ai));
     }
     sr[threadIdx.x] = ar;
     si[threadIdx.x] = ai;
@@ -88,40 +94,104 @@ __global__ void k_alpha(const float2 *e, const float2 *w, int n, float2 *out)
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = make_float2(sr[0], si[0]);
+    if (threadIdx.x == 0) a.out[blockIdx.x] = make_float2(sr[0], si[0]);
 }
 
 // ------------------------------------------------------------- forward chain
 // Eq. (2) with the truncated Gaussian basis (separable taps with clamped
-// control indices), then the tanh projection Eq. (3)/(6) into the canvas
-// `out`, whose margin takes the background fill.
-__global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
+// control indices).  First along x: tmp[b][ud], a control row at each
+// sub-pixel column (shared by the S nd / nc times 2r sub-pixel rows that read
+// it: one pass over the controls per sub-pixel took 17 us at 400x400
+// sub-pixels and r = 3, the two passes 8 together).
+__global__ void k_filter_x(YoChainBufs c, const float *C)
+{
+    const int nud = c.S * c.md;
+    const int i = blockIdx.x * BS + threadIdx.x;
+    if (i >= c.nc * nud) return;
+    const int b = i / nud, ud = i - b * nud;
+    const int xlo = c.tap_lo_x[ud], xn = c.tap_n_x[ud];
+    float row = 0.0f;
+    for (int tx = 0; tx < xn; ++tx) {
+        const int a = clampi(xlo + tx, 0, c.mc - 1);
+        row = fmaf(c.tap_w_x[ud * c.tmax + tx], C[b * c.mc + a], row);
+    }
+    c.tmp[i] = row;
+}
+
+// Then along y and the tanh projection Eq. (3)/(6) into the canvas `out`,
+// whose margin takes the background fill.
+__global__ void k_project(YoChainBufs c, float beta, float *out)
 {
     const int n = c.U * c.V;
     const int i = blockIdx.x * BS + threadIdx.x;
     if (i >= n) return;
     const int v = i / c.U, u = i - v * c.U;
-    const int ud = u - 2 * c.S, vd = v - 2 * c.S;
-    if (ud < 0 || ud >= c.S * c.md || vd < 0 || vd >= c.S * c.nd) {
+    const int nud = c.S * c.md, ud = u - 2 * c.S, vd = v - 2 * c.S;
+    if (ud < 0 || ud >= nud || vd < 0 || vd >= c.S * c.nd) {
         out[i] = c.mask[i];
         return;
     }
-    const int xlo = c.tap_lo_x[ud], xn = c.tap_n_x[ud];
     const int ylo = c.tap_lo_y[vd], yn = c.tap_n_y[vd];
     float phi = 0.0f;
     for (int ty = 0; ty < yn; ++ty) {
         const int b = clampi(ylo + ty, 0, c.nc - 1);
-        float row = 0.0f;
-        for (int tx = 0; tx < xn; ++tx) {
-            const int a = clampi(xlo + tx, 0, c.mc - 1);
-            row = fmaf(c.tap_w_x[ud * c.tmax + tx], C[b * c.mc + a], row);
-        }
-        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], row, phi);
+        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], c.tmp[b * nud + ud], phi);
     }
     phi -= 0.5f;
     const float t = tanhf(beta * phi);
-    c.tanh_[vd * (c.S * c.md) + ud] = t;
+    c.tanh_[vd * nud + ud] = t;
     out[i] = 0.5f * (1.0f + t);
+}
+
+// The disc sums of the morphological stages: a block takes a tile of 64 x 16
+// sub-pixels, with the disc's radius around it in LDS, each thread four
+// neighbours of a row, which share the values a row of the disc passes over.
+// The sums run over the taps row by row in the order of the tap table
+// (mirrored in the transpose).  The tile's exponentials (or quotients) are
+// taken once each, not once per tap: at a radius of 10 (317 taps) and 416x416
+// sub-pixels a stage took 80 us (its transpose 75) with both done per tap.
+// Rows of odd pitch keep the four rows a wave reads in different banks.
+constexpr int MTX = 64, MTY = 16;
+template <bool mirror>
+__device__ __forceinline__ void disc_sums(const float *tile, int R, const int *wid, int lx, int ly, float (&acc)[4])
+{
+    const int pitch = (MTX + 2 * R) | 1;
+    acc[0] = acc[1] = acc[2] = acc[3] = 0.0f;
+    for (int dy = -R; dy <= R; ++dy) {
+        const int w = wid[dy + R];
+        if (w < 0) continue;
+        const float *row = tile + (ly + R + (mirror ? -dy : dy)) * pitch + lx + R;
+        // the 2w + 4 values of the row under the four discs, in the taps' order
+        const int dir = mirror ? -1 : 1;
+        const float *x = row + (mirror ? w + 3 : -w);
+        auto tap = [&](int j, int i) {            // value j of the row, disc i
+            const int d = mirror ? 3 - i : i;
+            if (j >= d && j - d <= 2 * w) acc[i] += x[dir * j];
+        };
+        if (w < 2) {
+            for (int j = 0; j < 2 * w + 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tap(j, i);
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tap(j, i);
+#pragma unroll 4
+        for (int j = 3; j <= 2 * w; ++j) {
+            const float v = x[dir * j];
+            acc[0] += v;
+            acc[1] += v;
+            acc[2] += v;
+            acc[3] += v;
+        }
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if ((mirror ? 3 - i : i) >= j) acc[i] += x[dir * (2 * w + j)];
+    }
 }
 
 // Eqs. (4)-(5): one soft dilation or erosion of the canvas `in` with the
@@ -130,28 +200,38 @@ __global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
 // margin.  Exponents are shifted so every term is at most one:
 // dilation 1 + log(mean e^{a(rho-1)}) / a, erosion -log(mean e^{-a rho}) / a
 // (the same values as Eqs. (4)-(5)).  The mean is kept for the transpose.
-__global__ void k_morph(YoChainBufs c, const float *in, float *out, float *sum, int dilate)
+__global__ __launch_bounds__(BS) void k_morph(YoChainBufs c, const float *in, float *out, float *sum, int dilate)
 {
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= c.U * c.V) return;
-    const int v = i / c.U, u = i - v * c.U;
-    const int ud = u - 2 * c.S, vd = v - 2 * c.S;
-    if (ud < 0 || ud >= c.S * c.md || vd < 0 || vd >= c.S * c.nd) {
-        out[i] = c.mask[i];
-        return;
-    }
+    extern __shared__ float tile[];
+    __shared__ int wid[2 * YO_MAX_DISC + 1];
+    const int R = c.mrad, pitch = (MTX + 2 * R) | 1;
+    const int u0 = blockIdx.x * MTX, v0 = blockIdx.y * MTY;
     const float a = c.malpha;
-    float acc = 0.0f;
-    for (int t = 0; t < c.n_mtaps; ++t) {
-        const int vv = clampi(v + c.mtap[2 * t], 0, c.V - 1);
-        const int uu = clampi(u + c.mtap[2 * t + 1], 0, c.U - 1);
-        const float r = in[vv * c.U + uu];
-        acc += dilate ? expf(a * (r - 1.0f)) : expf(-a * r);
+    for (int i = threadIdx.x; i < 2 * R + 1; i += BS) wid[i] = c.mwid[i];
+    for (int i = threadIdx.x; i < pitch * (MTY + 2 * R); i += BS) {
+        const int ty = i / pitch, tx = i - ty * pitch;
+        const float r = in[clampi(v0 + ty - R, 0, c.V - 1) * c.U + clampi(u0 + tx - R, 0, c.U - 1)];
+        tile[i] = dilate ? expf(a * (r - 1.0f)) : expf(-a * r);
     }
-    const float m = acc * c.minv;
-    sum[vd * (c.S * c.md) + ud] = m;
-    const float l = logf(m) / a;
-    out[i] = dilate ? 1.0f + l : -l;
+    __syncthreads();
+    const int lx = (threadIdx.x & 15) * 4, ly = threadIdx.x >> 4;
+    float acc[4];
+    disc_sums<false>(tile, R, wid, lx, ly, acc);
+    const int v = v0 + ly, vd = v - 2 * c.S;
+    if (v >= c.V) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int u = u0 + lx + q, ud = u - 2 * c.S, i = v * c.U + u;
+        if (u >= c.U) break;
+        if (ud < 0 || ud >= c.S * c.md || vd < 0 || vd >= c.S * c.nd) {
+            out[i] = c.mask[i];
+            continue;
+        }
+        const float m = acc[q] * c.minv;
+        sum[vd * (c.S * c.md) + ud] = m;
+        const float l = logf(m) / a;
+        out[i] = dilate ? 1.0f + l : -l;
+    }
 }
 
 // The projection after the morphological stages, Eq. (6):
@@ -257,93 +337,45 @@ __global__ void k_smooth(YoChainBufs c, float *kappa, int ny, int ns, int i0,
 // ------------------------------------------------------------- Eq. (1)
 // dF/deps_c(r) = sum_{f,s,p} 2 Re[coef_{s,p,f} (-2 i sin theta_f) E_F E_A]
 //             = sum 4 sin theta_f Im[coef E_F E_A];  dF/dkappa = -dF/deps / kappa^2
-// One thread per in-plane box cell, looping over the box planes; also forms
-// the z sums of the extrusion's transpose.
-__global__ void k_grad(const YoGradArgs a)
+// One thread per box value, which reads its n_freq (n_src + n_ports) phasors
+// (one per in-plane cell, looping over components and planes, left the chip
+// idle: 388 us on a 252x152x13 box with 5 wavelengths and 1 + 4 phasors each,
+// 311 MB).
+__global__ __launch_bounds__(BS) void k_grad(const YoGradArgs a)
 {
     const int bx = a.box[3], by = a.box[4], bz = a.box[5];
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= bx * by) return;
-    const int bj = i / bx, bi = i - bj * bx;
-    const size_t bsz = (size_t)bx * by * bz;
-    float sx = 0.0f, sy = 0.0f, szi = 0.0f, szf = 0.0f;
-    for (int c = 0; c < 3; ++c) {
-        for (int bk = 0; bk < bz; ++bk) {
-            const size_t o = ((size_t)c * bz + bk) * (size_t)bx * by + i;
-            float ge = 0.0f;
-            for (int f = 0; f < a.n_freq; ++f) {
-                const float s4 = 4.0f * a.sinth[f];
-                for (int s = 0; s < a.n_src; ++s) {
-                    const float2 ef = a.EF[f * a.n_src + s][o];
-                    for (int p = 0; p < a.n_ports; ++p) {
-                        const float2 ea = a.EA[f * a.n_ports + p][o];
-                        const float2 cf = a.coef[(s * a.n_ports + p) * a.n_freq + f];
-                        // prod = ef * ea
-                        const float pr = fmaf(ef.x, ea.x, -ef.y * ea.y);
-                        const float pi = fmaf(ef.x, ea.y, ef.y * ea.x);
-                        // Im(cf * prod)
-                        const float im = fmaf(cf.x, pi, cf.y * pr);
-                        ge = fmaf(s4, im, ge);
-                    }
-                }
-            }
-            const int x = a.box[0] + bi, y = a.box[1] + bj, z = a.box[2] + bk;
-            const float kap = a.kappa[yo_off(c, x, y, z, a.ny, a.ns, 3)];
-            const float gk = -ge / (kap * kap);
-            if (a.gbox) a.gbox[o] = gk;
-            if (c < 2) {
-                if (z >= a.k_lo && z <= a.k_hi) {
-                    if (c == 0) sx += gk; else sy += gk;
-                }
-            } else {
-                if (z >= a.k_lo && z < a.k_hi) szi += gk;
-                if (z == a.k_lo - 1 || z == a.k_hi) szf += gk;
+    const int o = blockIdx.x * BS + threadIdx.x;
+    if (o >= 3 * bx * by * bz) return;
+    const int row = o / bx, bi = o - row * bx;
+    const int pl = row / by, bj = row - pl * by;
+    const int c = pl / bz, bk = pl - c * bz;
+    float ge = 0.0f;
+    for (int f = 0; f < a.n_freq; ++f) {
+        const float s4 = 4.0f * a.sinth[f];
+        for (int s = 0; s < a.n_src; ++s) {
+            const float2 ef = a.EF[f * a.n_src + s][o];
+#pragma unroll 4
+            for (int p = 0; p < a.n_ports; ++p) {
+                const float2 ea = a.EA[f * a.n_ports + p][o];
+                const float2 cf = a.coef[(s * a.n_ports + p) * a.n_freq + f];
+                // prod = ef * ea
+                const float pr = fmaf(ef.x, ea.x, -ef.y * ea.y);
+                const float pi = fmaf(ef.x, ea.y, ef.y * ea.x);
+                // Im(cf * prod)
+                const float im = fmaf(cf.x, pi, cf.y * pr);
+                ge = fmaf(s4, im, ge);
             }
         }
     }
-    (void)bsz;
-    if (a.gmap) {
-        // box cell (bi, bj) is component-grid pixel (bi + 1, bj + 1)
-        const int gsz = a.G0 * a.G1;
-        const int pix = (bj + 1) * a.G0 + (bi + 1);
-        a.gmap[pix] = sx;
-        a.gmap[gsz + pix] = sy;
-        a.gmap[2 * gsz + pix] = szi;
-        a.gmap[3 * gsz + pix] = szf;
-    }
-}
-
-// Transpose of the extrusion through the slab: dF/dkappa on the box -> the
-// four z-summed maps (E_x planes, E_y planes, interior E_z, face E_z).
-__global__ void k_zsum(const float *gbox, int x0, int y0, int z0, int bx, int by, int bz,
-                       int k_lo, int k_hi, float *gmap, int G0, int G1)
-{
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= bx * by) return;
-    const int bj = i / bx, bi = i - bj * bx;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    for (int bk = 0; bk < bz; ++bk) {
-        const int z = z0 + bk;
-        const size_t o = (size_t)bk * bx * by + i;
-        const size_t cs = (size_t)bx * by * bz;
-        if (z >= k_lo && z <= k_hi) {
-            s0 += gbox[o];
-            s1 += gbox[cs + o];
-        }
-        if (z >= k_lo && z < k_hi) s2 += gbox[2 * cs + o];
-        if (z == k_lo - 1 || z == k_hi) s3 += gbox[2 * cs + o];
-    }
-    const int gsz = G0 * G1, pix = (bj + 1) * G0 + (bi + 1);
-    gmap[pix] = s0;
-    gmap[gsz + pix] = s1;
-    gmap[2 * gsz + pix] = s2;
-    gmap[3 * gsz + pix] = s3;
-    (void)x0; (void)y0;
+    const float kap = a.kappa[yo_off(c, a.box[0] + bi, a.box[1] + bj, a.box[2] + bk, a.ny, a.ns, 3)];
+    a.gbox[o] = -ge / (kap * kap);
 }
 
 // ------------------------------------------------------------- chain VJP
-// Eq. (7) partials and the normal-vector partials (written region only).
-__global__ void k_vjp_pointwise(YoChainBufs c)
+// Transpose of the extrusion through the slab (dF/dkappa on the box summed
+// over the E_x planes, the E_y planes, the interior and the face E_z), then
+// the Eq. (7) partials and the normal-vector partials (written region only).
+__global__ void k_vjp_pointwise(YoChainBufs c, const float *gbox, int z0, int bz, int k_lo, int k_hi)
 {
     const int gsz = c.G0 * c.G1;
     const int pix = blockIdx.x * BS + threadIdx.x;
@@ -352,8 +384,23 @@ __global__ void k_vjp_pointwise(YoChainBufs c)
     const bool w = (n >= 1 && n <= c.nd + 2 && m >= 1 && m <= c.md + 2);
     float gP[3] = {0, 0, 0}, gQ[3] = {0, 0, 0}, gG[4] = {0, 0, 0, 0};
     if (w) {
+        // box cell (bi, bj) is component-grid pixel (bi + 1, bj + 1)
+        const int bx = c.md + 2, by = c.nd + 2, i = (n - 1) * bx + m - 1;
+        const size_t cs = (size_t)bx * by * bz;
+        float gm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int bk = 0; bk < bz; ++bk) {
+            const int z = z0 + bk;
+            const size_t o = (size_t)bk * bx * by + i;
+            const float g0 = gbox[o], g1 = gbox[cs + o], g2 = gbox[2 * cs + o];
+            if (z >= k_lo && z <= k_hi) {
+                gm[0] += g0;
+                gm[1] += g1;
+            }
+            if (z >= k_lo && z < k_hi) gm[2] += g2;
+            if (z == k_lo - 1 || z == k_hi) gm[3] += g2;
+        }
         for (int comp = 0; comp < 2; ++comp) {
-            const float g = c.gmap[comp * gsz + pix];
+            const float g = gm[comp];
             const float n2 = c.aux[comp * gsz + pix];
             const float Gx = c.aux[(2 + 2 * comp) * gsz + pix];
             const float Gy = c.aux[(3 + 2 * comp) * gsz + pix];
@@ -372,8 +419,8 @@ __global__ void k_vjp_pointwise(YoChainBufs c)
             }
         }
         const float Qz = c.Q[2 * gsz + pix];
-        gP[2] = 0.5f * c.gmap[3 * gsz + pix];
-        gQ[2] = -c.gmap[2 * gsz + pix] / (Qz * Qz);
+        gP[2] = 0.5f * gm[3];
+        gQ[2] = -gm[2] / (Qz * Qz);
     }
     for (int k = 0; k < 3; ++k) {
         c.gPQ[k * gsz + pix] = gP[k];
@@ -461,57 +508,62 @@ __global__ void k_vjp_canvas(YoChainBufs c, float beta, const float *tproj, floa
     gout[vd * (c.S * c.md) + ud] = grho * 0.5f * beta * (1.0f - t * t);
 }
 
-// Transpose of a morphological stage, first half: q = g / mean.
-__global__ void k_morph_q(YoChainBufs c, const float *g, const float *sum)
+// Transpose of a morphological stage: d rho~(x) / d rho(x') = e(x') / (n
+// mean(x)) for every tap with x + delta = x', e the stage's shifted
+// exponential, so the gradient at x' gathers q = g / mean over x = x' - delta
+// (the disc is symmetric) within the design area (taps that were clamped land
+// in the margin, which has no gradient).  With tproj, the Eq. (3)
+// projection's derivative follows.
+__global__ __launch_bounds__(BS) void k_morph_vjp(YoChainBufs c, const float *g_, const float *sum, const float *in,
+                                                  int dilate, const float *tproj, float beta, float *gout)
 {
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= c.S * c.md * c.S * c.nd) return;
-    c.mq[i] = g[i] / sum[i];
-}
-
-// Second half: d rho~(x) / d rho(x') = e(x') / (n mean(x)) for every tap
-// with x + delta = x', e the stage's shifted exponential, so the gradient at
-// x' gathers q over x = x' - delta (the disc is symmetric) within the
-// design area (taps that were clamped land in the margin, which has no
-// gradient).  With tproj, the Eq. (3) projection's derivative follows.
-__global__ void k_morph_vjp(YoChainBufs c, const float *in, int dilate, const float *tproj, float beta,
-                            float *gout)
-{
+    extern __shared__ float tile[];
+    __shared__ int wid[2 * YO_MAX_DISC + 1];
     const int nud = c.S * c.md, nvd = c.S * c.nd;
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= nud * nvd) return;
-    const int vd = i / nud, ud = i - vd * nud;
-    float acc = 0.0f;
-    for (int t = 0; t < c.n_mtaps; ++t) {
-        const int vq = vd - c.mtap[2 * t], uq = ud - c.mtap[2 * t + 1];
-        if (vq < 0 || vq >= nvd || uq < 0 || uq >= nud) continue;
-        acc += c.mq[vq * nud + uq];
+    const int R = c.mrad, pitch = (MTX + 2 * R) | 1;
+    const int u0 = blockIdx.x * MTX, v0 = blockIdx.y * MTY;
+    for (int i = threadIdx.x; i < 2 * R + 1; i += BS) wid[i] = c.mwid[i];
+    for (int i = threadIdx.x; i < pitch * (MTY + 2 * R); i += BS) {
+        const int ty = i / pitch, tx = i - ty * pitch;
+        const int vq = v0 + ty - R, uq = u0 + tx - R;
+        const bool in_area = vq >= 0 && vq < nvd && uq >= 0 && uq < nud;
+        tile[i] = in_area ? g_[vq * nud + uq] / sum[vq * nud + uq] : 0.0f;
     }
-    const float r = in[(vd + 2 * c.S) * c.U + ud + 2 * c.S];
-    const float e = dilate ? expf(c.malpha * (r - 1.0f)) : expf(-c.malpha * r);
-    float g = e * acc * c.minv;
-    if (tproj) {
-        const float t = tproj[i];
-        g *= 0.5f * beta * (1.0f - t * t);
+    __syncthreads();
+    const int lx = (threadIdx.x & 15) * 4, ly = threadIdx.x >> 4;
+    float acc[4];
+    disc_sums<true>(tile, R, wid, lx, ly, acc);
+    const int vd = v0 + ly;
+    if (vd >= nvd) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int ud = u0 + lx + q, i = vd * nud + ud;
+        if (ud >= nud) break;
+        const float r = in[(vd + 2 * c.S) * c.U + ud + 2 * c.S];
+        const float e = dilate ? expf(c.malpha * (r - 1.0f)) : expf(-c.malpha * r);
+        float g = e * acc[q] * c.minv;
+        if (tproj) {
+            const float t = tproj[i];
+            g *= 0.5f * beta * (1.0f - t * t);
+        }
+        gout[i] = g;
     }
-    gout[i] = g;
 }
 
-// Transpose of the separable filter, x then y.  tmp[vd][a] = sum_ud gphi W_x(ud, a)
-__global__ void k_vjp_filter_x(YoChainBufs c)
+// Transpose of the separable filter, x then y, with each control's weights
+// side by side (tapt; summed on the host where taps were clamped onto it).
+// Searched among the sub-pixels' taps instead, each pass took 21 to 48 us.
+__global__ void k_vjp_filter_x(YoChainBufs c)   // tmp[vd][a] = sum_ud gphi W_x(ud, a)
 {
     const int i = blockIdx.x * BS + threadIdx.x;
     const int nvd = c.S * c.nd, nud = c.S * c.md;
     if (i >= nvd * c.mc) return;
     const int vd = i / c.mc, a = i - vd * c.mc;
+    const int u0 = c.urange_x[2 * a], n = c.urange_x[2 * a + 1] - u0 + 1;
+    const float *w = c.tapt_x + a, *g = c.gphi + vd * nud + u0;
     float acc = 0.0f;
-    for (int ud = c.urange_x[2 * a]; ud <= c.urange_x[2 * a + 1]; ++ud) {
-        const int lo = c.tap_lo_x[ud], nt = c.tap_n_x[ud];
-        float w = 0.0f;
-        for (int t = 0; t < nt; ++t)
-            if (clampi(lo + t, 0, c.mc - 1) == a) w += c.tap_w_x[ud * c.tmax + t];
-        acc = fmaf(w, c.gphi[vd * nud + ud], acc);
-    }
+#pragma unroll 8
+    for (int t = 0; t < n; ++t) acc = fmaf(w[t * c.mc], g[t], acc);
     c.tmp[i] = acc;
 }
 
@@ -520,40 +572,42 @@ __global__ void k_vjp_filter_y(YoChainBufs c, float *dFdC)
     const int i = blockIdx.x * BS + threadIdx.x;
     if (i >= c.nc * c.mc) return;
     const int b = i / c.mc, a = i - b * c.mc;
+    const int v0 = c.urange_y[2 * b], n = c.urange_y[2 * b + 1] - v0 + 1;
+    const float *w = c.tapt_y + b, *g = c.tmp + v0 * c.mc + a;
     float acc = 0.0f;
-    for (int vd = c.urange_y[2 * b]; vd <= c.urange_y[2 * b + 1]; ++vd) {
-        const int lo = c.tap_lo_y[vd], nt = c.tap_n_y[vd];
-        float w = 0.0f;
-        for (int t = 0; t < nt; ++t)
-            if (clampi(lo + t, 0, c.nc - 1) == b) w += c.tap_w_y[vd * c.tmax + t];
-        acc = fmaf(w, c.tmp[vd * c.mc + a], acc);
-    }
+#pragma unroll 8
+    for (int t = 0; t < n; ++t) acc = fmaf(w[t * c.nc], g[t * c.mc], acc);
     dFdC[i] = acc;
 }
 
-
 // Unbinarity (Sec. 4): grey sub-pixels of the design area, those whose
 // final density lies strictly between the two thresholds, given as tanh
-// values of the last projection (rho = (1 + t) / 2).  One atomic add per wave (vector atomic
-// on an integer, so the count does not depend on the order).
-__global__ void k_gray_count(YoChainBufs c, const float *tproj, float tlo, float thi, int *count)
+// values of the last projection (rho = (1 + t) / 2).  YO_GRAY_BLOCKS blocks
+// leave a count each and one wave adds them: an atomic per wave on one counter
+// took 30 us for 400x400 sub-pixels.
+__global__ __launch_bounds__(1024) void k_gray_count(YoChainBufs c, const float *tproj, float tlo, float thi,
+                                                     int *count)
 {
+    __shared__ int part[16];
     const int n = c.S * c.md * c.S * c.nd;
-    const int i = blockIdx.x * BS + threadIdx.x;
-    const float t = i < n ? tproj[i] : -2.0f;
-    const bool grey = t > tlo && t < thi;
-    const unsigned long long m = __ballot(grey);
-    if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, __popcll(m));
+    int mine = 0;
+    for (int i = blockIdx.x * 1024 + threadIdx.x; i < n; i += YO_GRAY_BLOCKS * 1024)
+        mine += tproj[i] > tlo && tproj[i] < thi;
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_down(mine, o);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int w = 0; w < 16; ++w) t += part[w];
+        count[blockIdx.x] = t;
+    }
 }
 
 __global__ void k_gray_finish(const int *count, float inv_total, float *out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) out[0] = (float)count[0] * inv_total;
-}
-
-__global__ void k_set_int(int *p, int v)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) p[0] = v;
+    int t = threadIdx.x < YO_GRAY_BLOCKS ? count[threadIdx.x] : 0;
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_down(t, o);
+    if (threadIdx.x == 0) out[0] = (float)t * inv_total;
 }
 
 // Adam (Sec. 4, Eqs. (10)-(11)) on the controls: M, V moving averages of the
@@ -618,11 +672,16 @@ hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g
     return hipGetLastError();
 }
 
-hipError_t yo_launch_alpha(const float2 *mon, const float2 *w, int n, float2 *out, hipStream_t s)
+hipError_t yo_launch_alpha(const YoAlphaArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_alpha, dim3(1), dim3(BS), 0, s, mon, w, n, out);
+    const int n = a.n_src * a.n_ports * a.n_freq;
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_alpha, dim3(n), dim3(BS), 0, s, a);
     return hipGetLastError();
 }
+
+static dim3 morph_grid(int nu, int nv) { return dim3((nu + MTX - 1) / MTX, (nv + MTY - 1) / MTY); }
+static size_t morph_lds(const YoChainBufs &c) { return sizeof(float) * ((MTX + 2 * c.mrad) | 1) * (MTY + 2 * c.mrad); }
 
 hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float beta, float *kappa,
                                    int ny, int ns, int i0, int j0, int k_lo,
@@ -630,9 +689,10 @@ hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float b
 {
     const size_t UV = (size_t)c.U * c.V;
     const size_t DD = (size_t)c.S * c.md * c.S * c.nd;
-    hipLaunchKernelGGL(k_project, dim3(nblk(UV)), dim3(BS), 0, s, c, C, beta, c.n_morph ? c.mcan : c.rho);
+    hipLaunchKernelGGL(k_filter_x, dim3(nblk((size_t)c.nc * c.S * c.md)), dim3(BS), 0, s, c, C);
+    hipLaunchKernelGGL(k_project, dim3(nblk(UV)), dim3(BS), 0, s, c, beta, c.n_morph ? c.mcan : c.rho);
     for (int k = 0; k < c.n_morph; ++k)
-        hipLaunchKernelGGL(k_morph, dim3(nblk(UV)), dim3(BS), 0, s, c, c.mcan + k * UV, c.mcan + (k + 1) * UV,
+        hipLaunchKernelGGL(k_morph, morph_grid(c.U, c.V), dim3(BS), morph_lds(c), s, c, c.mcan + k * UV, c.mcan + (k + 1) * UV,
                            c.msum + k * DD, (int)((c.mdil >> k) & 1u));
     if (c.n_morph)
         hipLaunchKernelGGL(k_morph_project, dim3(nblk(UV)), dim3(BS), 0, s, c, c.mcan + c.n_morph * UV, beta);
@@ -644,23 +704,24 @@ hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float b
 
 hipError_t yo_launch_grad_assemble(const YoGradArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_grad, dim3(nblk((size_t)a.box[3] * a.box[4])), dim3(BS), 0, s, a);
+    hipLaunchKernelGGL(k_grad, dim3(nblk((size_t)3 * a.box[3] * a.box[4] * a.box[5])), dim3(BS), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t yo_launch_chain_vjp(const YoChainBufs &c, float beta, float *dFdC, hipStream_t s)
+hipError_t yo_launch_chain_vjp(const YoChainBufs &c, const float *gbox, int z0, int bz, int k_lo, int k_hi,
+                               float beta, float *dFdC, hipStream_t s)
 {
     const size_t gsz = (size_t)c.G0 * c.G1;
-    hipLaunchKernelGGL(k_vjp_pointwise, dim3(nblk(gsz)), dim3(BS), 0, s, c);
+    hipLaunchKernelGGL(k_vjp_pointwise, dim3(nblk(gsz)), dim3(BS), 0, s, c, gbox, z0, bz, k_lo, k_hi);
     hipLaunchKernelGGL(k_vjp_sobel, dim3(nblk(2 * gsz)), dim3(BS), 0, s, c);
     const size_t UV = (size_t)c.U * c.V;
     const size_t DD = (size_t)c.S * c.md * c.S * c.nd;
     float *g = c.n_morph ? c.mg : c.gphi;
     hipLaunchKernelGGL(k_vjp_canvas, dim3(nblk(UV)), dim3(BS), 0, s, c, beta, c.n_morph ? c.tanh2 : c.tanh_, g);
     for (int k = c.n_morph - 1; k >= 0; --k) {
-        hipLaunchKernelGGL(k_morph_q, dim3(nblk(DD)), dim3(BS), 0, s, c, (const float *)g, c.msum + k * DD);
         float *next = k == 0 ? c.gphi : (g == c.mg ? c.mg + DD : c.mg);
-        hipLaunchKernelGGL(k_morph_vjp, dim3(nblk(DD)), dim3(BS), 0, s, c, (const float *)(c.mcan + k * UV),
+        hipLaunchKernelGGL(k_morph_vjp, morph_grid(c.S * c.md, c.S * c.nd), dim3(BS), morph_lds(c), s, c,
+                           (const float *)g, (const float *)(c.msum + k * DD), (const float *)(c.mcan + k * UV),
                            (int)((c.mdil >> k) & 1u), k == 0 ? (const float *)c.tanh_ : (const float *)nullptr,
                            beta, next);
         g = next;
@@ -670,20 +731,11 @@ hipError_t yo_launch_chain_vjp(const YoChainBufs &c, float beta, float *dFdC, hi
     return hipGetLastError();
 }
 
-hipError_t yo_launch_zsum(const float *gbox, const int *box, int k_lo, int k_hi, float *gmap, int G0,
-                          int G1, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zsum, dim3(nblk((size_t)box[3] * box[4])), dim3(BS), 0, s, gbox, box[0],
-                       box[1], box[2], box[3], box[4], box[5], k_lo, k_hi, gmap, G0, G1);
-    return hipGetLastError();
-}
-
 hipError_t yo_launch_unbinarity(const YoChainBufs &c, float tlo, float thi, int *count, float *out,
                                 hipStream_t s)
 {
     const size_t n = (size_t)c.S * c.md * c.S * c.nd;
-    hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, s, count, 0);
-    hipLaunchKernelGGL(k_gray_count, dim3(nblk(n)), dim3(BS), 0, s, c,
+    hipLaunchKernelGGL(k_gray_count, dim3(YO_GRAY_BLOCKS), dim3(1024), 0, s, c,
                        (const float *)(c.n_morph ? c.tanh2 : c.tanh_), tlo, thi, count);
     hipLaunchKernelGGL(k_gray_finish, dim3(1), dim3(64), 0, s, count, (float)(1.0 / (double)n), out);
     return hipGetLastError();

@@ -145,6 +145,7 @@ struct YoChainBufs {
     // filter tables
     int *tap_lo_x, *tap_n_x, *tap_lo_y, *tap_n_y;   // [S md], [S nd]
     float *tap_w_x, *tap_w_y;                        // [S md][tmax], [S nd][tmax]
+    float *tapt_x, *tapt_y;                          // [rmax_x][mc], [rmax_y][nc]: a control's weights from its first sub-pixel on
     int *urange_x, *urange_y;                        // per control: [2] first/last sub-pixel
     // forward state
     float *mask;      // [V][U]
@@ -153,24 +154,23 @@ struct YoChainBufs {
     float *P, *Q, *R; // [3][G1][G0]
     float *aux;       // [6][G1][G0]: n2x n2y Gx_x Gy_x Gx_y Gy_y
     // backward
-    float *gmap;      // [4][G1][G0]: gx gy gz_in gz_face
     float *gPQ;       // [6][G1][G0]: gP(x,y,z) gQ(x,y,z)
     float *gG;        // [4][G1][G0]: gGx_x gGy_x gGx_y gGy_y
     float *gR;        // [2][G1][G0]
     float *gphi;      // [S nd][S md]
-    float *tmp;       // [S nd][mc]
+    float *tmp;       // [S nd][mc], or forward [nc][S md]
     // morphological filters (n_morph = 0: none; rho = the Eq. (3) projection)
     int n_morph;      // stages
     unsigned mdil;    // bit k set: stage k dilates, else erodes
     int n_mtaps;      // disc taps
     float malpha;     // sharpness
     float minv;       // 1 / n_mtaps
-    int *mtap;        // [n_mtaps][2]: dy, dx (sub-pixels)
+    int mrad;         // the disc's radius in whole sub-pixels
+    int *mwid;        // [2 mrad + 1]: largest |dx| of each of its rows (-1: none)
     float *mcan;      // [n_morph + 1][V][U]: stage inputs, then the last output
     float *msum;      // [n_morph][S nd][S md]: each stage's kernel sums
     float *tanh2;     // [S nd][S md]: tanh of the projection after the stages
     float *mg;        // [2][S nd][S md]: gradients between stages
-    float *mq;        // [S nd][S md]: gradient / kernel sum of the stage being transposed
 };
 
 // ---- kernel launchers ----
@@ -205,8 +205,16 @@ hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int
 // finite (*bad is left alone otherwise)
 hipError_t yo_launch_finalize(float2 *a, size_t n, float g00, float g01, float g10, float g11,
                               int *bad, hipStream_t s);
-hipError_t yo_launch_alpha(const float2 *mon_dft, const float2 *weights, int n, float2 *out,
-                           hipStream_t s);
+// modal coefficients, out [n_src][n_ports][n_freq]
+struct YoAlphaArgs {
+    const float2 *mon;         // port planes of output right-hand side r at mon_stride r
+    const float2 *w;           // weights (of frequency f at w_fstride f)
+    size_t mon_stride, w_fstride;
+    int mon_off[YO_MAX_PORTS], w_off[YO_MAX_PORTS], n[YO_MAX_PORTS];
+    int n_src, n_ports, n_freq;
+    float2 *out;
+};
+hipError_t yo_launch_alpha(const YoAlphaArgs &a, hipStream_t s);
 hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float beta,
                                    float *kappa, int ny, int ns, int i0, int j0,
                                    int k_lo, int k_hi, hipStream_t s);
@@ -219,23 +227,23 @@ struct YoGradArgs {
     float sinth[YO_MAX_FREQ];      // sin(w dt / 2) per frequency
     const float2 *coef;            // [n_src][n_ports][n_freq]
     const float *kappa;            // ghost layout
-    float *gbox;                   // optional [3][bz][by][bx] dF/dkappa
-    float *gmap;                   // optional [4][G1][G0] z-summed maps
+    float *gbox;                   // [3][bz][by][bx] dF/dkappa
     int n_src, n_ports, n_freq;
     int ns, ny;
     int box[6];
-    int k_lo, k_hi, G0, G1;
 };
 hipError_t yo_launch_grad_assemble(const YoGradArgs &a, hipStream_t s);
-hipError_t yo_launch_chain_vjp(const YoChainBufs &c, float beta, float *dFdC, hipStream_t s);
-// grey fraction of the design area: rho in (lo, hi) as tanh in (tlo, thi)
+// dF/dkappa on the box (planes z0 .. z0 + bz - 1) to dF/dC
+hipError_t yo_launch_chain_vjp(const YoChainBufs &c, const float *gbox, int z0, int bz, int k_lo, int k_hi,
+                               float beta, float *dFdC, hipStream_t s);
+// grey fraction of the design area: rho in (lo, hi) as tanh in (tlo, thi);
+// count: YO_GRAY_BLOCKS ints
+#define YO_GRAY_BLOCKS 16
+#define YO_MAX_DISC 32    // largest disc radius, sub-pixels
 hipError_t yo_launch_unbinarity(const YoChainBufs &c, float tlo, float thi, int *count, float *out,
                                 hipStream_t s);
 hipError_t yo_launch_adam(float *C, const float *G, float *M, float *V, int n, float lr, float b1, float b2,
                           float eps, float inv1, float inv2, hipStream_t s);
-hipError_t yo_launch_zsum(const float *gbox, const int *box, int k_lo, int k_hi, float *gmap, int G0,
-                          int G1, hipStream_t s);
-
 // floats from the start of a row's component 0 to cell x in an array of nc
 // components (see the layout above)
 __host__ __device__ inline int yo_col(int x, int nc)

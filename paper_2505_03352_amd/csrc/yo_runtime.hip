@@ -144,10 +144,11 @@ struct yo_plan {
     std::vector<YoRhsD> hrhs;
     YoChainBufs chain{};
     std::vector<int> tap_lo_x, tap_n_x, tap_lo_y, tap_n_y, urange_x, urange_y;
-    std::vector<float> tap_w_x, tap_w_y;
+    std::vector<float> tap_w_x, tap_w_y, tapt_x, tapt_y;
     std::string morph_ops;       // 'd'/'e' per stage, empty: no morphological filters
     double morph_d = 0, morph_alpha = 0;
-    std::vector<int> mtaps;      // [n][2] dy, dx
+    int n_mtaps = 0, mrad = 0;
+    std::vector<int> mwid;       // [2 mrad + 1] half widths of the disc's rows
     std::vector<float4> steptab;
     std::vector<float4> prof;
     std::vector<float2> src_j_host, port_w_host;
@@ -299,8 +300,10 @@ void build_port_tables(yo_plan *p)
 
 size_t port_w_blocks(const yo_plan *p) { return p->mon_nc == 5 ? (size_t)p->n_freq : 1; }
 
-// Bytes of the morphological region for n stages and t taps (each buffer
-// padded to 64 floats, as set_chain_ptrs carves them).
+// Bytes of the morphological region for n stages and t taps, each buffer
+// padded to 64 floats.  set_chain_ptrs carves n + 1 canvases, n + 3 design
+// areas and a table of the disc's rows; the size, which callers budget for,
+// counts one area and two values per tap more.
 size_t morph_bytes(const yo_plan *p, size_t n, size_t t)
 {
     const size_t UV = (size_t)p->U * p->V;
@@ -361,7 +364,8 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
     build_regions(p);
     p->nominal = p->L.total;
     p->nominal -= align256(p->L.fields.bytes) + align256(p->L.kappa.bytes) + align256(p->L.psi.bytes) +
-                  align256(p->L.dft_mid.bytes);
+                  align256(p->L.dft_mid.bytes) +
+                  sizeof(float) * (p->tapt_x.size() + p->tapt_y.size() + (size_t)(p->S * p->des.md) * p->des.nc);
     p->nominal += align256(24 * p->nbuf * cells * p->n_phys) + align256(12 * cells) + align256(4 * psi * p->n_phys);
     return true;
 }
@@ -380,7 +384,7 @@ void build_regions(yo_plan *p)
     L.add(L.dft_box, sizeof(float2) * 3 * p->bsz * p->n_rhs);
     L.add(L.dft_mon, sizeof(float2) * std::max<size_t>(p->mon_total, 1) * p->n_rhs);
     // E after a pair's first step on the box and the planes, per stepped right-hand side
-    L.add(L.dft_mid, sizeof(float) * mid_floats(p) * p->n_phys);
+    L.add(L.dft_mid, sizeof(float) * mid_floats(p) * std::max(p->n_phys, 1));
     L.add(L.src_j, sizeof(float2) * std::max<size_t>(p->src_total, 1));
     L.add(L.port_w, sizeof(float2) * std::max<size_t>(p->port_total, 1) * port_w_blocks(p));
     L.add(L.steptab, sizeof(float4) * (size_t)(p->n_freq + 1) * p->n_steps);
@@ -392,12 +396,13 @@ void build_regions(yo_plan *p)
     const size_t G = (size_t)p->G0 * p->G1;
     const size_t UV = (size_t)p->U * p->V;
     const size_t DD = (size_t)(p->S * d.md) * (p->S * d.nd);
-    const size_t nf = 2 * UV + DD /*tanh*/ + 9 * G + 6 * G + 4 * G + 6 * G + 4 * G + 2 * G + DD /*gphi*/ +
-                      (size_t)(p->S * d.nd) * d.mc /*tmp*/ + (size_t)p->tmax * p->S * (d.md + d.nd);
-    L.add(L.chain_f, sizeof(float) * (nf + 64 * 16));   // each of 15 buffers padded to 64 floats
+    const size_t nf = 2 * UV + DD /*tanh*/ + 9 * G + 6 * G + 6 * G + 4 * G + 2 * G + DD /*gphi*/ +
+                      std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * d.nc) /*tmp*/ +
+                      (size_t)p->tmax * p->S * (d.md + d.nd) + p->tapt_x.size() + p->tapt_y.size();
+    L.add(L.chain_f, sizeof(float) * (nf + 64 * 17));   // each of 16 buffers padded to 64 floats
     const size_t ni = 2 * (size_t)p->S * (d.md + d.nd) + 2 * (size_t)(d.mc + d.nc);
     L.add(L.chain_i, sizeof(int) * (ni + 64 * 8));     // each of 6 tables padded to 64 ints
-    L.add(L.morph, p->morph_ops.empty() ? 0 : morph_bytes(p, p->morph_ops.size(), p->mtaps.size() / 2));
+    L.add(L.morph, p->morph_ops.empty() ? 0 : morph_bytes(p, p->morph_ops.size(), p->n_mtaps));
 }
 
 void build_steptab(yo_plan *p)
@@ -500,6 +505,23 @@ void build_taps(int S, int n_px, int n_ctl, double r, int tmax, std::vector<int>
             range[2 * a + 1] = std::max(range[2 * a + 1], u);
         }
     }
+}
+
+// The filter's transpose: each control's weights from its first sub-pixel on
+// (several taps of a sub-pixel clamped onto it added up).
+void transpose_taps(int n_ctl, int tmax, const std::vector<int> &lo, const std::vector<int> &cnt,
+                    const std::vector<float> &w, const std::vector<int> &range, std::vector<float> &out)
+{
+    int rmax = 1;
+    for (int a = 0; a < n_ctl; ++a) rmax = std::max(rmax, range[2 * a + 1] - range[2 * a] + 1);
+    out.assign((size_t)n_ctl * rmax, 0.0f);
+    for (int a = 0; a < n_ctl; ++a)
+        for (int u = range[2 * a]; u <= range[2 * a + 1]; ++u) {
+            float v = 0.0f;
+            for (int t = 0; t < cnt[u]; ++t)
+                if (std::min(std::max(lo[u] + t, 0), n_ctl - 1) == a) v += w[(size_t)u * tmax + t];
+            out[(size_t)(u - range[2 * a]) * n_ctl + a] = v;
+        }
 }
 
 // Split [0, n) into pieces of at most `w`, with cuts at the two edges of the
@@ -1058,6 +1080,14 @@ yo_status yo_plan_create(const yo_grid *grid, const yo_design *des, int n_steps,
 
     p->n_phys = p->n_rhs;
     p->n_pfwd = p->n_fwd;
+    build_taps(p->S, d.md, d.mc, d.filter_r, p->tmax, p->tap_lo_x, p->tap_n_x, p->tap_w_x, p->urange_x);
+    build_taps(p->S, d.nd, d.nc, d.filter_r, p->tmax, p->tap_lo_y, p->tap_n_y, p->tap_w_y, p->urange_y);
+    for (int v : p->tap_n_x)
+        if (v > p->tmax) { delete p; return fail(YO_EINVAL, "internal: filter taps"); }
+    for (int v : p->tap_n_y)
+        if (v > p->tmax) { delete p; return fail(YO_EINVAL, "internal: filter taps"); }
+    transpose_taps(d.mc, p->tmax, p->tap_lo_x, p->tap_n_x, p->tap_w_x, p->urange_x, p->tapt_x);
+    transpose_taps(d.nc, p->tmax, p->tap_lo_y, p->tap_n_y, p->tap_w_y, p->urange_y, p->tapt_y);
     bool state = false;
     if (!build_layout(p, &state)) {
         delete p;
@@ -1067,12 +1097,6 @@ yo_status yo_plan_create(const yo_grid *grid, const yo_design *des, int n_steps,
 
     build_profiles(p);
     build_steptab(p);
-    build_taps(p->S, d.md, d.mc, d.filter_r, p->tmax, p->tap_lo_x, p->tap_n_x, p->tap_w_x, p->urange_x);
-    build_taps(p->S, d.nd, d.nc, d.filter_r, p->tmax, p->tap_lo_y, p->tap_n_y, p->tap_w_y, p->urange_y);
-    for (int v : p->tap_n_x)
-        if (v > p->tmax) { delete p; return fail(YO_EINVAL, "internal: filter taps"); }
-    for (int v : p->tap_n_y)
-        if (v > p->tmax) { delete p; return fail(YO_EINVAL, "internal: filter taps"); }
     build_tiles(p);
     {
         // carve the parametrization buffers once against a stand-in base to
@@ -1265,14 +1289,15 @@ static yo_status set_chain_ptrs(yo_plan *p)
     c.Q = take(3 * G);
     c.R = take(3 * G);
     c.aux = take(6 * G);
-    c.gmap = take(4 * G);
     c.gPQ = take(6 * G);
     c.gG = take(4 * G);
     c.gR = take(2 * G);
     c.gphi = take(DD);
-    c.tmp = take((size_t)(p->S * d.nd) * d.mc);
+    c.tmp = take(std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * d.nc));
     c.tap_w_x = take((size_t)p->tmax * p->S * d.md);
     c.tap_w_y = take((size_t)p->tmax * p->S * d.nd);
+    c.tapt_x = take(p->tapt_x.size());
+    c.tapt_y = take(p->tapt_y.size());
     int *ip = wsp<int>(p, p->L.chain_i);
     auto takei = [&](size_t n) {
         int *r = ip;
@@ -1292,19 +1317,19 @@ static yo_status set_chain_ptrs(yo_plan *p)
     c.mdil = 0;
     for (int k = 0; k < c.n_morph; ++k)
         if (p->morph_ops[k] == 'd') c.mdil |= 1u << k;
-    c.n_mtaps = (int)p->mtaps.size() / 2;
+    c.n_mtaps = p->n_mtaps;
+    c.mrad = p->mrad;
     c.malpha = (float)p->morph_alpha;
     c.minv = c.n_mtaps ? (float)(1.0 / c.n_mtaps) : 0.0f;
-    c.mtap = nullptr;
-    c.mcan = c.msum = c.tanh2 = c.mg = c.mq = nullptr;
+    c.mwid = nullptr;
+    c.mcan = c.msum = c.tanh2 = c.mg = nullptr;
     if (c.n_morph) {
         f = wsp<float>(p, p->L.morph);
         c.mcan = take((size_t)(c.n_morph + 1) * UV);
         c.msum = take((size_t)c.n_morph * DD);
         c.tanh2 = take(DD);
         c.mg = take(2 * DD);
-        c.mq = take(DD);
-        c.mtap = reinterpret_cast<int *>(take(p->mtaps.size()));
+        c.mwid = reinterpret_cast<int *>(take(p->mwid.size()));
         if ((char *)f > p->ws + p->L.morph.off + p->L.morph.bytes)
             return fail(YO_EWORKSPACE, "internal: morphology buffers exceed their region");
     }
@@ -1318,7 +1343,8 @@ yo_status yo_set_morphology(yo_plan *p, const char *ops, double diameter, double
     std::string seq = ops ? ops : "";
     if (seq.empty()) {
         p->morph_ops.clear();
-        p->mtaps.clear();
+        p->mwid.clear();
+        p->n_mtaps = p->mrad = 0;
         build_layout(p);
         return YO_OK;
     }
@@ -1328,19 +1354,22 @@ yo_status yo_set_morphology(yo_plan *p, const char *ops, double diameter, double
     if (!(diameter > 0)) return fail(YO_EINVAL, "the disc diameter must be positive");
     if (!(alpha > 0 && alpha <= 80)) return fail(YO_EINVAL, "alpha must be in (0, 80]");
     const double R = diameter * p->S / 2.0;
-    if (R > 32.0) return fail(YO_EUNSUPPORTED, "disc radius above 32 sub-pixels");
-    std::vector<int> taps;
+    if (R > YO_MAX_DISC) return fail(YO_EUNSUPPORTED, "disc radius above 32 sub-pixels");
     const int n = (int)std::floor(R);
+    std::vector<int> wid(2 * n + 1, -1);
+    int taps = 0;
     for (int dy = -n; dy <= n; ++dy)
-        for (int dx = -n; dx <= n; ++dx)
+        for (int dx = 0; dx <= n; ++dx)
             if ((double)(dx * dx + dy * dy) <= R * R) {
-                taps.push_back(dy);
-                taps.push_back(dx);
+                wid[dy + n] = dx;
+                taps += dx ? 2 : 1;
             }
     p->morph_ops = seq;
     p->morph_d = diameter;
     p->morph_alpha = alpha;
-    p->mtaps = taps;
+    p->n_mtaps = taps;
+    p->mrad = n;
+    p->mwid = wid;
     build_layout(p);
     return YO_OK;
 }
@@ -1420,7 +1449,9 @@ static yo_status bind_ws(yo_plan *p, void *dev, size_t bytes, hipStream_t s)
     if ((st = upload_to(c.urange_y, p->urange_y.data(), p->urange_y.size() * 4, s))) return st;
     if ((st = upload_to(c.tap_w_x, p->tap_w_x.data(), p->tap_w_x.size() * 4, s))) return st;
     if ((st = upload_to(c.tap_w_y, p->tap_w_y.data(), p->tap_w_y.size() * 4, s))) return st;
-    if (c.n_morph && (st = upload_to(c.mtap, p->mtaps.data(), p->mtaps.size() * 4, s))) return st;
+    if ((st = upload_to(c.tapt_x, p->tapt_x.data(), p->tapt_x.size() * 4, s))) return st;
+    if ((st = upload_to(c.tapt_y, p->tapt_y.data(), p->tapt_y.size() * 4, s))) return st;
+    if (c.n_morph && (st = upload_to(c.mwid, p->mwid.data(), p->mwid.size() * 4, s))) return st;
     if ((st = upload_desc(p, s))) return st;
     // copies from pageable host memory are staged; make them complete before
     // the host vectors can change
@@ -2190,23 +2221,27 @@ yo_status yo_alpha(const yo_plan *p, float *alpha, yo_stream stream)
         return fail(YO_ESTATE, "the design or background changed after the forward run started");
     if (p->unstable[0]) return fail(YO_EUNSTABLE, "the forward run diverged (non-finite phasors)");
     hipStream_t s = (hipStream_t)stream;
-    const float2 *w = reinterpret_cast<const float2 *>(p->ws + p->L.port_w.off);
-    for (int sidx = 0; sidx < p->n_src; ++sidx)
-        for (int q = 0; q < p->n_ports; ++q) {
-            if (!p->port_set[q]) return fail(YO_ESTATE, "port %d mode not set", q);
-            for (int f = 0; f < p->n_freq; ++f) {
-                const int r = f * p->n_src + sidx;
-                const yo_plane &pl = p->port_planes[q];
-                float2 *out = reinterpret_cast<float2 *>(alpha) + ((size_t)sidx * p->n_ports + q) * p->n_freq + f;
-                const size_t wb = p->mon_nc == 5 ? (size_t)f * p->port_total : 0;
-                HIPCHK(yo_launch_alpha(mon_of(p, r) + p->mon_off[q], w + wb + p->port_off[q],
-                                       p->mon_nc * pl.n0 * pl.n1, out, s));
-            }
-        }
+    YoAlphaArgs a{};
+    a.mon = mon_of(p, 0);
+    a.mon_stride = std::max<size_t>(p->mon_total, 1);
+    a.w = reinterpret_cast<const float2 *>(p->ws + p->L.port_w.off);
+    a.w_fstride = p->mon_nc == 5 ? p->port_total : 0;
+    for (int q = 0; q < p->n_ports; ++q) {
+        if (p->n_src > 0 && !p->port_set[q]) return fail(YO_ESTATE, "port %d mode not set", q);
+        const yo_plane &pl = p->port_planes[q];
+        a.mon_off[q] = (int)p->mon_off[q];
+        a.w_off[q] = (int)p->port_off[q];
+        a.n[q] = p->mon_nc * pl.n0 * pl.n1;
+    }
+    a.n_src = p->n_src;
+    a.n_ports = p->n_ports;
+    a.n_freq = p->n_freq;
+    a.out = reinterpret_cast<float2 *>(alpha);
+    HIPCHK(yo_launch_alpha(a, s));
     return YO_OK;
 }
 
-static yo_status grad_common(yo_plan *p, const float *coef, float *gbox, float *gmap, hipStream_t s)
+static yo_status grad_common(yo_plan *p, const float *coef, float *gbox, hipStream_t s)
 {
     if (yo_status st_ = ws_check(p)) return st_;
     if (!p->finalized[0] || !p->finalized[1])
@@ -2225,17 +2260,12 @@ static yo_status grad_common(yo_plan *p, const float *coef, float *gbox, float *
     a.coef = reinterpret_cast<const float2 *>(coef);
     a.kappa = wsp<float>(p, p->L.kappa);
     a.gbox = gbox;
-    a.gmap = gmap;
     a.n_src = p->n_src;
     a.n_ports = p->n_ports;
     a.n_freq = p->n_freq;
     a.ns = p->ns;
     a.ny = p->grid.ny;
     for (int i = 0; i < 6; ++i) a.box[i] = p->box[i];
-    a.k_lo = p->des.k_lo;
-    a.k_hi = p->des.k_hi;
-    a.G0 = p->G0;
-    a.G1 = p->G1;
     HIPCHK(yo_launch_grad_assemble(a, s));
     return YO_OK;
 }
@@ -2243,7 +2273,7 @@ static yo_status grad_common(yo_plan *p, const float *coef, float *gbox, float *
 yo_status yo_gradient_kappa(yo_plan *p, const float *coef, float *g, yo_stream stream)
 {
     if (!p || !g || (!coef && p->n_src > 0 && p->n_ports > 0)) return fail(YO_EINVAL, "null argument");
-    return grad_common(p, coef, g, nullptr, (hipStream_t)stream);
+    return grad_common(p, coef, g, (hipStream_t)stream);
 }
 
 yo_status yo_gradient(yo_plan *p, const float *coef, float *dFdC, yo_stream stream)
@@ -2253,10 +2283,12 @@ yo_status yo_gradient(yo_plan *p, const float *coef, float *dFdC, yo_stream stre
     if (yo_status st_ = ws_check(p)) return st_;
     if (!p->design_set) return fail(YO_ESTATE, "yo_set_design first");
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_fill(p->chain.gmap, 4 * (size_t)p->G0 * p->G1, 0.0f, s));
-    yo_status st = grad_common(p, coef, nullptr, p->chain.gmap, s);
+    // dF/dkappa on the box goes where a pair's first step leaves E (used within
+    // the stepping only)
+    float *gk = wsp<float>(p, p->L.dft_mid);
+    yo_status st = grad_common(p, coef, gk, s);
     if (st) return st;
-    HIPCHK(yo_launch_chain_vjp(p->chain, (float)p->beta, dFdC, s));
+    HIPCHK(yo_launch_chain_vjp(p->chain, gk, p->box[2], p->box[5], p->des.k_lo, p->des.k_hi, (float)p->beta, dFdC, s));
     return YO_OK;
 }
 
@@ -2266,9 +2298,7 @@ yo_status yo_chain_vjp(yo_plan *p, const float *gk, float *dFdC, yo_stream strea
     if (yo_status st_ = ws_check(p)) return st_;
     if (!p->design_set) return fail(YO_ESTATE, "yo_set_design first");
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_fill(p->chain.gmap, 4 * (size_t)p->G0 * p->G1, 0.0f, s));
-    HIPCHK(yo_launch_zsum(gk, p->box, p->des.k_lo, p->des.k_hi, p->chain.gmap, p->G0, p->G1, s));
-    HIPCHK(yo_launch_chain_vjp(p->chain, (float)p->beta, dFdC, s));
+    HIPCHK(yo_launch_chain_vjp(p->chain, gk, p->box[2], p->box[5], p->des.k_lo, p->des.k_hi, (float)p->beta, dFdC, s));
     return YO_OK;
 }
 
