@@ -137,8 +137,9 @@ __device__ __forceinline__ LaneX lane_x(PP P, int x0, int xn, int lane)
     L.xp = in ? yo_col(x, 4) * 4 : kFar;
     const int s = x0 / YO_SW, pos = x0 - s * YO_SW + lane;   // place in the tile's strip
     // (past the grid's last column up to the end of its line)
-    const bool pad = ((pos < YO_LEAD || pos >= YO_LEAD + YO_SW) && pos < 64 && lane < xn + 2 * YO_LEAD) ||
-                     (x >= P->nx && pos < ((YO_LEAD + P->nx - s * YO_SW + 31) & ~31));
+    // (both within the strip: further lanes' places are the next component's)
+    const bool pad = pos < 64 && (((pos < YO_LEAD || pos >= YO_LEAD + YO_SW) && lane < xn + 2 * YO_LEAD) ||
+                                  (x >= P->nx && pos < ((YO_LEAD + P->nx - s * YO_SW + 31) & ~31)));
     L.st = L.own || pad;
     L.xs = pad ? (s * 384 + pos) * 4 : (L.own ? L.xl : kFar);
     L.xps = pad ? (s * 256 + pos) * 4 : (L.own ? L.xp : kFar);
