@@ -11,10 +11,9 @@
 #define YO_TY 4           // rows per wave
 #define YO_TY2 6          // rows per wave of the two-step region's taller tiles
 #define YO_MAX_WPB 8      // waves per block of the step kernel: 4 or 8
-#define YO_PAIR_TY 2      // whole-grid pairs: rows per wave,
+#define YO_PAIR_TY 2      // whole-grid tiles: rows per wave,
 #define YO_PAIR_W 8       // waves per block,
-#define YO_PAIR_GROUP 32  // tiles that consecutive blocks take for one right-hand side,
-#define YO_PAIR_YROWS 12  // and the most y-slab rows a block may hold
+#define YO_PAIR_GROUP 32  // tiles that consecutive blocks take for one right-hand side
 
 // Field arrays carry a ghost row on either side of y.  A row of
 // nx cells is cut into ns strips of 60, each in a segment of nc x 64 floats, the
@@ -190,7 +189,10 @@ hipError_t yo_launch_step2(bool zslab, int rows, bool coop, const YoStepArgs &ar
                            hipStream_t s);
 // two steps over whole-grid tiles (one block each, YO_PAIR_W waves); shell:
 // tiles with x- or y-slabs, source planes or the grid's first column or row
-hipError_t yo_launch_pair(bool shell, bool dft, const YoStepArgs &args, int blocks, hipStream_t s);
+// gen: 1 planes normal to y or z, 2 and more than 32 x-slab columns in a strip
+hipError_t yo_launch_pair(bool shell, bool dft, int gen, const YoStepArgs &args, int blocks, hipStream_t s);
+// one step over the same tiles (all of them)
+hipError_t yo_launch_one(const YoStepArgs &args, int blocks, hipStream_t s);
 hipError_t yo_launch_dft(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_source(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_ctr(const YoCtrArgs &args, int set_value, hipStream_t s);

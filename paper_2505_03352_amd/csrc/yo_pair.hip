@@ -60,15 +60,18 @@ enum { F_OWN = 0, F_YSLAB = 4, F_IN = 8, F_X = 1 << 12, F_SRC = 1 << 13, F_X0 = 
 
 // CP: tiles that meet the x- or y-slabs, a source plane or the grid's first
 // column or row; else only the z-slabs' code is there.  DFT: E^{n+1} of the
-// design box and the port planes is stored for the running DFT.
-template <int TY, int W, bool CP, bool DFT>
+// design box and the port planes is stored for the running DFT.  GEN: 1 planes
+// normal to y or z too, 2 and up to 64 x-slab columns in a strip, else 32
+// (kernels of their own: the code costs the others registers, the columns LDS).  ONE: S1 and S2 only, stored:
+// one step.
+template <int TY, int W, bool CP, bool DFT, int GEN, bool ONE>
 __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<YoRhsD> R, const int step, const int now,
                                           const int4 t, const int w, const int lane, float *lds)
 {
     const int ny = P->ny, nz = P->nz;
     const unsigned gs = 1536u * P->ns, pstr = (unsigned)(ny + 1) * gs;   // state of a row, of a plane, bytes
     const unsigned ps = 1024u * P->ns;                                   // CPML memories of a row
-    const int nxt = buf_next(P, now, 2);
+    const int nxt = buf_next(P, now, ONE ? 1 : 2);
     const Rsrc FA = rsrc_of(R->F[now], array_bytes(P, 6));   // after step n
     const Rsrc FC = rsrc_of(R->F[nxt], array_bytes(P, 6));   // after step n+2
     const Rsrc KR = rsrc_of(P->kappa, array_bytes(P, 3));
@@ -89,11 +92,12 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     int xi = 0;
     if (CP && (t.w & 1)) {
         lane_xslab(P, L, cxE, cxH);
-        xi = L.px >= 0 ? slab_index(L.x, P->nx, P->plo[0], P->phi[0]) : 0;
+        // the lane's place among the strip's slab columns
+        const unsigned long long m = __ballot(L.px >= 0);
+        xi = L.px >= 0 ? __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0)) : 0;
     }
     const bool ylow = jb < ylo;
     const int py0 = ylow ? jb : jb - yh0 + ylo;             // slab row of row 0
-    const int sr0 = ylow ? jb : jb - yh0;                   // and its place in the LDS
     int fl0 = 0;
     unsigned rb[TY];
 #pragma unroll
@@ -109,17 +113,25 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     if (CP && (t.w & 1)) fl0 |= F_X;
     if (CP && x0 == 0) fl0 |= F_X0;
     if (CP) {
-        // the source plane (normal to x) and this wave's rows
+        // the source plane and this wave's rows
         const int sp = R->src.index, lo0 = R->src.lo0, n0 = R->src.n0;
-        if (R->src_j && sp + (R->src_nc == 5 ? 1 : 0) >= x0 - 2 && sp <= x0 + xn + 1 && jb < lo0 + n0 && jb + TY > lo0)
+        if (GEN && R->src.axis) {
+            const bool y = R->src.axis == 1;
+            const int ja = y ? sp : R->src.lo1, jn = y ? 2 : R->src.n1;
+            if (R->src_j && lo0 < x0 + xn + 2 && lo0 + n0 > x0 - 2 && jb < ja + jn && jb + TY > ja) fl0 |= F_SRC;
+        } else if (R->src_j && sp + (R->src_nc == 5 ? 1 : 0) >= x0 - 2 && sp <= x0 + xn + 1 && jb < lo0 + n0 && jb + TY > lo0)
             fl0 |= F_SRC;
     }
-    if (DFT) {
+    if constexpr (DFT) {
         const bool xbox = x0 < P->box[0] + P->box[3] && x0 + xn > P->box[0];
         if (!xbox) fl0 &= ~(0xf << F_BOX);
-        for (int q = 0; q < P->n_ports; ++q) {
+        for (int q = 0; CP && q < P->n_ports; ++q) {
             const int ix = P->ports[q].index, lo0 = P->ports[q].lo0, n0 = P->ports[q].n0;
-            if (ix + (P->mon_nc == 5) >= x0 && ix < x0 + xn && jb < lo0 + n0 && jb + TY > lo0)
+            if (GEN && P->ports[q].axis) {
+                const bool y = P->ports[q].axis == 1;
+                const int ja = y ? ix : P->ports[q].lo1, jn = y ? 2 : P->ports[q].n1;
+                if (lo0 < x0 + xn && lo0 + n0 > x0 && jb < ja + jn && jb + TY > ja) fl0 |= F_MON;
+            } else if (ix + (P->mon_nc == 5) >= x0 && ix < x0 + xn && jb < lo0 + n0 && jb + TY > lo0)
                 fl0 |= F_MON;
         }
     }
@@ -132,19 +144,20 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
 
     // LDS: rows for the neighbouring waves (12 slots of W x 64), then the
     // memories of step n+1 that the second step reads one plane later: y-slab
-    // rows (slab row, value, plane parity), x-slab columns (row, value, parity)
+    // rows (block row, value, plane parity), x-slab columns (row, value, parity)
     float *const ex = lds + lane;
     auto slot = [&](int q, int ww) -> float & { return ex[(q * W + ww) * 64]; };
-    float *const ystash = lds + 12 * W * 64 + lane;
-    float *const xstash = lds + 12 * W * 64 + YO_PAIR_YROWS * 4 * 2 * 64 + w * TY * 4 * 2 * 32 + xi;
-    auto yst = [&](int r, int v, int par) -> float & { return ystash[(((sr0 + r) * 4 + v) * 2 + par) * 64]; };
-    auto xst = [&](int r, int v, int par) -> float & { return xstash[((r * 4 + v) * 2 + par) * 32]; };
+    constexpr int XL = GEN == 2 ? 64 : 32;
+    float *const ystash = lds + 12 * W * 64 + w * TY * 4 * 2 * 64 + lane;
+    float *const xstash = lds + 12 * W * 64 + W * TY * 4 * 2 * 64 + w * TY * 4 * 2 * XL + xi;
+    auto yst = [&](int r, int v, int par) -> float & { return ystash[((r * 4 + v) * 2 + par) * 64]; };
+    auto xst = [&](int r, int v, int par) -> float & { return xstash[((r * 4 + v) * 2 + par) * XL]; };
 
     // by plane parity: E^n, Ht^{n+1/2}, E^{n+1}, kappa, Ht^{n+3/2} and the z
     // memories of step n+1 (the second of a plane's two is the plane before)
     float E0[2][3][TY], H[2][3][TY], E1_[2][3][TY], K[2][3][TY], H2_[2][3][TY];
     float zH_[2][2][TY], zE_[2][2][TY];
-    const int kb = k0 == 0 ? 0 : k0 - 2;
+    const int kb = k0 == 0 ? 0 : k0 - (ONE ? 1 : 2);
 #pragma unroll
     for (int r = 0; r < TY; ++r) {
         const unsigned o = (unsigned)kb * pstr + rb[r];
@@ -176,6 +189,7 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
         const int pz = slab_index(k, nz, zlo, zhi), pzm = slab_index(km, nz, zlo, zhi);
         const bool kin = k < nz, kmin = km >= 0;   // k >= 0 always, km < nz
         const bool ownk = km >= k0 && km < k1;
+        auto own1 = [&](int r) { return k >= k0 && (fl >> (F_OWN + r) & 1); };   // a step alone: k < k1
         {
             // planes past the grid read zero (past the buffer)
             const unsigned oh = (unsigned)min(k, nz - 1) * pstr, oe = (unsigned)min(k + 1, nz - 1) * pstr;
@@ -246,8 +260,16 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                         float n0, n1;
                         dxEz = pml_diff(dxEz, cxH, qx[2][r], n0);
                         dxEy = pml_diff(dxEy, cxH, qx[3][r], n1);
-                        xst(r, 0, par) = n0;
-                        xst(r, 1, par) = n1;
+                        if constexpr (ONE) {
+                            if (own1(r) && L.own) {
+                                const unsigned o = xb2 + (unsigned)(k * ny + jb + r) * xrow;
+                                bstore(n0, PS, L.px, o + 2 * xw);
+                                bstore(n1, PS, L.px, o + 3 * xw);
+                            }
+                        } else {
+                            xst(r, 0, par) = n0;
+                            xst(r, 1, par) = n1;
+                        }
                     }
                 }
                 if ((fl >> (F_YSLAB + r) & 1) && kin) {
@@ -255,25 +277,40 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                     float n0, n1;
                     dyEz = pml_diff(dyEz, cy, qy[2][r], n0);
                     dyEx = pml_diff(dyEx, cy, qy[3][r], n1);
-                    yst(r, 0, par) = n0;
-                    yst(r, 1, par) = n1;
+                    if constexpr (ONE) {
+                        if (own1(r)) {
+                            const unsigned o = yb2 + (unsigned)k * ypl + (unsigned)(py0 + r) * ps;
+                            bstore(n0, PS, xps + 512, o);
+                            bstore(n1, PS, xps + 768, o);
+                        }
+                    } else {
+                        yst(r, 0, par) = n0;
+                        yst(r, 1, par) = n1;
+                    }
                 }
             }
             if (pz >= 0 && (fl >> (F_IN + r) & 1)) {
                 dzEy = pml_diff(dzEy, cz, zH[0][r], zH[0][r]);
                 dzEx = pml_diff(dzEx, cz, zH[1][r], zH[1][r]);
+                if (ONE && own1(r)) {
+                    const unsigned o = zb2 + (unsigned)(pz * ny + jb + r) * ps;
+                    bstore(zH[0][r], PS, xps + 512, o);
+                    bstore(zH[1][r], PS, xps + 768, o);
+                }
             }
             Hc[0][r] = Hc[0][r] - fmaf(sy, dyEz, -(sz * dzEy));
             Hc[1][r] = Hc[1][r] - fmaf(sz, dzEx, -(sx * dxEz));
             Hc[2][r] = Hc[2][r] - fmaf(sx, dxEy, -(sy * dyEx));
         }
-        slot(8, w) = Hc[0][TY - 1];
-        slot(9, w) = Hc[2][TY - 1];
+        // (a step alone has no second barrier: slots by parity)
+        const int s8 = ONE ? 8 + 2 * par : 8;
+        slot(s8, w) = Hc[0][TY - 1];
+        slot(s8 + 1, w) = Hc[2][TY - 1];
         block_sync_lds();
 
         // ---- S2 ----
         if (pz >= 0) cz = cpml_uniform(profz, 0, k);
-        const float hxd = slot(8, wd), hzd = slot(9, wd);
+        const float hxd = slot(s8, wd), hzd = slot(s8 + 1, wd);
 #pragma unroll
         for (int r = 0; r < TY; ++r) {
             const float hd0 = r > 0 ? Hc[0][r > 0 ? r - 1 : 0] : hxd;
@@ -290,8 +327,16 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                         float n0, n1;
                         dxHz = pml_diff(dxHz, cxE, qx[0][r], n0);
                         dxHy = pml_diff(dxHy, cxE, qx[1][r], n1);
-                        xst(r, 2, par) = n0;
-                        xst(r, 3, par) = n1;
+                        if constexpr (ONE) {
+                            if (own1(r) && L.own) {
+                                const unsigned o = xb2 + (unsigned)(k * ny + jb + r) * xrow;
+                                bstore(n0, PS, L.px, o);
+                                bstore(n1, PS, L.px, o + xw);
+                            }
+                        } else {
+                            xst(r, 2, par) = n0;
+                            xst(r, 3, par) = n1;
+                        }
                     }
                 }
                 if ((fl >> (F_YSLAB + r) & 1) && kin) {
@@ -299,13 +344,26 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                     float n0, n1;
                     dyHz = pml_diff(dyHz, cy, qy[0][r], n0);
                     dyHx = pml_diff(dyHx, cy, qy[1][r], n1);
-                    yst(r, 2, par) = n0;
-                    yst(r, 3, par) = n1;
+                    if constexpr (ONE) {
+                        if (own1(r)) {
+                            const unsigned o = yb2 + (unsigned)k * ypl + (unsigned)(py0 + r) * ps;
+                            bstore(n0, PS, xps, o);
+                            bstore(n1, PS, xps + 256, o);
+                        }
+                    } else {
+                        yst(r, 2, par) = n0;
+                        yst(r, 3, par) = n1;
+                    }
                 }
             }
             if (pz >= 0 && (fl >> (F_IN + r) & 1)) {
                 dzHy = pml_diff(dzHy, cz, zE[0][r], zE[0][r]);
                 dzHx = pml_diff(dzHx, cz, zE[1][r], zE[1][r]);
+                if (ONE && own1(r)) {
+                    const unsigned o = zb2 + (unsigned)(pz * ny + jb + r) * ps;
+                    bstore(zE[0][r], PS, xps, o);
+                    bstore(zE[1][r], PS, xps + 256, o);
+                }
             }
             E1[0][r] = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy)), Ec[0][r]);
             E1[1][r] = fmaf(Kc[1][r], fmaf(sz, dzHx, -(sx * dxHz)), Ec[1][r]);
@@ -337,11 +395,33 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
             if (!CP || !(fl & F_SRC)) return;
             Const<YoRhsD> Rc = opaque(R);
             const int lo1 = Rc->src.lo1, n1 = Rc->src.n1;
-            if (kk < lo1 || kk >= lo1 + n1) return;
+            if (!(GEN && Rc->src.axis) && (kk < lo1 || kk >= lo1 + n1)) return;
             const int lo0 = Rc->src.lo0, n0 = Rc->src.n0, snc = Rc->src_nc;
             Const<float> st = (Const<float>)(uintptr_t)(Rc->steptab + n);
             const float stx = st[0], sty = st[1];
             const int pl = n0 * n1, d = L.x - Rc->src.index;
+            if constexpr (GEN > 0) {
+                // any normal: the place across the plane and in it, and the
+                // plane's component that goes to each of E's (-1: none)
+                const Global<const float2> sj = (Global<const float2>)(uintptr_t)Rc->src_j;
+                const int ax = Rc->src.axis, ix = Rc->src.index;
+#pragma unroll
+                for (int r = 0; r < TY; ++r) {
+                    const int j = jb + r;
+                    const int dn = (ax == 0 ? L.x : ax == 1 ? j : kk) - ix;
+                    const int a = (ax == 0 ? j : L.x) - lo0, b = (ax == 2 ? j : kk) - lo1;
+                    if (!(dn == 0 || (snc == 5 && dn == 1)) || a < 0 || a >= n0 || b < 0 || b >= n1) continue;
+                    const Global<const float2> q = sj + b * n0 + a;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const int m = (c - ax + 3) % 3;
+                        const int t = m == 0 ? (snc == 5 && dn == 0 ? 2 : -1) : m - 1 + (dn ? 3 : 0);
+                        if (t >= 0)
+                            e[c][r] = fmaf(-kv[c][r], fmaf(q[t * pl].x, stx, q[t * pl].y * sty), e[c][r]);
+                    }
+                }
+                return;
+            }
             if (!(d == 0 || (snc == 5 && d == 1))) return;
             const Global<const float2> sj = (Global<const float2>)(uintptr_t)Rc->src_j;
 #pragma unroll
@@ -360,6 +440,20 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
         };
         conductor(k, E1);
         source(k, step, E1, Kc);
+        if constexpr (ONE) {
+            if (k < k0) return;
+            const unsigned o = (unsigned)k * pstr;
+#pragma unroll
+            for (int r = 0; r < TY; ++r) {
+                if (!(fl >> (F_OWN + r) & 1)) continue;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    bstore_nt(E1[c][r], FC, xs + 256 * c, o + rb[r]);
+                    bstore_nt(Hc[c][r], FC, xs + 768 + 256 * c, o + rb[r]);
+                }
+            }
+            return;
+        }
         if constexpr (DFT) {
             // E^{n+1} on this tile's cells of the design box and the port planes,
             // for the running DFT (k_dft, which adds both steps after this launch)
@@ -377,12 +471,32 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                         for (int c = 0; c < 3; ++c) mid[c * bz * by * bx + o] = E1[c][r];
                     }
                 }
-                if (fl & F_MON) {
+                if (CP && (fl & F_MON)) {
                     const Global<float> mon = mid + 3 * bz * by * bx;
                     const int np = Pc->n_ports, nc = Pc->mon_nc;
                     for (int q = 0; q < np; ++q) {
                         const int lo0 = Pc->ports[q].lo0, n0 = Pc->ports[q].n0, n1 = Pc->ports[q].n1;
                         const int bk1 = k - Pc->ports[q].lo1, d = L.x - Pc->ports[q].index;
+                        if constexpr (GEN > 0) {
+                            const int ax = Pc->ports[q].axis, ix = Pc->ports[q].index, pl = n0 * n1;
+#pragma unroll
+                            for (int r = 0; r < TY; ++r) {
+                                const int j = jb + r;
+                                const int dn = (ax == 0 ? L.x : ax == 1 ? j : k) - ix;
+                                const int a = (ax == 0 ? j : L.x) - lo0, b = (ax == 2 ? j : k) - Pc->ports[q].lo1;
+                                if (!L.own || !(fl >> (F_OWN + r) & 1) || !(dn == 0 || (nc == 5 && dn == 1)) || a < 0 ||
+                                    a >= n0 || b < 0 || b >= n1)
+                                    continue;
+                                const int o = Pc->mon_off[q] + b * n0 + a;
+#pragma unroll
+                                for (int c = 0; c < 3; ++c) {
+                                    const int m = (c - ax + 3) % 3;
+                                    const int t = m == 0 ? (nc == 5 && dn == 0 ? 2 : -1) : m - 1 + (dn ? 3 : 0);
+                                    if (t >= 0) mon[o + t * pl] = E1[c][r];
+                                }
+                            }
+                            continue;
+                        }
                         if (bk1 < 0 || bk1 >= n1 || !L.own || !(d == 0 || (nc == 5 && d == 1))) continue;
                         const int pl = n0 * n1, o = Pc->mon_off[q] + bk1 * n0;
 #pragma unroll
@@ -523,13 +637,13 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     };
     for (;;) {
         plane(E0[0], E0[1], H[0], H[1], E1_[0], E1_[1], K[0], K[1], H2_[0], H2_[1], zH_[0], zH_[1], zE_[0], zE_[1]);
-        if (++k > k1) break;
+        if (++k > k1 - ONE) break;
         plane(E0[1], E0[0], H[1], H[0], E1_[1], E1_[0], K[1], K[0], H2_[1], H2_[0], zH_[1], zH_[0], zE_[1], zE_[0]);
-        if (++k > k1) break;
+        if (++k > k1 - ONE) break;
     }
 }
 
-template <int TY, int W, bool CP, bool DFT>
+template <int TY, int W, bool CP, bool DFT, int GEN, bool ONE>
 __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
 {
     const int nb = gridDim.x, b = blockIdx.x;
@@ -546,7 +660,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
     const Const<YoPlanD> P = constant(sl.plan);
     const int step = *constant(P->step_ctr) + a.k_offset;
     // the host schedules a pair only where both steps remain
-    if (step + 1 >= P->n_steps) return;
+    if (step + (ONE ? 0 : 1) >= P->n_steps) return;
     const int now = P->nbuf == 3 ? step % 3 : (constant(P->step_ctr)[1] + a.b_offset) & 1;
     const int blk = (wave0 - a.prefix[s]) / W;
     // consecutive blocks take neighbouring strips of the same rows (whose row
@@ -562,22 +676,37 @@ __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
     const int ti = g * G + in_g % gsz;
     extern __shared__ float lds[];
     const Const<int> tp = (Const<int>)(uintptr_t)(sl.tiles + ti);
-    wave_pair<TY, W, CP, DFT>(P, constant(P->rhs + r), step, now, int4{tp[0], tp[1], tp[2], tp[3]}, w, lane, lds);
+    wave_pair<TY, W, CP, DFT, GEN, ONE>(P, constant(P->rhs + r), step, now, int4{tp[0], tp[1], tp[2], tp[3]}, w, lane, lds);
 }
 
 }  // namespace
 
-hipError_t yo_launch_pair(bool shell, bool dft, const YoStepArgs &args, int blocks, hipStream_t s)
+hipError_t yo_launch_pair(bool shell, bool dft, int gen, const YoStepArgs &args, int blocks, hipStream_t s)
 {
     if (blocks <= 0) return hipSuccess;
     if (args.wpb != YO_PAIR_W) return hipErrorInvalidValue;
-    const size_t lds = sizeof(float) * 12 * YO_PAIR_W * 64;
-    const size_t lds_shell = lds + sizeof(float) * (YO_PAIR_YROWS * 4 * 2 * 64 + YO_PAIR_W * YO_PAIR_TY * 4 * 2 * 32);
-    const dim3 g(blocks), b(64 * YO_PAIR_W);
     constexpr int T = YO_PAIR_TY, W = YO_PAIR_W;
-    if (shell && dft) hipLaunchKernelGGL((k_yee_pair<T, W, true, true>), g, b, lds_shell, s, args);
-    else if (shell) hipLaunchKernelGGL((k_yee_pair<T, W, true, false>), g, b, lds_shell, s, args);
-    else if (dft) hipLaunchKernelGGL((k_yee_pair<T, W, false, true>), g, b, lds, s, args);
-    else hipLaunchKernelGGL((k_yee_pair<T, W, false, false>), g, b, lds, s, args);
+    const size_t lds = sizeof(float) * 12 * W * 64;
+    // (two blocks per CU with 32 x-slab columns a strip, one with 64)
+    const size_t lds_shell = lds + sizeof(float) * W * T * 4 * 2 * (64 + (gen == 2 ? 64 : 32));
+    auto go = [&](auto kernel, size_t bytes) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * W), bytes, s, args);
+        return hipGetLastError();
+    };
+    if (!shell) return dft ? go(k_yee_pair<T, W, false, true, 0, false>, lds) : go(k_yee_pair<T, W, false, false, 0, false>, lds);
+    if (gen == 2)
+        return dft ? go(k_yee_pair<T, W, true, true, 2, false>, lds_shell) : go(k_yee_pair<T, W, true, false, 2, false>, lds_shell);
+    if (gen == 1)
+        return dft ? go(k_yee_pair<T, W, true, true, 1, false>, lds_shell) : go(k_yee_pair<T, W, true, false, 1, false>, lds_shell);
+    return dft ? go(k_yee_pair<T, W, true, true, 0, false>, lds_shell) : go(k_yee_pair<T, W, true, false, 0, false>, lds_shell);
+}
+
+hipError_t yo_launch_one(const YoStepArgs &args, int blocks, hipStream_t s)
+{
+    if (blocks <= 0) return hipSuccess;
+    if (args.wpb != YO_PAIR_W) return hipErrorInvalidValue;
+    constexpr int T = YO_PAIR_TY, W = YO_PAIR_W;
+    hipLaunchKernelGGL((k_yee_pair<T, W, true, false, 1, true>), dim3(blocks), dim3(64 * W),
+                       sizeof(float) * 12 * W * 64, s, args);
     return hipGetLastError();
 }

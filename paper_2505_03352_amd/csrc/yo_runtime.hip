@@ -170,11 +170,10 @@ struct yo_plan {
     // and the shell's tiles they replace in steps that go in pairs (its last
     // n_c4 tiles, those of class 4)
     int nz2 = 0, n_c4 = 0;
-    // whole-grid pairs (build_all_tiles): their tiles, the table's last n_all
-    // (0: the plan's pairs go through the two-step region and its
-    // surroundings), the first n_allc of them clear of the x- and y-slabs
-    // and the planes
+    // whole-grid tiles (build_all_tiles), the table's last n_all, the first
+    // n_allc of them clear of the x- and y-slabs and the planes
     int n_all = 0, n_allc = 0;
+    int gen = 0;                 // the kernel their launches need (yo_launch_pair)
     bool bg_set = false, design_set = false;
     double beta = 0;
     int steps_done = 0;
@@ -194,10 +193,6 @@ struct yo_plan {
     int static_dev = -1;
     unsigned static_epoch = 0;
     hipStream_t cap_stream = nullptr;
-    // YO_TILE_OVERLAP: the stream the two-step launch runs on, and the
-    // events that fork it from the caller's stream and join it back
-    hipStream_t side_stream = nullptr;
-    hipEvent_t ov_fork = nullptr, ov_join = nullptr;
     // launch timing: the last tm_n steps of each advance run eagerly, with
     // HIP events around the launches of part tm_part (0 or 1, or 2 for
     // every part); tm_ev[q] holds the event pairs of part q (see part_range)
@@ -730,34 +725,32 @@ int short_chunk(const yo_plan *p)
     return kc;
 }
 
-// Whole-grid pairs (yo_pair.hip): tiles of one strip of columns, at most
-// W TY - 4 rows and a chunk of planes, one block each.  They take every cell
-// two steps per launch, the absorbing layers and the sources included, where
-// the kernel can: planes normal to x only, and y-slab rows and x-slab columns
-// that fit its LDS.  Planes per tile: the chip holds about kPairSlots blocks,
-// a tile costs its planes plus the three it recomputes, so the chunk with the
-// fewest rounds times planes is taken.
+// Whole-grid tiles (yo_pair.hip): one strip of columns, at most W TY - 4 rows
+// and a chunk of planes, one block each.  They take every cell, the absorbing
+// layers and the sources included, two steps per launch (or one).  Planes per
+// tile: the chip holds about kPairSlots blocks, a tile costs its planes plus
+// the three it recomputes, so the chunk with the fewest rounds times planes is
+// taken.
 constexpr int kPairSlots = 512;
 void build_all_tiles(yo_plan *p)
 {
     p->n_all = p->n_allc = 0;
     const int n[3] = {p->grid.nx, p->grid.ny, p->grid.nz};
     constexpr int LR = YO_PAIR_W * YO_PAIR_TY;
-    for (const yo_plane &pl : p->src_planes)
-        if (pl.axis != 0) return;
-    for (const yo_plane &pl : p->port_planes)
-        if (pl.axis != 0) return;
-    if (p->plo[0] + p->phi[0] > 32 || p->plo[1] > YO_PAIR_YROWS || p->phi[1] > YO_PAIR_YROWS) return;
+    // the kernel with the general code: planes not normal to x, or strips that
+    // meet more than 32 x-slab columns
+    p->gen = 0;
+    for (const yo_plane &pl : p->src_planes) p->gen |= pl.axis != 0;
+    for (const yo_plane &pl : p->port_planes) p->gen |= pl.axis != 0;
+    for (int x = 0; x < n[0]; x += 60) {
+        const int a = std::max(x - 2, 0), b = std::min(x + 62, n[0]);
+        const int lo = std::max(0, std::min(b, p->plo[0]) - a), hi = std::max(0, b - std::max(a, n[0] - p->phi[0]));
+        if (lo + hi > 32) p->gen = 2;
+    }
     const int nyb = (n[1] + LR - 5) / (LR - 4);
     std::vector<int> yj, yn;
     for (int b = 0, j = 0; b < nyb; ++b) {
         const int jn = n[1] / nyb + (b < n[1] % nyb ? 1 : 0);
-        int lo = 0, hi = 0;
-        for (int q = j - 2; q < j - 2 + LR; ++q) {
-            lo += q >= 0 && q < p->plo[1];
-            hi += q < n[1] && q >= n[1] - p->phi[1];
-        }
-        if (lo && hi) return;
         yj.push_back(j);
         yn.push_back(jn);
         j += jn;
@@ -795,8 +788,13 @@ void build_all_tiles(yo_plan *p)
     auto clear = [&](const int4 &t) {
         const int xa = (t.x & 0xffff) - 2, xb = (t.x & 0xffff) + (t.x >> 16) + 2;
         bool plane = false;
-        auto meets = [&](const yo_plane &pl, int nc) { plane = plane || (pl.index + (nc == 5) >= xa && pl.index < xb); };
-        for (const yo_plane &pl : p->src_planes) meets(pl, 2);
+        const int ya = (t.y & 0xffff) - 2, yb = (t.y & 0xffff) + (t.y >> 16) + 2;
+        auto meets = [&](const yo_plane &pl, int nc) {
+            const int px = pl.axis == 0 ? pl.index : pl.lo0, wx = pl.axis == 0 ? 1 + (nc == 5) : pl.n0;
+            const int py = pl.axis == 1 ? pl.index : pl.lo1, wy = pl.axis == 1 ? 2 : pl.n1;
+            plane = plane || (px + wx > xa && px < xb && (pl.axis == 0 || (py + wy > ya && py < yb)));
+        };
+        for (const yo_plane &pl : p->src_planes) meets(pl, 5);
         for (const yo_plane &pl : p->port_planes) meets(pl, p->mon_nc);
         return !(t.w & 3) && !plane && (t.x & 0xffff) && (t.y & 0xffff);
     };
@@ -900,7 +898,7 @@ void build_tiles(yo_plan *p)
     for (int i = 0; i < 6; ++i) p->r2[i] = 0;
     p->n_all = p->n_allc = 0;
     if (pr) build_pair_tiles(p, lo, hi);
-    if (pr || p->tsteps == 1) build_all_tiles(p);
+    build_all_tiles(p);
 }
 
 // Entries of the tile table: `times` the single-step count at the shortest
@@ -1131,9 +1129,6 @@ void yo_plan_destroy(yo_plan *p)
         }
     }
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
-    if (p->side_stream) (void)hipStreamDestroy(p->side_stream);
-    if (p->ov_fork) (void)hipEventDestroy(p->ov_fork);
-    if (p->ov_join) (void)hipEventDestroy(p->ov_join);
     for (int q = 0; q < 8; ++q)
         for (hipEvent_t e : p->tm_ev[q]) (void)hipEventDestroy(e);
     delete p;
@@ -1812,7 +1807,10 @@ static void aux_args(yo_plan *const *plans, const int *which, int cnt, bool dft,
 // tiles of launch part `part`: 0 interior, 1 CPML shell, 2 two-step region,
 // 3 the interior around it (single steps), 4 the z-slabs under the two-step
 // region (two steps, YO_TILE_ZPAIRS), 5 the CPML shell of steps that go in
-// pairs (without the tiles of part 4), 6 whole-grid pairs (two steps)
+// pairs (without the tiles of part 4), 6 and 7 whole-grid pairs (two steps:
+// tiles clear of slabs and planes, the others), 8 both, for one step.  The
+// stepping takes 6 to 8; 0 and 1 where those launches are to be timed; 2 to 5
+// are there for yo_time_kernel
 static void part_range(const yo_plan *p, int part, int &t0, int &t1)
 {
     switch (part) {
@@ -1823,6 +1821,7 @@ static void part_range(const yo_plan *p, int part, int &t0, int &t1)
     case 4: t0 = p->n_tiles + p->n2 + p->nfr; t1 = t0 + p->nz2; break;
     case 6: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + p->n_allc; break;
     case 7: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2 + p->n_allc; t1 = t0 + p->n_all - p->n_allc; break;
+    case 8: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + p->n_all; break;
     default: t0 = p->n_int; t1 = p->n_tiles - (p->nz2 ? p->n_c4 : 0); break;
     }
 }
@@ -1866,13 +1865,14 @@ static int step_args(yo_plan *const *plans, const int *which, int cnt, int part,
 
 // Launch one part's step kernel (the variant its tiling flags choose).
 static hipError_t launch_part(const yo_plan *p0, int part, const YoStepArgs &a, int blocks, hipStream_t s,
-                              bool dft = false)
+                              int gen, bool dft = false)
 {
     const int f = p0->tflags;
     if (part == 2)
         return yo_launch_step2(false, (f & YO_TILE_PAIR6) ? YO_TY2 : YO_TY, (f & YO_TILE_COOP_PAIRS) != 0, a,
                                blocks, s);
-    if (part >= 6) return yo_launch_pair(part == 7, dft, a, blocks, s);
+    if (part == 8) return yo_launch_one(a, blocks, s);
+    if (part >= 6) return yo_launch_pair(part == 7, dft, gen, a, blocks, s);
     if (part == 4) return yo_launch_step2(true, YO_TY, false, a, blocks, s);
     if (part == 3)
         return yo_launch_step((f & YO_TILE_XINT) ? 1 : 0, false, !(f & YO_TILE_NOPF_INT), a, blocks, s);
@@ -1884,47 +1884,37 @@ static hipError_t launch_part(const yo_plan *p0, int part, const YoStepArgs &a, 
 }
 
 // Launch `n_launch` steps (k_offset 0..n_launch-1) of a plan list, then add
-// n_launch to every plan's counter.  Per step: DFT of E^n (when `with_dft`),
-// the step launches (interior, CPML shell), the source.  Plans must share
-// every tiling flag but the x-split ones.
-// DFT launches: at the steps k of the call with k % dft_every == 0 (the
-// kernel itself skips steps its plan does not sample).  pairs: the steps go
-// two at a time where two remain (the two-step region in one launch for
-// both, the interior around it and the CPML shell one step at a time, the
-// source after each step); the caller guarantees no DFT at the second step
-// of a pair.  With YO_TILE_OVERLAP the two-step launch of a pair goes on
-// the first plan's side stream, forked after the launches before it and
-// joined before the pair's second step: the first step's frame, shell and
-// source read only step n's buffer and write cells of step n+1's buffer that
-// the two-step launch does not (it reads step n's and writes R2's rim of
-// step n+1's and R2 of step n+2's), so the two may run at once.
+// n_launch to every plan's counter.  Plans must share every tiling flag but
+// the x-split ones.  DFT launches (when `with_dft`): at the steps k of the
+// call with k % dft_every == 0 (the kernel itself skips steps its plan does
+// not sample).  pairs: the steps go two per launch where two remain, every
+// plan having that many left in its run.  split: single steps as the
+// launches of parts 0 and 1 and the source, else as one launch.
 static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, int n_launch,
                               bool with_dft, hipStream_t s, yo_plan *timed = nullptr,
-                              int dft_every = 1, bool pairs = false)
+                              int dft_every = 1, bool pairs = false, bool split = false)
 {
-    yo_plan *const p0 = plans[0];
-    // whole-grid pairs where every plan's can go that way
-    bool whole = pairs;
-    for (int i = 0; i < n; ++i) whole = whole && plans[i]->n_all > 0;
-    // whole-grid pairs whose second step may be sampled keep it for k_dft (even
-    // strides sample the state before a pair only)
-    const bool mid = whole && with_dft && dft_every % 2;
-    const bool overlap = pairs && !whole && (p0->tflags & YO_TILE_OVERLAP) && p0->side_stream;
+    // pairs whose second step may be sampled keep it for k_dft (even strides
+    // sample the state before a pair only)
+    const bool mid = pairs && with_dft && dft_every % 2;
+    int gen = 0;
+    for (int i = 0; i < n; ++i) gen = std::max(gen, plans[i]->gen);
     for (int base = 0; base < n; base += YO_MAX_SLOTS) {
         const int cnt = std::min(YO_MAX_SLOTS, n - base);
-        static thread_local YoStepArgs A[8];
+        static thread_local YoStepArgs A[9];
         int b = 0;   // launches so far that advanced the state
-        int blocks[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int part = 0; part < (pairs ? 8 : 2); ++part)
-            blocks[part] = step_args(plans + base, which + base, cnt, part, A[part]);
+        int blocks[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (int part : {0, 1, 6, 7, 8})
+            if (part < 2 ? split : part == 8 ? !split : pairs)
+                blocks[part] = step_args(plans + base, which + base, cnt, part, A[part]);
         YoAuxArgs ad, as;
         aux_args(plans + base, which + base, cnt, true, ad);
         aux_args(plans + base, which + base, cnt, false, as);
-        auto launch = [&](int part, int k, hipStream_t on) -> yo_status {
+        auto launch = [&](int part, int k) -> yo_status {
             A[part].k_offset = k;
             A[part].b_offset = b;
             const bool dft = mid && part >= 6;
-            const bool tm = timed && base == 0 && blocks[part] &&
+            const bool tm = timed && base == 0 && blocks[part] && part < 8 &&
                             (timed->tm_part == part || timed->tm_part == 2);
             if (tm) {
                 std::vector<hipEvent_t> &ev = timed->tm_ev[part];
@@ -1934,63 +1924,41 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
                     HIPCHK(hipEventCreate(&e));
                     ev.push_back(e);
                 }
-                HIPCHK(hipEventRecord(ev[need - 2], on));
-                HIPCHK(launch_part(plans[base], part, A[part], blocks[part], on, dft));
-                HIPCHK(hipEventRecord(ev[need - 1], on));
+                HIPCHK(hipEventRecord(ev[need - 2], s));
+                HIPCHK(launch_part(plans[base], part, A[part], blocks[part], s, gen, dft));
+                HIPCHK(hipEventRecord(ev[need - 1], s));
                 timed->tm_done[part]++;
             } else {
-                HIPCHK(launch_part(plans[base], part, A[part], blocks[part], on, dft));
+                HIPCHK(launch_part(plans[base], part, A[part], blocks[part], s, gen, dft));
             }
             return YO_OK;
         };
+        auto sample = [&](int k, int both) -> yo_status {
+            ad.k_offset = k;
+            ad.b_offset = b;
+            ad.pair = both;
+            HIPCHK(yo_launch_dft(ad, s));
+            return YO_OK;
+        };
         yo_status st;
-        for (int k = 0; k < n_launch;) {
+        for (int k = 0; k < n_launch; ++b) {
             const bool pair = pairs && k + 1 < n_launch;
-            if (with_dft && k % dft_every == 0 && !(pair && mid)) {
-                ad.k_offset = k;
-                ad.b_offset = b;
-                HIPCHK(yo_launch_dft(ad, s));
-            }
-            if (whole && pair) {
-                if ((st = launch(6, k, s))) return st;
-                if ((st = launch(7, k, s))) return st;
-                if (mid) {
-                    ad.k_offset = k;
-                    ad.b_offset = b;
-                    ad.pair = 1;
-                    HIPCHK(yo_launch_dft(ad, s));
-                    ad.pair = 0;
-                }
-                ++b;
-                k += 2;
-            } else if (pair) {
-                // the two-step launches (R2, and with YO_TILE_ZPAIRS the
-                // z-slabs under it: part 5 is then the shell without them)
-                hipStream_t s2 = overlap ? p0->side_stream : s;
-                if (overlap) {
-                    HIPCHK(hipEventRecord(p0->ov_fork, s));
-                    HIPCHK(hipStreamWaitEvent(s2, p0->ov_fork, 0));
-                }
-                if ((st = launch(2, k, s2))) return st;
-                if ((st = launch(4, k, s2))) return st;
-                if (overlap) HIPCHK(hipEventRecord(p0->ov_join, s2));
-                for (int q = 0; q < 2; ++q) {
-                    if (q == 1 && overlap) HIPCHK(hipStreamWaitEvent(s, p0->ov_join, 0));
-                    if ((st = launch(3, k + q, s))) return st;
-                    if ((st = launch(5, k + q, s))) return st;
-                    as.k_offset = k + q;
-                    HIPCHK(yo_launch_source(as, s));
-                }
-                k += 2;
-            } else {
+            if (with_dft && k % dft_every == 0 && !(pair && mid))
+                if ((st = sample(k, 0))) return st;
+            if (pair) {
+                if ((st = launch(6, k))) return st;
+                if ((st = launch(7, k))) return st;
+                if (mid && (st = sample(k, 1))) return st;
+            } else if (split) {
                 for (int part = 0; part < 2; ++part)
-                    if ((st = launch(part, k, s))) return st;
+                    if ((st = launch(part, k))) return st;
                 as.k_offset = k;
                 as.b_offset = b;
                 HIPCHK(yo_launch_source(as, s));
-                ++b;
-                k += 1;
+            } else {
+                if ((st = launch(8, k))) return st;
             }
+            k += pair ? 2 : 1;
         }
         YoCtrArgs ca{};
         ca.n = cnt;
@@ -2002,30 +1970,14 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
     return YO_OK;
 }
 
-// Steps of a call may go two at a time where every plan has the count left in
-// its run: 2 over the whole grid (plans with one step per sweep asked for
-// take these too: same buffers, same results), 1 over the two-step region
-// (plans with a third buffer, tiling flag 512), there only if no DFT falls on
-// a pair's second step (no DFT in the call, or pulse DFTs on even steps); 0
-// not.
-static int pairs_ok(yo_plan *const *plans, int n, int n_launch, bool with_dft, int every)
+// Steps of a call go two per launch (plans with one step per sweep asked for
+// take that too: same buffers, same results) where every plan has the count
+// left in its run.
+static bool pairs_ok(yo_plan *const *plans, int n, int n_launch)
 {
-    bool region = true, whole = true;
-    for (int i = 0; i < n; ++i) {
-        const yo_plan *p = plans[i];
-        if (p->steps_done + n_launch > p->n_steps) return 0;
-        // (a plan whose two-step region came out empty has no frame tiles either)
-        region = region && p->tsteps == 2 && (p->tflags & YO_TILE_PAIRS) && p->n2 > 0;
-        whole = whole && p->n_all > 0;
-    }
-    if (whole) return 2;
-    if (!region) return 0;
-    if (with_dft) {
-        if (every % 2) return 0;
-        for (int i = 0; i < n; ++i)
-            if (!plans[i]->pulse) return 0;
-    }
-    return 1;
+    for (int i = 0; i < n; ++i)
+        if (plans[i]->steps_done + n_launch > plans[i]->n_steps) return false;
+    return true;
 }
 
 // The DFT stride every plan of the list samples, when they share one and all
@@ -2076,12 +2028,6 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
     }
     hipStream_t s = (hipStream_t)stream;
     if (chunk < 1) chunk = 1;
-    if ((plans[0]->tflags & YO_TILE_OVERLAP) && !plans[0]->side_stream) {
-        yo_plan *p0 = plans[0];
-        HIPCHK(hipEventCreateWithFlags(&p0->ov_fork, hipEventDisableTiming));
-        HIPCHK(hipEventCreateWithFlags(&p0->ov_join, hipEventDisableTiming));
-        HIPCHK(hipStreamCreateWithFlags(&p0->side_stream, hipStreamNonBlocking));
-    }
     // launch timing (yo_set_timing on the first plan): the last tm_n steps
     // of this call run eagerly with events around the timed part
     yo_plan *timed = plans[0]->tm_n > 0 ? plans[0] : nullptr;
@@ -2111,8 +2057,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         GraphEntry ge[4];
         while (n_steps - tail - done >= chunk) {
             const bool need_dft = chunk_needs_dft(plans, which, n, chunk);
-            const int po = pairs_ok(plans, n, chunk, need_dft, every);
-            const bool pairs = po == 2 || (po == 1 && chunk % 2 == 0);
+            const bool pairs = pairs_ok(plans, n, chunk);
             const int variant = (need_dft ? 1 : 0) | (pairs ? 2 : 0);
             const std::string kv = key + (need_dft ? "|dft" : "|nodft") + (pairs ? "|pairs" : "");
             if (!ge[variant].exec) {
@@ -2142,7 +2087,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
             }
             HIPCHK(hipGraphLaunch(ge[variant].exec, s));
             done += chunk;
-            bump(chunk, po == 2);
+            bump(chunk, pairs);
         }
     }
     while (done < n_steps) {
@@ -2151,13 +2096,15 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         const int k = std::min(chunk, lim);
         const bool need_dft = chunk_needs_dft(plans, which, n, k);
         const int every = dft_every(plans, n);
-        // (a plan without a third buffer whose single-step parts are timed runs them)
-        const bool single = in_tail && timed && timed->tm_part < 2 && timed->tsteps == 1;
-        const int po = single ? 0 : pairs_ok(plans, n, k, need_dft, every);
-        yo_status st = launch_steps(plans, which, n, k, need_dft, s, in_tail ? timed : nullptr, every, po != 0);
+        // single-step launches that are to be timed are run, but in plans whose
+        // split asks for pairs
+        const bool split = in_tail && timed && timed->tm_part < 2 &&
+                           !(timed->tsteps == 2 && (timed->tflags & YO_TILE_PAIRS));
+        const bool pairs = !split && pairs_ok(plans, n, k);
+        yo_status st = launch_steps(plans, which, n, k, need_dft, s, in_tail ? timed : nullptr, every, pairs, split);
         if (st) return st;
         done += k;
-        bump(k, po == 2);
+        bump(k, pairs);
     }
     for (int i = 0; i < n; ++i)
         plans[i]->steps_done = std::min(plans[i]->n_steps, start[i] + n_steps);
@@ -2433,7 +2380,7 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     HIPCHK(hipEventRecord(e0, s));
-    for (int k = 0; k < n_launch; ++k) HIPCHK(launch_part(p, cls, A, blocks, s));
+    for (int k = 0; k < n_launch; ++k) HIPCHK(launch_part(p, cls, A, blocks, s, p->gen));
     HIPCHK(hipEventRecord(e1, s));
     HIPCHK(hipEventSynchronize(e1));
     float ms = 0.0f;

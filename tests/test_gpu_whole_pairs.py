@@ -1,8 +1,10 @@
-"""Two steps per launch over the whole grid (launch parts 6 and 7) against
-single steps, bitwise, at the sizes where its tiles can go wrong: strips of
-60 columns, blocks of 12 rows, slabs of unequal and no width, source and port
-planes at strip edges, the two-term ports' five component planes, and grids
-large enough to take the tiles clear of the slabs in a launch of their own."""
+"""The whole-grid tiles (launch parts 6 and 7), two steps per launch and one,
+against the single-step launches of parts 0 and 1, bitwise, at the sizes where
+they can go wrong: strips of 60 columns, blocks of 12 rows, slabs of unequal
+and no width and of more columns than a strip's common share, source and port
+planes at strip edges and of every normal, the two-term ports' five component
+planes, and grids large enough to take the tiles clear of the slabs in a
+launch of their own."""
 import numpy as np
 import pytest
 import torch
@@ -12,27 +14,41 @@ from workloads import Plane
 gpu = pytest.mark.gpu
 
 
-def _plan(nx, ny, nz, npml, tb, device, src_x, port_x, two_term=False, steps=23, nf=1):
+def _plane(axis, index, npml, n, cut):
+    lo = [npml[2 * a] for a in range(3) if a != axis]
+    num = [n[a] - npml[2 * a] - npml[2 * a + 1] for a in range(3) if a != axis]
+    return Plane(axis, index, lo[0] + cut, lo[1], num[0] - cut, num[1])
+
+
+def _plan(nx, ny, nz, npml, tb, device, src, port, two_term=False, steps=23, nf=1):
     from paper_2505_03352_amd.plan import FreqSpec, Plan
     grid = dict(nx=nx, ny=ny, nz=nz, dx=40e-9, dy=36e-9, dz=45e-9, courant=0.4, npml=npml, pml_kappa_max=1.5,
                 pml_a_max=0.1)
     design = dict(i0=nx // 2, j0=ny // 2, md=1, nd=1, k_lo=nz // 2, k_hi=nz // 2, mc=1, nc=1, filter_r=1.0,
                   supersample=2, eps_core=12.11, eps_clad=2.085, sobel_delta=1e-6)
-    y0, z0, n0, n1 = npml[2], npml[4], ny - npml[2] - npml[3], nz - npml[4] - npml[5]
-    src, port = Plane(0, src_x, y0, z0, n0, n1), Plane(0, port_x, y0 + 1, z0, n0 - 1, n1)
+    # a plane: its index along x, or (normal, index)
+    src, port = (_plane(*(q if isinstance(q, tuple) else (0, q)), npml, (nx, ny, nz), cut)
+                 for q, cut in ((src, 0), (port, 1)))
     dt = 0.4 * 36e-9 / 299792458.0
     f = [FreqSpec(2 * np.pi / (19.0 + q) / dt, 5.0, steps - 5, 5 - q % 2) for q in range(nf)]
     return Plan(grid, design, steps, f, [src], [port], device=device, two_term=two_term, time_blocking=tb)
 
 
 CASES = [
-    # nx, ny, nz, npml, source x, port x, two-term, wavelengths
+    # nx, ny, nz, npml, source and port plane, two-term, wavelengths
     (60, 24, 12, (5, 5, 4, 4, 3, 3), 6, 50, False, 1),
     (61, 25, 13, (5, 5, 4, 4, 3, 3), 7, 54, True, 1),
     (119, 37, 21, (8, 6, 3, 12, 0, 4), 58, 61, False, 1),
     (121, 36, 16, (0, 9, 0, 5, 2, 0), 59, 60, True, 1),
     (182, 62, 40, (10, 10, 10, 10, 8, 8), 60, 120, False, 1),
     (420, 330, 14, (6, 6, 6, 6, 4, 4), 40, 380, False, 16),
+    (75, 31, 15, (5, 5, 4, 4, 3, 3), (1, 6), (1, 14), False, 1),
+    (75, 31, 15, (5, 5, 4, 4, 3, 3), (2, 4), (1, 15), True, 1),
+    (66, 40, 18, (5, 5, 4, 4, 3, 3), 12, (2, 11), True, 1),
+    (140, 50, 16, (6, 6, 16, 20, 3, 3), 62, (1, 24), False, 1),      # y-slabs of over a block of rows
+    (90, 30, 14, (20, 19, 4, 4, 3, 3), 40, 60, True, 1),             # both x-slabs in one strip
+    (130, 30, 14, (40, 36, 4, 4, 3, 3), 50, (2, 6), False, 1),       # and of over 32 columns
+    (420, 330, 14, (6, 6, 6, 6, 4, 4), (1, 40), (1, 300), False, 16),
 ]
 
 
@@ -48,33 +64,18 @@ def test_whole_grid_tiles_own_every_cell_once(nx, ny, nz, npml, sx, px, two, nf)
     p.close()
 
 
-@pytest.mark.parametrize("planes", ["y", "wide"])
-def test_plans_the_whole_grid_kernel_cannot_take(planes):
-    """A plane normal to y, or slabs of more rows than its LDS holds: no such
-    tiles, and the pairs go through the two-step region as before."""
-    from paper_2505_03352_amd.plan import FreqSpec, Plan
-    npml = (6,) * 6 if planes == "y" else (6, 6, 13, 6, 6, 6)
-    grid = dict(nx=150, ny=60, nz=40, dx=40e-9, dy=40e-9, dz=40e-9, courant=0.5, npml=npml)
-    design = dict(i0=70, j0=30, md=4, nd=4, k_lo=18, k_hi=20, mc=2, nc=2, filter_r=1.0, supersample=2,
-                  eps_core=12.11, eps_clad=2.085, sobel_delta=1e-6)
-    pl = Plane(1, 20, 12, 11, 16, 12) if planes == "y" else Plane(0, 16, 14, 11, 16, 12)
-    p = Plan(grid, design, 50, [FreqSpec(1e15, 0.0, 40, 8)], [pl], [], device="cpu", time_blocking=2)
-    p.set_tiling(4, 10, 512)
-    assert len(p.tile_table(6)) == len(p.tile_table(7)) == 0 and len(p.tile_table(2)) > 0
-    p.close()
-
-
 @gpu
 @pytest.mark.parametrize("nx,ny,nz,npml,sx,px,two,nf", CASES)
-def test_whole_grid_pairs_bitwise_equal_single_steps(nx, ny, nz, npml, sx, px, two, nf):
+def test_whole_grid_steps_bitwise_equal_split_single_steps(nx, ny, nz, npml, sx, px, two, nf):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2505_03352_amd.plan import advance_many
     rng = np.random.default_rng(nx)
     kap = torch.as_tensor(1.0 / rng.uniform(2.0, 12.0, (3, nz, ny, nx)), dtype=torch.float32)
     out = {}
-    for tb, fl in ((2, 0), (1, 0), (2, 512)):    # (2, 0): single steps
-        print(f"[gpu] whole pairs {nx}x{ny}x{nz} tb={tb} flags={fl}", flush=True)
+    # split: timed single-step launches, plain; one: a step per call
+    for how, tb, fl in (("split", 1, 0), ("pairs", 1, 0), ("pairs", 2, 512), ("one", 2, 0)):
+        print(f"[gpu] whole grid {nx}x{ny}x{nz} planes {sx} {px} {how} tb={tb} flags={fl}", flush=True)
         p = _plan(nx, ny, nz, npml, tb, "cuda", sx, px, two, nf=nf)
         p.bind()
         p.set_background(kap, torch.zeros(p.canvas_shape))
@@ -89,21 +90,31 @@ def test_whole_grid_pairs_bitwise_equal_single_steps(nx, ny, nz, npml, sx, px, t
         gen = torch.Generator(device="cuda").manual_seed(5)
         for q in range(p.n_rhs):
             p.set_fields(q, *(torch.randn(p.shape, generator=gen, device="cuda") for _ in range(2)))
-        pairs = tb == 1 or fl == 512
-        assert (len(p.tile_table(7)) > 0) == pairs
-        assert (len(p.tile_table(6)) > 0) == (pairs and nf == 16)
+        assert len(p.tile_table(7)) > 0
+        assert (len(p.tile_table(6)) > 0) == (nf == 16)
+        if how == "split":
+            p.set_timing(0, 100)
+
+        def go(n, chunk, graph):
+            if how != "one":
+                return advance_many([p], [3], n, chunk=chunk, use_graph=graph)
+            for _ in range(n):
+                advance_many([p], [3], 1, chunk=1, use_graph=graph)
+
         # graphs of pairs, plain pairs, and odd counts whose last step goes alone;
         # the run's last steps are in the DFT window
-        advance_many([p], [3], 10, chunk=5, use_graph=True)
-        advance_many([p], [3], 7, chunk=7, use_graph=False)
+        go(10, 5, True)
+        go(7, 7, False)
         some = range(0, p.n_rhs, max(1, p.n_rhs // 4))
         got = [x for q in some for x in p.get_fields(q)]
-        advance_many([p], [3], 6, chunk=6, use_graph=True)
+        go(6, 6, True)
+        if how == "split":
+            assert p.timing(0)[1] == (23 if len(p.tile_table(0)) else 0)
         p.finalize(3)
         got += [p.get_dft(q, region) for q in some for region in (0, 1)]
-        out[tb, fl] = [x.cpu().numpy() for x in got]
+        out[how, tb] = [x.cpu().numpy() for x in got]
         p.close()
-    assert all(np.abs(a).max() > 0 for a in out[2, 0])
-    for k in ((1, 0), (2, 512)):
-        for a, b in zip(out[2, 0], out[k]):
+    assert all(np.abs(a).max() > 0 for a in out["split", 1])
+    for k in out:
+        for a, b in zip(out["split", 1], out[k]):
             assert np.array_equal(a, b), k
