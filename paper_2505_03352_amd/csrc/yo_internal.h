@@ -102,7 +102,7 @@ struct YoSlot {
     const YoPlanD *plan;
     const int4 *tiles;       // tile list of this launch's class
     int rhs0, nrhs;
-    int ntile, pad_;
+    int ntile, nzc;          // tiles; whole-grid tiles: z-chunks of each
 };
 
 struct YoStepArgs {

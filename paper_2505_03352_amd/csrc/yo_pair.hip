@@ -670,13 +670,16 @@ __global__ __launch_bounds__(64 * W, 4) void k_yee_pair(const YoStepArgs a)
     // with one tile after another over the right-hand sides, 5.8 in groups)
     const int G = YO_PAIR_GROUP;
     const int g = blk / (G * sl.nrhs), in_g = blk - g * (G * sl.nrhs);
-    const int gsz = min(G, sl.ntile - g * G);
+    const int gsz = min(G, sl.ntile * sl.nzc - g * G);
     if (gsz <= 0) return;
     const int r = sl.rhs0 + in_g / gsz;
-    const int ti = g * G + in_g % gsz;
+    // the tile's chunk of planes, chunks outermost
+    const int ti = g * G + in_g % gsz, zc = ti / sl.ntile;
+    const int kq = P->nz / sl.nzc, kr = P->nz % sl.nzc;
+    const int k0 = zc * kq + min(zc, kr), k1 = k0 + kq + (zc < kr);
     extern __shared__ float lds[];
-    const Const<int> tp = (Const<int>)(uintptr_t)(sl.tiles + ti);
-    wave_pair<TY, W, CP, DFT, GEN, ONE>(P, constant(P->rhs + r), step, now, int4{tp[0], tp[1], tp[2], tp[3]}, w, lane, lds);
+    const Const<int> tp = (Const<int>)(uintptr_t)(sl.tiles + ti - zc * sl.ntile);
+    wave_pair<TY, W, CP, DFT, GEN, ONE>(P, constant(P->rhs + r), step, now, int4{tp[0], tp[1], k0 | k1 << 16, tp[3]}, w, lane, lds);
 }
 
 }  // namespace

@@ -725,13 +725,9 @@ int short_chunk(const yo_plan *p)
     return kc;
 }
 
-// Whole-grid tiles (yo_pair.hip): one strip of columns, at most W TY - 4 rows
-// and a chunk of planes, one block each.  They take every cell, the absorbing
-// layers and the sources included, two steps per launch (or one).  Planes per
-// tile: the chip holds about kPairSlots blocks, a tile costs its planes plus
-// the three it recomputes, so the chunk with the fewest rounds times planes is
-// taken.
-constexpr int kPairSlots = 512;
+// Whole-grid tiles (yo_pair.hip): one strip of columns and at most W TY - 4
+// rows, all planes (each launch cuts those, see whole_split).  They take every
+// cell, the absorbing layers and the sources included.
 void build_all_tiles(yo_plan *p)
 {
     p->n_all = p->n_allc = 0;
@@ -755,33 +751,19 @@ void build_all_tiles(yo_plan *p)
         yn.push_back(jn);
         j += jn;
     }
-    const long flat = (long)((n[0] + 59) / 60) * nyb * std::max(p->n_phys, 1);
-    int nzc = 1;
-    long best = -1;
-    for (int q = 1; q == 1 || n[2] / q >= 4; ++q) {
-        const long cost = (flat * q + kPairSlots - 1) / kPairSlots * ((n[2] + q - 1) / q + 3);
-        if (best < 0 || cost < best) {
-            best = cost;
-            nzc = q;
-        }
-    }
     const size_t t0 = p->tiles_host.size();
-    for (int c = 0, k = 0; c < nzc; ++c) {
-        const int kn = n[2] / nzc + (c < n[2] % nzc ? 1 : 0);
-        for (int b = 0; b < nyb; ++b)
-            for (int x = 0; x < n[0]; x += 60) {
-                const int xn = std::min(60, n[0] - x);
-                int4 t;
-                t.x = x | (xn << 16);
-                t.y = yj[b] | (yn[b] << 16);
-                t.z = k | ((k + kn) << 16);
-                t.w = (x - 2 < p->plo[0] || x + xn + 2 > n[0] - p->phi[0] ? 1 : 0) |
-                      (yj[b] - 2 < p->plo[1] || yj[b] - 2 + LR > n[1] - p->phi[1] ? 2 : 0) |
-                      (k < p->plo[2] || k + kn > n[2] - p->phi[2] ? 4 : 0);
-                p->tiles_host.push_back(t);
-            }
-        k += kn;
-    }
+    for (int b = 0; b < nyb; ++b)
+        for (int x = 0; x < n[0]; x += 60) {
+            const int xn = std::min(60, n[0] - x);
+            int4 t;
+            t.x = x | (xn << 16);
+            t.y = yj[b] | (yn[b] << 16);
+            t.z = n[2] << 16;
+            t.w = (x - 2 < p->plo[0] || x + xn + 2 > n[0] - p->phi[0] ? 1 : 0) |
+                  (yj[b] - 2 < p->plo[1] || yj[b] - 2 + LR > n[1] - p->phi[1] ? 2 : 0) |
+                  (p->plo[2] || p->phi[2] ? 4 : 0);
+            p->tiles_host.push_back(t);
+        }
     p->n_all = (int)(p->tiles_host.size() - t0);
     // tiles clear of the x- and y-slabs, the planes and the grid's first column
     // and row
@@ -798,15 +780,50 @@ void build_all_tiles(yo_plan *p)
         for (const yo_plane &pl : p->port_planes) meets(pl, p->mon_nc);
         return !(t.w & 3) && !plane && (t.x & 0xffff) && (t.y & 0xffff);
     };
-    // go first, in a launch of their own without the code for all that, where either launch fills the chip several times over; else one launch
-    // takes all (320x240x96 with 6 right-hand sides: 463 us per step in one,
-    // 516 in two, whose tails leave the chip idle; 600x400x120 with 25: 6.2 ms in
-    // one, 5.8 in two)
+    // go first
     const auto first = p->tiles_host.begin() + t0;
-    const long inner = std::count_if(first, p->tiles_host.end(), clear), rhs = std::max(p->n_phys, 1);
-    const bool two = inner * rhs >= 4 * kPairSlots && (p->n_all - inner) * rhs >= 4 * kPairSlots;
-    p->n_allc = two ? (int)inner : 0;
-    if (two) std::stable_partition(first, p->tiles_host.end(), clear);
+    p->n_allc = (int)std::count_if(first, p->tiles_host.end(), clear);
+    std::stable_partition(first, p->tiles_host.end(), clear);
+}
+
+// Where a whole-grid launch cuts the planes: into chunks of at most `c`.  The
+// chip holds about kPairSlots blocks; a block costs its planes plus the three
+// it recomputes, so over all the plans of the launch the chunk with the fewest
+// rounds times planes is taken.  With at most a block per CU a plane takes 2/3
+// of its time beside another block (56x56x36, 2 right-hand sides: 4.2 us;
+// 91x103x88: 6.5).
+// `two`: the tiles clear of slabs and planes go in a launch of their own
+// without the code for those, where either launch fills the chip several times
+// over; else one launch takes all (320x240x96 with 6 right-hand sides: 463 us
+// per step in one, 516 in two, whose tails leave the chip idle; 600x400x120
+// with 25: 6.2 ms in one, 5.8 in two).
+constexpr int kPairSlots = 512;
+struct WholeSplit {
+    int c = 1;
+    bool two = false;
+    int chunks(const yo_plan *p) const { return (p->grid.nz + c - 1) / c; }
+};
+WholeSplit whole_split(yo_plan *const *plans, const int *nrhs, int n)
+{
+    int top = 1;
+    for (int i = 0; i < n; ++i) top = std::max(top, plans[i]->grid.nz);
+    WholeSplit best;
+    long least = -1;
+    for (WholeSplit w{top, false}; w.c >= std::min(top, 2); --w.c) {
+        long inner = 0, all = 0, planes = 0;
+        for (int i = 0; i < n; ++i) {
+            const long q = w.chunks(plans[i]);
+            inner += (long)plans[i]->n_allc * nrhs[i] * q;
+            all += (long)plans[i]->n_all * nrhs[i] * q;
+            planes = std::max<long>(planes, (plans[i]->grid.nz + q - 1) / q);
+        }
+        const long cost = (2 * all <= kPairSlots ? 2 : 3 * ((all + kPairSlots - 1) / kPairSlots)) * (planes + 3);
+        if (least >= 0 && cost >= least) continue;
+        least = cost;
+        best = w;
+        best.two = inner >= 4 * kPairSlots && all - inner >= 4 * kPairSlots;
+    }
+    return best;
 }
 
 // Tile table: the interior tiles, then the CPML shell, each in space order
@@ -1811,7 +1828,7 @@ static void aux_args(yo_plan *const *plans, const int *which, int cnt, bool dft,
 // tiles clear of slabs and planes, the others), 8 both, for one step.  The
 // stepping takes 6 to 8; 0 and 1 where those launches are to be timed; 2 to 5
 // are there for yo_time_kernel
-static void part_range(const yo_plan *p, int part, int &t0, int &t1)
+static void part_range(const yo_plan *p, int part, bool two, int &t0, int &t1)
 {
     switch (part) {
     case 0: t0 = 0; t1 = p->n_int; break;
@@ -1819,9 +1836,9 @@ static void part_range(const yo_plan *p, int part, int &t0, int &t1)
     case 2: t0 = p->n_tiles; t1 = p->n_tiles + p->n2; break;
     case 3: t0 = p->n_tiles + p->n2; t1 = t0 + p->nfr; break;
     case 4: t0 = p->n_tiles + p->n2 + p->nfr; t1 = t0 + p->nz2; break;
-    case 6: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + p->n_allc; break;
-    case 7: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2 + p->n_allc; t1 = t0 + p->n_all - p->n_allc; break;
-    case 8: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + p->n_all; break;
+    case 6: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = t0 + (two ? p->n_allc : 0); break;
+    case 7: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2 + (two ? p->n_allc : 0); t1 = (int)p->tiles_host.size(); break;
+    case 8: t0 = p->n_tiles + p->n2 + p->nfr + p->nz2; t1 = (int)p->tiles_host.size(); break;
     default: t0 = p->n_int; t1 = p->n_tiles - (p->nz2 ? p->n_c4 : 0); break;
     }
 }
@@ -1830,6 +1847,16 @@ static void part_range(const yo_plan *p, int part, int &t0, int &t1)
 // returns the number of blocks (0: no plan has tiles there).
 static int step_args(yo_plan *const *plans, const int *which, int cnt, int part, YoStepArgs &a)
 {
+    WholeSplit ws;
+    if (part >= 6) {
+        int nrhs[YO_MAX_SLOTS];
+        for (int i = 0; i < cnt; ++i) {
+            int r0, r1;
+            set_rhs_range(plans[i], which[i], r0, r1);
+            nrhs[i] = std::max(r1 - r0, 0);
+        }
+        ws = whole_split(plans, nrhs, cnt);
+    }
     memset(&a, 0, sizeof(YoStepArgs));
     a.n_slots = cnt;
     const int wpb = part >= 6 ? YO_PAIR_W : (plans[0]->tflags & YO_TILE_WPB8) ? 8 : 4;
@@ -1845,16 +1872,17 @@ static int step_args(yo_plan *const *plans, const int *which, int cnt, int part,
         set_rhs_range(p, which[i], r0, r1);
         YoSlot &sl = a.slot[i];
         int t0, t1;
-        part_range(p, part, t0, t1);
+        part_range(p, part, ws.two, t0, t1);
         sl.plan = wsp<YoPlanD>(p, p->L.desc_plan);
         sl.tiles = wsp<int4>(p, p->L.tiles) + t0;
         sl.rhs0 = r0;
         sl.nrhs = std::max(r1 - r0, 1);
         sl.ntile = (r1 > r0) ? t1 - t0 : 0;
+        sl.nzc = part >= 6 ? ws.chunks(p) : 1;
         a.prefix[i] = tot;
         // waves come in groups of wpb per right-hand side: wpb tiles, or in
         // the cooperative layout one tile
-        const int groups = coop ? sl.ntile : (sl.ntile + wpb - 1) / wpb;
+        const int groups = coop ? sl.ntile * sl.nzc : (sl.ntile + wpb - 1) / wpb;
         tot += sl.nrhs * groups * wpb;
     }
     a.prefix[cnt] = tot;
@@ -2313,12 +2341,18 @@ yo_status yo_tile_table(const yo_plan *p, int part, int *out, int cap, int *n)
 {
     if (!p || !n || (cap > 0 && !out)) return fail(YO_EINVAL, "null argument");
     if (part < 0 || part > 7) return fail(YO_EINVAL, "part must be 0 to 7");
+    // (whole-grid tiles as a launch of all the plan's right-hand sides cuts them)
+    yo_plan *const self = const_cast<yo_plan *>(p);
+    const int rhs = std::max(p->n_phys, 1);
+    const WholeSplit ws = part >= 6 ? whole_split(&self, &rhs, 1) : WholeSplit{};
+    const int nzc = part >= 6 ? ws.chunks(p) : 1, nz = p->grid.nz;
     int t0, t1;
-    part_range(p, part, t0, t1);
-    *n = t1 - t0;
-    for (int t = t0; t < t1 && t - t0 < cap; ++t) {
-        const int4 tt = p->tiles_host[t];
-        int *o = out + 7 * (t - t0);
+    part_range(p, part, ws.two, t0, t1);
+    *n = (t1 - t0) * nzc;
+    for (int t = 0; t < *n && t < cap; ++t) {
+        const int zc = t / (t1 - t0);
+        const int4 tt = p->tiles_host[t0 + t - zc * (t1 - t0)];
+        int *o = out + 7 * t;
         o[0] = tt.x & 0xffff;
         o[1] = o[0] + (tt.x >> 16);
         o[2] = tt.y & 0xffff;
@@ -2326,6 +2360,11 @@ yo_status yo_tile_table(const yo_plan *p, int part, int *out, int cap, int *n)
         o[4] = tt.z & 0xffff;
         o[5] = tt.z >> 16;
         o[6] = tt.w;
+        if (part >= 6) {
+            o[4] = zc * (nz / nzc) + std::min(zc, nz % nzc);
+            o[5] = o[4] + nz / nzc + (zc < nz % nzc ? 1 : 0);
+            o[6] = (tt.w & 3) | (o[4] < p->plo[2] || o[5] > nz - p->phi[2] ? 4 : 0);
+        }
     }
     return YO_OK;
 }
@@ -2348,7 +2387,8 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
     const yo_grid &g = p->grid;
     double own = 0.0, in_pml = 0.0;
     int ta, tb;
-    part_range(p, cls, ta, tb);
+    const int nrhs = std::max(r1 - r0, 0);
+    part_range(p, cls, cls >= 6 && whole_split(&p, &nrhs, 1).two, ta, tb);
     for (int t = ta; t < tb; ++t) {
         const int4 tt = p->tiles_host[t];
         const int x0 = tt.x & 0xffff, x1 = x0 + (tt.x >> 16);
