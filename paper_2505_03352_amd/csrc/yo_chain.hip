@@ -49,6 +49,26 @@ __global__ void k_from_ghost(const float *src, float *dst, unsigned n, int c0, i
     }
 }
 
+// Which planes hold one value per component: a block per plane (and column
+// of the components compared with the plane's first cell, bit by bit).
+__global__ __launch_bounds__(1024) void k_kplane(const float *kappa, float4 *kplane, int ny, int nx, int ns, int k_lo,
+                                                 int k_hi)
+{
+    const int k = blockIdx.x;
+    float v[3];
+    int differs = k >= k_lo && k <= k_hi;
+    for (int c = 0; c < 3; ++c) {
+        v[c] = kappa[yo_off(c, 0, 0, k, ny, ns, 3)];
+        if (k >= k_lo && k <= k_hi) continue;
+        for (int i = threadIdx.x; i < ny * nx; i += blockDim.x) {
+            const int y = i / nx, x = i - y * nx;
+            differs |= __float_as_uint(kappa[yo_off(c, x, y, k, ny, ns, 3)]) != __float_as_uint(v[c]);
+        }
+    }
+    differs = __syncthreads_or(differs);
+    if (threadIdx.x == 0) kplane[k] = make_float4(v[0], v[1], v[2], differs ? 0.0f : 1.0f);
+}
+
 // Ehat = (g00 Re S + g01 Im S) + i (g10 Re S + g11 Im S): least-squares
 // amplitude/phase from the DFT sums S = sum E^n exp(+i w n dt).  Any
 // non-finite phasor (all-ones exponent bits) sets *bad to 1: one atomic per
@@ -647,6 +667,13 @@ hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_to_ghost, dim3(blocks), dim3(BS), 0, s, dense, ghost, (unsigned)n, c0, nc,
                        (unsigned)nz, (unsigned)ny, (unsigned)nx, ns);
+    return hipGetLastError();
+}
+
+hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
+                            hipStream_t s)
+{
+    hipLaunchKernelGGL(k_kplane, dim3(nz), dim3(1024), 0, s, kappa, kplane, ny, nx, ns, k_lo, k_hi);
     return hipGetLastError();
 }
 

@@ -71,7 +71,8 @@ struct YoPlanD {
     int nx, ny, nz, ns;      // ns: strips per row
     float sx, sy, sz, pad0;
     int plo[3], phi[3];      // PML cells low/high per axis
-    const float *kappa;      // ghost layout (ghost values unused)
+    const float *kappa;      // ghost layout (ghosts zero)
+    const float4 *kplane;    // [nz]: a plane's one kappa per component and 1, or 0 in .w where it has no one value
     const float4 *prof[3];   // per axis [n_a][2]: (b, c, 1/kappa, 0) at the E, then at the Ht sites
     unsigned psi_off[3], psi_n[3];   // floats
     unsigned psi_bytes;      // CPML memory per right-hand side
@@ -201,6 +202,9 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s);
 // array with nc components
 hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
                               int ny, int nx, int ns, hipStream_t s);
+// kplane from kappa; planes k_lo .. k_hi are taken as not uniform
+hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
+                            hipStream_t s);
 hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
                                 int ny, int nx, int ns, hipStream_t s);
 // in-place phasor fit of n complex sums; sets *bad to 1 if a result is not

@@ -76,6 +76,7 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     const Rsrc FC = rsrc_of(R->F[nxt], array_bytes(P, 6));   // after step n+2
     const Rsrc KR = rsrc_of(P->kappa, array_bytes(P, 3));
     const Rsrc PS = rsrc_of(R->psi, P->psi_bytes);
+    const Const<float> kplane = (Const<float>)(uintptr_t)P->kplane;
     const float sx = P->sx, sy = P->sy, sz = P->sz;
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
     const int J0 = t.y & 0xffff, JN = t.y >> 16;
@@ -188,12 +189,14 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
         const int km = k - 1;
         const int pz = slab_index(k, nz, zlo, zhi), pzm = slab_index(km, nz, zlo, zhi);
         const bool kin = k < nz, kmin = km >= 0;   // k >= 0 always, km < nz
+        const bool kuni = kin && kplane[4 * min(k, nz - 1) + 3] != 0.0f;
         const bool ownk = km >= k0 && km < k1;
         auto own1 = [&](int r) { return k >= k0 && (fl >> (F_OWN + r) & 1); };   // a step alone: k < k1
         {
-            // planes past the grid read zero (past the buffer)
+            // planes past the grid read zero (past the buffer), and so does kappa
+            // where the plane has one value per component
             const unsigned oh = (unsigned)min(k, nz - 1) * pstr, oe = (unsigned)min(k + 1, nz - 1) * pstr;
-            const int ve = k + 1 < nz ? xl : kFar, vh = kin ? xl + 768 : kFar, vk = kin ? xk : kFar;
+            const int ve = k + 1 < nz ? xl : kFar, vh = kin ? xl + 768 : kFar, vk = kin && !kuni ? xk : kFar;
 #pragma unroll
             for (int r = 0; r < TY; ++r) {
                 const unsigned e = oe + rb[r], h = oh + rb[r], q = h >> 1;
@@ -309,6 +312,15 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
         block_sync_lds();
 
         // ---- S2 ----
+        if (kuni) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const unsigned v = __float_as_uint(kplane[4 * k + c]), kl = xk != kFar ? v : 0u;
+#pragma unroll
+                for (int r = 0; r < TY; ++r)
+                    Kc[c][r] = __uint_as_float(__float_as_uint(Kc[c][r]) | ((fl >> (F_IN + r) & 1) ? kl : 0u));
+            }
+        }
         if (pz >= 0) cz = cpml_uniform(profz, 0, k);
         const float hxd = slot(s8, wd), hzd = slot(s8 + 1, wd);
 #pragma unroll

@@ -48,7 +48,7 @@ struct Region {
 };
 
 struct Layout {
-    Region fields, kappa, psi, dft_box, dft_mon, dft_mid, src_j, port_w, steptab, prof, desc_plan,
+    Region fields, kappa, kplane, psi, dft_box, dft_mon, dft_mid, src_j, port_w, steptab, prof, desc_plan,
         desc_rhs, ctr, tiles, chain_f, chain_i, morph;
     size_t total = 0;
     size_t add(Region &r, size_t bytes)
@@ -359,7 +359,7 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
     build_regions(p);
     p->nominal = p->L.total;
     p->nominal -= align256(p->L.fields.bytes) + align256(p->L.kappa.bytes) + align256(p->L.psi.bytes) +
-                  align256(p->L.dft_mid.bytes) +
+                  align256(p->L.dft_mid.bytes) + align256(p->L.kplane.bytes) +
                   sizeof(float) * (p->tapt_x.size() + p->tapt_y.size() + (size_t)(p->S * p->des.md) * p->des.nc);
     p->nominal += align256(24 * p->nbuf * cells * p->n_phys) + align256(12 * cells) + align256(4 * psi * p->n_phys);
     return true;
@@ -375,6 +375,7 @@ void build_regions(yo_plan *p)
     L = Layout{};
     L.add(L.fields, sizeof(float) * fields_per_rhs(p) * p->n_phys);
     L.add(L.kappa, sizeof(float) * 3 * p->row_f * p->rows);
+    L.add(L.kplane, sizeof(float4) * g.nz);
     L.add(L.psi, sizeof(float) * p->psi_per_rhs * p->n_phys);
     L.add(L.dft_box, sizeof(float2) * 3 * p->bsz * p->n_rhs);
     L.add(L.dft_mon, sizeof(float2) * std::max<size_t>(p->mon_total, 1) * p->n_rhs);
@@ -1181,6 +1182,7 @@ static yo_status rebuild_descriptors(yo_plan *p)
     P.sx = (float)p->sx; P.sy = (float)p->sy; P.sz = (float)p->sz;
     for (int a = 0; a < 3; ++a) { P.plo[a] = p->plo[a]; P.phi[a] = p->phi[a]; }
     P.kappa = wsp<float>(p, p->L.kappa);
+    P.kplane = wsp<float4>(p, p->L.kplane);
     const float4 *prof = wsp<float4>(p, p->L.prof);
     P.prof[0] = prof;
     P.prof[1] = prof + 2 * (size_t)g.nx;
@@ -1618,6 +1620,9 @@ yo_status yo_set_background(yo_plan *p, const float *kappa, const float *mask, y
     hipStream_t s = (hipStream_t)stream;
     const yo_grid &g = p->grid;
     HIPCHK(yo_launch_to_ghost(kappa, wsp<float>(p, p->L.kappa), 3, 0, 3, g.nz, g.ny, g.nx, p->ns, s));
+    // (yo_set_design writes the slab and its faces)
+    HIPCHK(yo_launch_kplane(wsp<float>(p, p->L.kappa), wsp<float4>(p, p->L.kplane), g.nz, g.ny, g.nx, p->ns,
+                            p->des.k_lo - 1, p->des.k_hi, s));
     HIPCHK(hipMemcpyAsync(p->chain.mask, mask, sizeof(float) * p->U * p->V, hipMemcpyDeviceToDevice, s));
     p->bg_set = true;
     p->design_set = false;

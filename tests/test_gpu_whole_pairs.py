@@ -71,7 +71,10 @@ def test_whole_grid_steps_bitwise_equal_split_single_steps(nx, ny, nz, npml, sx,
         pytest.skip("no GPU")
     from paper_2505_03352_amd.plan import advance_many
     rng = np.random.default_rng(nx)
-    kap = torch.as_tensor(1.0 / rng.uniform(2.0, 12.0, (3, nz, ny, nx)), dtype=torch.float32)
+    kap = 1.0 / rng.uniform(2.0, 12.0, (3, nz, ny, nx))
+    kap[:, 2::3] = kap[:, 2::3, :1, :1]     # every third plane of one kappa per component
+    kap[1, 5, -1, -1] *= 1.25               # but for its last cell
+    kap = torch.as_tensor(kap, dtype=torch.float32)
     out = {}
     # split: timed single-step launches, plain; one: a step per call
     for how, tb, fl in (("split", 1, 0), ("pairs", 1, 0), ("pairs", 2, 512), ("one", 2, 0)):
