@@ -183,15 +183,14 @@ yo_status yo_set_dft_stride(yo_plan *plan, int stride);
 
 /* Temporal blocking (Sec. 2: the diamond / wavefront tilings of x-y-z-t that
  * fdtd-z shares with DiamondTorre, advancing several steps per pass over
- * memory), host only, before yo_bind_workspace (YO_ESTATE after).  steps = 2
- * gives every right-hand side a third state buffer (the state after step s
- * lives in buffer s % 3), so that the interior cells two clear of every
- * absorbing slab and of every source and port plane (the two-step region)
- * can be advanced two steps in one launch that reads each of their planes
- * once; tiling flag 512 (yo_set_tiling) then turns the pairs on.  Steps
- * whose DFT the plan needs (the time-harmonic window) and a run's odd last
- * step go one at a time.  Results are bitwise those of single steps.
- * steps = 1 (the default) removes the buffer.  Changes yo_workspace_bytes.
+ * memory), host only, before yo_bind_workspace (YO_ESTATE after).  Every plan
+ * is stepped two steps per launch where its run has them left (one in a
+ * launch of its own at the end of an odd count), whatever is set here, each
+ * plane's state read once for both; results are bitwise those of single
+ * steps.  steps = 2 gives every right-hand side a third state buffer (the
+ * state after step s lives in buffer s % 3) and allows the tiling flags from
+ * 512 on, which the launches that yo_time_kernel measures need.  steps = 1
+ * (the default) removes the buffer.  Changes yo_workspace_bytes.
  * YO_EINVAL for other values. */
 yo_status yo_set_time_blocking(yo_plan *plan, int steps);
 
@@ -208,9 +207,11 @@ yo_status yo_bind_workspace(yo_plan *plan, void *dev, size_t bytes, yo_stream st
  * library's own static workspace of the current device instead of a
  * caller-owned buffer; everything else works as after yo_bind_workspace.
  * Allocates nothing (no hipMalloc, no allocating library call).  The static
- * workspace holds at most 32 MiB (the tiny 56x56x36 device with one forward
- * and one adjoint right-hand side needs about 21 MiB): a plan whose
- * yo_workspace_bytes exceeds that gets YO_EWORKSPACE and stays unbound.  The
+ * workspace holds plans of at most 32 MiB (the tiny 56x56x36 device with one
+ * forward and one adjoint right-hand side needs about 21 MiB), counted with
+ * rows of nx + 2 floats rounded up to 32 and a ghost layer on all sides (the
+ * array itself has 96 MiB, as the layout's rows may be longer): a larger plan
+ * gets YO_EWORKSPACE and stays unbound.  The
  * device's array is shared by every plan bound to it and keeps the last
  * binding's contents; this call clears the plan's part of it to zero and
  * uploads the plan's tables (synchronising `stream`).  Binding another plan
@@ -285,12 +286,15 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n_plans, 
 /* Host-side step count of the last reset/advance of `plan`. */
 yo_status yo_steps_done(const yo_plan *plan, int *steps);
 
-/* Work split of the time-stepping kernel.  Each step runs two launches: the
- * interior tiles (clear of every absorbing slab, no CPML code) and the CPML
- * shell.  rows: rows per wave, must be 4; zchunk: z-planes per tile, 4..63;
+/* Work split of the launches by tile class, which yo_time_kernel measures and
+ * timed single steps run (yo_set_timing); the stepping's own launches take
+ * whole-grid tiles and choose their split by themselves (the planes they are
+ * cut at, over all the plans of the call).  A step in launches by class is two:
+ * the interior tiles (clear of every absorbing slab, no CPML code) and the
+ * CPML shell.  rows: rows per wave, must be 4; zchunk: z-planes per tile, 4..63;
  * flags, a sum of:
- *    1  the CPML x-shell is cut into full 62-cell strips instead of just
- *       the absorbing columns
+ *    1  the CPML x-shell is cut into whole 60-column strips, also where none
+ *       is left for the interior
  *    2  8 waves per block instead of 4
  *    4  shell: cooperative blocks (the block's waves are stacked in y and
  *       pass the rows they share through LDS instead of each loading them)
@@ -299,12 +303,11 @@ yo_status yo_steps_done(const yo_plan *plan, int *steps);
  *   16  interior: cooperative blocks
  *   32  interior: no prefetch of the next plane's operands
  *   64  shell: no prefetch
- *  128  the CPML x-shell strips take what is left of each row once the
- *       interior is cut into whole 62-cell strips (overrides 1)
+ *  128  as 1 in the launches of paired steps (with 512; overrides 1)
  *  256  tiles that meet only the x-slabs run in the interior launch, which
  *       then carries the x-axis CPML code
- *  512  two steps per launch over the two-step region where the run
- *       allows (needs yo_set_time_blocking(plan, 2); not with 16): its
+ *  512  two steps per launch over the two-step region, the cells two clear
+ *       of every absorbing slab and of every source and port plane (needs yo_set_time_blocking(plan, 2); not with 16): its
  *       tiles are strips of at most 60 cells, 4 rows and zchunk planes, and
  *       the rest of the interior runs as single-step tiles around it (with
  *       256, together with the tiles that meet only the x-slabs).  The
@@ -312,12 +315,7 @@ yo_status yo_steps_done(const yo_plan *plan, int *steps);
  *       two-step region's margin; the shell takes the layer between), and
  *       with 128 the two-step strips are whole 60-cell strips between the
  *       x-normal source and port planes, the shell strips the rest
- * 1024  with 512 (else YO_EINVAL): the two-step launch of a pair of steps
- *       runs on a second stream of the plan (created at its first advance,
- *       default priority), concurrently with the first step's other
- *       launches, and is joined back before the second step; advance calls
- *       on the caller's stream still complete in stream order, captured
- *       into a graph as well
+ * 1024  with 512 (else YO_EINVAL): no effect
  * 2048  with 512 (else YO_EINVAL): where the two-step region is the whole
  *       interior (no source or port plane cuts it, as with 128 when the
  *       planes lie in the shell strips), the z-slabs under it also go two
@@ -393,8 +391,10 @@ yo_status yo_model_bytes(const yo_plan *plan, int which, double *bytes_per_step,
  * count both; YO_ESTATE unless two steps remain in the run), 3: the interior
  * around it, 4: the two-step launch of the z-slabs under it (tiling flag
  * 2048; two steps like 2), 5: the CPML shell of the steps that go in pairs
- * (without the tiles of 4); other values YO_EINVAL; an empty part reports
- * zeros and launches nothing) over the
+ * (without the tiles of 4), 6 and 7: the stepping's own launches of two steps
+ * (counted like 2): whole-grid tiles clear of the x- and y-slabs and the planes
+ * where those fill a launch of their own, and the other tiles or all; other
+ * values YO_EINVAL; an empty part reports zeros and launches nothing) over the
  * right-hand sides selected by the last yo_reset, at the current step, with
  * HIP events on `stream`; blocks until done.  The launches re-run the same
  * step (they read the current buffers and do not advance the counter), so
@@ -406,13 +406,14 @@ yo_status yo_model_bytes(const yo_plan *plan, int which, double *bytes_per_step,
 yo_status yo_time_kernel(yo_plan *plan, int cls, int n_launch, float *avg_ms, double *bytes,
                          double *cells, yo_stream stream);
 
-/* The tiles of one launch part (as yo_time_kernel numbers them, 0 to 5)
+/* The tiles of one launch part (as yo_time_kernel numbers them, 0 to 7)
  * under the plan's current tiling: *n = their number, and the first
  * min(n, cap) written to host memory `out` as 7 ints each: x0, x1, y0, y1,
  * z0, z1 (the cells [x0, x1) x [y0, y1) x [z0, z1) the tile owns) and its
  * CPML class (bit a: the tile meets the absorbing slab of axis a).  Host
- * only; needs no workspace.  For checking a split: in single steps parts 0
- * and 1 own every cell once, in steps that go in pairs parts 2 to 5. */
+ * only; needs no workspace.  For checking a split: parts 0 and 1 own every
+ * cell once, so do parts 2 to 5 (part 3's and 5's in single steps), and so do
+ * 6 and 7, cut as a launch of all the plan's right-hand sides cuts them. */
 yo_status yo_tile_table(const yo_plan *plan, int part, int *out, int cap, int *n);
 
 /* Unbinarity (Sec. 4): the fraction of the design area's high-resolution
@@ -432,9 +433,10 @@ yo_status yo_adam_step(float *dev_C, const float *dev_G, float *dev_M, float *de
 /* Launch timing inside a solve: with n_last > 0, every later yo_advance,
  * yo_run or yo_advance_many (with this plan first in its list) runs its
  * last n_last steps with plain launches and records a pair of HIP events on
- * its stream around each launch of `part` (0 interior tiles, 1 CPML shell,
- * 2 every part, including the launches of the steps that go in pairs under
- * tiling flag 512: parts 2 to 5 of yo_time_kernel); the pairs accumulate over calls until
+ * its stream around each launch of `part` (0 interior tiles, 1 CPML shell:
+ * those steps then go one at a time in launches by class, but in plans whose
+ * tiling asks for pairs (512); 2 every launch of the stepping as it is: parts 6
+ * and 7 of yo_time_kernel); the pairs accumulate over calls until
  * the next yo_set_timing with n_last > 0, which clears them.  n_last = 0
  * turns it off and keeps what was recorded.  n_last <= 4096; the events
  * are created as needed (outside graph capture: the timed steps are never
@@ -444,7 +446,8 @@ yo_status yo_set_timing(yo_plan *plan, int part, int n_last);
 
 /* Mean duration of the launches of `part` (0 interior, 1 CPML shell, 2 the
  * two-step region, 3 the interior around it, 4 the z-slabs under it, 5 the
- * CPML shell of steps that go in pairs; see yo_time_kernel) timed since the last
+ * CPML shell of steps that go in pairs, 6 and 7 the whole-grid tiles of two
+ * steps; see yo_time_kernel) timed since the last
  * yo_set_timing (waits for the last of them); count = how many (0: none,
  * avg_ms = 0). */
 yo_status yo_get_timing(yo_plan *plan, int part, float *avg_ms, int *count);

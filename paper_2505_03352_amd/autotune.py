@@ -1,6 +1,8 @@
-"""Autotuner for the time-stepping kernel's work split.
+"""Autotuner for the work split of the launches by tile class.
 
-Each step runs two launches, the interior tiles and the CPML shell; their
+(The stepping's own launches take whole-grid tiles, two steps each, and choose
+their split by themselves; the tuner times them beside the rest.)  A step in
+launches by class is two, the interior tiles and the CPML shell; their
 layout choices are independent except for what the two share (z-planes per
 tile, waves per block, how the x-shell strips are cut).  For
 each shared setting the tuner times every interior choice (cooperative
@@ -15,9 +17,7 @@ also times two steps per launch (the two-step region's launch, with flag
 2048 the z-slabs' two-step launch, the interior around them and the shell of
 the paired steps, each with its own best choice) and keeps that when it is
 faster per step; with two steps per launch chosen, it then times whole
-steps with the two-step launch on a second stream beside the first step's
-other launches (flag 1024) against the same launches in one stream, and keeps
-the faster.  Every split gives bitwise the same fields, so tuning only
+steps with flag 1024 and without and keeps the faster.  Every split gives bitwise the same fields, so tuning only
 changes speed.
 
 `tuned_splits.json` beside this file ships splits the tuner chose on an

@@ -49,24 +49,38 @@ __global__ void k_from_ghost(const float *src, float *dst, unsigned n, int c0, i
     }
 }
 
-// Which planes hold one value per component: a block per plane (and column
-// of the components compared with the plane's first cell, bit by bit).
-__global__ __launch_bounds__(1024) void k_kplane(const float *kappa, float4 *kplane, int ny, int nx, int ns, int k_lo,
-                                                 int k_hi)
+// Which planes hold one value per component: each plane's first cell, then
+// blocks that compare its cells with it bit by bit, a wave per row, strips
+// (yo_col) side by side, a lane a column, and clear the plane's mark where one
+// differs.  (600x400x120: 400 us with one block a plane.)
+__global__ void k_kplane_first(const float *kappa, float4 *kplane, int nz, int ny, int ns, int k_lo, int k_hi)
 {
-    const int k = blockIdx.x;
-    float v[3];
-    int differs = k >= k_lo && k <= k_hi;
-    for (int c = 0; c < 3; ++c) {
-        v[c] = kappa[yo_off(c, 0, 0, k, ny, ns, 3)];
-        if (k >= k_lo && k <= k_hi) continue;
-        for (int i = threadIdx.x; i < ny * nx; i += blockDim.x) {
-            const int y = i / nx, x = i - y * nx;
-            differs |= __float_as_uint(kappa[yo_off(c, x, y, k, ny, ns, 3)]) != __float_as_uint(v[c]);
+    const int k = blockIdx.x * BS + threadIdx.x;
+    if (k >= nz) return;
+    const float *v = kappa + yo_off(0, 0, 0, k, ny, ns, 3);
+    kplane[k] = make_float4(v[0], v[64], v[128], k >= k_lo && k <= k_hi ? 0.0f : 1.0f);
+}
+
+__global__ __launch_bounds__(BS) void k_kplane(const float *kappa, float4 *kplane, int ny, int nx, int ns, int k_lo,
+                                               int k_hi)
+{
+    const int k = blockIdx.x, lane = threadIdx.x & 63;
+    if (k >= k_lo && k <= k_hi) return;
+    const float *v = kappa + yo_off(0, 0, 0, k, ny, ns, 3);
+    const unsigned first[3] = {__float_as_uint(v[0]), __float_as_uint(v[64]), __float_as_uint(v[128])};
+    bool differs = false;
+    for (int y = blockIdx.y * (BS / 64) + (threadIdx.x >> 6); y < ny; y += gridDim.y * (BS / 64)) {
+        const float *row = kappa + yo_off(0, 0, y, k, ny, ns, 3) - YO_LEAD;
+        for (int s = 0; s < ns; ++s) {
+            const bool in = lane >= YO_LEAD && lane < YO_LEAD + YO_SW && s * YO_SW + lane - YO_LEAD < nx;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const unsigned u = __float_as_uint(row[(s * 3 + c) * 64 + lane]);
+                differs = differs || (in && u != first[c]);
+            }
         }
     }
-    differs = __syncthreads_or(differs);
-    if (threadIdx.x == 0) kplane[k] = make_float4(v[0], v[1], v[2], differs ? 0.0f : 1.0f);
+    if (differs) kplane[k].w = 0.0f;
 }
 
 // Ehat = (g00 Re S + g01 Im S) + i (g10 Re S + g11 Im S): least-squares
@@ -673,7 +687,8 @@ hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c
 hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_kplane, dim3(nz), dim3(1024), 0, s, kappa, kplane, ny, nx, ns, k_lo, k_hi);
+    hipLaunchKernelGGL(k_kplane_first, dim3(nblk(nz)), dim3(BS), 0, s, kappa, kplane, nz, ny, ns, k_lo, k_hi);
+    hipLaunchKernelGGL(k_kplane, dim3(nz, 16), dim3(BS), 0, s, kappa, kplane, ny, nx, ns, k_lo, k_hi);
     return hipGetLastError();
 }
 

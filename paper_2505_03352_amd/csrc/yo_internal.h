@@ -15,15 +15,17 @@
 #define YO_PAIR_W 8       // waves per block,
 #define YO_PAIR_GROUP 32  // tiles that consecutive blocks take for one right-hand side
 
-// Field arrays carry a ghost row on either side of y.  A row of
-// nx cells is cut into ns strips of 60, each in a segment of nc x 64 floats, the
-// components of a strip side by side: component c of cell (x, j, k), j in
-// [-1, ny], of an array with nc components sits at
+// Field arrays carry a ghost row on either side of y.  A row of nx cells is cut
+// into ns strips of 60, each in a segment of nc x 64 floats, the components of a
+// strip side by side: component c of cell (x, j, k), j in [-1, ny], of an array
+// with nc components sits at
 //   (((k * (ny + 1) + (j + 1)) * ns + s) * nc + c) * 64 + 2 + x - 60 s,
-// s = x / 60 (row ny of a plane is row -1 of the next, a ghost of both).  The 2 floats on either side of the 60 are pads: the lanes of a
-// wave that own no cell of its strip lie over them and store values nobody
-// reads, so that every row of a strip is stored in whole 128-byte lines, and a
-// component's offset from a strip's first is a constant of the instruction.
+// s = x / 60 (row ny of a plane is row -1 of the next, a ghost of both).  The 2
+// floats on either side of the 60 are pads: the lanes of a wave that own no cell
+// of its strip lie over them and store values nobody reads, so that every row of
+// a strip is stored in whole 128-byte lines (stores of 240-byte rows across
+// lines reached 2.8 TB/s, of whole lines 4.7), and a component's offset from a
+// strip's first is a constant of the instruction.
 // The state of one right-hand side and buffer is one such array with nc = 6
 // (Ex Ey Ez Ht_x Ht_y Ht_z), kappa one with nc = 3.  Ghost rows are zero and
 // never written, and columns and planes outside the grid are read past the
@@ -39,9 +41,9 @@ struct YoPlaneD {
 // One right-hand side: its own field state, absorbing-layer memories, DFT
 // sums, source plane and per-step phase table.
 struct YoRhsD {
-    // state buffers, ghost layout, nc = 6 (E then Ht): nbuf = 3 when the plan
-    // may advance its interior two steps per sweep, the state after step s in
-    // F[s % 3]; else 2, which a launch that advances the state swaps
+    // state buffers, layout above, nc = 6 (E then Ht): two, which a launch that
+    // advances the state swaps, or with time blocking asked for three (nbuf), the
+    // state after step s in F[s % 3]
     float *F[3];
     // CPML memories: one slot per state buffer, of each axis four values (the
     // two of E's components, the two of Ht's): axis a's slot q at float offset
@@ -72,7 +74,7 @@ struct YoPlanD {
     float sx, sy, sz, pad0;
     int plo[3], phi[3];      // PML cells low/high per axis
     const float *kappa;      // ghost layout (ghosts zero)
-    const float4 *kplane;    // [nz]: a plane's one kappa per component and 1, or 0 in .w where it has no one value
+    const float4 *kplane;    // [nz]: a plane's one kappa per component, .w 1 (0: it has no one value)
     const float4 *prof[3];   // per axis [n_a][2]: (b, c, 1/kappa, 0) at the E, then at the Ht sites
     unsigned psi_off[3], psi_n[3];   // floats
     unsigned psi_bytes;      // CPML memory per right-hand side

@@ -1,6 +1,6 @@
-// Two Yee steps per launch over the whole grid (temporal blocking with the
-// absorbing layers and the sources inside).  Update, layout and expressions
-// as in yo_step.hip, whose single steps these two equal bitwise.
+// The time stepping: two Yee steps per launch over the whole grid, absorbing
+// layers and sources inside (temporal blocking), or one.  Update, layout and
+// expressions as in yo_step.hip, whose single steps these equal bitwise.
 //
 // A block of W waves marches up z over one strip of columns (yo_col) and a
 // stack of W TY rows, TY a wave; per plane k it takes, from the state after
@@ -10,24 +10,35 @@
 //   S3  Ht^{n+3/2} at plane k-1    (E^{n+1} at k-1 and k)
 //   S4  E^{n+2}    at plane k-1    (kappa, Ht^{n+3/2} at k-1 and k-2)
 // and stores S3 and S4, so a plane's state is read once and written once for
-// two steps.  Each row is worked on by one wave; the one row a stage needs of
-// the neighbouring wave (above for Ht, below for E) comes through LDS, with
-// two barriers per plane.  The rows at the block's ends (two below, two
-// above) and the lanes at the strip's (two on either side) are recomputed
-// from their own loads and not stored, as are the two planes below and one
-// above a z-chunk.
+// two steps; a step alone is S1 and S2, stored.  Each row is worked on by one
+// wave; the one row a stage needs of the neighbouring wave (above for Ht, below
+// for E) comes through LDS, with two barriers per plane.  The rows at the
+// block's ends (two below, two above) and the lanes at the strip's (two on
+// either side) are recomputed from their own loads and not stored, as are the
+// two planes below and one above a z-chunk.
 //
-// What bounds it: memory traffic (per cell and pair of steps 24 bytes in and
-// 24 out, times 16/12 rows and 64/60 columns on the way in) and, below about
-// a chip full of blocks, the latency of one plane.  Two rows a wave and eight
-// waves keep the kernel at 128 registers (16 waves per CU, two blocks).
-// Measured per step of the pair (HIP events):
-//   600x400x120, 25 right-hand sides 5.8 ms (two-step interior and one-step
-//   shell at the start of this work: 11.0), 7.4 ps per cell-update clear of
-//   the slabs, 10 in them; 320x240x96, 6: 463 us (871); 91x103x88, 2: 32 us
-//   (142).  3 rows a wave: 5.9 ms, 562 us, 48 us; 4 rows and 4 waves: 6.5 ms,
-//   536 us, 35 us; 16 waves of 2 rows: 6.3 ms, 587 us, 48 us; loading the next
-//   plane's operands during S4: no faster (8.3 against 8.4 ps).
+// What bounds it: on large grids the traffic between the L2s and memory.  Per
+// cell and pair of steps 24 bytes of state in, times 16/12 rows and 64/60
+// columns, 24 out and, in planes of more than one kappa, 12 of kappa in;
+// counted on 320x240x96 with 6 right-hand sides before kappa's planes: 3.2 GB
+// in and 1.4 GB out in 850 us, 5.4 TB/s, no more shared in the L2s than that.
+// On small ones the latency of a plane (4 us of a block alone on its CU, 6.5 of
+// two): nearly as many scalar as vector instructions, and a quarter to half of
+// the waves' time in waits.  Two rows a wave and eight waves keep the kernel at
+// 128 registers (16 waves per CU, two blocks).
+// Measured per step of the pair (HIP events; in brackets the two-step interior
+// with a one-step shell it replaced):
+//   600x400x120, 25 right-hand sides 5.0 ms (11.0), 6.3 ps per cell-update clear
+//   of the slabs and 8.9 in them; 430x450x64, 6: 655 us (1390); 320x240x96, 6:
+//   391 us (871); 91x103x88, 2: 27 us (142).  kappa loaded in every plane: 5.35
+//   ms, 753, 425 and 27 us.
+// Other shapes, when these stood at 5.8 ms, 463 and 32 us: 3 rows a wave 5.9 ms,
+// 562 and 48 us; 4 rows and 4 waves 6.5 ms, 536 and 35 us; 16 waves of 2 rows
+// 6.3 ms, 587 and 48 us.  At 5.8 ms, 423 and 27 us: 16 waves of one row 5.7 ms,
+// 529 and 29 us (for the clear tiles alone, or 3 rows there: 1 to 2 % of the
+// first); the next plane's operands loaded ahead of this one's stores 447 and 29
+// us (spills); streaming loads 6.9 ms, 475 and 35 us; the clear tiles' code for
+// the clear tiles of a mixed launch 431 and 27 us.
 #include "yo_device.h"
 
 namespace {

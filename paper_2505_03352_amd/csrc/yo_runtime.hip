@@ -95,7 +95,7 @@ enum {
     YO_TILE_XFULL = 128,      // x-shell strips as narrow as whole 62-cell interior strips allow
     YO_TILE_XINT = 256,       // tiles inside the x-slabs only run in the interior launch (x CPML code)
     YO_TILE_PAIRS = 512,      // the two-step region advances two steps per sweep (yo_set_time_blocking)
-    YO_TILE_OVERLAP = 1024,   // with 512: the two-step launch runs beside the first step's frame and shell
+    YO_TILE_OVERLAP = 1024,   // with 512: no effect (one launch takes the grid)
     YO_TILE_ZPAIRS = 2048,    // with 512: the z-slabs under the two-step region take two steps per launch too
     YO_TILE_PAIR6 = 4096,     // with 512: the two-step region's tiles have YO_TY2 rows (else YO_TY)
     YO_TILE_COOP_PAIRS = 8192,  // with 512: the two-step region in cooperative blocks
@@ -1818,7 +1818,7 @@ static void aux_args(yo_plan *const *plans, const int *which, int cnt, bool dft,
         a.nrhs[i] = std::max(r1 - r0, 0);
         a.npts[i] = npts;
         a.prefix[i] = tot;
-        tot += (int)(((long)npts * a.nrhs[i] + 255) / 256);
+        tot += (npts + 255) / 256 * a.nrhs[i];
     }
     a.prefix[cnt] = tot;
     a.total_blocks = tot;

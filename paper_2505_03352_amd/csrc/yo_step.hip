@@ -1,9 +1,11 @@
-// Fused Yee time step for gfx950.  Each step is two launches over every
-// selected right-hand side of every plan in the call: the interior tiles
-// (clear of every absorbing slab, no CPML code) and the CPML shell; each
-// advances its tiles by one full step (Ht half step, then E step).  Two
-// small kernels bracket them: the running DFT of E^n (design box and port
-// planes) before the step, and the soft current source after it.
+// Fused single Yee steps for gfx950 in launches by tile class, and two steps
+// over the region clear of slabs and planes: what yo_time_kernel and the tuner
+// measure, and what runs where single-step launches are timed; the stepping
+// itself is yo_pair.hip's.  A single step is two launches over every selected
+// right-hand side of every plan in the call: the interior tiles (clear of
+// every absorbing slab, no CPML code) and the CPML shell; each advances its
+// tiles by one full step (Ht half step, then E step).  The soft current source
+// follows.  Also the running DFT (design box and port planes) around the steps.
 //
 // Update (paper Sec. 2: time-harmonic sources, steady-state phasors):
 //   Ht^{n+1/2} = Ht^{n-1/2} - curl_e E^n                        (forward differences)
@@ -12,23 +14,21 @@
 // the difference d becomes d/k + psi with psi <- b psi + c d.
 //
 // Work decomposition (one wave = 64 lanes):
-//   * lane l handles x = x0 - 1 + l.  Lanes 1..xn own their cells; lane 0
-//     (x0-1) and the lane after the last owned one are halo lanes whose
-//     values reach the owners through DPP whole-wave shifts.
+//   * lane l handles x = x0 - 2 + l.  Lanes 2..xn+1 own their cells; the
+//     lanes on either side are halo lanes whose values reach the owners
+//     through DPP whole-wave shifts.
 //   * a wave owns rows j0..j0+jn-1 (jn <= 4) and recomputes the Ht of row
 //     j0-1, which the E update of row j0 needs (or, in cooperative blocks,
 //     takes it and the E row above from its neighbours through LDS).
 //   * a wave marches z-planes k0..k1-1, carrying E of the next plane and the
 //     Ht of the previous plane in registers; it starts one plane early to
 //     recompute Ht(k0-1).
-// A step reads the state buffer of step n and writes that of step n+1 (two
-// buffers, or three in rotation when the plan's interior may take two steps
-// per sweep); the Ht CPML memories are double-buffered by step parity, so a
-// halo recompute reads old values no other wave overwrites in this launch,
-// and every recomputed halo value is bitwise equal to the one its owner
-// stores (same expression, same inputs, no contraction).  Field arrays carry
-// a zero ghost layer, so every load is unconditional: indices outside the
-// grid are clamped onto the ghost layer and read zero.
+// A step reads the state buffer of step n and writes that of step n+1, and
+// likewise the slots of the CPML memories, so a halo recompute reads old values
+// no other wave overwrites in this launch, and every recomputed halo value is
+// bitwise equal to the one its owner stores (same expression, same inputs, no
+// contraction).  Every load is unconditional: rows outside the grid are ghost
+// rows, columns and planes outside it are read past the buffer; all zero.
 //
 // A CPML tile's class (bit a: it meets the absorbing slab of axis a) picks
 // an instantiation with the CPML code of exactly those axes, or the shell
@@ -908,18 +908,19 @@ __global__ __launch_bounds__(64 * YO_MAX_WPB) void k_yee_step2(const YoStepArgs 
     wave_step2<TY, ZP, false>(P, P.rhs[r], step, sl.tiles[ti], 0, wpb, lane, nullptr);
 }
 
-// locate point q of slot s in the aux work list
+// locate point q of slot s in the aux work list: whole blocks per right-hand
+// side, so that its descriptor is the block's
 __device__ __forceinline__ bool aux_point(const YoAuxArgs &a, int &s, int &r, int &q)
 {
     const int blk = blockIdx.x;
     s = 0;
     while (s + 1 < a.n_slots && blk >= a.prefix[s + 1]) ++s;
-    const long g = (long)(blk - a.prefix[s]) * blockDim.x + threadIdx.x;
-    const long per = a.npts[s];
-    if (per <= 0 || g >= per * a.nrhs[s]) return false;
-    r = a.rhs0[s] + (int)(g / per);
-    q = (int)(g % per);
-    return true;
+    const int per = (a.npts[s] + 255) / 256;
+    if (per <= 0) return false;
+    const int lb = blk - a.prefix[s], rr = lb / per;
+    r = a.rhs0[s] + rr;
+    q = (lb - rr * per) * 256 + (int)threadIdx.x;
+    return rr < a.nrhs[s] && q < a.npts[s];
 }
 
 // Component plane tt of a port or source plane (normal `axis`, cell index
@@ -984,18 +985,33 @@ __global__ __launch_bounds__(256) void k_dft(const YoAuxArgs a)
         acc = R.dft_mon + qm;
         fstride = R.mon_fstride;
     }
-    for (int f = 0; f < R.n_dft; ++f) {
-        const float4 *st = R.dfttab + (size_t)f * P.n_steps + step;
-        float2 v = acc[(size_t)f * fstride];
-        if (d0) {
-            v.x = fmaf(e, st[0].z, v.x);
-            v.y = fmaf(e, st[0].w, v.y);
+    // four frequencies' sums and phases loaded together: one after another their
+    // round trips were most of the kernel's time
+    const int nf = R.n_dft;
+    for (int f0 = 0; f0 < nf; f0 += 4) {
+        float2 v[4], p0[4], p1[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = f0 + i;
+            if (f >= nf) break;
+            const float4 *st = R.dfttab + (size_t)f * P.n_steps + step;
+            v[i] = acc[(size_t)f * fstride];
+            if (d0) p0[i] = make_float2(st[0].z, st[0].w);
+            if (d1) p1[i] = make_float2(st[1].z, st[1].w);
         }
-        if (d1) {
-            v.x = fmaf(e1, st[1].z, v.x);
-            v.y = fmaf(e1, st[1].w, v.y);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (f0 + i >= nf) break;
+            if (d0) {
+                v[i].x = fmaf(e, p0[i].x, v[i].x);
+                v[i].y = fmaf(e, p0[i].y, v[i].y);
+            }
+            if (d1) {
+                v[i].x = fmaf(e1, p1[i].x, v[i].x);
+                v[i].y = fmaf(e1, p1[i].y, v[i].y);
+            }
+            acc[(size_t)(f0 + i) * fstride] = v[i];
         }
-        acc[(size_t)f * fstride] = v;
     }
 }
 
