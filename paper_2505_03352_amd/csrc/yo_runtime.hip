@@ -1472,7 +1472,9 @@ static yo_status bind_ws(yo_plan *p, void *dev, size_t bytes, hipStream_t s)
     HIPCHK(hipStreamSynchronize(s));
     p->bg_set = false;
     p->design_set = false;
+    // the counters in the workspace are zero, and so are their host copies
     p->steps_done = 0;
+    p->flips = 0;
     for (int q = 0; q < 2; ++q) p->finalized[q] = p->unstable[q] = false;
     return YO_OK;
 }
