@@ -27,9 +27,10 @@ __global__ void k_fill(float *p, size_t n, float v)
 // that its side is whole lines; indices fit 32 bits (the library's grids have
 // under 2^31 values in three components), 64-bit divisions here cost more than
 // the copy
-__global__ void k_to_ghost(const float *src, float *dst, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
+__global__ void k_to_ghost(const float *src, const YoGhost to, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
                            unsigned nx, int ns)
 {
+    float *dst = to.F[to.now ? *to.now : 0];
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const unsigned row = i / nx, x = i - row * nx;
         const unsigned pl = row / ny, y = row - pl * ny;
@@ -38,9 +39,10 @@ __global__ void k_to_ghost(const float *src, float *dst, unsigned n, int c0, int
     }
 }
 
-__global__ void k_from_ghost(const float *src, float *dst, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
+__global__ void k_from_ghost(const YoGhost from, float *dst, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
                              unsigned nx, int ns)
 {
+    const float *src = from.F[from.now ? *from.now : 0];
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const unsigned row = i / nx, x = i - row * nx;
         const unsigned pl = row / ny, y = row - pl * ny;
@@ -672,7 +674,7 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
+hipError_t yo_launch_to_ghost(const float *dense, const YoGhost &ghost, int ncomp, int c0, int nc, int nz,
                               int ny, int nx, int ns, hipStream_t s)
 {
     const size_t n = (size_t)ncomp * nz * ny * nx;
@@ -692,7 +694,7 @@ hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, 
     return hipGetLastError();
 }
 
-hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
+hipError_t yo_launch_from_ghost(const YoGhost &ghost, float *dense, int ncomp, int c0, int nc, int nz,
                                 int ny, int nx, int ns, hipStream_t s)
 {
     const size_t n = (size_t)ncomp * nz * ny * nx;

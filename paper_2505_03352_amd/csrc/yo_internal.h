@@ -88,7 +88,9 @@ struct YoPlanD {
     YoPlaneD ports[YO_MAX_PORTS];
     int mon_off[YO_MAX_PORTS];
     int mon_total;
-    int *step_ctr;           // device counters of this plan: steps, launches that swapped its buffers
+    // device counters of this plan: steps, launches of the run that took any, and
+    // for the forward and the adjoint right-hand sides the buffer their state is in
+    int *step_ctr;
     int n_rhs;
     // component planes of a port's monitor (and of its adjoint source): 2 =
     // the tangential E on the plane; 5 = those, the normal E half a cell past
@@ -135,8 +137,18 @@ struct YoAuxArgs {
 
 struct YoCtrArgs {
     int n;
-    int add, add_b;          // steps, launches
-    int *ctr[YO_MAX_SLOTS];
+    int add;                 // steps the launches before took, or 0: a reset
+    int pairs;               // they went two per launch, an odd last one alone
+    const YoPlanD *plan[YO_MAX_SLOTS];
+    int which[YO_MAX_SLOTS]; // sides selected
+};
+
+// A ghost-layout array on one side of a copy: F[*now], of the buffers of a
+// right-hand side the one that holds its state (known on the device only, as
+// a caller may replay launches it captured), or F[0] without `now`.
+struct YoGhost {
+    float *F[3];
+    const int *now;
 };
 
 // Parametrization buffers of one plan.
@@ -198,16 +210,16 @@ hipError_t yo_launch_pair(bool shell, bool dft, int gen, const YoStepArgs &args,
 hipError_t yo_launch_one(const YoStepArgs &args, int blocks, hipStream_t s);
 hipError_t yo_launch_dft(const YoAuxArgs &args, hipStream_t s);
 hipError_t yo_launch_source(const YoAuxArgs &args, hipStream_t s);
-hipError_t yo_launch_ctr(const YoCtrArgs &args, int set_value, hipStream_t s);
+hipError_t yo_launch_ctr(const YoCtrArgs &args, hipStream_t s);
 hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s);
 // dense [ncomp][nz][ny][nx] <-> components c0 .. c0+ncomp-1 of a ghost-layout
 // array with nc components
-hipError_t yo_launch_to_ghost(const float *dense, float *ghost, int ncomp, int c0, int nc, int nz,
+hipError_t yo_launch_to_ghost(const float *dense, const YoGhost &ghost, int ncomp, int c0, int nc, int nz,
                               int ny, int nx, int ns, hipStream_t s);
 // kplane from kappa; planes k_lo .. k_hi are taken as not uniform
 hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
                             hipStream_t s);
-hipError_t yo_launch_from_ghost(const float *ghost, float *dense, int ncomp, int c0, int nc, int nz,
+hipError_t yo_launch_from_ghost(const YoGhost &ghost, float *dense, int ncomp, int c0, int nc, int nz,
                                 int ny, int nx, int ns, hipStream_t s);
 // in-place phasor fit of n complex sums; sets *bad to 1 if a result is not
 // finite (*bad is left alone otherwise)

@@ -177,7 +177,6 @@ struct yo_plan {
     bool bg_set = false, design_set = false;
     double beta = 0;
     int steps_done = 0;
-    int flips = 0;               // two buffers: launches that swapped them since the reset
     int active = 0;              // which right-hand sides the last reset selected
     // per side (0 forward, 1 adjoint): phasors fitted by a finalize since
     // the side's last reset, and non-finite ones among them (watchdog)
@@ -1472,9 +1471,7 @@ static yo_status bind_ws(yo_plan *p, void *dev, size_t bytes, hipStream_t s)
     HIPCHK(hipStreamSynchronize(s));
     p->bg_set = false;
     p->design_set = false;
-    // the counters in the workspace are zero, and so are their host copies
     p->steps_done = 0;
-    p->flips = 0;
     for (int q = 0; q < 2; ++q) p->finalized[q] = p->unstable[q] = false;
     return YO_OK;
 }
@@ -1621,7 +1618,7 @@ yo_status yo_set_background(yo_plan *p, const float *kappa, const float *mask, y
     if (yo_status st_ = ws_check(p)) return st_;
     hipStream_t s = (hipStream_t)stream;
     const yo_grid &g = p->grid;
-    HIPCHK(yo_launch_to_ghost(kappa, wsp<float>(p, p->L.kappa), 3, 0, 3, g.nz, g.ny, g.nx, p->ns, s));
+    HIPCHK(yo_launch_to_ghost(kappa, YoGhost{{wsp<float>(p, p->L.kappa)}, nullptr}, 3, 0, 3, g.nz, g.ny, g.nx, p->ns, s));
     // (yo_set_design writes the slab and its faces)
     HIPCHK(yo_launch_kplane(wsp<float>(p, p->L.kappa), wsp<float4>(p, p->L.kplane), g.nz, g.ny, g.nx, p->ns,
                             p->des.k_lo - 1, p->des.k_hi, s));
@@ -1784,11 +1781,10 @@ yo_status yo_reset(yo_plan *p, int which, yo_stream stream)
     }
     YoCtrArgs ca{};
     ca.n = 1;
-    ca.add = ca.add_b = 0;
-    ca.ctr[0] = wsp<int>(p, p->L.ctr);
-    HIPCHK(yo_launch_ctr(ca, 1, s));
+    ca.plan[0] = wsp<YoPlanD>(p, p->L.desc_plan);
+    ca.which[0] = which;
+    HIPCHK(yo_launch_ctr(ca, s));
     p->steps_done = 0;
-    p->flips = 0;
     p->active = which;
     for (int q = 0; q < 2; ++q)
         if (which & (1 << q)) {
@@ -1998,9 +1994,12 @@ static yo_status launch_steps(yo_plan *const *plans, const int *which, int n, in
         YoCtrArgs ca{};
         ca.n = cnt;
         ca.add = n_launch;
-        ca.add_b = b;
-        for (int i = 0; i < cnt; ++i) ca.ctr[i] = wsp<int>(plans[base + i], plans[base + i]->L.ctr);
-        HIPCHK(yo_launch_ctr(ca, 0, s));
+        ca.pairs = pairs;
+        for (int i = 0; i < cnt; ++i) {
+            ca.plan[i] = wsp<YoPlanD>(plans[base + i], plans[base + i]->L.desc_plan);
+            ca.which[i] = which[base + i];
+        }
+        HIPCHK(yo_launch_ctr(ca, s));
     }
     return YO_OK;
 }
@@ -2070,12 +2069,8 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
     // steps_done is advanced per chunk so chunk_needs_dft sees the current steps
     std::vector<int> start(n);
     for (int i = 0; i < n; ++i) start[i] = plans[i]->steps_done;
-    auto bump = [&](int k, bool whole) {
-        for (int i = 0; i < n; ++i) {
-            yo_plan *p = plans[i];
-            p->flips += whole ? (k + 1) / 2 : std::max(0, std::min(k, p->n_steps - p->steps_done));
-            p->steps_done += k;
-        }
+    auto bump = [&](int k) {
+        for (int i = 0; i < n; ++i) plans[i]->steps_done += k;
     };
     int done = 0;
     if (use_graph && n_steps - tail >= chunk) {
@@ -2122,7 +2117,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
             }
             HIPCHK(hipGraphLaunch(ge[variant].exec, s));
             done += chunk;
-            bump(chunk, pairs);
+            bump(chunk);
         }
     }
     while (done < n_steps) {
@@ -2139,7 +2134,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         yo_status st = launch_steps(plans, which, n, k, need_dft, s, in_tail ? timed : nullptr, every, pairs, split);
         if (st) return st;
         done += k;
-        bump(k, pairs);
+        bump(k);
     }
     for (int i = 0; i < n; ++i)
         plans[i]->steps_done = std::min(plans[i]->n_steps, start[i] + n_steps);
@@ -2458,17 +2453,23 @@ yo_status yo_get_dft(const yo_plan *p, int rhs, int region, float *out, yo_strea
     return YO_OK;
 }
 
+// the state of right-hand side `rhs`, in the buffer its side's run left it in
+static YoGhost state_of(const yo_plan *p, int rhs)
+{
+    const YoRhsD &R = p->hrhs[rhs];
+    return YoGhost{{R.F[0], R.F[1], R.F[2]}, p->hplan.step_ctr + 2 + (rhs >= p->n_pfwd)};
+}
+
 yo_status yo_set_fields(yo_plan *p, int rhs, const float *E, const float *H, yo_stream stream)
 {
     if (!p || !E || !H) return fail(YO_EINVAL, "null argument");
     if (rhs < 0 || rhs >= p->n_phys) return fail(YO_EINVAL, "rhs out of range");
     if (yo_status st_ = ws_check(p)) return st_;
     const yo_grid &g = p->grid;
-    const YoRhsD &R = p->hrhs[rhs];
-    const int par = p->nbuf == 3 ? p->steps_done % 3 : p->flips & 1;
+    const YoGhost F = state_of(p, rhs);
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_to_ghost(E, R.F[par], 3, 0, 6, g.nz, g.ny, g.nx, p->ns, s));
-    HIPCHK(yo_launch_to_ghost(H, R.F[par], 3, 3, 6, g.nz, g.ny, g.nx, p->ns, s));
+    HIPCHK(yo_launch_to_ghost(E, F, 3, 0, 6, g.nz, g.ny, g.nx, p->ns, s));
+    HIPCHK(yo_launch_to_ghost(H, F, 3, 3, 6, g.nz, g.ny, g.nx, p->ns, s));
     return YO_OK;
 }
 
@@ -2478,11 +2479,10 @@ yo_status yo_get_fields(const yo_plan *p, int rhs, float *E, float *H, yo_stream
     if (rhs < 0 || rhs >= p->n_phys) return fail(YO_EINVAL, "rhs out of range");
     if (yo_status st_ = ws_check(p)) return st_;
     const yo_grid &g = p->grid;
-    const YoRhsD &R = p->hrhs[rhs];
-    const int par = p->nbuf == 3 ? p->steps_done % 3 : p->flips & 1;
+    const YoGhost F = state_of(p, rhs);
     hipStream_t s = (hipStream_t)stream;
-    HIPCHK(yo_launch_from_ghost(R.F[par], E, 3, 0, 6, g.nz, g.ny, g.nx, p->ns, s));
-    HIPCHK(yo_launch_from_ghost(R.F[par], H, 3, 3, 6, g.nz, g.ny, g.nx, p->ns, s));
+    HIPCHK(yo_launch_from_ghost(F, E, 3, 0, 6, g.nz, g.ny, g.nx, p->ns, s));
+    HIPCHK(yo_launch_from_ghost(F, H, 3, 3, 6, g.nz, g.ny, g.nx, p->ns, s));
     return YO_OK;
 }
 
@@ -2491,7 +2491,8 @@ yo_status yo_get_kappa(const yo_plan *p, float *kappa, yo_stream stream)
     if (!p || !kappa) return fail(YO_EINVAL, "null argument");
     if (yo_status st_ = ws_check(p)) return st_;
     const yo_grid &g = p->grid;
-    HIPCHK(yo_launch_from_ghost(reinterpret_cast<const float *>(p->ws + p->L.kappa.off), kappa, 3,
+    const YoGhost K{{reinterpret_cast<float *>(p->ws + p->L.kappa.off)}, nullptr};
+    HIPCHK(yo_launch_from_ghost(K, kappa, 3,
                                 0, 3, g.nz, g.ny, g.nx, p->ns, (hipStream_t)stream));
     return YO_OK;
 }

@@ -1044,18 +1044,25 @@ __global__ __launch_bounds__(256) void k_source(const YoAuxArgs a)
     F[o] = fmaf(-P.kappa[yo_off(c, cx, cy, cz, P.ny, P.ns, 3)], j, F[o]);
 }
 
-__global__ void k_ctr(const YoCtrArgs a, int set_value)
+// The counters after the launches of a.add steps, of which those within the
+// plan's run took place, or at a reset.  Each side keeps its own buffer: the
+// number of swaps depends on how a run was cut into calls, and a side's state
+// stays where its run left it while the other side runs.
+__global__ void k_ctr(const YoCtrArgs a)
 {
     const int i = threadIdx.x;
-    if (i < a.n) {
-        if (set_value) {
-            a.ctr[i][0] = a.add;
-            a.ctr[i][1] = a.add_b;
-        } else {
-            a.ctr[i][0] += a.add;
-            a.ctr[i][1] += a.add_b;
-        }
-    }
+    if (i >= a.n) return;
+    const YoPlanD &P = *a.plan[i];
+    int *c = P.step_ctr;
+    if (!a.add) c[0] = c[1] = 0;
+    const int left = max(P.n_steps - c[0], 0);
+    const int paired = a.pairs ? a.add & ~1 : 0;
+    const int two = min(paired, left) / 2, one = clampi(left - paired, 0, a.add - paired);
+    c[0] += a.add;
+    c[1] += two + one;
+    for (int q = 0; q < 2; ++q)
+        if (a.which[i] >> q & 1)
+            c[2 + q] = !a.add ? 0 : (c[2 + q] + (P.nbuf == 3 ? 2 * two : two) + one) % P.nbuf;
 }
 
 }  // namespace
@@ -1141,8 +1148,8 @@ hipError_t yo_launch_source(const YoAuxArgs &args, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t yo_launch_ctr(const YoCtrArgs &args, int set_value, hipStream_t s)
+hipError_t yo_launch_ctr(const YoCtrArgs &args, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ctr, dim3(1), dim3(64), 0, s, args, set_value);
+    hipLaunchKernelGGL(k_ctr, dim3(1), dim3(64), 0, s, args);
     return hipGetLastError();
 }
