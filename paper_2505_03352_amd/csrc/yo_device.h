@@ -105,6 +105,13 @@ __device__ __forceinline__ unsigned array_bytes(PP P, int nc)
     return (unsigned)((P->nz * (P->ny + 1) + 1) * P->ns) * (unsigned)(64 * nc * sizeof(float));
 }
 
+// one slot of a right-hand side's CPML memories
+template <class PP>
+__device__ __forceinline__ Rsrc psi_rsrc(PP P, const float *psi, int slot)
+{
+    return rsrc_of(psi + (size_t)slot * P->psi_slot, 4u * P->psi_slot);
+}
+
 // Lane offsets past every buffer (all are below 4 GiB less 4 KiB): loads give
 // zero, stores are dropped.  Component offsets are added to it.
 constexpr int kFar = (int)0xfffff000u;

@@ -45,10 +45,10 @@ struct YoRhsD {
     // advances the state swaps, or with time blocking asked for three (nbuf), the
     // state after step s in F[s % 3]
     float *F[3];
-    // CPML memories: one slot per state buffer, of each axis four values (the
-    // two of E's components, the two of Ht's): axis a's slot q at float offset
-    // psi_off[a] + q psi_n[a]; rows of the y- and z-slabs ([nz][Wy], [Wz][ny])
-    // as the field rows' strips with nc = 4, those of the x-slabs
+    // CPML memories: one slot of psi_slot floats per state buffer, of each axis
+    // four values (the two of E's components, the two of Ht's): axis a's at
+    // float offset psi_off[a]; rows of the y- and z-slabs ([nz][Wy], [Wz][ny]) as
+    // the field rows' strips with nc = 4, those of the x-slabs
     // [side][nz][ny][4][lo], or [nz][ny][4][lo + hi] where the slabs differ
     float *psi;
     float2 *dft_box;         // [3][bz][by][bx]
@@ -76,8 +76,7 @@ struct YoPlanD {
     const float *kappa;      // ghost layout (ghosts zero)
     const float4 *kplane;    // [nz]: a plane's one kappa per component, .w 1 (0: it has no one value)
     const float4 *prof[3];   // per axis [n_a][2]: (b, c, 1/kappa, 0) at the E, then at the Ht sites
-    unsigned psi_off[3], psi_n[3];   // floats
-    unsigned psi_bytes;      // CPML memory per right-hand side
+    unsigned psi_off[3], psi_slot;   // floats
     int psi_xrow, psi_xw, psi_xside;  // x-slab rows: floats per row, per value, and to the high slab
     int box[6];              // x0 y0 z0 bx by bz
     int n_ports;

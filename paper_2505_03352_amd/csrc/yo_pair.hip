@@ -86,7 +86,7 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     const Rsrc FA = rsrc_of(R->F[now], array_bytes(P, 6));   // after step n
     const Rsrc FC = rsrc_of(R->F[nxt], array_bytes(P, 6));   // after step n+2
     const Rsrc KR = rsrc_of(P->kappa, array_bytes(P, 3));
-    const Rsrc PS = rsrc_of(R->psi, P->psi_bytes);
+    const Rsrc PS = rsrc_of(R->psi, 4u * P->nbuf * P->psi_slot);   // every slot
     const Const<float> kplane = (Const<float>)(uintptr_t)P->kplane;
     const float sx = P->sx, sy = P->sy, sz = P->sz;
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
@@ -147,9 +147,9 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
                 fl0 |= F_MON;
         }
     }
-    const unsigned zb0 = 4u * (P->psi_off[2] + now * P->psi_n[2]), zb2 = 4u * (P->psi_off[2] + nxt * P->psi_n[2]);
-    const unsigned yb0 = 4u * (P->psi_off[1] + now * P->psi_n[1]), yb2 = 4u * (P->psi_off[1] + nxt * P->psi_n[1]);
-    const unsigned xb0 = 4u * (P->psi_off[0] + now * P->psi_n[0]), xb2 = 4u * (P->psi_off[0] + nxt * P->psi_n[0]);
+    const unsigned zb0 = 4u * (P->psi_off[2] + now * P->psi_slot), zb2 = 4u * (P->psi_off[2] + nxt * P->psi_slot);
+    const unsigned yb0 = 4u * (P->psi_off[1] + now * P->psi_slot), yb2 = 4u * (P->psi_off[1] + nxt * P->psi_slot);
+    const unsigned xb0 = 4u * (P->psi_off[0] + now * P->psi_slot), xb2 = 4u * (P->psi_off[0] + nxt * P->psi_slot);
     const unsigned ypl = (unsigned)(ylo + P->phi[1]) * ps;   // a plane's y-slab rows
     const unsigned xrow = 4u * P->psi_xrow, xw = 4u * P->psi_xw;
     const float4 *profy = P->prof[1], *profz = P->prof[2];

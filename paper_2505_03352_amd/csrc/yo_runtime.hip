@@ -125,7 +125,7 @@ struct yo_plan {
     size_t row_f = 0;            // floats of one component's rows: 64 per strip
     size_t rows = 0;             // rows of an array: nz planes of ny + 1, and a last ghost
     size_t psi_per_rhs = 0;      // floats
-    size_t psi_axis_off[3] = {0, 0, 0}, psi_axis_n[3] = {0, 0, 0};   // per axis: offset, floats per slot
+    size_t psi_slot = 0, psi_axis_off[3] = {0, 0, 0};   // floats of a slot, and each axis' place in it
     int psi_xrow = 0, psi_xw = 0, psi_xside = 0;   // x-slab rows (YoPlanD)
     size_t nominal = 0;          // workspace bytes the limits of the interface count (build_layout)
     size_t bsz = 0;              // box cells
@@ -174,6 +174,7 @@ struct yo_plan {
     // n_allc of them clear of the x- and y-slabs and the planes
     int n_all = 0, n_allc = 0;
     int gen = 0;                 // the kernel their launches need (yo_launch_pair)
+    bool whole = true;           // the stepping takes them (build_layout)
     bool bg_set = false, design_set = false;
     double beta = 0;
     int steps_done = 0;
@@ -307,7 +308,7 @@ size_t morph_bytes(const yo_plan *p, size_t n, size_t t)
 }
 
 
-// CPML memories of one right-hand side: per axis one slot per state buffer.
+// CPML memories of one right-hand side: one slot per state buffer.
 void set_psi_layout(yo_plan *p)
 {
     const yo_grid &g = p->grid;
@@ -315,13 +316,12 @@ void set_psi_layout(yo_plan *p)
                          (size_t)p->plo[2] + p->phi[2]};
     const size_t slot[3] = {4 * (size_t)g.nz * g.ny * W[0], 256 * (size_t)g.nz * W[1] * p->ns,
                             256 * W[2] * g.ny * p->ns};
-    size_t off = 0;
+    p->psi_slot = 0;
     for (int a = 0; a < 3; ++a) {
-        p->psi_axis_off[a] = off;
-        p->psi_axis_n[a] = slot[a];
-        off += p->nbuf * slot[a];
+        p->psi_axis_off[a] = p->psi_slot;
+        p->psi_slot += slot[a];
     }
-    p->psi_per_rhs = off;
+    p->psi_per_rhs = p->nbuf * p->psi_slot;
     // x-slabs of one width: each side by itself, so that the rows of a tile
     // (which meets one side) are one run of memory
     const bool even = p->plo[0] == p->phi[0];
@@ -336,9 +336,14 @@ size_t mid_floats(const yo_plan *p) { return (3 * p->bsz + std::max<size_t>(p->m
 // Layout of the workspace.  The limits of the interface (2 GiB of state and of
 // CPML memories per right-hand side, the static workspace) count rows of
 // nx + 2 floats rounded up to whole lines and, with two buffers, one slot of
-// E's memories: what they admit always fits the layout's own limits (offsets
-// below 4 GiB), save for CPML memories above 1.5 GiB on grids 61 or 62 wide.
-// False when a limit is passed; *state says which.
+// E's memories: what they admit always fits the layout's own (offsets below
+// 4 GiB into a state buffer and into a slot of the memories).  Strips are at most
+// twice such a row, so a buffer stays below 2 (2 GiB), and a slot below 2 (4/6)
+// (2 GiB).  Where all slots together pass 4 GiB (y- and z-slabs of over half of
+// a grid whose rows fill half of their strips), the plan is stepped by the
+// launches by tile class, whose kernels take a slot at a time: a second buffer
+// resource in the whole-grid kernels cost every plan registers (the one-step
+// kernel 104 to 128 and a spill).  False when a limit is passed; *state says which.
 bool build_layout(yo_plan *p, bool *state = nullptr)
 {
     const yo_grid &g = p->grid;
@@ -354,7 +359,8 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
     const size_t lim = (size_t)1 << 31, own = 0xfffff000u;
     const bool st = 6 * cells * sizeof(float) < lim && 6 * p->rows * p->row_f * sizeof(float) < own;
     if (state) *state = !st;
-    if (!st || psi * sizeof(float) >= lim || p->psi_per_rhs * sizeof(float) >= own) return false;
+    if (!st || psi * sizeof(float) >= lim || p->psi_slot * sizeof(float) >= own) return false;
+    p->whole = p->psi_per_rhs * sizeof(float) < own;
     build_regions(p);
     p->nominal = p->L.total;
     p->nominal -= align256(p->L.fields.bytes) + align256(p->L.kappa.bytes) + align256(p->L.psi.bytes) +
@@ -1187,11 +1193,8 @@ static yo_status rebuild_descriptors(yo_plan *p)
     P.prof[1] = prof + 2 * (size_t)g.nx;
     P.prof[2] = prof + 2 * (size_t)(g.nx + g.ny);
     for (int i = 0; i < 6; ++i) P.box[i] = p->box[i];
-    for (int a = 0; a < 3; ++a) {
-        P.psi_off[a] = (unsigned)p->psi_axis_off[a];
-        P.psi_n[a] = (unsigned)p->psi_axis_n[a];
-    }
-    P.psi_bytes = (unsigned)(p->psi_per_rhs * sizeof(float));
+    for (int a = 0; a < 3; ++a) P.psi_off[a] = (unsigned)p->psi_axis_off[a];
+    P.psi_slot = (unsigned)p->psi_slot;
     P.psi_xrow = p->psi_xrow;
     P.psi_xw = p->psi_xw;
     P.psi_xside = p->psi_xside;
@@ -2014,6 +2017,14 @@ static bool pairs_ok(yo_plan *const *plans, int n, int n_launch)
     return true;
 }
 
+// do whole-grid launches take every plan of the list?
+static bool whole_ok(yo_plan *const *plans, int n)
+{
+    for (int i = 0; i < n; ++i)
+        if (!plans[i]->whole) return false;
+    return true;
+}
+
 // The DFT stride every plan of the list samples, when they share one and all
 // stand at a step it divides (then the DFT kernel need only be launched on
 // every stride-th step of a call); else 1.
@@ -2073,6 +2084,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         for (int i = 0; i < n; ++i) plans[i]->steps_done += k;
     };
     int done = 0;
+    const bool whole = whole_ok(plans, n);
     if (use_graph && n_steps - tail >= chunk) {
         std::string key = "c" + std::to_string(chunk);
         for (int i = 0; i < n; ++i)
@@ -2087,7 +2099,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         GraphEntry ge[4];
         while (n_steps - tail - done >= chunk) {
             const bool need_dft = chunk_needs_dft(plans, which, n, chunk);
-            const bool pairs = pairs_ok(plans, n, chunk);
+            const bool pairs = whole && pairs_ok(plans, n, chunk);
             const int variant = (need_dft ? 1 : 0) | (pairs ? 2 : 0);
             const std::string kv = key + (need_dft ? "|dft" : "|nodft") + (pairs ? "|pairs" : "");
             if (!ge[variant].exec) {
@@ -2100,7 +2112,7 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
                 if (!p0->cap_stream) HIPCHK(hipStreamCreateWithFlags(&p0->cap_stream, hipStreamNonBlocking));
                 HIPCHK(hipStreamBeginCapture(p0->cap_stream, hipStreamCaptureModeThreadLocal));
                 yo_status st = launch_steps(plans, which, n, chunk, need_dft, p0->cap_stream, nullptr,
-                                            every, pairs);
+                                            every, pairs, !whole);
                 hipGraph_t graph = nullptr;
                 hipError_t e = hipStreamEndCapture(p0->cap_stream, &graph);
                 if (st) {
@@ -2128,8 +2140,8 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         const int every = dft_every(plans, n);
         // single-step launches that are to be timed are run, but in plans whose
         // split asks for pairs
-        const bool split = in_tail && timed && timed->tm_part < 2 &&
-                           !(timed->tsteps == 2 && (timed->tflags & YO_TILE_PAIRS));
+        const bool split = !whole || (in_tail && timed && timed->tm_part < 2 &&
+                                      !(timed->tsteps == 2 && (timed->tflags & YO_TILE_PAIRS)));
         const bool pairs = !split && pairs_ok(plans, n, k);
         yo_status st = launch_steps(plans, which, n, k, need_dft, s, in_tail ? timed : nullptr, every, pairs, split);
         if (st) return st;
@@ -2413,7 +2425,7 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
     const double steps = (cls == 2 || cls == 4 || cls >= 6) ? 2.0 : 1.0;
     *bytes = steps * (own * (48.0 * R + 12.0) + 32.0 * R * in_pml);
     *cells = steps * own * R;
-    if (!blocks || r1 <= r0) {
+    if (!blocks || r1 <= r0 || (cls >= 6 && !p->whole)) {
         *avg_ms = 0.0f;
         *bytes = *cells = 0.0;
         return YO_OK;

@@ -49,9 +49,9 @@ namespace {
 struct CpmlCtx {
     int ny, nz, ns;
     int plo[3], phi[3], W[3];
-    unsigned so[3], sn[3];   // each axis' slots read and written, bytes
+    unsigned so[3];          // each axis' memories in a slot, bytes
     int xrow, xw;            // x-slab rows: bytes per row and per value
-    Rsrc ps;                 // this right-hand side's CPML memories
+    Rsrc po, pn;             // this right-hand side's CPML memories, the slots read and written
     Cpml cyE, cyH;           // lane l: row j0 - 1 + l
     Cpml czE, czH;           // lane l: plane k0 - 1 + l
     int j0m, k0m;            // j0 - 1, k0 - 1
@@ -93,12 +93,12 @@ __device__ __forceinline__ void psi_pair(const CpmlCtx &C, int v, int j, int k, 
     const int vl = A == 0 ? L.px : L.xp + 256 * v, st = A == 0 ? C.xw : 256;
     const unsigned ov = A == 0 ? o + v * C.xw : o;
     float n0, n1;
-    d0 = pml_diff(d0, c, PRE ? q[0] : bload(C.ps, vl, C.so[A] + ov), n0);
-    d1 = pml_diff(d1, c, PRE ? q[1] : bload(C.ps, vl, C.so[A] + ov + st), n1);
+    d0 = pml_diff(d0, c, PRE ? q[0] : bload(C.po, vl, C.so[A] + ov), n0);
+    d1 = pml_diff(d1, c, PRE ? q[1] : bload(C.po, vl, C.so[A] + ov + st), n1);
     if (store) {
         const int vs = A == 0 ? L.px : L.xps + 256 * v;
-        bstore(n0, C.ps, vs, C.sn[A] + ov);
-        bstore(n1, C.ps, vs, C.sn[A] + ov + st);
+        bstore(n0, C.pn, vs, C.so[A] + ov);
+        bstore(n1, C.pn, vs, C.so[A] + ov + st);
     }
 }
 
@@ -116,10 +116,8 @@ __device__ __forceinline__ void h_cpml(const CpmlCtx &C, int j, int k, const Lan
         psi_pair<2, PRE>(C, 2, j, k, L, lane_cpml(C.czH, k - C.k0m), own_row && L.st, q[2], dzEy, dzEx);
 }
 
-// CPML corrections of the six differences of one owned E site row (each E
-// memory is read and written by its owner only: one slot, read and written
-// in place, or with three state buffers the slot of the step read and the
-// next one written).  PRE as for h_cpml.
+// CPML corrections of the six differences of one owned E site row, from the
+// slot of the state read to that of the state written.  PRE as for h_cpml.
 template <int PM, bool PRE>
 __device__ __forceinline__ void e_cpml(const CpmlCtx &C, int j, int k, const LaneX &L, const Cpml &cxE,
                                        const float (&q)[3][2], float &dxHz, float &dxHy, float &dyHz,
@@ -148,8 +146,8 @@ __device__ __forceinline__ void psi_preload(const CpmlCtx &C, int v, int j, int 
         in = in && use;
         const int vl = !in ? kFar : a == 0 ? (L.px >= 0 ? L.px : kFar) : L.xp + 256 * v;
         const unsigned so = in ? C.so[a] + o + (a == 0 ? v * C.xw : 0) : 0u, st = !in ? 0u : a == 0 ? C.xw : 256u;
-        out[a][0] = bload(C.ps, vl, so);
-        out[a][1] = bload(C.ps, vl, so + st);
+        out[a][0] = bload(C.po, vl, so);
+        out[a][1] = bload(C.po, vl, so + st);
     }
 }
 
@@ -220,12 +218,12 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
             C.plo[a] = P.plo[a];
             C.phi[a] = P.phi[a];
             C.W[a] = P.plo[a] + P.phi[a];
-            C.so[a] = 4u * (P.psi_off[a] + now * P.psi_n[a]);
-            C.sn[a] = 4u * (P.psi_off[a] + nxt * P.psi_n[a]);
+            C.so[a] = 4u * P.psi_off[a];
         }
         C.xrow = P.psi_xrow * 4;
         C.xw = P.psi_xw * 4;
-        C.ps = rsrc_of(R.psi, P.psi_bytes);
+        C.po = psi_rsrc(&P, R.psi, now);
+        C.pn = psi_rsrc(&P, R.psi, nxt);
         C.j0m = j0 - 1;
         C.k0m = k0 - 1;
         const Cpml one = {1.0f, 0.0f, 1.0f};
@@ -585,13 +583,13 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
     // R2's outermost layer, whose step-n+1 state the tiles around R2 read
     const int ra0 = P.r2[0], ra1 = P.r2[1], rb0 = P.r2[2], rb1 = P.r2[3], rc0 = P.r2[4], rc1 = P.r2[5];
     const bool rim_x = own_x && (x == ra0 || x == ra1 - 1);
-    // z-axis CPML memories (ZP): byte offsets of slot q's memories at row j
-    // of slab plane pz
+    // z-axis CPML memories (ZP): the slots of the three states, and byte offsets
+    // of the memories at row j of slab plane pz
     const int zlo = P.plo[2], zhi = P.phi[2];
-    const Rsrc PS = rsrc_of(R.psi, P.psi_bytes);
-    const int s0 = step % 3, s1 = (step + 1) % 3, s2 = (step + 2) % 3;
-    auto zo = [&](int q, int pz, int j) -> unsigned {   // slot q
-        return 4u * (P.psi_off[2] + q * P.psi_n[2]) + (unsigned)((pz * ny + j) * P.ns) * 1024u;
+    const Rsrc P0 = psi_rsrc(&P, R.psi, step % 3), P1 = psi_rsrc(&P, R.psi, (step + 1) % 3),
+               P2 = psi_rsrc(&P, R.psi, (step + 2) % 3);
+    auto zo = [&](int pz, int j) -> unsigned {
+        return 4u * P.psi_off[2] + (unsigned)((pz * ny + j) * P.ns) * 1024u;
     };
     auto ro = [&](int j, int k) -> unsigned {
         return (unsigned)(clampi(k, 0, nz - 1) * rows + (clampi(j, -1, ny) + 1)) * gs;
@@ -711,9 +709,9 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
             const float dyEx = Ec[0][r + 1] - Ec[0][r];
             float dzEy_ = dzEy, dzEx_ = dzEx;
             if (ZP && pz >= 0) {
-                const unsigned o = zo(s0, pz, j0 - 2 + r);
-                dzEy_ = pml_diff(dzEy, czH, bload(PS, L.xp + 512, o), qH1[0][r]);                       // Hx
-                dzEx_ = pml_diff(dzEx, czH, bload(PS, L.xp + 768, o), qH1[1][r]);   // Hy
+                const unsigned o = zo(pz, j0 - 2 + r);
+                dzEy_ = pml_diff(dzEy, czH, bload(P0, L.xp + 512, o), qH1[0][r]);                       // Hx
+                dzEx_ = pml_diff(dzEx, czH, bload(P0, L.xp + 768, o), qH1[1][r]);   // Hy
             }
             Hh[0][r] = Ho[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
             Hh[1][r] = Ho[1][r] - fmaf(sz, dzEx_, -(sx * dxEz));
@@ -737,9 +735,9 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                 const float dyHx = Hh[0][r] - Hh[0][r - 1];
                 float dzHy_ = dzHy, dzHx_ = dzHx;
                 if (ZP && pz >= 0) {
-                    const unsigned o = zo(s0, pz, j);
-                    dzHy_ = pml_diff(dzHy, czE, bload(PS, L.xp, o), qE1[0][r]);                       // Ex
-                    dzHx_ = pml_diff(dzHx, czE, bload(PS, L.xp + 256, o), qE1[1][r]);   // Ey
+                    const unsigned o = zo(pz, j);
+                    dzHy_ = pml_diff(dzHy, czE, bload(P0, L.xp, o), qE1[0][r]);                       // Ex
+                    dzHx_ = pml_diff(dzHx, czE, bload(P0, L.xp + 256, o), qE1[1][r]);   // Ey
                 }
                 float ex = fmaf(Kc[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), Ec[0][r]);
                 float ey = fmaf(Kc[1][r], fmaf(sz, dzHx_, -(sx * dxHz)), Ec[1][r]);
@@ -762,8 +760,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     bstore_nt(Hh[1][r], FB, xs_ + 1024, o);
                     bstore_nt(Hh[2][r], FB, xs_ + 1280, o);
                     if (ZP && pz >= 0) {
-                        bstore(qH1[0][r], PS, L.xps + 512, zo(s1, pz, j));
-                        bstore(qH1[1][r], PS, L.xps + 768, zo(s1, pz, j));
+                        bstore(qH1[0][r], P1, L.xps + 512, zo(pz, j));
+                        bstore(qH1[1][r], P1, L.xps + 768, zo(pz, j));
                     }
                 }
             }
@@ -788,8 +786,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                     dzEx_ = pml_diff(dzEx, czHp, qH1p[1][r], n1);   // Hy
                     if (st_x && r >= 2 && r - 2 < jn && km >= k0 && km < k1) {
                         const int j = j0 - 2 + r;
-                        bstore(n0, PS, L.xps + 512, zo(s2, pzp, j));
-                        bstore(n1, PS, L.xps + 768, zo(s2, pzp, j));
+                        bstore(n0, P2, L.xps + 512, zo(pzp, j));
+                        bstore(n1, P2, L.xps + 768, zo(pzp, j));
                     }
                 }
                 H2[0][r] = Hhp[0][r] - fmaf(sy, dyEz, -(sz * dzEy_));
@@ -816,8 +814,8 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
                         dzHy_ = pml_diff(dzHy, czEp, qE1p[0][r], n0);   // Ex
                         dzHx_ = pml_diff(dzHx, czEp, qE1p[1][r], n1);   // Ey
                         if (st_x) {
-                            bstore(n0, PS, L.xps, zo(s2, pzp, j));
-                            bstore(n1, PS, L.xps + 256, zo(s2, pzp, j));
+                            bstore(n0, P2, L.xps, zo(pzp, j));
+                            bstore(n1, P2, L.xps + 256, zo(pzp, j));
                         }
                     }
                     float ex = fmaf(Kp[0][r], fmaf(sy, dyHz, -(sz * dzHy_)), E1p[0][r]);
