@@ -101,7 +101,9 @@ struct YoPlanD {
 // A tile is one wave's work (or, in the cooperative layout, one block's):
 // owned x in [x0, x0+xn) (xn <= 60), rows [j0, j0+jn) (jn <= YO_TY, or
 // YO_TY * waves per block), planes [k0, k1).  Packed as int4
-// (x0 | xn << 16, j0 | jn << 16, k0 | k1 << 16, tile class).
+// (x0 | xn << 16, j0 | jn << 16, k0 | k1 << 16, tile class); k1 may need all of
+// its 16 bits.
+__host__ __device__ inline int yo_high(int v) { return (int)((unsigned)v >> 16); }
 struct YoSlot {
     const YoPlanD *plan;
     const int4 *tiles;       // tile list of this launch's class

@@ -91,7 +91,7 @@ __device__ __forceinline__ void wave_pair(const Const<YoPlanD> P, const Const<Yo
     const float sx = P->sx, sy = P->sy, sz = P->sz;
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
     const int J0 = t.y & 0xffff, JN = t.y >> 16;
-    const int k0 = t.z & 0xffff, k1 = t.z >> 16;
+    const int k0 = t.z & 0xffff, k1 = yo_high(t.z);
     const int jb = J0 - 2 + w * TY;        // this wave's first row
     LaneX L = lane_x(P, x0, xn, lane);
     const int xl = L.xl, xk = L.xk, xp = L.xp;

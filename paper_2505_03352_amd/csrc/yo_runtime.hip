@@ -2372,7 +2372,7 @@ yo_status yo_tile_table(const yo_plan *p, int part, int *out, int cap, int *n)
         o[2] = tt.y & 0xffff;
         o[3] = o[2] + (tt.y >> 16);
         o[4] = tt.z & 0xffff;
-        o[5] = tt.z >> 16;
+        o[5] = yo_high(tt.z);
         o[6] = tt.w;
         if (part >= 6) {
             o[4] = zc * (nz / nzc) + std::min(zc, nz % nzc);
@@ -2407,7 +2407,7 @@ yo_status yo_time_kernel(yo_plan *p, int cls, int n_launch, float *avg_ms, doubl
         const int4 tt = p->tiles_host[t];
         const int x0 = tt.x & 0xffff, x1 = x0 + (tt.x >> 16);
         const int y0 = tt.y & 0xffff, y1 = y0 + (tt.y >> 16);
-        const int z0 = tt.z & 0xffff, z1 = tt.z >> 16;
+        const int z0 = tt.z & 0xffff, z1 = yo_high(tt.z);
         own += (double)(x1 - x0) * (y1 - y0) * (z1 - z0);
         if (tt.w) {
             for (int z = z0; z < z1; ++z)

@@ -178,7 +178,7 @@ __device__ __forceinline__ void wave_step(const YoPlanD &P, const YoRhsD &R, con
 
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
     const int J0 = t.y & 0xffff, JN = t.y >> 16;
-    const int k0 = t.z & 0xffff, k1 = t.z >> 16;
+    const int k0 = t.z & 0xffff, k1 = yo_high(t.z);
     const int j0 = COOP ? J0 + w * TY : J0;
     const int jn = COOP ? clampi(JN - w * TY, 0, TY) : JN;
     const bool bottom = !COOP || w == 0;
@@ -560,7 +560,7 @@ __device__ __forceinline__ void wave_step2(const YoPlanD &P, const YoRhsD &R, co
 
     const int x0 = t.x & 0xffff, xn = t.x >> 16;
     const int J0 = t.y & 0xffff, JN = t.y >> 16;
-    const int k0 = t.z & 0xffff, k1 = t.z >> 16;
+    const int k0 = t.z & 0xffff, k1 = yo_high(t.z);
     const int j0 = COOP ? J0 + w * TY : J0;
     const int jn = COOP ? clampi(JN - w * TY, 0, TY) : JN;
     const bool bottom = !COOP || w == 0;

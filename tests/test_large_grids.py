@@ -40,8 +40,29 @@ def test_cpml_memories_below_the_stated_limit_are_taken(nx, ny, nz, npml, tb):
     assert e.value.status == _abi.YO_EUNSUPPORTED
 
 
+# planes past 2^15, in strips of both kinds of tile (with and without slabs in x
+# and y) and in one that is narrower
+TALL = [(64, 8, 40000, (0, 0, 0, 0, 5, 5)), (20, 30, 33000, (3, 3, 4, 4, 0, 6))]
+
+
+@pytest.mark.parametrize("nx,ny,nz,npml", TALL)
+@pytest.mark.parametrize("tb,flags", [(1, 0), (2, 512), (2, 512 | 2048 | 128)])
+def test_tiles_of_a_tall_grid_own_every_cell_once(nx, ny, nz, npml, tb, flags):
+    p = _plan(nx, ny, nz, npml, tb=tb)
+    p.set_tiling(4, 40, flags)
+    for parts in ((0, 1), (2, 3, 4, 5), (6, 7)):
+        t = np.concatenate([p.tile_table(q) for q in parts])
+        if parts[0] == 2 and not len(p.tile_table(2)):
+            continue
+        cov = np.zeros((nz, ny, nx), np.int8)
+        for x0, x1, y0, y1, z0, z1, _ in t:
+            cov[z0:z1, y0:y1, x0:x1] += 1
+        assert cov.min() == 1 and cov.max() == 1, parts
+    p.close()
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("nx,ny,nz,npml", [WIDE_SLABS])
+@pytest.mark.parametrize("nx,ny,nz,npml", [WIDE_SLABS] + TALL)
 def test_a_tall_grid_steps_as_a_short_one(nx, ny, nz, npml):
     """Random fields in the lowest or highest 60 planes, bitwise those of a grid
     of 120 planes after 16 steps (which carry them 32 planes at most)."""
