@@ -434,9 +434,9 @@ yo_status yo_adam_step(float *dev_C, const float *dev_G, float *dev_M, float *de
  * yo_run or yo_advance_many (with this plan first in its list) runs its
  * last n_last steps with plain launches and records a pair of HIP events on
  * its stream around each launch of `part` (0 interior tiles, 1 CPML shell:
- * those steps then go one at a time in launches by class, but in plans whose
- * tiling asks for pairs (512); 2 every launch of the stepping as it is: parts 6
- * and 7 of yo_time_kernel); the pairs accumulate over calls until
+ * those steps then go one at a time in launches by class; 2 every launch of the
+ * stepping as it is: parts 6 and 7 of yo_time_kernel, and the parts that the
+ * stepping does not launch record none); the pairs accumulate over calls until
  * the next yo_set_timing with n_last > 0, which clears them.  n_last = 0
  * turns it off and keeps what was recorded.  n_last <= 4096; the events
  * are created as needed (outside graph capture: the timed steps are never

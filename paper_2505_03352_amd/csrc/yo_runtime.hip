@@ -2138,10 +2138,8 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n, int n_
         const int k = std::min(chunk, lim);
         const bool need_dft = chunk_needs_dft(plans, which, n, k);
         const int every = dft_every(plans, n);
-        // single-step launches that are to be timed are run, but in plans whose
-        // split asks for pairs
-        const bool split = !whole || (in_tail && timed && timed->tm_part < 2 &&
-                                      !(timed->tsteps == 2 && (timed->tflags & YO_TILE_PAIRS)));
+        // single-step launches that are to be timed are run
+        const bool split = !whole || (in_tail && timed->tm_part < 2);
         const bool pairs = !split && pairs_ok(plans, n, k);
         yo_status st = launch_steps(plans, which, n, k, need_dft, s, in_tail ? timed : nullptr, every, pairs, split);
         if (st) return st;
