@@ -88,3 +88,19 @@ def _check(name, tb, tiling, part):
 @pytest.mark.parametrize("flags", [512, 512 | 128, 512 | 256 | 1 | 64, 512 | 2048 | 128 | 8, 512 | 8192 | 4096 | 2])
 def test_single_step_launches_are_timed_in_plans_that_ask_for_pairs(name, flags, part):
     _check(name, 2, (4, 10, flags), part)
+
+
+# every interior choice (16 cooperative, 32 no prefetch) and shell choice (4
+# cooperative, 8 code by class, 64 no prefetch, 16384 six rows) with the cuts
+# along x (1, 128, 256), waves per block (2) and chunk lengths from 4 to 63
+VARIANTS = [(16, 0), (8, 1), (4, 2), (48, 3), (16, 4), (16, 13), (8, 70), (4, 23), (16, 45), (8, 122), (16, 77), (8, 53),
+            (16, 16384 | 73), (10, 16384 | 2), (16, 128), (16, 201), (8, 178), (16, 129), (4, 232), (16, 329), (16, 456),
+            (8, 256), (16, 304), (63, 256 | 16 | 2), (5, 256 | 48 | 4 | 8), (7, 16 | 32 | 4 | 64 | 2), (10, 4 | 8 | 64),
+            (10, 8 | 64), (16, 16384 | 8), (8, 16384 | 64 | 2), (4, 16384 | 8 | 64 | 1)]
+
+
+@pytest.mark.parametrize("tb", [1, 2])
+@pytest.mark.parametrize("zc,flags", VARIANTS)
+@pytest.mark.parametrize("name", sorted(GRIDS))
+def test_every_single_step_variant_gives_the_whole_grid_fields(name, zc, flags, tb):
+    _check(name, tb, (4, zc, flags), 1)
