@@ -104,3 +104,50 @@ VARIANTS = [(16, 0), (8, 1), (4, 2), (48, 3), (16, 4), (16, 13), (8, 70), (4, 23
 @pytest.mark.parametrize("name", sorted(GRIDS))
 def test_every_single_step_variant_gives_the_whole_grid_fields(name, zc, flags, tb):
     _check(name, tb, (4, zc, flags), 1)
+
+
+def _buffers(p):
+    """The state buffers of right-hand side 0 as the library lays them out:
+    [buffer][strip of 60 cells: 64 floats of each of 6 components], rows of
+    planes of ny + 1 from row -1 on."""
+    nx, ny, nz = (p.grid[k] for k in ("nx", "ny", "nz"))
+    ns = -(-nx // 60)
+    rows = nz * (ny + 1) + 1
+    off = (-p.workspace.data_ptr()) % 256
+    raw = p.workspace[off:off + 3 * rows * ns * 6 * 64 * 4].view(torch.float32).cpu().numpy()
+    raw = raw.reshape(3, rows, ns, 6, 64)[:, 1:].reshape(3, nz, ny + 1, ns, 6, 64)[:, :, :ny, :, :, 2:62]
+    return raw.transpose(0, 4, 1, 2, 3, 5).reshape(3, 6, nz, ny, ns * 60)[..., :nx]
+
+
+@pytest.mark.parametrize("start", [3, 4])
+@pytest.mark.parametrize("zc,flags", [(16, 512), (5, 512 | 2), (10, 512 | 4096), (8, 512 | 8192 | 2),
+                                      (10, 512 | 8192 | 4096), (10, 512 | 2048 | 128), (4, 512 | 2048 | 128 | 2)])
+@pytest.mark.parametrize("name", sorted(GRIDS))
+def test_two_step_launches_of_the_regions_write_the_state_two_steps_on(name, zc, flags, start):
+    """Launch parts 2 and 4 (timed, not stepped): each of their cells in the
+    buffer two steps on, and the two-step region's outermost layer in the next."""
+    print(f"[gpu] two-step region {name} tiling=(4,{zc},{flags}) after step {start}", flush=True)
+    p = _plan(name, 2, (4, zc, flags))
+    p.advance(3, start)
+    parts = [q for q in (2, 4) if len(p.tile_table(q))]
+    assert 2 in parts
+    for q in parts:
+        assert p.time_kernel(q, 1)[0] > 0
+    torch.cuda.synchronize()
+    got = _buffers(p)
+    want = {}
+    for n in (1, 2):
+        p.advance(3, 1)
+        want[n] = torch.cat(p.get_fields(0)).cpu().numpy()
+    tiles = {q: p.tile_table(q) for q in parts}
+    p.close()
+    lo = [tiles[2][:, 2 * a].min() for a in range(3)]
+    hi = [tiles[2][:, 2 * a + 1].max() for a in range(3)]
+    for q in parts:
+        for x0, x1, y0, y1, z0, z1, _ in tiles[q]:
+            box = np.s_[:, z0:z1, y0:y1, x0:x1]
+            assert np.array_equal(got[(start + 2) % 3][box], want[2][box])
+    box = np.s_[:, lo[2]:hi[2], lo[1]:hi[1], lo[0]:hi[0]]
+    rim = np.ones([hi[a] - lo[a] for a in (2, 1, 0)], bool)
+    rim[1:-1, 1:-1, 1:-1] = False
+    assert np.array_equal(got[(start + 1) % 3][box][:, rim], want[1][box][:, rim])
