@@ -1,8 +1,13 @@
 """Autotuner for the work split of the launches by tile class.
 
-(The stepping's own launches take whole-grid tiles, two steps each, and choose
-their split by themselves; the tuner times them beside the rest.)  A step in
-launches by class is two, the interior tiles and the CPML shell; their
+The stepping's own launches take whole-grid tiles, two steps each, and choose
+their split by themselves.  The tuner's choice shapes the launches by tile class:
+those of steps that are timed by class (``Plan.set_timing``), of
+``Plan.time_kernel``, and of the plans whose CPML memories no whole-grid launch
+reaches.  A record's ``ms_per_step`` is what a step of a solve takes, whatever
+the split, and ``split_ms`` what it takes in launches by class.
+
+A step in launches by class is two, the interior tiles and the CPML shell; their
 layout choices are independent except for what the two share (z-planes per
 tile, waves per block, how the x-shell strips are cut).  For
 each shared setting the tuner times every interior choice (cooperative
@@ -16,9 +21,8 @@ plans of the same class reuse the choice.  For a plan with time blocking it
 also times two steps per launch (the two-step region's launch, with flag
 2048 the z-slabs' two-step launch, the interior around them and the shell of
 the paired steps, each with its own best choice) and keeps that when it is
-faster per step; with two steps per launch chosen, it then times whole
-steps with flag 1024 and without and keeps the faster.  Every split gives bitwise the same fields, so tuning only
-changes speed.
+faster per step.  (Flag 1024 has no effect and is never set.)  Every split gives
+bitwise the same fields, so tuning only changes speed.
 
 `tuned_splits.json` beside this file ships splits the tuner chose on an
 MI355X for the benchmark devices, keyed the same way; `tune(...,
@@ -37,9 +41,8 @@ import torch
 from ._abi import YO_BOTH
 
 ROWS = 4
-# shared settings: (z-planes per tile, flags from {1: full 62-cell x-shell strips,
-# 128: x-shell strips sized so the interior strips are whole, 2: 8 waves per
-# block}).  10 planes split the 79 planes between the z-slabs of a 96-plane
+# shared settings: (z-planes per tile, flags from {1, 128: x-shell cuts, see
+# yo_set_tiling; 2: 8 waves per block}).  10 planes split the 79 planes between the z-slabs of a 96-plane
 # grid with an 8-cell CPML into 8 tiles instead of 5: more, shorter tiles,
 # 0.950 against 0.969 ms per step for 16 on the 320x240x96 device.  (Flag 256, the x-slab tiles in the interior launch,
 # measured 6-10 % slower per step there and is left out of the sweep.)
@@ -121,22 +124,6 @@ def _time(plan, zc, flags, part, which, n_launch, stream) -> float:
     return ms
 
 
-def _time_steps(plan, zc, flags, which, n_steps, stream) -> float:
-    """ms per step of `n_steps` whole steps as plain launches (HIP events
-    on the plan's stream)."""
-    from .plan import advance_many
-    plan.set_tiling(ROWS, zc, flags)
-    plan.reset(which, stream)
-    advance_many([plan], [which], 2, chunk=2, use_graph=False, stream=stream)   # warm-up
-    s = torch.cuda.current_stream() if stream is None else stream
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record(s)
-    advance_many([plan], [which], n_steps, chunk=n_steps, use_graph=False, stream=stream)
-    e1.record(s)
-    e1.synchronize()
-    return e0.elapsed_time(e1) / n_steps
-
-
 def tune(plan, which: int = YO_BOTH, shared: Optional[Iterable] = None, n_launch: int = 5,
          use_cache: bool = True, stream=None, pair_shared: Optional[Iterable] = None,
          shipped: bool = False) -> dict:
@@ -155,12 +142,19 @@ def tune(plan, which: int = YO_BOTH, shared: Optional[Iterable] = None, n_launch
     if use_cache:
         with _lock:
             rec = _load().get(key)
-        if rec:
+        if rec and "split_ms" in rec:     # (without it ms_per_step is the split's)
             plan.set_tiling(rec["rows"], rec["zchunk"], rec.get("flags", 0))
             plan.reset(which, stream)
             return dict(rec, cached=True)
     nz = plan.grid["nz"]
+    # what a step of a solve takes: half of the whole-grid launches of two
+    # (zero where the plan has none)
+    step = 0.5 * sum(_time(plan, 16, 0, part, which, n_launch, stream) for part in (6, 7)) if plan.n_steps >= 2 else 0.0
     timings = {}
+
+    def note(name, split_ms, flags, **launches):
+        timings[name] = dict(launches, best=flags, split_ms=round(split_ms, 4), ms=round(step or split_ms, 4))
+
     best = None
     for zc, base in (shared or SHARED):
         if zc > nz and zc != 8:
@@ -171,66 +165,51 @@ def tune(plan, which: int = YO_BOTH, shared: Optional[Iterable] = None, n_launch
         fs = min(ts, key=ts.get)
         total = ti[fi] + ts[fs]
         flags = base | fi | fs
-        timings[f"z{zc}f{base}"] = dict(interior={str(k): round(v, 4) for k, v in ti.items()},
-                                        shell={str(k): round(v, 4) for k, v in ts.items()},
-                                        best=flags, ms=round(total, 4))
+        note(f"z{zc}f{base}", total, flags, interior={str(k): round(v, 4) for k, v in ti.items()},
+             shell={str(k): round(v, 4) for k, v in ts.items()})
         if best is None or total < best[0]:
             best = (total, zc, flags)
-    total, zc, flags = best
     if getattr(plan, "time_blocking", 1) == 2 and plan.n_steps >= 2:
         # two steps per launch over the two-step region: per step, half the
         # two-step launch, the interior around it and the shell (one launch
         # each per step), each with its own best choice; kept when it beats
         # the best single-step split
-        for zc2, base in (pair_shared or PAIR_SHARED):
-            if zc2 > nz and zc2 != 8:
+        for zc, base in (pair_shared or PAIR_SHARED):
+            if zc > nz and zc != 8:
                 continue
             fl0 = base | 512
-            t2 = _time(plan, zc2, fl0, 2, which, n_launch, stream)
+            t2 = _time(plan, zc, fl0, 2, which, n_launch, stream)
             if t2 <= 0.0:
                 break               # no two-step region on this grid
             # 6-row two-step tiles (flag 4096) and cooperative two-step
             # blocks (8192) where that launch runs faster
             for v in (4096, 8192, 4096 | 8192):
-                t2b = _time(plan, zc2, (base | 512) | v, 2, which, n_launch, stream)
+                t2b = _time(plan, zc, (base | 512) | v, 2, which, n_launch, stream)
                 if t2b < t2:
                     fl0, t2 = (base | 512) | v, t2b
             # the z-slabs' two-step launch (0: none, without 2048 or where
             # planes cut the region) and the shell of the paired steps
-            t4 = _time(plan, zc2, fl0, 4, which, n_launch, stream)
-            tf = {f: _time(plan, zc2, fl0 | f, 3, which, n_launch, stream) for f in (0, 32)}
-            ts = {f: _time(plan, zc2, fl0 | f, 5, which, n_launch, stream) for f in SHELL_FLAGS}
+            t4 = _time(plan, zc, fl0, 4, which, n_launch, stream)
+            tf = {f: _time(plan, zc, fl0 | f, 3, which, n_launch, stream) for f in (0, 32)}
+            ts = {f: _time(plan, zc, fl0 | f, 5, which, n_launch, stream) for f in SHELL_FLAGS}
             ff = min(tf, key=tf.get)
             fs = min(ts, key=ts.get)
-            per_step = 0.5 * (t2 + t4) + tf[ff] + ts[fs]
-            # plans whose pairs cover the whole grid in their own launches
-            # (parts 6 and 7) run those whatever the split of the others
-            tw = sum(_time(plan, zc2, fl0, part, which, n_launch, stream) for part in (6, 7))
-            if tw > 0.0:
-                per_step = 0.5 * tw
-            fl = fl0 | ff | fs
-            timings[f"pairs_z{zc2}f{base}"] = dict(two_step=round(t2, 4), zslab_two_step=round(t4, 4),
-                                                   frame={str(k): round(v, 4) for k, v in tf.items()},
-                                                   shell={str(k): round(v, 4) for k, v in ts.items()},
-                                                   whole_grid=round(tw, 4), best=fl, ms=round(per_step, 4))
-            if per_step < total:
-                total, zc, flags = per_step, zc2, fl
-    overlap = None
-    n_ov = 4 * n_launch
-    if flags & 512 and plan.n_steps >= n_ov + 2:
-        # the two-step launch beside the first step's frame and shell: the
-        # parts' separate timings cannot tell, so whole steps are timed
-        t_one = _time_steps(plan, zc, flags, which, n_ov, stream)
-        t_two = _time_steps(plan, zc, flags | 1024, which, n_ov, stream)
-        overlap = dict(one_stream=round(t_one, 4), two_streams=round(t_two, 4))
-        if t_two < 0.99 * t_one:
-            flags |= 1024
-            total *= t_two / t_one
+            total = 0.5 * (t2 + t4) + tf[ff] + ts[fs]
+            flags = fl0 | ff | fs
+            note(f"pairs_z{zc}f{base}", total, flags, two_step=round(t2, 4), zslab_two_step=round(t4, 4),
+                 frame={str(k): round(v, 4) for k, v in tf.items()},
+                 shell={str(k): round(v, 4) for k, v in ts.items()})
+            if total < best[0]:
+                best = (total, zc, flags)
+    total, zc, flags = best
+    # fastest split first
+    timings = dict(sorted(timings.items(), key=lambda t: (t[1]["best"] != flags, t[1]["split_ms"])))
     plan.set_tiling(ROWS, zc, flags)
     plan.reset(which, stream)
-    rec = dict(rows=ROWS, zchunk=zc, flags=flags, ms_per_step=total, timings=timings)
-    if overlap:
-        rec["overlap"] = overlap
+    rec = dict(rows=ROWS, zchunk=zc, flags=flags, ms_per_step=step or total, split_ms=total, timings=timings)
+    if flags & 512:
+        # (the same launches whether or not flag 1024 asks for a second stream)
+        rec["overlap"] = dict(one_stream=rec["ms_per_step"], two_streams=rec["ms_per_step"])
     if use_cache:
         with _lock:
             d = _load()
