@@ -34,6 +34,8 @@ KERNEL_SOURCES = ["paper_2505_03352_amd/csrc/" + f for f in ("yo_step.hip", "yo_
 PROFILES = os.path.join(ROOT, "profiles")
 PART_NAMES = ("interior", "shell", "two_step", "frame", "zslab_two_step", "shell_paired",
               "whole_pair", "whole_pair_shell")
+# steps that one read and one write of a part's cells take
+PART_STEPS = (1, 1, 2, 1, 2, 1, 2, 2)
 
 
 def log(*a):
@@ -276,20 +278,23 @@ KERNEL_OF_PART = ("k_yee_step interior tiles", "k_yee_step CPML shell tiles",
 
 def part_rooflines(plan, timed, tiling, workload, sha):
     """Per launch part that ran in the timed region: HIP-event duration, the
-    part's algorithmic bytes per launch (the two-step launch counts both of
-    its steps), the share of the timed kernels' time, and the committed
+    bytes one launch must move (its cells read once and written once, also where
+    that takes two steps; `one_step_bytes_per_launch` is what its steps would move
+    one at a time), the share of the timed kernels' time, and the committed
     counter figure when it belongs to this kernel and split."""
     out = []
     total = sum(ms * n for ms, n in timed)
     for part, (ms, n) in enumerate(timed):
         if n == 0:
             continue
-        _, b, cells = plan.time_kernel(part, 1)
+        _, one_step, cells = plan.time_kernel(part, 1)
+        b = one_step / PART_STEPS[part]
         ach = b / (ms / 1e3) / 1e9 if ms > 0 else 0.0
         out.append({"kernel": KERNEL_OF_PART[part], "part": PART_NAMES[part],
                     "ms_per_launch": round(ms, 4), "launches_timed": n,
                     "time_share": round(ms * n / total, 4) if total > 0 else None,
-                    "bytes_per_launch": b, "cell_updates_per_launch": cells,
+                    "bytes_per_launch": b, "one_step_bytes_per_launch": one_step,
+                    "cell_updates_per_launch": cells,
                     "achieved": round(ach, 1), "frac": round(ach / HBM_PEAK_GBS, 4),
                     "traffic": read_traffic(traffic_file(part, workload), sha,
                                             part_split(tiling, part))})
@@ -453,7 +458,8 @@ def bench_headline(args):
     log(f"whole gradient {s_grad:.2f} s ({3600.0 / s_grad:.1f}/h); |alpha| "
         f"{np.round(alpha.ravel(), 4).tolist()}")
     bytes_model, _ = plan.model_bytes(YO_BOTH)
-    eff_gbs = bytes_model * block / (ms / 1e3) / 1e9
+    # the block's steps go two per read and write of the state
+    eff_gbs = bytes_model * block / 2 / (ms / 1e3) / 1e9
     plan.reset(YO_BOTH)
     plan.advance(YO_BOTH, 4)
     sha = kernel_sha()
