@@ -331,6 +331,7 @@ void set_psi_layout(yo_plan *p)
 }
 
 void build_regions(yo_plan *p);
+size_t nominal_bytes(const yo_plan *p, size_t cells, size_t psi);
 size_t mid_floats(const yo_plan *p) { return (3 * p->bsz + std::max<size_t>(p->mon_total, 1) + 63) & ~(size_t)63; }
 
 // Layout of the workspace.  The limits of the interface (2 GiB of state and of
@@ -362,11 +363,7 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
     if (!st || psi * sizeof(float) >= lim || p->psi_slot * sizeof(float) >= own) return false;
     p->whole = p->psi_per_rhs * sizeof(float) < own;
     build_regions(p);
-    p->nominal = p->L.total;
-    p->nominal -= align256(p->L.fields.bytes) + align256(p->L.kappa.bytes) + align256(p->L.psi.bytes) +
-                  align256(p->L.dft_mid.bytes) + align256(p->L.kplane.bytes) +
-                  sizeof(float) * (p->tapt_x.size() + p->tapt_y.size() + (size_t)(p->S * p->des.md) * p->des.nc);
-    p->nominal += align256(24 * p->nbuf * cells * p->n_phys) + align256(12 * cells) + align256(4 * psi * p->n_phys);
+    p->nominal = nominal_bytes(p, cells, psi);
     return true;
 }
 
@@ -404,6 +401,33 @@ void build_regions(yo_plan *p)
     const size_t ni = 2 * (size_t)p->S * (d.md + d.nd) + 2 * (size_t)(d.mc + d.nc);
     L.add(L.chain_i, sizeof(int) * (ni + 64 * 8));     // each of 6 tables padded to 64 ints
     L.add(L.morph, p->morph_ops.empty() ? 0 : morph_bytes(p, p->morph_ops.size(), p->n_mtaps));
+}
+
+// What the static workspace's limit counts a plan with (floats of a component and
+// of the CPML memories as above): a measure of its own, so that the plans it
+// admits do not change with the layout.  Beside the regions that both have: 24
+// bytes of CPML profile per cell of an axis, descriptors of 432 and 144 bytes,
+// tiles of 62 columns, 4 rows and 4 planes (three tables with two steps per
+// launch asked for), and the parametrization's buffers without the tables and
+// halves of passes that came later.
+size_t nominal_bytes(const yo_plan *p, size_t cells, size_t psi)
+{
+    const yo_design &d = p->des;
+    const yo_grid &g = p->grid;
+    const Layout &L = p->L;
+    const size_t G = (size_t)p->G0 * p->G1, UV = (size_t)p->U * p->V;
+    const size_t DD = (size_t)(p->S * d.md) * (p->S * d.nd);
+    const size_t tiles = (size_t)(g.nx / 62 + 4) * (g.ny / 4 + 4) * (g.nz / 4 + 4) * (p->tsteps == 2 ? 3 : 1);
+    size_t total = 0;
+    for (const size_t bytes : {24 * p->nbuf * cells * p->n_phys, 12 * cells, 4 * psi * p->n_phys, L.dft_box.bytes,
+                               L.dft_mon.bytes, L.src_j.bytes, L.port_w.bytes, L.steptab.bytes,
+                               (size_t)24 * (g.nx + g.ny + g.nz), (size_t)432, (size_t)144 * p->n_phys, L.ctr.bytes,
+                               sizeof(int4) * tiles,
+                               sizeof(float) * (2 * UV + 2 * DD + 31 * G + (size_t)(p->S * d.nd) * d.mc +
+                                                (size_t)p->tmax * p->S * (d.md + d.nd) + 64 * 16),
+                               L.chain_i.bytes, L.morph.bytes})
+        total += align256(bytes);
+    return total;
 }
 
 void build_steptab(yo_plan *p)
