@@ -139,24 +139,29 @@ __global__ void k_alpha(const YoAlphaArgs a)
 // sub-pixel column (shared by the S nd / nc times 2r sub-pixel rows that read
 // it: one pass over the controls per sub-pixel took 17 us at 400x400
 // sub-pixels and r = 3, the two passes 8 together).
-__global__ void k_filter_x(YoChainBufs c, const float *C)
+__device__ __forceinline__ float filter_x(const YoChainBufs &c, const float *C, int b, int ud)
 {
-    const int nud = c.S * c.md;
-    const int i = blockIdx.x * BS + threadIdx.x;
-    if (i >= c.nc * nud) return;
-    const int b = i / nud, ud = i - b * nud;
     const int xlo = c.tap_lo_x[ud], xn = c.tap_n_x[ud];
     float row = 0.0f;
     for (int tx = 0; tx < xn; ++tx) {
         const int a = clampi(xlo + tx, 0, c.mc - 1);
         row = fmaf(c.tap_w_x[ud * c.tmax + tx], C[b * c.mc + a], row);
     }
-    c.tmp[i] = row;
+    return row;
+}
+
+__global__ void k_filter_x(YoChainBufs c, const float *C)
+{
+    const int nud = c.S * c.md;
+    const int i = blockIdx.x * BS + threadIdx.x;
+    if (i >= c.nc * nud) return;
+    const int b = i / nud;
+    c.tmp[i] = filter_x(c, C, b, i - b * nud);
 }
 
 // Then along y and the tanh projection Eq. (3)/(6) into the canvas `out`,
-// whose margin takes the background fill.
-__global__ void k_project(YoChainBufs c, float beta, float *out)
+// whose margin takes the background fill.  C: no control rows in tmp.
+__global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
 {
     const int n = c.U * c.V;
     const int i = blockIdx.x * BS + threadIdx.x;
@@ -171,7 +176,7 @@ __global__ void k_project(YoChainBufs c, float beta, float *out)
     float phi = 0.0f;
     for (int ty = 0; ty < yn; ++ty) {
         const int b = clampi(ylo + ty, 0, c.nc - 1);
-        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], c.tmp[b * nud + ud], phi);
+        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], C ? filter_x(c, C, b, ud) : c.tmp[b * nud + ud], phi);
     }
     phi -= 0.5f;
     const float t = tanhf(beta * phi);
@@ -733,8 +738,10 @@ hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float b
 {
     const size_t UV = (size_t)c.U * c.V;
     const size_t DD = (size_t)c.S * c.md * c.S * c.nd;
-    hipLaunchKernelGGL(k_filter_x, dim3(nblk((size_t)c.nc * c.S * c.md)), dim3(BS), 0, s, c, C);
-    hipLaunchKernelGGL(k_project, dim3(nblk(UV)), dim3(BS), 0, s, c, beta, c.n_morph ? c.mcan : c.rho);
+    const bool rows = yo_filter_by_rows(c.nc, c.S * c.nd);
+    if (rows) hipLaunchKernelGGL(k_filter_x, dim3(nblk((size_t)c.nc * c.S * c.md)), dim3(BS), 0, s, c, C);
+    hipLaunchKernelGGL(k_project, dim3(nblk(UV)), dim3(BS), 0, s, c, rows ? (const float *)nullptr : C, beta,
+                       c.n_morph ? c.mcan : c.rho);
     for (int k = 0; k < c.n_morph; ++k)
         hipLaunchKernelGGL(k_morph, morph_grid(c.U, c.V), dim3(BS), morph_lds(c), s, c, c.mcan + k * UV, c.mcan + (k + 1) * UV,
                            c.msum + k * DD, (int)((c.mdil >> k) & 1u));

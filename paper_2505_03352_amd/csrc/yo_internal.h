@@ -173,7 +173,7 @@ struct YoChainBufs {
     float *gG;        // [4][G1][G0]: gGx_x gGy_x gGx_y gGy_y
     float *gR;        // [2][G1][G0]
     float *gphi;      // [S nd][S md]
-    float *tmp;       // [S nd][mc], or forward [nc][S md]
+    float *tmp;       // [S nd][mc], or forward [nc][S md] (yo_filter_by_rows)
     // morphological filters (n_morph = 0: none; rho = the Eq. (3) projection)
     int n_morph;      // stages
     unsigned mdil;    // bit k set: stage k dilates, else erodes
@@ -187,6 +187,11 @@ struct YoChainBufs {
     float *tanh2;     // [S nd][S md]: tanh of the projection after the stages
     float *mg;        // [2][S nd][S md]: gradients between stages
 };
+
+// Is the filter's x pass made once for each control row?  Not where there are
+// more of those than sub-pixel rows that could share them: each sub-pixel then
+// filters its own, and no rows are kept.
+inline bool yo_filter_by_rows(int nc, int nvd) { return nc <= nvd; }
 
 // ---- kernel launchers ----
 // pm: 0 = interior tiles (no CPML code), 1 = interior tiles plus tiles inside

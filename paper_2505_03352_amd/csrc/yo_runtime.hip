@@ -367,6 +367,14 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
     return true;
 }
 
+// rows of one filter pass, back or forward
+size_t tmp_floats(const yo_plan *p)
+{
+    const yo_design &d = p->des;
+    const size_t rows = yo_filter_by_rows(d.nc, p->S * d.nd) ? d.nc : 0;
+    return std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * rows);
+}
+
 // Workspace regions (fields, CPML memories and descriptors per stepped
 // right-hand side; DFT results per output right-hand side).
 void build_regions(yo_plan *p)
@@ -395,7 +403,7 @@ void build_regions(yo_plan *p)
     const size_t UV = (size_t)p->U * p->V;
     const size_t DD = (size_t)(p->S * d.md) * (p->S * d.nd);
     const size_t nf = 2 * UV + DD /*tanh*/ + 9 * G + 6 * G + 6 * G + 4 * G + 2 * G + DD /*gphi*/ +
-                      std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * d.nc) /*tmp*/ +
+                      tmp_floats(p) +
                       (size_t)p->tmax * p->S * (d.md + d.nd) + p->tapt_x.size() + p->tapt_y.size();
     L.add(L.chain_f, sizeof(float) * (nf + 64 * 17));   // each of 16 buffers padded to 64 floats
     const size_t ni = 2 * (size_t)p->S * (d.md + d.nd) + 2 * (size_t)(d.mc + d.nc);
@@ -1333,7 +1341,7 @@ static yo_status set_chain_ptrs(yo_plan *p)
     c.gG = take(4 * G);
     c.gR = take(2 * G);
     c.gphi = take(DD);
-    c.tmp = take(std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * d.nc));
+    c.tmp = take(tmp_floats(p));
     c.tap_w_x = take((size_t)p->tmax * p->S * d.md);
     c.tap_w_y = take((size_t)p->tmax * p->S * d.nd);
     c.tapt_x = take(p->tapt_x.size());
