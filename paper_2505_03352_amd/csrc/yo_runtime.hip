@@ -548,12 +548,10 @@ void transpose_taps(int n_ctl, int tmax, const std::vector<int> &lo, const std::
     int rmax = 1;
     for (int a = 0; a < n_ctl; ++a) rmax = std::max(rmax, range[2 * a + 1] - range[2 * a] + 1);
     out.assign((size_t)n_ctl * rmax, 0.0f);
-    for (int a = 0; a < n_ctl; ++a)
-        for (int u = range[2 * a]; u <= range[2 * a + 1]; ++u) {
-            float v = 0.0f;
-            for (int t = 0; t < cnt[u]; ++t)
-                if (std::min(std::max(lo[u] + t, 0), n_ctl - 1) == a) v += w[(size_t)u * tmax + t];
-            out[(size_t)(u - range[2 * a]) * n_ctl + a] = v;
+    for (int u = 0; u < (int)cnt.size(); ++u)
+        for (int t = 0; t < cnt[u]; ++t) {
+            const int a = std::min(std::max(lo[u] + t, 0), n_ctl - 1);
+            out[(size_t)(u - range[2 * a]) * n_ctl + a] += w[(size_t)u * tmax + t];
         }
 }
 
