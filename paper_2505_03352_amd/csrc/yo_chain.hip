@@ -138,7 +138,7 @@ __global__ void k_alpha(const YoAlphaArgs a)
 // control indices).  First along x: tmp[b][ud], a control row at each
 // sub-pixel column (shared by the S nd / nc times 2r sub-pixel rows that read
 // it: one pass over the controls per sub-pixel took 17 us at 400x400
-// sub-pixels and r = 3, the two passes 8 together).
+// sub-pixels and r = 3, the two passes 8 together; yo_filter_by_rows says where).
 __device__ __forceinline__ float filter_x(const YoChainBufs &c, const float *C, int b, int ud)
 {
     const int xlo = c.tap_lo_x[ud], xn = c.tap_n_x[ud];
@@ -160,7 +160,9 @@ __global__ void k_filter_x(YoChainBufs c, const float *C)
 }
 
 // Then along y and the tanh projection Eq. (3)/(6) into the canvas `out`,
-// whose margin takes the background fill.  C: no control rows in tmp.
+// whose margin takes the background fill.  Rows: x is done (tmp), else C's rows
+// are filtered here.
+template <bool Rows>
 __global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
 {
     const int n = c.U * c.V;
@@ -176,7 +178,7 @@ __global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
     float phi = 0.0f;
     for (int ty = 0; ty < yn; ++ty) {
         const int b = clampi(ylo + ty, 0, c.nc - 1);
-        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], C ? filter_x(c, C, b, ud) : c.tmp[b * nud + ud], phi);
+        phi = fmaf(c.tap_w_y[vd * c.tmax + ty], Rows ? c.tmp[b * nud + ud] : filter_x(c, C, b, ud), phi);
     }
     phi -= 0.5f;
     const float t = tanhf(beta * phi);
@@ -738,10 +740,13 @@ hipError_t yo_launch_chain_forward(const YoChainBufs &c, const float *C, float b
 {
     const size_t UV = (size_t)c.U * c.V;
     const size_t DD = (size_t)c.S * c.md * c.S * c.nd;
-    const bool rows = yo_filter_by_rows(c.nc, c.S * c.nd);
-    if (rows) hipLaunchKernelGGL(k_filter_x, dim3(nblk((size_t)c.nc * c.S * c.md)), dim3(BS), 0, s, c, C);
-    hipLaunchKernelGGL(k_project, dim3(nblk(UV)), dim3(BS), 0, s, c, rows ? (const float *)nullptr : C, beta,
-                       c.n_morph ? c.mcan : c.rho);
+    float *rho = c.n_morph ? c.mcan : c.rho;
+    if (yo_filter_by_rows(c.nc, c.S * c.md, c.S * c.nd, c.tmax)) {
+        hipLaunchKernelGGL(k_filter_x, dim3(nblk((size_t)c.nc * c.S * c.md)), dim3(BS), 0, s, c, C);
+        hipLaunchKernelGGL(k_project<true>, dim3(nblk(UV)), dim3(BS), 0, s, c, C, beta, rho);
+    } else {
+        hipLaunchKernelGGL(k_project<false>, dim3(nblk(UV)), dim3(BS), 0, s, c, C, beta, rho);
+    }
     for (int k = 0; k < c.n_morph; ++k)
         hipLaunchKernelGGL(k_morph, morph_grid(c.U, c.V), dim3(BS), morph_lds(c), s, c, c.mcan + k * UV, c.mcan + (k + 1) * UV,
                            c.msum + k * DD, (int)((c.mdil >> k) & 1u));

@@ -188,10 +188,17 @@ struct YoChainBufs {
     float *mg;        // [2][S nd][S md]: gradients between stages
 };
 
-// Is the filter's x pass made once for each control row?  Not where there are
-// more of those than sub-pixel rows that could share them: each sub-pixel then
-// filters its own, and no rows are kept.
-inline bool yo_filter_by_rows(int nc, int nvd) { return nc <= nvd; }
+// Is the filter's x pass made once for each control row, in a launch of its own?
+// Not where there are more of those than sub-pixel rows that could share them:
+// each sub-pixel then filters its own, and no rows are kept.  Nor where a
+// sub-pixel has few taps: of a radius up to 2 (tmax 6) the launch costs more than
+// it saves below some 700x700 sub-pixels (yo_set_design whole, one pass and two:
+// 96x96 at radius 1.5 12.5 and 16.0 us, at 3 17.0 and 15.7; 600x600 at 2 17.9 and
+// 18.4; 1200x1200 at 1.5 32.0 and 29.8).
+inline bool yo_filter_by_rows(int nc, int nud, int nvd, int tmax)
+{
+    return nc <= nvd && (tmax > 6 || (size_t)nud * nvd >= (size_t)1 << 19);
+}
 
 // ---- kernel launchers ----
 // pm: 0 = interior tiles (no CPML code), 1 = interior tiles plus tiles inside

@@ -371,7 +371,7 @@ bool build_layout(yo_plan *p, bool *state = nullptr)
 size_t tmp_floats(const yo_plan *p)
 {
     const yo_design &d = p->des;
-    const size_t rows = yo_filter_by_rows(d.nc, p->S * d.nd) ? d.nc : 0;
+    const size_t rows = yo_filter_by_rows(d.nc, p->S * d.md, p->S * d.nd, p->tmax) ? d.nc : 0;
     return std::max((size_t)(p->S * d.nd) * d.mc, (size_t)(p->S * d.md) * rows);
 }
 
