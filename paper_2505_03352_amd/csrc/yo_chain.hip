@@ -4,6 +4,8 @@
 // All of this is 2-D or plane-sized work next to the 3-D time stepping; the
 // kernels are plain one-thread-per-output gathers (no atomics, fixed
 // summation order, so results do not depend on scheduling).
+#include <type_traits>
+
 #include "yo_internal.h"
 
 namespace {
@@ -194,6 +196,9 @@ __global__ void k_project(YoChainBufs c, const float *C, float beta, float *out)
 // taken once each, not once per tap: at a radius of 10 (317 taps) and 416x416
 // sub-pixels a stage took 80 us (its transpose 75) with both done per tap.
 // Rows of odd pitch keep the four rows a wave reads in different banks.
+// Small discs wait for single reads: with the rows of one and three taps in loops
+// and one tile value in flight at a time four stages of 13 taps took 43.4 us with
+// the rest of yo_set_design (a thread and an exponential per tap: 38.6), now 38.4.
 constexpr int MTX = 64, MTY = 16;
 template <bool mirror>
 __device__ __forceinline__ void disc_sums(const float *tile, int R, const int *wid, int lx, int ly, float (&acc)[4])
@@ -207,20 +212,27 @@ __device__ __forceinline__ void disc_sums(const float *tile, int R, const int *w
         // the 2w + 4 values of the row under the four discs, in the taps' order
         const int dir = mirror ? -1 : 1;
         const float *x = row + (mirror ? w + 3 : -w);
-        auto tap = [&](int j, int i) {            // value j of the row, disc i
+        auto tap = [&](int j, int i, int n) {     // value j of the row, disc i; n values a disc
             const int d = mirror ? 3 - i : i;
-            if (j >= d && j - d <= 2 * w) acc[i] += x[dir * j];
+            if (j >= d && j - d < n) acc[i] += x[dir * j];
+        };
+        // (rows too short for the shared middle, at lengths the compiler knows: their
+        // reads are in flight together)
+        auto few = [&](auto n) {
+#pragma unroll
+            for (int j = 0; j < n() + 3; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tap(j, i, n());
         };
         if (w < 2) {
-            for (int j = 0; j < 2 * w + 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) tap(j, i);
+            if (w) few(std::integral_constant<int, 3>());
+            else few(std::integral_constant<int, 1>());
             continue;
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) tap(j, i);
+            for (int i = 0; i < 4; ++i) tap(j, i, 5);
 #pragma unroll 4
         for (int j = 3; j <= 2 * w; ++j) {
             const float v = x[dir * j];
@@ -251,6 +263,7 @@ __global__ __launch_bounds__(BS) void k_morph(YoChainBufs c, const float *in, fl
     const int u0 = blockIdx.x * MTX, v0 = blockIdx.y * MTY;
     const float a = c.malpha;
     for (int i = threadIdx.x; i < 2 * R + 1; i += BS) wid[i] = c.mwid[i];
+#pragma unroll 4
     for (int i = threadIdx.x; i < pitch * (MTY + 2 * R); i += BS) {
         const int ty = i / pitch, tx = i - ty * pitch;
         const float r = in[clampi(v0 + ty - R, 0, c.V - 1) * c.U + clampi(u0 + tx - R, 0, c.U - 1)];
@@ -566,6 +579,7 @@ __global__ __launch_bounds__(BS) void k_morph_vjp(YoChainBufs c, const float *g_
     const int R = c.mrad, pitch = (MTX + 2 * R) | 1;
     const int u0 = blockIdx.x * MTX, v0 = blockIdx.y * MTY;
     for (int i = threadIdx.x; i < 2 * R + 1; i += BS) wid[i] = c.mwid[i];
+#pragma unroll 4
     for (int i = threadIdx.x; i < pitch * (MTY + 2 * R); i += BS) {
         const int ty = i / pitch, tx = i - ty * pitch;
         const int vq = v0 + ty - R, uq = u0 + tx - R;
