@@ -1487,16 +1487,26 @@ static yo_status bind_ws(yo_plan *p, void *dev, size_t bytes, hipStream_t s)
     if ((st = upload(p, p->L.steptab, p->steptab.data(), p->steptab.size() * sizeof(float4), s))) return st;
     if ((st = upload(p, p->L.tiles, p->tiles_host.data(), p->tiles_host.size() * sizeof(int4), s))) return st;
     const YoChainBufs &c = p->chain;
-    if ((st = upload_to(c.tap_lo_x, p->tap_lo_x.data(), p->tap_lo_x.size() * 4, s))) return st;
-    if ((st = upload_to(c.tap_n_x, p->tap_n_x.data(), p->tap_n_x.size() * 4, s))) return st;
-    if ((st = upload_to(c.tap_lo_y, p->tap_lo_y.data(), p->tap_lo_y.size() * 4, s))) return st;
-    if ((st = upload_to(c.tap_n_y, p->tap_n_y.data(), p->tap_n_y.size() * 4, s))) return st;
-    if ((st = upload_to(c.urange_x, p->urange_x.data(), p->urange_x.size() * 4, s))) return st;
-    if ((st = upload_to(c.urange_y, p->urange_y.data(), p->urange_y.size() * 4, s))) return st;
-    if ((st = upload_to(c.tap_w_x, p->tap_w_x.data(), p->tap_w_x.size() * 4, s))) return st;
-    if ((st = upload_to(c.tap_w_y, p->tap_w_y.data(), p->tap_w_y.size() * 4, s))) return st;
-    if ((st = upload_to(c.tapt_x, p->tapt_x.data(), p->tapt_x.size() * 4, s))) return st;
-    if ((st = upload_to(c.tapt_y, p->tapt_y.data(), p->tapt_y.size() * 4, s))) return st;
+    // the filter's tables lie side by side: one copy for each kind, as a copy costs
+    // some 20 us whatever its size
+    std::vector<float> fl;
+    std::vector<int> in;
+    auto put = [](auto &to, const auto *base, const auto *at, const auto &v) {
+        to.resize(at - base + v.size());
+        std::copy(v.begin(), v.end(), to.begin() + (at - base));
+    };
+    put(fl, c.tap_w_x, c.tap_w_x, p->tap_w_x);
+    put(fl, c.tap_w_x, c.tap_w_y, p->tap_w_y);
+    put(fl, c.tap_w_x, c.tapt_x, p->tapt_x);
+    put(fl, c.tap_w_x, c.tapt_y, p->tapt_y);
+    put(in, c.tap_lo_x, c.tap_lo_x, p->tap_lo_x);
+    put(in, c.tap_lo_x, c.tap_n_x, p->tap_n_x);
+    put(in, c.tap_lo_x, c.tap_lo_y, p->tap_lo_y);
+    put(in, c.tap_lo_x, c.tap_n_y, p->tap_n_y);
+    put(in, c.tap_lo_x, c.urange_x, p->urange_x);
+    put(in, c.tap_lo_x, c.urange_y, p->urange_y);
+    if ((st = upload_to(c.tap_w_x, fl.data(), fl.size() * 4, s))) return st;
+    if ((st = upload_to(c.tap_lo_x, in.data(), in.size() * 4, s))) return st;
     if (c.n_morph && (st = upload_to(c.mwid, p->mwid.data(), p->mwid.size() * 4, s))) return st;
     if ((st = upload_desc(p, s))) return st;
     // copies from pageable host memory are staged; make them complete before
