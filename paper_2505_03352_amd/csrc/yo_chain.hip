@@ -4,6 +4,7 @@
 // All of this is 2-D or plane-sized work next to the 3-D time stepping; the
 // kernels are plain one-thread-per-output gathers (no atomics, fixed
 // summation order, so results do not depend on scheduling).
+#include <algorithm>
 #include <type_traits>
 
 #include "yo_internal.h"
@@ -28,9 +29,11 @@ __global__ void k_fill(float *p, size_t n, float v)
 // components (interior only; ghosts untouched).  Flat over the dense array, so
 // that its side is whole lines; indices fit 32 bits (the library's grids have
 // under 2^31 values in three components), 64-bit divisions here cost more than
-// the copy
+// the copy.  Plane: of kappa, also each plane's first cell, and a mark that k_kplane
+// clears.
+template <bool Plane>
 __global__ void k_to_ghost(const float *src, const YoGhost to, unsigned n, int c0, int nc, unsigned nz, unsigned ny,
-                           unsigned nx, int ns)
+                           unsigned nx, int ns, float4 *kplane)
 {
     float *dst = to.F[to.now ? *to.now : 0];
     for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
@@ -38,6 +41,11 @@ __global__ void k_to_ghost(const float *src, const YoGhost to, unsigned n, int c
         const unsigned pl = row / ny, y = row - pl * ny;
         const unsigned q = pl / nz, z = pl - q * nz;
         dst[yo_off(c0 + (int)q, (int)x, (int)y, (int)z, (int)ny, ns, nc)] = src[i];
+        if (Plane && !x && !y) {
+            float *e = reinterpret_cast<float *>(kplane + z);
+            e[q] = src[i];
+            if (!q) e[3] = 1.0f;
+        }
     }
 }
 
@@ -53,23 +61,22 @@ __global__ void k_from_ghost(const YoGhost from, float *dst, unsigned n, int c0,
     }
 }
 
-// Which planes hold one value per component: each plane's first cell, then
-// blocks that compare its cells with it bit by bit, a wave per row, strips
-// (yo_col) side by side, a lane a column, and clear the plane's mark where one
-// differs.  (600x400x120: 400 us with one block a plane.)
-__global__ void k_kplane_first(const float *kappa, float4 *kplane, int nz, int ny, int ns, int k_lo, int k_hi)
-{
-    const int k = blockIdx.x * BS + threadIdx.x;
-    if (k >= nz) return;
-    const float *v = kappa + yo_off(0, 0, 0, k, ny, ns, 3);
-    kplane[k] = make_float4(v[0], v[64], v[128], k >= k_lo && k <= k_hi ? 0.0f : 1.0f);
-}
-
+// Which planes hold one value per component: blocks that compare a plane's cells
+// with its first bit by bit, a wave per row, strips (yo_col) side by side, a lane
+// a column, and clear the plane's mark where one differs.  (600x400x120: 400 us
+// with one block a plane.)  The canvas' mask is copied on the way (two launches
+// fewer: 13 us of yo_set_background on 30x26x18 cells, not 18).
 __global__ __launch_bounds__(BS) void k_kplane(const float *kappa, float4 *kplane, int ny, int nx, int ns, int k_lo,
-                                               int k_hi)
+                                               int k_hi, const float *mask, float *mask_out, size_t n)
 {
+    for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * BS + threadIdx.x; i < n;
+         i += (size_t)gridDim.x * gridDim.y * BS)
+        mask_out[i] = mask[i];
     const int k = blockIdx.x, lane = threadIdx.x & 63;
-    if (k >= k_lo && k <= k_hi) return;
+    if (k >= k_lo && k <= k_hi) {
+        if (!blockIdx.y && !threadIdx.x) kplane[k].w = 0.0f;
+        return;
+    }
     const float *v = kappa + yo_off(0, 0, 0, k, ny, ns, 3);
     const unsigned first[3] = {__float_as_uint(v[0]), __float_as_uint(v[64]), __float_as_uint(v[128])};
     bool differs = false;
@@ -702,16 +709,19 @@ hipError_t yo_launch_to_ghost(const float *dense, const YoGhost &ghost, int ncom
     if (!n) return hipSuccess;
     int blocks = nblk(n);
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(k_to_ghost, dim3(blocks), dim3(BS), 0, s, dense, ghost, (unsigned)n, c0, nc,
-                       (unsigned)nz, (unsigned)ny, (unsigned)nx, ns);
+    hipLaunchKernelGGL(k_to_ghost<false>, dim3(blocks), dim3(BS), 0, s, dense, ghost, (unsigned)n, c0, nc,
+                       (unsigned)nz, (unsigned)ny, (unsigned)nx, ns, (float4 *)nullptr);
     return hipGetLastError();
 }
 
-hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
-                            hipStream_t s)
+hipError_t yo_launch_background(const float *dense, float *kappa, float4 *kplane, int nz, int ny, int nx, int ns,
+                                int k_lo, int k_hi, const float *mask, float *mask_out, size_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_kplane_first, dim3(nblk(nz)), dim3(BS), 0, s, kappa, kplane, nz, ny, ns, k_lo, k_hi);
-    hipLaunchKernelGGL(k_kplane, dim3(nz, 16), dim3(BS), 0, s, kappa, kplane, ny, nx, ns, k_lo, k_hi);
+    const size_t m = (size_t)3 * nz * ny * nx;
+    hipLaunchKernelGGL(k_to_ghost<true>, dim3(std::min(nblk(m), 65536)), dim3(BS), 0, s, dense, YoGhost{{kappa}, nullptr},
+                       (unsigned)m, 0, 3, (unsigned)nz, (unsigned)ny, (unsigned)nx, ns, kplane);
+    hipLaunchKernelGGL(k_kplane, dim3(nz, 16), dim3(BS), 0, s, (const float *)kappa, kplane, ny, nx, ns, k_lo, k_hi, mask,
+                       mask_out, n);
     return hipGetLastError();
 }
 

@@ -229,9 +229,10 @@ hipError_t yo_launch_fill(float *p, size_t n, float v, hipStream_t s);
 // array with nc components
 hipError_t yo_launch_to_ghost(const float *dense, const YoGhost &ghost, int ncomp, int c0, int nc, int nz,
                               int ny, int nx, int ns, hipStream_t s);
-// kplane from kappa; planes k_lo .. k_hi are taken as not uniform
-hipError_t yo_launch_kplane(const float *kappa, float4 *kplane, int nz, int ny, int nx, int ns, int k_lo, int k_hi,
-                            hipStream_t s);
+// a background: kappa and its kplane (planes k_lo .. k_hi are taken as not
+// uniform), and the n values of the canvas' mask
+hipError_t yo_launch_background(const float *dense, float *kappa, float4 *kplane, int nz, int ny, int nx, int ns,
+                                int k_lo, int k_hi, const float *mask, float *mask_out, size_t n, hipStream_t s);
 hipError_t yo_launch_from_ghost(const YoGhost &ghost, float *dense, int ncomp, int c0, int nc, int nz,
                                 int ny, int nx, int ns, hipStream_t s);
 // in-place phasor fit of n complex sums; sets *bad to 1 if a result is not

@@ -1661,11 +1661,9 @@ yo_status yo_set_background(yo_plan *p, const float *kappa, const float *mask, y
     if (yo_status st_ = ws_check(p)) return st_;
     hipStream_t s = (hipStream_t)stream;
     const yo_grid &g = p->grid;
-    HIPCHK(yo_launch_to_ghost(kappa, YoGhost{{wsp<float>(p, p->L.kappa)}, nullptr}, 3, 0, 3, g.nz, g.ny, g.nx, p->ns, s));
     // (yo_set_design writes the slab and its faces)
-    HIPCHK(yo_launch_kplane(wsp<float>(p, p->L.kappa), wsp<float4>(p, p->L.kplane), g.nz, g.ny, g.nx, p->ns,
-                            p->des.k_lo - 1, p->des.k_hi, s));
-    HIPCHK(hipMemcpyAsync(p->chain.mask, mask, sizeof(float) * p->U * p->V, hipMemcpyDeviceToDevice, s));
+    HIPCHK(yo_launch_background(kappa, wsp<float>(p, p->L.kappa), wsp<float4>(p, p->L.kplane), g.nz, g.ny, g.nx, p->ns,
+                                p->des.k_lo - 1, p->des.k_hi, mask, p->chain.mask, (size_t)p->U * p->V, s));
     p->bg_set = true;
     p->design_set = false;
     p->mat_gen++;
