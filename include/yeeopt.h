@@ -287,7 +287,8 @@ yo_status yo_advance_many(yo_plan *const *plans, const int *which, int n_plans, 
 yo_status yo_steps_done(const yo_plan *plan, int *steps);
 
 /* Work split of the launches by tile class, which yo_time_kernel measures and
- * timed single steps run (yo_set_timing); the stepping's own launches take
+ * timed single steps run (yo_set_timing), as does a plan whose CPML memories pass
+ * 4 GiB in the library's layout; the stepping's own launches take
  * whole-grid tiles and choose their split by themselves (the planes they are
  * cut at, over all the plans of the call).  A step in launches by class is two:
  * the interior tiles (clear of every absorbing slab, no CPML code) and the

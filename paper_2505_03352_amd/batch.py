@@ -19,14 +19,13 @@ from ._abi import YO_BOTH
 from .plan import Plan, advance_many
 
 
-# Split for shared launches of uneven designs: x-shell strips that leave
-# whole interior strips, CPML shell with per-class code and no prefetch, 10
-# z-planes per tile (8 designs of 128..320 x 96..240 x 64..96 cells: 9.74 s
-# against 9.91 s with 16 planes and 10.02 s with flags 73)
+# Split of the launches by tile class, which plans in one call must share (the
+# stepping itself takes whole-grid tiles, whatever is set here): x-shell strips
+# that leave whole interior strips, CPML shell with per-class code and no
+# prefetch, 10 z-planes per tile
 DEFAULT_FLAGS = 200
 DEFAULT_ZCHUNK = 10
-# the same with two steps per launch over each plan's interior (plans made
-# with time_blocking=2; bitwise the same results)
+# the same for plans made with time_blocking=2
 DEFAULT_FLAGS_PAIRS = 200 | 512
 
 

@@ -85,14 +85,14 @@ unsigned g_scratch_epoch[YO_MAX_DEVICES];
 
 // Tiling flags (yo_set_tiling)
 enum {
-    YO_TILE_XSTRIPS = 1,      // CPML x-shell as full 62-cell strips
+    YO_TILE_XSTRIPS = 1,      // CPML x-shell in whole strips of YO_SW, also where none is left for the interior
     YO_TILE_WPB8 = 2,         // 8 waves per block (else 4)
     YO_TILE_COOP_SHELL = 4,   // CPML shell: cooperative blocks
     YO_TILE_CLASS_CODE = 8,   // CPML shell: each tile runs its own class's code
     YO_TILE_COOP_INT = 16,    // interior: cooperative blocks
     YO_TILE_NOPF_INT = 32,    // interior: no prefetch of the next plane
     YO_TILE_NOPF_SHELL = 64,  // CPML shell: no prefetch of the next plane
-    YO_TILE_XFULL = 128,      // x-shell strips as narrow as whole 62-cell interior strips allow
+    YO_TILE_XFULL = 128,      // the same in the launches of paired steps
     YO_TILE_XINT = 256,       // tiles inside the x-slabs only run in the interior launch (x CPML code)
     YO_TILE_PAIRS = 512,      // the two-step region advances two steps per sweep (yo_set_time_blocking)
     YO_TILE_OVERLAP = 1024,   // with 512: no effect (one launch takes the grid)

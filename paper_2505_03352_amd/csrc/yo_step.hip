@@ -1,11 +1,12 @@
 // Fused single Yee steps for gfx950 in launches by tile class, and two steps
 // over the region clear of slabs and planes: what yo_time_kernel and the tuner
-// measure, and what runs where single-step launches are timed; the stepping
-// itself is yo_pair.hip's.  A single step is two launches over every selected
-// right-hand side of every plan in the call: the interior tiles (clear of
-// every absorbing slab, no CPML code) and the CPML shell; each advances its
-// tiles by one full step (Ht half step, then E step).  The soft current source
-// follows.  Also the running DFT (design box and port planes) around the steps.
+// measure, and what runs where single-step launches are timed and in plans whose
+// CPML memories pass 4 GiB (build_layout); the stepping itself is yo_pair.hip's.
+// A single step is two launches over every selected right-hand side of every plan
+// in the call: the interior tiles (clear of every absorbing slab, no CPML code)
+// and the CPML shell; each advances its tiles by one full step (Ht half step, then
+// E step).  The soft current source follows.  Also the running DFT (design box and
+// port planes) around the steps, and the step counters.
 //
 // Update (paper Sec. 2: time-harmonic sources, steady-state phasors):
 //   Ht^{n+1/2} = Ht^{n-1/2} - curl_e E^n                        (forward differences)

@@ -62,8 +62,8 @@ class Plan:
         for pulse excitation (one run per source and per port for all
         wavelengths; the DFT samples every stride-th step, default 1).
         two_term: the modal coefficient with both of its terms (App. A).
-        time_blocking: 2 gives the plan a third state buffer so that tiling
-        flag 512 can advance its interior two steps per launch."""
+        time_blocking: 2 gives the plan a third state buffer, which the launches
+        of tiling flag 512 need; every plan steps two steps per launch."""
         self.device = torch.device(device)
         self.grid = dict(grid)
         self.design = dict(design)
@@ -377,7 +377,7 @@ def plan_for(dev, device="cuda", stream=None, C=None, beta=None, set_design=True
     (omega0 rad/s, sigma steps, t0 steps[, DFT stride]) for pulse excitation;
     two_term: the two-term modal coefficient; static_workspace: bind the
     library's static workspace instead of allocating one; time_blocking: 2
-    for a plan that may take two steps per launch (tiling flag 512)."""
+    for a plan whose tiling may have flag 512 (see Plan)."""
     grid, design = grid_design_of(dev)
     p = Plan(grid, design, dev.n_steps, freqs_of(dev), [m.plane for m in dev.sources],
              [m.plane for m in dev.ports], device=device, pulse=pulse, two_term=two_term,

@@ -303,9 +303,8 @@ class GpuExecutor:
         self.torch = torch
         self.build = build                 # payload -> workloads.Device-like description
         self.device = torch.device(device)
-        # plans take two steps per launch over their interior by default
-        # (bitwise the same results); the split: whole interior x-strips,
-        # per-class shell code without prefetch, 10-plane tiles
+        # (2 gives each plan a third state buffer; any plan steps two steps per
+        # launch.)  The split that requests in one launch share: batch.DEFAULT_FLAGS
         self.time_blocking = int(time_blocking)
         self.tiling = tiling if tiling is not None else (4, 10, 200 | (512 if self.time_blocking == 2 else 0))
         self.use_graph = use_graph
